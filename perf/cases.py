@@ -1,0 +1,311 @@
+"""Performance cases of libqgalore: the calls a training program makes, over the range of sizes it makes them at.
+
+Kinds of case
+  step        one weight matrix through `step` (fp32 Adam states) or `step_zp` (zero-point weight)
+  step_many   all linear weights of `layers` decoder layers (hidden h, FFN f, rank r) in one grouped `step_many`;
+              `pad`: rows stored at a pitch of a multiple of 16 elements, `zp`: zero-point weights
+  step8       the same matrices one call each through `step8` (8-bit Adam states, the paper's default optimizer)
+  refresh     subspace refresh of `count` matrices of one shape
+  linear      forward and backward pass of the INT8 linear layers of one decoder layer on `tokens` tokens
+
+Inputs follow the repository's synthetic workloads (inputs.py): W ~ N(0, 0.02) quantized to INT8, G = A B^T + noise in
+bf16 with a rank-16 signal, P an orthonormal factor quantized to INT4, beta = (0.9, 0.999), lr = 1e-3, alpha = 0.25.
+The Adam states are those of a run under way (t = 100), at the magnitude of the projected gradient.
+"""
+import math
+
+import torch
+
+from paper_2407_08296_amd import qgalore as qg
+from paper_2407_08296_amd.inputs import LLAMA_SHAPES
+
+DEV = "cuda"
+BLOCK = qg.GROUP
+G_STD = 4e-4          # standard deviation of a gradient element: sqrt(16) * 0.01^2
+
+
+def _model(config, **more):
+    h, f, layers, r = LLAMA_SHAPES[config]
+    return dict(h=h, f=f, layers=layers, r=r, **more)
+
+
+def listed():
+    return [
+        # one small matrix: two dependent launches of a handful of tiles, where latency is everything
+        dict(name="step_512", kind="step", m=512, n=512, r=128, zp=False),
+        # the optimizer step of whole models, every linear weight in one grouped call (the library's main use)
+        dict(name="step_130m", kind="step_many", pad=False, zp=False, **_model(1)),
+        dict(name="step_350m", kind="step_many", pad=False, zp=False, **_model(2)),
+        # FFN width 5461: rows of the down projections start at odd offsets
+        dict(name="step_1b", kind="step_many", pad=False, zp=False, **_model(3)),
+        # the same model with its rows padded and asymmetric weights
+        dict(name="step_1b_zp_padded", kind="step_many", pad=True, zp=True, **_model(3)),
+        # the headline workload: 224 matrices, 6.5e9 weights
+        dict(name="step_7b", kind="step_many", pad=False, zp=False, **_model(4)),
+        # one 7B decoder layer stepped matrix by matrix with 8-bit states, as it is when a layer's gradients are
+        # consumed as soon as they exist
+        dict(name="step8_7b_layer", kind="step8", h=4096, f=11008, layers=1, r=1024),
+        # lazy refresh of a single small matrix: a chain of small dependent kernels
+        dict(name="refresh_768", kind="refresh", m=768, n=768, r=256, count=1),
+        # refresh of the attention matrices of four 7B decoder layers in one call
+        dict(name="refresh_7b_attention", kind="refresh", m=4096, n=4096, r=1024, count=16),
+        # the layers around the step: one sequence through a small model's layer ...
+        dict(name="linear_130m_256", kind="linear", h=768, f=2048, tokens=256, transposed=False),
+        # ... a ragged number of tokens through a layer whose FFN width is odd ...
+        dict(name="linear_1b_1000", kind="linear", h=2048, f=5461, tokens=1000, transposed=False),
+        # ... and a full batch (16 sequences of 256) through a 7B layer
+        dict(name="linear_7b_4096", kind="linear", h=4096, f=11008, tokens=4096, transposed=False),
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def _rank(rng, lo, hi):
+    return max(8, _log_int(rng, lo, hi) // 8 * 8)
+
+
+def _size(rng, lo, hi):
+    """A size of the range; two in three are multiples of 16, the rest whatever comes (odd ones among them)."""
+    v = _log_int(rng, lo, hi)
+    return v if rng.random() < 1 / 3 else max(16, v // 16 * 16)
+
+
+def draw(rng):
+    kind = rng.choice(["step", "step", "step_many", "step_many", "step_many", "step8", "refresh", "refresh", "linear", "linear"])
+    if kind == "step":
+        m, n = _size(rng, 256, 11008), _size(rng, 256, 11008)
+        return dict(kind=kind, m=m, n=n, r=_rank(rng, 64, min(1024, m)), zp=rng.random() < 0.3)
+    if kind in ("step_many", "step8"):
+        h = _size(rng, 512, 4096)
+        f = _size(rng, 2 * h, 3 * h)
+        most = 32 if kind == "step_many" else 4
+        layers = _log_int(rng, 1, most)
+        c = dict(kind=kind, h=h, f=f, layers=layers, r=_rank(rng, 128, h // 4))
+        if kind == "step_many":
+            c.update(pad=rng.random() < 0.3, zp=rng.random() < 0.3)
+        return c
+    if kind == "refresh":
+        m, n = _size(rng, 512, 4096), _size(rng, 512, 4096)
+        return dict(kind=kind, m=m, n=n, r=_rank(rng, 128, min(m, n) // 4), count=_log_int(rng, 1, 16))
+    h = _size(rng, 512, 4096)
+    return dict(kind="linear", h=h, f=_size(rng, 2 * h, 3 * h), tokens=_log_int(rng, 64, 4096), transposed=rng.random() < 0.3)
+
+
+# ------------------------------------------------------------------------------------------------------ shapes
+def _layer(c):
+    """(m, n) of q, k, v, o, gate, up, down of one decoder layer."""
+    h, f = c["h"], c["f"]
+    return [(h, h)] * 4 + [(f, h)] * 2 + [(h, f)]
+
+
+def _matrices(c):
+    if c["kind"] == "step":
+        return [(c["m"], c["n"])]
+    return _layer(c) * c["layers"]
+
+
+def _groups(n):
+    return (n + BLOCK - 1) // BLOCK
+
+
+def _pitch(c, n):
+    return (n + 15) // 16 * 16 if c.get("pad") else n
+
+
+# ------------------------------------------------------------------------------------------------------ inputs
+class _Arena:
+    """One flat tensor from which the tensors of all matrices are cut (64-element steps: 16-byte aligned)."""
+
+    def __init__(self, sizes, dtype):
+        self.at, end = [], 0
+        for s in sizes:
+            self.at.append(end)
+            end += (s + 63) // 64 * 64
+        self.flat = torch.zeros(end, dtype=dtype, device=DEV)
+
+    def view(self, i, *shape):
+        return self.flat[self.at[i]:self.at[i] + math.prod(shape)].view(*shape)
+
+
+def _gradient(m, n, gen):
+    a = torch.randn(m, 16, device=DEV, generator=gen) * 0.01
+    b = torch.randn(n, 16, device=DEV, generator=gen) * 0.01
+    e = torch.randn(m, n, device=DEV, generator=gen)
+    return torch.addmm(e, a, b.t(), beta=1e-4).to(torch.bfloat16)
+
+
+def _projection(m, r, gen):
+    """INT4 codes and scales of the orthonormal factor of a Gaussian m x r matrix."""
+    q, _ = qg.orthonormalize(torch.randn(m, r, device=DEV, generator=gen))
+    return qg.quant_int4(q)
+
+
+def _weight(m, n, gen, zp):
+    w = torch.randn(m, n, device=DEV, generator=gen) * 0.02
+    return qg.quant_int8_zp(w) if zp else qg.quant_int8(w)
+
+
+def _steps(c, gen):
+    mats, r, zp, eight = _matrices(c), c["r"], bool(c.get("zp")), c["kind"] == "step8"
+    lds = [_pitch(c, n) for _, n in mats]
+    wide = [m * ld for (m, _), ld in zip(mats, lds)]
+    low = [r * ld for ld in lds]
+    blocks = [m * _groups(n) for m, n in mats]
+    s = dict(
+        G=_Arena(wide, torch.bfloat16), Wq=_Arena(wide, torch.int8), Ws=_Arena(blocks, torch.float32),
+        Pq=_Arena([m * r // 2 for m, _ in mats], torch.uint8),
+        Ps=_Arena([(m * r + BLOCK - 1) // BLOCK for m, _ in mats], torch.float32), N=_Arena(low, torch.bfloat16))
+    if zp:
+        s["Wz"] = _Arena(blocks, torch.float32)
+    if eight:
+        state_blocks = [(e + BLOCK - 1) // BLOCK for e in low]
+        s.update(R=_Arena(low, torch.float32), Mq=_Arena(low, torch.uint8), Ms=_Arena(state_blocks, torch.float32),
+                 Vq=_Arena(low, torch.uint8), Vs=_Arena(state_blocks, torch.float32))
+    else:
+        s.update(M=_Arena(low, torch.float32), V=_Arena(low, torch.float32))
+    projections = {m: _projection(m, r, gen) for m in {m for m, _ in mats}}
+    out = []
+    for i, ((m, n), ld) in enumerate(zip(mats, lds)):
+        s["G"].view(i, m, ld)[:, :n] = _gradient(m, n, gen)
+        w = _weight(m, n, gen, zp)
+        s["Wq"].view(i, m, ld)[:, :n] = w[0]
+        s["Ws"].view(i, m, _groups(n)).copy_(w[1])
+        pq, ps = projections[m]
+        t = dict(Pq=s["Pq"].view(i, pq.numel()), Ps=s["Ps"].view(i, ps.numel()), G=s["G"].view(i, m, ld),
+                 Wq=s["Wq"].view(i, m, ld), Ws=s["Ws"].view(i, m, _groups(n)), N=s["N"].view(i, r, ld))
+        t["Pq"].copy_(pq)
+        t["Ps"].copy_(ps)
+        if zp:
+            t["Wz"] = s["Wz"].view(i, m, _groups(n))
+            t["Wz"].copy_(w[2])
+        mom = torch.randn(r, ld, device=DEV, generator=gen) * (0.25 * G_STD)
+        var = (0.5 + torch.rand(r, ld, device=DEV, generator=gen)) * G_STD**2
+        if eight:
+            t["R"] = s["R"].view(i, r, ld)
+            for name, x, signed in (("M", mom, True), ("V", var, False)):
+                codes, scales = qg.state8_quant(x, signed)
+                t[name + "q"], t[name + "s"] = s[name + "q"].view(i, codes.numel()), s[name + "s"].view(i, scales.numel())
+                t[name + "q"].copy_(codes)
+                t[name + "s"].copy_(scales)
+        else:
+            t["M"], t["V"] = s["M"].view(i, r, ld), s["V"].view(i, r, ld)
+            t["M"].copy_(mom)
+            t["V"].copy_(var)
+        out.append((m, n, ld, t))
+    return s, out
+
+
+def prepare(case, seed):
+    gen = torch.Generator(device=DEV).manual_seed(int(seed))
+    kind = case["kind"]
+    if kind in ("step", "step_many", "step8"):
+        arenas, mats = _steps(case, gen)
+        state = dict(kind=kind, r=case["r"], zp=bool(case.get("zp")), mats=mats, hp=qg.hparams(), seed=int(seed) & 0xFFFFFFFF,
+                     t=100)
+        state["out"] = {k: a.flat for k, a in arenas.items() if k not in ("G", "Pq", "Ps")}
+        if kind == "step_many":
+            state["plan"] = qg.StepPlan([
+                qg.MatrixState(m, n, case["r"], t["Pq"], t["Ps"], t["G"], t["Wq"], t["Ws"], t["M"], t["V"], None, t["N"],
+                               ld if ld != n else 0, t.get("Wz")) for m, n, ld, t in mats])
+        return state
+    if kind == "refresh":
+        m, n, r = case["m"], case["n"], case["r"]
+        pq, ps = _projection(m, r, gen)
+        count = case["count"]
+        nbytes = qg.lib().qg_refresh_workspace_bytes(count, m, n, r)
+        return dict(kind=kind, m=m, n=n, r=r, count=count, Pq=[pq.clone() for _ in range(count)],
+                    Ps=[ps.clone() for _ in range(count)], G=[_gradient(m, n, gen) for _ in range(count)],
+                    workspace=torch.empty(nbytes, dtype=torch.uint8, device=DEV))
+    tokens = case["tokens"]
+    layers = []
+    for m, n in _layer(case):
+        rows, cols = (n, m) if case["transposed"] else (m, n)
+        wq, ws = _weight(rows, cols, gen, False)
+        x = torch.randn(tokens, n, device=DEV, generator=gen).to(torch.bfloat16)
+        dy = (torch.randn(tokens, m, device=DEV, generator=gen) * 1e-3).to(torch.bfloat16)
+        layers.append((m, n, wq, ws, x, dy))
+    return dict(kind=kind, layers=layers, transposed=case["transposed"])
+
+
+# ------------------------------------------------------------------------------------------------------ one pass
+def run(state):
+    kind = state["kind"]
+    if kind in ("step", "step_many", "step8"):
+        state["t"] += 1
+        hp, seed, t, r = state["hp"], state["seed"], state["t"], state["r"]
+        if kind == "step_many":
+            qg.step_many(state["plan"], hp, seed, t)
+        else:
+            for m, n, _, a in state["mats"]:
+                if kind == "step8":
+                    qg.step8(a["Pq"], a["Ps"], a["G"], a["Wq"], a["Ws"], a["Mq"], a["Ms"], a["Vq"], a["Vs"], a["R"], a["N"],
+                             m, n, r, hp, seed, t)
+                elif state["zp"]:
+                    qg.step_zp(a["Pq"], a["Ps"], a["G"], a["Wq"], a["Ws"], a["Wz"], a["M"], a["V"], None, a["N"], m, n, r,
+                               hp, seed, t)
+                else:
+                    qg.step(a["Pq"], a["Ps"], a["G"], a["Wq"], a["Ws"], a["M"], a["V"], None, a["N"], m, n, r, hp, seed, t)
+        return state["out"]
+    if kind == "refresh":
+        m, n, r = state["m"], state["n"], state["r"]
+        if state["count"] == 1:
+            return qg.subspace_refresh(state["Pq"][0], state["Ps"][0], state["G"][0], m, n, r,
+                                       workspace=state["workspace"])[:4]
+        return qg.subspace_refresh_many(state["Pq"], state["Ps"], state["G"], m, n, r, workspace=state["workspace"])[:4]
+    out = []
+    if state["transposed"]:
+        for m, n, wq, ws, x, _ in state["layers"]:
+            out.append(qg.int8_linear_t_forward(x, wq, ws))
+        for m, n, wq, ws, x, dy in reversed(state["layers"]):
+            out.append(qg.int8_linear_t_backward(dy, x, wq, ws, m, n))
+    else:
+        for m, n, wq, ws, x, _ in state["layers"]:
+            out.append(qg.int8_linear_forward(x, wq, ws))
+        for m, n, wq, ws, x, dy in reversed(state["layers"]):
+            out.append(qg.int8_linear_backward(dy, x, wq, ws, m, n))
+    return out
+
+
+# ------------------------------------------------------------------------------------------------------ work
+def work(case):
+    kind = case["kind"]
+    nbytes = flops = 0.0
+    if kind in ("step", "step_many", "step8"):
+        r = case["r"]
+        for m, n in _matrices(case):
+            flops += 4.0 * m * n * r                                     # P^T G and P N
+            nbytes += 2.0 * m * n + 2.0 * m * n                          # G read; codes of W read and written
+            nbytes += 8.0 * m * _groups(n) * (2 if case.get("zp") else 1)  # scales (and zero points) of W
+            nbytes += m * r / 2 + 4 * math.ceil(m * r / BLOCK)           # P
+            if kind == "step8":
+                nbytes += r * n * (4 + 4 + 2) + 16.0 * math.ceil(r * n / BLOCK)   # R, two states read and written, N
+            else:
+                nbytes += r * n * (16 + 2)                               # M and V read and written, N
+    elif kind == "refresh":
+        m, n, r, count = case["m"], case["n"], case["r"], case["count"]
+        # three bf16 products; Gram matrix, triangular factor, its inverse and the product with it, twice, in fp64
+        flops = count * (6.0 * m * n * r + 2 * (2.0 * m * r * r + 2.0 * r**3 / 3))
+        nbytes = count * (2.0 * m * n + 2 * (m * r / 2 + 4 * math.ceil(m * r / BLOCK)) + 8)
+    else:
+        t = case["tokens"]
+        for m, n in _layer(case):
+            flops += 6.0 * t * m * n
+            rows, cols = (n, m) if case["transposed"] else (m, n)
+            nbytes += m * n + 4.0 * rows * _groups(cols) + 2.0 * m * n   # W read, G written
+            nbytes += 4.0 * t * n + 4.0 * t * m                          # x, dx, y, dy
+    return {"bytes": nbytes, "flops": flops}
+
+
+def tolerance(case):
+    """About four times what the same mathematics in another order of summation shows (rows of P and G, columns of G,
+    contraction indices of the layer permuted): M and V 2e-7, N and the layer's outputs 6e-5 with single bf16 roundings
+    (2^-7) that fall the other way, INT8 codes below 1e-4, the refreshed INT4 codes 4e-4 and the cosine 2e-4."""
+    if case["kind"] == "refresh":
+        return {"rel": 1e-3, "max": 5e-3, "differ": 2e-3}
+    if case["kind"] == "linear":
+        return {"rel": 2.5e-4, "max": 3.2e-2}
+    if case.get("zp"):   # a zero point is a rounded quotient: where it moves by one, so does every code of its block
+        return {"rel": 4e-3, "max": 0.9, "differ": 2e-3}
+    return {"rel": 2e-4, "max": 3.2e-2, "differ": 4e-4}
