@@ -309,3 +309,100 @@ def tolerance(case):
     if case.get("zp"):   # a zero point is a rounded quotient: where it moves by one, so does every code of its block
         return {"rel": 4e-3, "max": 0.9, "differ": 2e-3}
     return {"rel": 2e-4, "max": 3.2e-2, "differ": 4e-4}
+
+
+# ------------------------------------------------------------------------------------------------------ 64-bit answer
+def _scaled(codes, scales):
+    """codes * scales with one scale per BLOCK elements of the last dimension."""
+    n = codes.shape[-1]
+    return codes.double() * scales.double().repeat_interleave(BLOCK, -1)[..., :n]
+
+
+def _int4(pq, ps, m, r):
+    nib = torch.stack([pq & 15, pq >> 4], 1).view(-1)
+    return _scaled(nib.double() - 8.0, ps).view(m, r)
+
+
+def _table8(signed):
+    """The dynamic 8-bit tables of the Adam states: 2^L values spaced linearly over each decade, from 1 downwards."""
+    top = 6 if signed else 7
+    pos = []
+    for p in range(1, 2 ** (top + 1)):
+        level = p.bit_length() - 1
+        pos.append(10.0 ** (level - top) * (0.1 + 0.9 * (p - 2**level + 1) / 2**level))
+    both = [-x for x in reversed(pos)] + [0.0] + pos + pos[-1:] if signed else [0.0] + pos
+    return torch.tensor(both, dtype=torch.float64, device=DEV)
+
+
+def _int8_block_scales(x, zp):
+    """Scales of the blocks of BLOCK columns of x: absmax / 127, or the range that holds zero / 255."""
+    m, n = x.shape
+    b = torch.nn.functional.pad(x, (0, _groups(n) * BLOCK - n)).view(m, -1, BLOCK)
+    return (b.amax(-1).clamp(min=0) - b.amin(-1).clamp(max=0)) / 255 if zp else b.abs().amax(-1) / 127
+
+
+def _exact_steps(case, state):
+    hp, r, eight, t = state["hp"], case["r"], case["kind"] == "step8", state["t"] + 1
+    out = {k: None if k in ("Wq", "Wz", "Mq", "Vq") else v.double() for k, v in state["out"].items()}
+    at = {k: 0 for k in out}
+
+    def put(k, x):
+        out[k][at[k]:at[k] + x.numel()] = x.reshape(-1)
+
+    for m, n, ld, a in state["mats"]:
+        P = _int4(a["Pq"], a["Ps"], m, r)
+        R = P.t() @ a["G"].double()
+        if eight:
+            M, V = (_scaled(_table8(s)[a[q].long()], a[sc]).view(r, ld) for q, sc, s in (("Mq", "Ms", True), ("Vq", "Vs", False)))
+        else:
+            M, V = a["M"].double(), a["V"].double()
+        M, V = hp.beta1 * M + (1 - hp.beta1) * R, hp.beta2 * V + (1 - hp.beta2) * R * R
+        N = M / (1 - hp.beta1**t) / ((V / (1 - hp.beta2**t)).sqrt() + hp.eps)
+        codes = a["Wq"][:, :n].double()
+        if case.get("zp"):
+            codes = codes - a["Wz"].double().repeat_interleave(BLOCK, 1)[:, :n]
+        W = _scaled(codes, a["Ws"]) - hp.lr * hp.alpha * (P @ N[:, :n])
+        put("Ws", _int8_block_scales(W, case.get("zp")))
+        if eight:
+            put("R", R)
+            for k, x in (("Ms", M), ("Vs", V)):
+                x = torch.nn.functional.pad(x.reshape(-1), (0, -x.numel() % BLOCK))
+                put(k, x.view(-1, BLOCK).abs().amax(1))
+            put("N", N)
+        else:   # what lies between a row's end and the next row is not part of the result
+            for k, x in (("M", M), ("V", V), ("N", N)):
+                out[k][at[k]:at[k] + r * ld].view(r, ld)[:, :n] = x[:, :n]
+        for k in out:
+            at[k] += (a[k].numel() + 63) // 64 * 64
+    return out
+
+
+def exact(case, seed):
+    """What one pass returns, in 64 bits; None for codes and zero points (rounded values).  hp holds 32-bit floats."""
+    state = prepare(case, seed)
+    if case["kind"] in ("step", "step_many", "step8"):
+        return _exact_steps(case, state)
+    if case["kind"] == "refresh":
+        scales, cosines = [], []
+        for pq, ps, g in zip(state["Pq"], state["Ps"], state["G"]):
+            m, r, G = case["m"], case["r"], g.double()
+            P = _int4(pq, ps, m, r)
+            Q, T = torch.linalg.qr(G @ (P.t() @ G).to(torch.bfloat16).double().t())
+            Q = Q * T.diagonal().sign()
+            x = torch.nn.functional.pad(Q.reshape(-1), (0, -Q.numel() % BLOCK)).view(-1, BLOCK)
+            s = x.abs().amax(1) / 7
+            new = ((x / s[:, None]).round() * s[:, None]).view(-1)[:m * r].view(m, r)
+            weight = (new.t() @ G).square().sum(1)
+            cos = (P * new).sum(0) / (P.norm(dim=0) * new.norm(dim=0))
+            scales.append(s)
+            cosines.append((weight * cos).sum() / weight.sum())
+        cos = torch.stack(cosines)
+        return [None, scales[0] if case["count"] == 1 else scales, cos, None]
+    forward, backward = [], []
+    for _, _, wq, ws, x, dy in state["layers"]:
+        W, X, D = _scaled(wq, ws), x.double(), dy.double()
+        if case["transposed"]:
+            W = W.t()
+        forward.append(X @ W.t())
+        backward.insert(0, (D @ W, X.t() @ D if case["transposed"] else D.t() @ X))
+    return forward + backward
