@@ -17,8 +17,6 @@
 // the first round's pivots positive for cond(Y) well beyond 1e8 at no cost in the result.  A column that is
 // numerically dependent on its predecessors (a last-round pivot no larger than the shift) is reported through
 // `info`; every kernel runs to completion whatever the data.
-#include <type_traits>
-
 #include "qg_cossim.h"
 #include "qg_tile_gemm.h"
 
@@ -230,151 +228,177 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
     S[e] = sum;
 }
 
-// S += sigma I with sigma = 2^-46 trace(S) (at least 128 units of fp64 roundoff of the largest eigenvalue): keeps
-// the pivots of a Gram matrix with cond(Y) beyond ~1e8 positive.  The shift changes L, not the factor Q in exact
-// arithmetic (Y X^T for any triangular X with a positive diagonal has the same Gram-Schmidt factor); the second
-// round, on a matrix with a far smaller condition number, removes what it costs in orthogonality.  sigma is kept
-// for the pivot check of k_chol_diag.
-__global__ __launch_bounds__(256) void k_gram_shift(double* __restrict__ S, int r, double* __restrict__ shift, BatchStride st) {
-    __shared__ double red[256];
-    S += blockIdx.z * st.S;
-    shift += blockIdx.z * st.shift;
-    const int t = threadIdx.x;
-    double acc = 0.0;
-    for (int i = t; i < r; i += 256) acc += S[(int64_t)i * r + i];
-    red[t] = acc;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) red[t] += red[t + w];
-        __syncthreads();
-    }
-    const double sigma = red[0] > 0.0 ? 0x1p-46 * red[0] : 0.0;
-    for (int i = t; i < r; i += 256) S[(int64_t)i * r + i] += sigma;
-    if (t == 0) shift[0] = sigma;
-}
-
 // ---------------------------------------------------------------------------------------------------------------
-// Blocked Cholesky S = L L^T in place (lower triangle), right-looking, one block column per step kb:
-//   k_chol_diag:   L_kk from the diagonal block, and X_kk = L_kk^-1 (to Dinv[kb] and to the diagonal block of X)
-//   k_chol_panel:  L_ik = S_ik X_kk^T for the blocks below
-//   k_chol_update: S_ij -= L_ik L_jk^T for i >= j > kb
+// Blocked Cholesky S + sigma I = L L^T in place (lower triangle), right-looking, one block column per step kb:
+//   chol_diag_block: L_kk from the diagonal block, and X_kk = L_kk^-1 (to Dinv[kb] and to the diagonal block of X)
+//   k_chol_panel:    L_ik = S_ik X_kk^T for the blocks below
+//   k_chol_update:   S_ij -= L_ik L_jk^T for i >= j > kb, and in the same launch the next diagonal block (by the
+//                    workgroup that has just updated it) and block row kb of X = L^-1
 // Rows and columns at or past r (r not a multiple of 64) behave like an identity block.  A pivot that is not positive
 // is replaced by 1 so that the factorization runs to completion whatever the data.
+//
+// sigma = 2^-46 trace(S) (at least 128 units of fp64 roundoff of the largest eigenvalue) keeps the pivots of a Gram
+// matrix with cond(Y) beyond ~1e8 positive.  The shift changes L, not the factor Q in exact arithmetic (Y X^T for any
+// triangular X with a positive diagonal has the same Gram-Schmidt factor); the second round, on a matrix with a far
+// smaller condition number, removes what it costs in orthogonality.  Each diagonal block gets it when it is factored.
 // ---------------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ S, int r, int kb, double* __restrict__ Dinv,
-                                                   double* __restrict__ X, int32_t* __restrict__ info,
-                                                   const double* __restrict__ shift, double flag_factor, BatchStride st) {
+constexpr int kSB = 16;               // sub-block of the diagonal block: one fp64 MFMA tile
+constexpr int kPitchD = kNB + 1;      // LDS pitch of the diagonal block (odd: 16 rows of a fragment on 16 bank pairs)
+
+__device__ __forceinline__ double readlane_f64(double x, int lane) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, x);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
+// acc += A B for 16 x 16 blocks in LDS: element (i, k) of A at a[i * a_pi + k * a_pk], (k, j) of B at b[k * b_pk + j * b_pj].
+__device__ __forceinline__ f64x4 mma16(const double* a, int a_pi, int a_pk, const double* b, int b_pk, int b_pj, f64x4 acc,
+                                       int lane) {
+    const double* ap = a + (lane & 15) * a_pi + (lane >> 4) * a_pk;
+    const double* bp = b + (lane >> 4) * b_pk + (lane & 15) * b_pj;
+#pragma unroll
+    for (int k = 0; k < kSB; k += 4) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[k * a_pk], bp[k * b_pk], acc, 0, 0, 0);
+    return acc;
+}
+
+// Sum of the diagonal of S (r x r), the same value in every thread; red: 4 doubles of LDS.
+__device__ __forceinline__ double trace_of(const double* __restrict__ S, int r, double* red) {
+    double acc = 0.0;
+    for (int i = threadIdx.x; i < r; i += 256) acc += S[(int64_t)i * r + i];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// Factors the 64 x 64 block in T (pitch kPitchD, lower triangle, complete when called: no barrier needed before) and
+// inverts the factor; writes L_kk to S and X_kk to Dinv and X.  A serial chain of 64 pivots, so everything is arranged
+// around its latency: one wave holds 16 columns of all 64 rows in registers (lane = row) and takes pivot and
+// multipliers from other lanes with v_readlane (no LDS round trip or barrier per column); the four waves then update
+// what is right of the 16 columns with fp64 MFMAs.  The inverse is built from the four 16 x 16 diagonal inverses
+// (one wave each) and three block diagonals of MFMA products.  One barrier pair per 16 columns; with the matrix in LDS
+// and two barriers per column (the form before) a 64 x 64 block took 91 us, this one about 12 us.
+__device__ __forceinline__ void chol_diag_block(double* T, double* rdg, double* __restrict__ S, int r, int kb,
+                                                double* __restrict__ Dinv, double* __restrict__ X, int32_t* __restrict__ info,
+                                                double sigma, double flag_factor) {
+    constexpr int P = kPitchD, NSB = kNB / kSB;
+    const int t = threadIdx.x, lane = t & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int base = kb * kNB;
     // a pivot at or below flag_factor * sigma is reported: 0 in the first round (only pivots that are not positive),
     // 16 in the last, where a pivot that small is the shift alone, i.e. a column that is numerically dependent
-    const double floor_d = flag_factor * shift[blockIdx.z * st.shift];
-    S += blockIdx.z * st.S;
-    Dinv += blockIdx.z * st.D;
-    X += blockIdx.z * st.X;
-    info += blockIdx.z;
-    constexpr int P = kNB + 1;
-    __shared__ double T[kNB * P];
-    __shared__ double dg[kNB], rdg[kNB];
-    const int t = threadIdx.x;
-    const int base = kb * kNB;
-    for (int e = t; e < kNB * kNB; e += 256) {     // consecutive threads along a row
-        const int i = e >> 6, c = e & 63;
-        const int gi = base + i, gc = base + c;
-        T[i * P + c] = (gi < r && gc < r) ? S[(int64_t)gi * r + gc] : (i == c ? 1.0 : 0.0);
-    }
-    const int i = t & 63, cg = t >> 6;              // row i, columns cg, cg + 4, ...
-    for (int j = 0; j < kNB; ++j) {
-        __syncthreads();
-        double d = T[j * P + j];
-        if (!(d > floor_d)) {                       // too small, not positive, or NaN
-            if (t == 0 && base + j < r) atomicCAS(info, 0, base + j + 1);
-            if (!(d > 0.0)) d = 1.0;
-        }
-        const double rs = rsqrt_f64(d);             // column j is scaled by 1 / L_jj, kept for the inverse below
-        if (cg == 0) {
-            if (i > j) T[i * P + j] *= rs;
-            if (i == j) {
-                dg[j] = d * rs;                     // T[j][j] itself stays until every thread has read it
-                rdg[j] = rs;
-            }
-        }
-        __syncthreads();
-        // row i loses lij * L[c][j] in its columns c = c0, c0 + 4, ... <= i.  Unrolled to a fixed count that depends
-        // on j alone, with every LDS read issued before the first use (clamped addresses, predicated stores): as a
-        // loop with a data-dependent trip count each iteration waited out its own LDS round trip.
-        const double lij = T[i * P + j];
-        const int c0 = j + 1 + ((cg - (j + 1)) & 3);
-        auto update = [&](auto qn) {
-            constexpr int QN = decltype(qn)::value;
-            double a[QN], b[QN];
+    const double floor_d = flag_factor * sigma;
+    if (t < kNB && base + t < r) T[t * P + t] += sigma;
+    __syncthreads();
+    for (int p = 0; p < NSB; ++p) {
+        const int c0 = p * kSB;
+        if (wave == 0) {
+            double a[kSB];
 #pragma unroll
-            for (int q = 0; q < QN; ++q) {
-                const int cc = min(c0 + 4 * q, kNB - 1);
-                a[q] = T[i * P + cc];
-                b[q] = T[cc * P + j];
+            for (int c = 0; c < kSB; ++c) a[c] = T[lane * P + c0 + c];
+#pragma unroll
+            for (int j = 0; j < kSB; ++j) {
+                double d = readlane_f64(a[j], c0 + j);
+                if (!(d > floor_d)) {                   // too small, not positive, or NaN
+                    if (lane == 0 && base + c0 + j < r) atomicCAS(info, 0, base + c0 + j + 1);
+                    if (!(d > 0.0)) d = 1.0;
+                }
+                const double rs = rsqrt_f64(d);         // column j is scaled by 1 / L_jj, kept for the inverse below
+                if (lane == 0) rdg[c0 + j] = rs;
+                a[j] = lane == c0 + j ? d * rs : a[j] * rs;
+#pragma unroll
+                for (int c = j + 1; c < kSB; ++c) a[c] = fma(-a[j], readlane_f64(a[j], c0 + c), a[c]);
             }
 #pragma unroll
-            for (int q = 0; q < QN; ++q) {
-                const int c = c0 + 4 * q;
-                if (c <= i) T[i * P + c] = a[q] - lij * b[q];
-            }
-        };
-        const int need = (kNB - 1 - j + 3) >> 2;    // columns left of the four column groups, rounded up
-        if (need > 12) update(std::integral_constant<int, 16>());
-        else if (need > 8) update(std::integral_constant<int, 12>());
-        else if (need > 4) update(std::integral_constant<int, 8>());
-        else update(std::integral_constant<int, 4>());
+            for (int c = 0; c < kSB; ++c)
+                if (lane >= c0 + c) T[lane * P + c0 + c] = a[c];
+        }
+        __syncthreads();
+        // what is right of the 16 columns: block (i, j) -= L_ip L_jp^T, p < j <= i
+        const int left = NSB - 1 - p;
+        for (int b = wave; b < left * (left + 1) / 2; b += 4) {
+            int bi, bj;
+            lower_pair(b, bi, bj);
+            const int ri = (p + 1 + bi) * kSB, rj = (p + 1 + bj) * kSB;
+            const f64x4 u = mma16(T + ri * P + c0, P, 1, T + rj * P + c0, 1, P, f64x4{0.0, 0.0, 0.0, 0.0}, lane);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) T[(ri + 4 * v + (lane >> 4)) * P + rj + (lane & 15)] -= u[v];
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    if (t < kNB) T[t * P + t] = dg[t];
-    __syncthreads();
+    // L out; the strict upper triangle, which nothing reads as a factor, then receives X^T: X[i][c] at T[c][i], c < i;
+    // the diagonal of X is rdg.
     for (int e = t; e < kNB * kNB; e += 256) {
         const int ii = e >> 6, c = e & 63;
         if (c <= ii && base + ii < r) S[(int64_t)(base + ii) * r + base + c] = T[ii * P + c];
     }
-    // X = L^-1 by forward substitution on all 64 columns of the identity at once, right-looking: once row j of X is
-    // final, every later row's residual loses its L[i][j] X[j][.] term.  The residuals (and then X) live transposed
-    // in the strict upper triangle of T, which the factor does not use: X[i][c] at T[c][i] for c < i; the diagonal
-    // of X is 1 / L_jj (rdg).
-    for (int e = t; e < kNB * kNB; e += 256) {
-        const int ii = e >> 6, c = e & 63;
-        if (c > ii) T[ii * P + c] = 0.0;
-    }
-    for (int j = 0; j < kNB; ++j) {
-        __syncthreads();
-        const double xjj = rdg[j];
-        if (t < j) T[t * P + j] *= xjj;             // row j of X: residual / L_jj
-        __syncthreads();
-        if (i > j) {
-            const double lij = T[i * P + j];
-            auto update = [&](auto qn) {            // rows c = cg, cg + 4, ... <= j of X^T, as in the factorization
-                constexpr int QN = decltype(qn)::value;
-                double a[QN], b[QN];
+    // diagonal blocks: lane c of wave w owns column c of X_ww (forward substitution in registers)
+    {
+        const int c0 = wave * kSB, c = lane & 15;
+        double x[kSB];
 #pragma unroll
-                for (int q = 0; q < QN; ++q) {
-                    const int cc = min(cg + 4 * q, kNB - 1);
-                    a[q] = T[cc * P + i];
-                    b[q] = T[cc * P + j];
-                }
+        for (int i = 0; i < kSB; ++i) {
+            double s = i == c ? 1.0 : 0.0;
 #pragma unroll
-                for (int q = 0; q < QN; ++q) {
-                    const int c = cg + 4 * q;
-                    if (c <= j) T[c * P + i] = a[q] - lij * (c < j ? b[q] : xjj);
-                }
-            };
-            const int need = (j >> 2) + 1;
-            if (need > 12) update(std::integral_constant<int, 16>());
-            else if (need > 8) update(std::integral_constant<int, 12>());
-            else if (need > 4) update(std::integral_constant<int, 8>());
-            else update(std::integral_constant<int, 4>());
+            for (int k = 0; k < i; ++k) s = fma(-T[(c0 + i) * P + c0 + k], x[k], s);
+            x[i] = s * rdg[c0 + i];
+        }
+        if (lane < kSB) {
+#pragma unroll
+            for (int i = 1; i < kSB; ++i)
+                if (i > c) T[(c0 + c) * P + c0 + i] = x[i];
         }
     }
     __syncthreads();
+    // element (i, c) of X inside a diagonal block of X, and of its transpose, as MFMA operands
+    auto xd = [&](int row, int col) { return col < row ? T[col * P + row] : (col == row ? rdg[row] : 0.0); };
+    for (int d = 1; d < NSB; ++d) {                     // block diagonal d: X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj, i = j + d
+        const int j = wave, i = wave + d;
+        const int ri = i * kSB, rj = j * kSB;
+        const bool on = i < NSB;                        // wave-uniform
+        f64x4 w{0.0, 0.0, 0.0, 0.0};
+        if (on) {
+            const int row = lane & 15, kq = lane >> 4;
+#pragma unroll
+            for (int k = 0; k < kSB; k += 4)            // k = j: X_jj is triangular, its upper triangle holds other things
+                w = __builtin_amdgcn_mfma_f64_16x16x4f64(T[(ri + row) * P + rj + k + kq], xd(rj + k + kq, rj + row), w, 0, 0, 0);
+            for (int kb2 = j + 1; kb2 < i; ++kb2)       // X_kj at T[rj + column][kk + row]
+                w = mma16(T + ri * P + kb2 * kSB, P, 1, T + rj * P + kb2 * kSB, 1, P, w, lane);
+            // -X_ii W: W's accumulator layout (row 4 v + l / 16, column l % 16) is the B operand layout of k = 4 v + l / 16
+            f64x4 x{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x = __builtin_amdgcn_mfma_f64_16x16x4f64(xd(ri + row, ri + 4 * v + kq), w[v], x, 0, 0, 0);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) T[(rj + row) * P + ri + 4 * v + kq] = -x[v];
+        }
+        __syncthreads();
+    }
     for (int e = t; e < kNB * kNB; e += 256) {
         const int ii = e >> 6, c = e & 63;
-        const double x = c < ii ? T[c * P + ii] : (c == ii ? rdg[ii] : 0.0);
+        const double x = xd(ii, c);
         Dinv[(int64_t)kb * kNB * kNB + e] = x;
         if (base + ii < r && base + c < r) X[(int64_t)(base + ii) * r + base + c] = x;
     }
+}
+
+// The first diagonal block: also forms sigma, kept for the later ones.
+__global__ __launch_bounds__(256) void k_chol_first(double* __restrict__ S, int r, double* __restrict__ Dinv,
+                                                    double* __restrict__ X, int32_t* __restrict__ info,
+                                                    double* __restrict__ shift, double flag_factor, BatchStride st) {
+    S += blockIdx.z * st.S;
+    __shared__ double T[kNB * kPitchD];
+    __shared__ double rdg[kNB], red[4];
+    for (int e = threadIdx.x; e < kNB * kNB; e += 256) {     // consecutive threads along a row
+        const int i = e >> 6, c = e & 63;
+        T[i * kPitchD + c] = (i < r && c < r) ? S[(int64_t)i * r + c] : (i == c ? 1.0 : 0.0);
+    }
+    const double tr = trace_of(S, r, red);
+    const double sigma = tr > 0.0 ? 0x1p-46 * tr : 0.0;
+    if (threadIdx.x == 0) shift[blockIdx.z * st.shift] = sigma;
+    chol_diag_block(T, rdg, S, r, 0, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma, flag_factor);
 }
 
 __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int r, int kb, const double* __restrict__ Dinv,
@@ -408,50 +432,15 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int 
     });
 }
 
-__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int r, int kb, BatchStride st) {
-    S += blockIdx.z * st.S;
-    __shared__ double At[kNB * kPitchKF];
-    __shared__ double Bt[kNB * kPitchKF];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
-    int pi, pj;
-    lower_pair(blockIdx.x, pi, pj);
-    const int ib = kb + 1 + pi, jb = kb + 1 + pj;
-    BlockStage<kNB, kKC, kPitchKF, double> sa, sb;
-    f64x4 acc[2][2];
-    zero_acc(acc);
-    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
-    sb.fetch(S, r, jb * kNB, kb * kNB, r, r);
-    for (int kc = 0; kc < kNB; kc += kKC) {
-        sa.commit(At);
-        sb.commit(Bt);
-        __syncthreads();
-        if (kc + kKC < kNB) {
-            sa.fetch(S, r, ib * kNB, kb * kNB + kc + kKC, r, r);
-            sb.fetch(S, r, jb * kNB, kb * kNB + kc + kKC, r, r);
-        }
-        mma_chunk(At, kPitchKF, 1, Bt, kPitchKF, 1, acc, lane, wi, wj);
-        __syncthreads();
-    }
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = ib * kNB + row, gj = jb * kNB + col;
-        if (gi < r && gj < r) S[(int64_t)gi * r + gj] -= x;
-    });
-}
-
 // ---------------------------------------------------------------------------------------------------------------
-// X = L^-1, block row ib (all block rows above are complete):  X_ik = -X_ii (sum_{j=k}^{i-1} L_ij X_jk),  k < i
+// X = L^-1, block (ib, kb) with kb < ib (all block rows above are complete):  X_ik = -X_ii (sum_{j=k}^{i-1} L_ij X_jk).
+// At, Bt: kNB * kPitchKF and kNB * kPitchT doubles of LDS.
 // ---------------------------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S, double* __restrict__ X,
-                                                   const double* __restrict__ Dinv, int r, int ib, BatchStride st) {
-    S += blockIdx.z * st.S;
-    X += blockIdx.z * st.X;
-    Dinv += blockIdx.z * st.D;
+__device__ __forceinline__ void trinv_block(const double* __restrict__ S, double* __restrict__ X,
+                                            const double* __restrict__ Dinv, int r, int ib, int kb, double* At, double* Bt) {
     // phase 1: At (L chunk, k fast) and Bt (X chunk, k slow); phase 2: Tm (the sum) and At (X_ii chunk)
-    __shared__ double At[kNB * kPitchKF];
-    __shared__ double Bt[kNB * kPitchT];
     static_assert(kNB * kPitchT >= kKC * kPitchKS, "the intermediate reuses the X chunk's buffer");
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
-    const int kb = blockIdx.x;
     f64x4 acc[2][2];
     zero_acc(acc);
     BlockStage<kNB, kKC, kPitchKF, double> sa;
@@ -487,6 +476,67 @@ __global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S,
         const int gi = ib * kNB + row, gj = kb * kNB + col;
         if (gi < r && gj < r) X[(int64_t)gi * r + gj] = -x;
     });
+}
+
+__global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S, double* __restrict__ X,
+                                                   const double* __restrict__ Dinv, int r, int ib, BatchStride st) {
+    __shared__ double At[kNB * kPitchKF];
+    __shared__ double Bt[kNB * kPitchT];
+    trinv_block(S + blockIdx.z * st.S, X + blockIdx.z * st.X, Dinv + blockIdx.z * st.D, r, ib, blockIdx.x, At, Bt);
+}
+
+// Workgroups 0 .. pairs-1: the trailing blocks of step kb, block (kb+1, kb+1) first, which goes on to be factored;
+// workgroups pairs .. pairs+kb-1: block row kb of X (L's row kb and X_kk are final, X's rows above too).  In one
+// launch the three fill the chip together, and a block column costs two launches where it took four.
+__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int r, int kb, int pairs,
+                                                     double* __restrict__ Dinv, double* __restrict__ X,
+                                                     int32_t* __restrict__ info, const double* __restrict__ shift,
+                                                     double flag_factor, BatchStride st) {
+    S += blockIdx.z * st.S;
+    X += blockIdx.z * st.X;
+    Dinv += blockIdx.z * st.D;
+    constexpr int A_LEN = kNB * kPitchKF, B_LEN = kNB * kPitchT;
+    static_assert(A_LEN + B_LEN >= kNB * kPitchD && B_LEN >= kNB * kPitchKF, "one buffer serves the three roles");
+    __shared__ double buf[A_LEN + B_LEN];
+    __shared__ double rdg[kNB];
+    double *At = buf, *Bt = buf + A_LEN;
+    if ((int)blockIdx.x >= pairs) {
+        trinv_block(S, X, Dinv, r, kb, blockIdx.x - pairs, At, Bt);
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
+    int pi, pj;
+    lower_pair(blockIdx.x, pi, pj);
+    const int ib = kb + 1 + pi, jb = kb + 1 + pj;
+    BlockStage<kNB, kKC, kPitchKF, double> sa, sb;
+    f64x4 acc[2][2];
+    zero_acc(acc);
+    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
+    sb.fetch(S, r, jb * kNB, kb * kNB, r, r);
+    for (int kc = 0; kc < kNB; kc += kKC) {
+        sa.commit(At);
+        sb.commit(Bt);
+        __syncthreads();
+        if (kc + kKC < kNB) {
+            sa.fetch(S, r, ib * kNB, kb * kNB + kc + kKC, r, r);
+            sb.fetch(S, r, jb * kNB, kb * kNB + kc + kKC, r, r);
+        }
+        mma_chunk(At, kPitchKF, 1, Bt, kPitchKF, 1, acc, lane, wi, wj);
+        __syncthreads();
+    }
+    if (blockIdx.x != 0) {
+        for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
+            const int gi = ib * kNB + row, gj = jb * kNB + col;
+            if (gi < r && gj < r) S[(int64_t)gi * r + gj] -= x;
+        });
+        return;
+    }
+    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
+        const int gi = ib * kNB + row, gj = ib * kNB + col;
+        buf[row * kPitchD + col] = (gi < r && gj < r) ? S[(int64_t)gi * r + gj] - x : (row == col ? 1.0 : 0.0);
+    });
+    __syncthreads();
+    chol_diag_block(buf, rdg, S, r, kb + 1, Dinv, X, info + blockIdx.z, shift[blockIdx.z * st.shift], flag_factor);
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -630,17 +680,14 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     const unsigned B = (unsigned)batch;
     hipLaunchKernelGGL(k_gram, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
-    hipLaunchKernelGGL(k_gram_shift, dim3(1, 1, B), blk, 0, stream, S, (int)r, shift, st);
-    for (int kb = 0; kb < nt; ++kb) {
-        hipLaunchKernelGGL(k_chol_diag, dim3(1, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, X, info, shift, flag_factor, st);
-        const int below = nt - kb - 1;
-        if (below > 0) {
-            hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
-            hipLaunchKernelGGL(k_chol_update, dim3(below * (below + 1) / 2, 1, B), blk, 0, stream, S, (int)r, kb, st);
-        }
+    hipLaunchKernelGGL(k_chol_first, dim3(1, 1, B), blk, 0, stream, S, (int)r, Dinv, X, info, shift, flag_factor, st);
+    for (int kb = 0; kb + 1 < nt; ++kb) {
+        const int below = nt - kb - 1, left = below * (below + 1) / 2;
+        hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
+        hipLaunchKernelGGL(k_chol_update, dim3(left + kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
+                           flag_factor, st);
     }
-    for (int ib = 1; ib < nt; ++ib)
-        hipLaunchKernelGGL(k_trinv_row, dim3(ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
+    if (nt > 1) hipLaunchKernelGGL(k_trinv_row, dim3(nt - 1, 1, B), blk, 0, stream, S, X, Dinv, (int)r, nt - 1, st);
     hipLaunchKernelGGL(k_apply, dim3((unsigned)((m + kNB - 1) / kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
 }
 

@@ -82,6 +82,19 @@ def test_orthonormalize_matches_the_positive_diagonal_qr(m, n, r):
     assert np.abs(got.T @ got - np.eye(r)).max() <= 1e-6
 
 
+@pytest.mark.parametrize("r", [8, 16, 24, 56, 64, 72, 80, 120, 128, 136, 192, 200])
+def test_orthonormalize_around_the_block_sizes(r):
+    """r around the 16- and 64-wide blocks of the factorization (the last block column from 8 to 64 wide), column norms
+    over two decades: Q within fp32 rounding (2^-24) times a few of the Gram-Schmidt factor in 64 bits."""
+    g = np.random.default_rng(r)
+    Y = (g.standard_normal((r + 57, r)) * np.logspace(0, -2, r)[None, :]).astype(np.float32)
+    Qd, info = qg.orthonormalize(dev(Y))
+    got = host(Qd).astype(np.float64)
+    assert int(host(info)[0]) == 0
+    assert np.abs(got - Q.orthonormalize(Y)).max() <= 1e-6
+    assert np.abs(got.T @ got - np.eye(r)).max() <= 1e-6
+
+
 def test_orthonormalize_graded_columns():
     """Column norms spread over four decades and strong correlation: cond(Y) ~ 1e5."""
     m, r = 777, 200
