@@ -34,6 +34,13 @@ int launch_project_adam(const uint8_t*, const float*, const uint16_t*, float*, f
 int launch_project_adam_many(const PlanHeader*, const PlanHeader*, int, int64_t, const qg_hparams*, hipStream_t);
 int project_mode(int64_t m, int64_t n, int64_t ld, int64_t r);       // edge class the grouped projection needs for a matrix
 int backproject_mode(int64_t m, int64_t n, int64_t ld, int64_t r);   // ... and the grouped back-projection
+// tile configuration of a launch (edge class, 128 x 128 and 128 x 256 tiles of the projection; 128-row tiles of the
+// back-projection) and the tiles of a matrix in it
+int proj_config(int mode, int64_t tiles128, int64_t tiles256);
+int bp_config(int64_t tiles128);
+int64_t proj_tiles(int cfg, int64_t n, int64_t r);
+int64_t proj_tiles_r(int cfg, int64_t r);
+int64_t bp_tiles_m(int cfg, int64_t m);
 constexpr int kAdamChunkElems = 256 * 4 * 4;  // must equal kAdamChunk of qg_adam.hip
 
 static int check_mnr(int64_t m, int64_t n, int64_t r, int group) {
@@ -192,6 +199,18 @@ extern "C" int qg_plan_build(int count, const qg_matrix_desc* descs, void* plan_
         const int a = project_mode(d.m, d.n, ld, d.r), b = backproject_mode(d.m, d.n, ld, d.r);
         return a > b ? a : b;
     };
+    for (int cls = 0; cls < kPlanClasses; ++cls) {
+        int64_t t128 = 0, t256 = 0, b128 = 0;
+        for (int i = 0; i < count; ++i) {
+            const qg_matrix_desc& d = descs[i];
+            if (matrix_class(d) != cls) continue;
+            t128 += proj_tiles(kProj128, d.n, d.r);
+            t256 += proj_tiles(kProj256, d.n, d.r);
+            b128 += bp_tiles_m(kBp128, d.m) * ((d.n + kManyBpBN - 1) / kManyBpBN);
+        }
+        h.proj_cfg[cls] = (uint32_t)proj_config(cls, t128, t256);
+        h.bp_cfg[cls] = (uint32_t)bp_config(b128);
+    }
     uint64_t adam = 0, proj[kPlanClasses] = {0, 0, 0}, bp[kPlanClasses] = {0, 0, 0};
     int out = 0;
     for (int cls = 0; cls < kPlanClasses; ++cls) {
@@ -208,10 +227,10 @@ extern "C" int qg_plan_build(int count, const qg_matrix_desc* descs, void* plan_
             pm.adam_chunk0 = (uint32_t)adam;
             pm.proj_tile0 = (uint32_t)proj[cls];
             pm.bp_tile0 = (uint32_t)bp[cls];
-            pm.proj_tiles_r = (uint32_t)((d.r + kManyProjBM - 1) / kManyProjBM);
-            pm.bp_tiles_m = (uint32_t)((d.m + kManyBpBM - 1) / kManyBpBM);
+            pm.proj_tiles_r = (uint32_t)proj_tiles_r((int)h.proj_cfg[cls], d.r);
+            pm.bp_tiles_m = (uint32_t)bp_tiles_m((int)h.bp_cfg[cls], d.m);
             adam += (uint64_t)((d.r * pm.ld + kAdamChunkElems - 1) / kAdamChunkElems);
-            proj[cls] += (uint64_t)pm.proj_tiles_r * (uint64_t)((d.n + kManyProjBN - 1) / kManyProjBN);
+            proj[cls] += (uint64_t)proj_tiles((int)h.proj_cfg[cls], d.n, d.r);
             bp[cls] += (uint64_t)pm.bp_tiles_m * (uint64_t)((d.n + kManyBpBN - 1) / kManyBpBN);
             mats[out++] = pm;
             ++h.class_count[cls];

@@ -1,6 +1,8 @@
 // Host dispatch of the projection and back-projection kernels (see qg_gemm_kernels.h).
 #include "qg_gemm_kernels.h"
 
+#include <type_traits>
+
 namespace qg {
 
 // ---------------------------------------------------------------------------
@@ -21,61 +23,81 @@ int backproject_mode(int64_t m, int64_t n, int64_t ld, int64_t r) {
     return edge_mode(m, kManyBpBM, n, ld, kManyBpBN, r, 32, r);
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MINWG>
-static int launch_project_cfg(const uint8_t* Pq, const float* Ps, const uint16_t* G, float* R, int m, int n, int ld,
-                              int r, hipStream_t stream) {
-    const uint32_t tiles_r = (uint32_t)((r + BM - 1) / BM), tiles_n = (uint32_t)((n + BN - 1) / BN);
-    const uint32_t tiles = tiles_r * tiles_n;
-    const dim3 grid(grid8(tiles)), block(WGM * WGN * 64);
-    switch (edge_mode(r, BM, n, ld, BN, m, BK, r)) {
-        case kExact:
-            hipLaunchKernelGGL((k_project<BM, BN, BK, WGM, WGN, kExact, MINWG>), grid, block, 0, stream, Pq, Ps, G, R, m,
-                               n, ld, r, tiles_r, tiles);
-            break;
-        case kMasked:
-            hipLaunchKernelGGL((k_project<BM, BN, BK, WGM, WGN, kMasked, MINWG>), grid, block, 0, stream, Pq, Ps, G, R,
-                               m, n, ld, r, tiles_r, tiles);
-            break;
-        default:
-            hipLaunchKernelGGL((k_project<BM, BN, BK, WGM, WGN, kUnaligned, MINWG>), grid, block, 0, stream, Pq, Ps, G,
-                               R, m, n, ld, r, tiles_r, tiles);
-    }
-    return check_launch();
+// Tile configurations: tile, K step, wave grid, pipeline depth (LDS stages of the direct loads), workgroups per CU the
+// instance is compiled for in the three edge modes.
+template <int BM_, int BN_, int BK_, int WGM_, int WGN_, int NS_, int W0, int W1, int W2>
+struct ProjCfg {
+    static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_, NS = NS_, NT = WGM_ * WGN_ * 64;
+    static constexpr int kWg[3] = {W0, W1, W2};
+};
+template <int BM_, int BK_, int WGn_, int WGm_, int NS_, bool PREF_, int W0, int W1, int W2>
+struct BpCfg {
+    static constexpr int BM = BM_, BN = kGroup, BK = BK_, WGn = WGn_, WGm = WGm_, NS = NS_, NT = WGn_ * WGm_ * 64;
+    static constexpr bool PREF = PREF_;
+    static constexpr int kWg[3] = {W0, W1, W2};
+};
+template <typename F>
+static auto with_mode(int mode, F f) {
+    if (mode == kExact) return f(std::integral_constant<int, kExact>());
+    if (mode == kMasked) return f(std::integral_constant<int, kMasked>());
+    return f(std::integral_constant<int, kUnaligned>());
+}
+// Projection tiles (rows of R x columns), and the rule that picks one for a launch.  A K step of one workgroup alone on
+// its CU is bound by its own serial chain (fragment reads, MFMAs, dequantization, barrier): 0.31 us for 128 x 128, 0.23 us
+// for 64 x 128, against 0.11 and 0.05 us of MFMA time, so a launch with few tiles takes the smaller ones, with four tiles
+// in flight and the dequantization between the MFMAs; a launch with 128 x 256 workgroups enough (three fit a CU) lets
+// the workgroups cover for each other and takes the tile with the least staging per MFMA.  Measured (us per step, tiles
+// 64 x 128 / 128 x 128 / 128 x 256): one 2048 x 2048 matrix, r = 512, 37 / 48 / 53; 28 matrices of the 350M layer,
+// r = 256 (256 + 304 tiles of 128 x 128) 155 / 172 / 208; 84 of the 130M layer (624 of 128 x 256) 229 / 219 / 233;
+// 7 of the 7B layer (1112) 1585 / 1268 / 1258.  Unaligned rows are staged through registers, which leaves the
+// 128 x 256 instance two workgroups per CU: 1.09 ms with 128 x 128 against 1.29 for the 1B model's 24 odd matrices.
+template <typename F>
+static auto with_proj(int cfg, F f) {
+    if (cfg == kProj64) return f(ProjCfg<64, 128, 32, 2, 2, 4, 2, 2, 2>());
+    if (cfg == kProj128) return f(ProjCfg<128, 128, 32, 2, 2, 4, 3, 3, 3>());
+    return f(ProjCfg<kManyProjBM, kManyProjBN, 32, 2, 2, 2, 3, 3, 2>());
+}
+// tiles128: 128 x 128 tiles of the launch, tiles256: 128 x 256 tiles
+int proj_config(int mode, int64_t tiles128, int64_t tiles256) {
+    if (tiles128 <= 320) return kProj64;
+    return mode == kUnaligned || tiles256 < 1024 ? kProj128 : kProj256;
+}
+int64_t proj_tiles(int cfg, int64_t n, int64_t r) {
+    return with_proj(cfg, [&](auto c) { return ((r + c.BM - 1) / c.BM) * ((n + c.BN - 1) / c.BN); });
+}
+int64_t proj_tiles_r(int cfg, int64_t r) { return with_proj(cfg, [&](auto c) { return (r + c.BM - 1) / c.BM; }); }
+static int proj_config_of(int64_t n, int64_t ld, int64_t r, int64_t count) {
+    return proj_config((ld % 8) != 0 || (r % 16) != 0 ? kUnaligned : kExact, proj_tiles(kProj128, n, r) * count,
+                       proj_tiles(kProj256, n, r) * count);
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MINWG>
-static int launch_project_adam_cfg(const uint8_t* Pq, const float* Ps, const uint16_t* G, float* R, float* M, float* V,
-                                   uint16_t* N, int m, int n, int ld, int r, const AdamCoef& coef, hipStream_t stream) {
-    const uint32_t tiles_r = (uint32_t)((r + BM - 1) / BM), tiles_n = (uint32_t)((n + BN - 1) / BN);
-    const uint32_t tiles = tiles_r * tiles_n;
-    const dim3 grid(grid8(tiles)), block(WGM * WGN * 64);
-    switch (edge_mode(r, BM, n, ld, BN, m, BK, r)) {
-        case kExact:
-            hipLaunchKernelGGL((k_project_adam<BM, BN, BK, WGM, WGN, kExact, MINWG>), grid, block, 0, stream, Pq, Ps, G,
-                               R, M, V, N, m, n, ld, r, tiles_r, tiles, coef);
-            break;
-        case kMasked:
-            hipLaunchKernelGGL((k_project_adam<BM, BN, BK, WGM, WGN, kMasked, MINWG>), grid, block, 0, stream, Pq, Ps,
-                               G, R, M, V, N, m, n, ld, r, tiles_r, tiles, coef);
-            break;
-        default:
-            hipLaunchKernelGGL((k_project_adam<BM, BN, BK, WGM, WGN, kUnaligned, MINWG>), grid, block, 0, stream, Pq,
-                               Ps, G, R, M, V, N, m, n, ld, r, tiles_r, tiles, coef);
-    }
-    return check_launch();
+// Back-projection: 128 rows x one block of 256 columns, three workgroups per CU, once that gives every CU a workgroup and
+// a half; below that 64 rows with four tiles in flight (us per step, 64 / 128 rows: 512 x 512, r = 128, 18.9 / 23.5;
+// 2048 x 2048, r = 512 (128 tiles) 46 / 53; 4096 x 4096, r = 1024 (512 tiles) 143 / 141; the weight tile shares the
+// staging LDS, the VALU-heavy update epilogue of one workgroup overlaps the main loops of the others).
+template <typename F>
+static auto with_bp(int cfg, F f) {
+    if (cfg == kBp64) return f(BpCfg<64, 32, 2, 2, 4, false, 2, 2, 2>());
+    return f(BpCfg<kManyBpBM, 32, 2, 2, 2, false, 3, 3, 2>());   // the checked variant needs more registers
 }
+int bp_config(int64_t tiles128) { return tiles128 < 384 ? kBp64 : kBp128; }
+int64_t bp_tiles_m(int cfg, int64_t m) { return with_bp(cfg, [&](auto c) { return (m + c.BM - 1) / c.BM; }); }
 
+#define QG_PROJ(KERNEL, C, M, ...) (KERNEL<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, M, C::kWg[M]>)
 // ld: row pitch in elements of G, R, M, V, N (n for dense rows).
 int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, float* R, float* M, float* V,
                         uint16_t* N, int64_t m, int64_t n, int64_t ld, int64_t r, int64_t step, const qg_hparams* hp,
                         hipStream_t stream) {
     const AdamCoef coef = make_adam_coef(hp, step);
-    const int64_t big_tiles = ((r + 127) / 128) * ((n + 255) / 256);
-    if (big_tiles >= 384)
-        return launch_project_adam_cfg<128, 256, 32, 2, 2, 2>(Pq, Ps, G, R, M, V, N, (int)m, (int)n, (int)ld, (int)r, coef,
-                                                              stream);
-    return launch_project_adam_cfg<128, 128, 32, 2, 2, 2>(Pq, Ps, G, R, M, V, N, (int)m, (int)n, (int)ld, (int)r, coef,
-                                                          stream);
+    return with_proj(proj_config_of(n, ld, r, 1), [&](auto c) {
+        using C = decltype(c);
+        return with_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), [&](auto mode) {
+            const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles = tr * (uint32_t)((n + C::BN - 1) / C::BN);
+            hipLaunchKernelGGL(QG_PROJ(k_project_adam, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream, Pq, Ps, G, R, M,
+                               V, N, (int)m, (int)n, (int)ld, (int)r, tr, tiles, coef);
+            return check_launch();
+        });
+    });
 }
 
 // Grouped launches: the plan stores the matrices class by class (kExact, kMasked, kUnaligned); each class that is
@@ -94,92 +116,46 @@ int launch_project_adam_many(const PlanHeader* plan_host, const PlanHeader* plan
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
         const uint32_t tiles = plan_host->proj_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
-        const dim3 grid(grid8(tiles)), block(256);
-        if (cls == kExact)
-            hipLaunchKernelGGL((k_project_adam_many<kManyProjBM, kManyProjBN, 32, 2, 2, kExact, 2>), grid, block, 0,
-                               stream, plan_dev, first, cnt, tiles, write_R, coef);
-        else if (cls == kMasked)
-            hipLaunchKernelGGL((k_project_adam_many<kManyProjBM, kManyProjBN, 32, 2, 2, kMasked, 2>), grid, block, 0,
-                               stream, plan_dev, first, cnt, tiles, write_R, coef);
-        else
-            hipLaunchKernelGGL((k_project_adam_many<kManyProjBM, kManyProjBN, 32, 2, 2, kUnaligned, 2>), grid, block, 0,
-                               stream, plan_dev, first, cnt, tiles, write_R, coef);
-        if (int e = check_launch()) return e;
+        const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
+            using C = decltype(c);
+            return with_mode(cls, [&](auto mode) {
+                hipLaunchKernelGGL(QG_PROJ(k_project_adam_many, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream,
+                                   plan_dev, first, cnt, tiles, write_R, coef);
+                return check_launch();
+            });
+        });
+        if (e) return e;
     }
     return QG_OK;
 }
 
-// Tile choice: 128 x 256 tiles of R with two workgroups resident per CU (one's staging and epilogue overlap the
-// other's MFMA work) when that still yields enough workgroups to fill 256 CUs twice; 128 x 128 tiles otherwise.
 int launch_project(const uint8_t* Pq, const float* Ps, const uint16_t* G, float* R, int64_t m, int64_t n, int64_t ld,
                    int64_t r, hipStream_t stream) {
-    const int64_t big_tiles = ((r + 127) / 128) * ((n + 255) / 256);
-    if (big_tiles >= 384)
-        return launch_project_cfg<128, 256, 32, 2, 2, 2>(Pq, Ps, G, R, (int)m, (int)n, (int)ld, (int)r, stream);
-    return launch_project_cfg<128, 128, 32, 2, 2, 2>(Pq, Ps, G, R, (int)m, (int)n, (int)ld, (int)r, stream);
+    return with_proj(proj_config_of(n, ld, r, 1), [&](auto c) {
+        using C = decltype(c);
+        return with_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), [&](auto mode) {
+            const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles = tr * (uint32_t)((n + C::BN - 1) / C::BN);
+            hipLaunchKernelGGL(QG_PROJ(k_project, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream, Pq, Ps, G, R, (int)m,
+                               (int)n, (int)ld, (int)r, tr, tiles);
+            return check_launch();
+        });
+    });
 }
 
-// R_z = dequant(P_z)^T G_z for `count` (<= kProjBatchMax) matrices of one shape in one launch, with the tiles of the
-// grouped step (same arithmetic per element as launch_project: the order of the sum over m does not depend on the
+// R_z = dequant(P_z)^T G_z for `count` (<= kProjBatchMax) matrices of one shape in one launch (same arithmetic per element as launch_project: the order of the sum over m does not depend on the
 // tile shape).
 int launch_project_batch(const ProjBatch& batch, int count, float* R, int64_t strideR, int64_t m, int64_t n, int64_t ld,
                          int64_t r, hipStream_t stream) {
-    constexpr int BM = kManyProjBM, BN = kManyProjBN;
-    const uint32_t tiles_r = (uint32_t)((r + BM - 1) / BM), tiles_n = (uint32_t)((n + BN - 1) / BN);
-    const uint32_t tiles_per = tiles_r * tiles_n, tiles = tiles_per * (uint32_t)count;
-    const dim3 grid(grid8(tiles)), block(256);
-    switch (edge_mode(r, BM, n, ld, BN, m, 32, r)) {
-        case kExact:
-            hipLaunchKernelGGL((k_project_batch<BM, BN, 32, 2, 2, kExact, 2>), grid, block, 0, stream, batch, R, strideR,
-                               (int)m, (int)n, (int)ld, (int)r, tiles_r, tiles_per, tiles);
-            break;
-        case kMasked:
-            hipLaunchKernelGGL((k_project_batch<BM, BN, 32, 2, 2, kMasked, 2>), grid, block, 0, stream, batch, R, strideR,
-                               (int)m, (int)n, (int)ld, (int)r, tiles_r, tiles_per, tiles);
-            break;
-        default:
-            hipLaunchKernelGGL((k_project_batch<BM, BN, 32, 2, 2, kUnaligned, 2>), grid, block, 0, stream, batch, R,
-                               strideR, (int)m, (int)n, (int)ld, (int)r, tiles_r, tiles_per, tiles);
-    }
-    return check_launch();
-}
-
-// Workgroups per CU the back-projection instances are compiled for (the checked variants need more registers).
-static constexpr int kBpWgPerCu[3] = {3, 3, 2};
-
-template <int BMm, int BK, int WGn, int WGm, bool PREF>
-static int launch_backproject_cfg(const uint8_t* Pq, const float* Ps, const uint16_t* N, int8_t* Wq, float* Ws,
-                                  float* Wz, float* Udbg, int m, int n, int ld, int r, float alpha, float lr,
-                                  uint32_t key, hipStream_t stream) {
-    const uint32_t tiles_m = (uint32_t)((m + BMm - 1) / BMm), tiles_n = (uint32_t)((n + kGroup - 1) / kGroup);
-    const uint32_t tiles = tiles_m * tiles_n;
-    const dim3 grid(grid8(tiles)), block(WGn * WGm * 64);
-#define QG_LAUNCH_BP(MODE, DUMP)                                                                                    \
-    hipLaunchKernelGGL((k_backproject<BMm, BK, WGn, WGm, MODE, DUMP, PREF, kBpWgPerCu[MODE]>), grid, block, 0, stream, \
-                       Pq, Ps, N, Wq, Ws, nullptr, Udbg, m, n, ld, r, alpha, lr, key, tiles_m, tiles)
-#define QG_LAUNCH_BP_ZP(MODE)                                                                                        \
-    hipLaunchKernelGGL((k_backproject<BMm, BK, WGn, WGm, MODE, false, PREF, kBpWgPerCu[MODE], true>), grid, block, 0, \
-                       stream, Pq, Ps, N, Wq, Ws, Wz, nullptr, m, n, ld, r, alpha, lr, key, tiles_m, tiles)
-    const int mode = edge_mode(m, BMm, n, ld, kGroup, r, BK, r);
-    if (Wz != nullptr) {   // zero-point weights (no U dump)
-        if (mode == kExact) QG_LAUNCH_BP_ZP(kExact);
-        else if (mode == kMasked) QG_LAUNCH_BP_ZP(kMasked);
-        else QG_LAUNCH_BP_ZP(kUnaligned);
-        return check_launch();
-    }
-    switch (mode) {
-        case kExact:
-            if (Udbg) QG_LAUNCH_BP(kExact, true); else QG_LAUNCH_BP(kExact, false);
-            break;
-        case kMasked:
-            if (Udbg) QG_LAUNCH_BP(kMasked, true); else QG_LAUNCH_BP(kMasked, false);
-            break;
-        default:
-            if (Udbg) QG_LAUNCH_BP(kUnaligned, true); else QG_LAUNCH_BP(kUnaligned, false);
-    }
-#undef QG_LAUNCH_BP
-#undef QG_LAUNCH_BP_ZP
-    return check_launch();
+    return with_proj(proj_config_of(n, ld, r, count), [&](auto c) {
+        using C = decltype(c);
+        return with_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), [&](auto mode) {
+            const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles_per = tr * (uint32_t)((n + C::BN - 1) / C::BN);
+            const uint32_t tiles = tiles_per * (uint32_t)count;
+            hipLaunchKernelGGL(QG_PROJ(k_project_batch, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream, batch, R,
+                               strideR, (int)m, (int)n, (int)ld, (int)r, tr, tiles_per, tiles);
+            return check_launch();
+        });
+    });
 }
 
 // ld: row pitch in elements of N and Wq (n for dense rows); the U dump, if asked for, is dense.
@@ -187,10 +163,27 @@ int launch_backproject(const uint8_t* Pq, const float* Ps, const uint16_t* N, in
                        float* Udbg, int64_t m, int64_t n, int64_t ld, int64_t r, float alpha, float lr, uint64_t seed,
                        int64_t step, hipStream_t stream) {
     const uint32_t key = sr_key(seed, (uint64_t)step, 0u);
-    // 128-row tiles, weight tile sharing the staging LDS, several workgroups per CU: the VALU-heavy update epilogue
-    // of one workgroup overlaps the MFMA main loops of the others.
-    return launch_backproject_cfg<128, 32, 2, 2, false>(Pq, Ps, N, Wq, Ws, Wz, Udbg, (int)m, (int)n, (int)ld, (int)r, alpha,
-                                                           lr, key, stream);
+    return with_bp(bp_config(bp_tiles_m(kBp128, m) * ((n + kGroup - 1) / kGroup)), [&](auto c) {
+        using C = decltype(c);
+        return with_mode(edge_mode(m, C::BM, n, ld, kGroup, r, C::BK, r), [&](auto mode) {
+            constexpr int MODE = mode();
+            const uint32_t tm = (uint32_t)((m + C::BM - 1) / C::BM), tiles = tm * (uint32_t)((n + kGroup - 1) / kGroup);
+            const dim3 grid(grid8(tiles)), block(C::NT);
+            if (Wz != nullptr)   // zero-point weights (no U dump)
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::PREF, C::kWg[MODE], true>),
+                                   grid, block, 0, stream, Pq, Ps, N, Wq, Ws, Wz, nullptr, (int)m, (int)n, (int)ld, (int)r,
+                                   alpha, lr, key, tm, tiles);
+            else if (Udbg != nullptr)
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, true, C::PREF, C::kWg[MODE]>), grid,
+                                   block, 0, stream, Pq, Ps, N, Wq, Ws, nullptr, Udbg, (int)m, (int)n, (int)ld, (int)r, alpha,
+                                   lr, key, tm, tiles);
+            else
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::PREF, C::kWg[MODE]>), grid,
+                                   block, 0, stream, Pq, Ps, N, Wq, Ws, nullptr, nullptr, (int)m, (int)n, (int)ld, (int)r,
+                                   alpha, lr, key, tm, tiles);
+            return check_launch();
+        });
+    });
 }
 
 int launch_project_many(const PlanHeader* plan_host, const PlanHeader* plan_dev, hipStream_t stream) {
@@ -198,17 +191,15 @@ int launch_project_many(const PlanHeader* plan_host, const PlanHeader* plan_dev,
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
         const uint32_t tiles = plan_host->proj_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
-        const dim3 grid(grid8(tiles)), block(256);
-        if (cls == kExact)
-            hipLaunchKernelGGL((k_project_many<kManyProjBM, kManyProjBN, 32, 2, 2, kExact, 2>), grid, block, 0, stream,
-                               plan_dev, first, cnt, tiles);
-        else if (cls == kMasked)
-            hipLaunchKernelGGL((k_project_many<kManyProjBM, kManyProjBN, 32, 2, 2, kMasked, 2>), grid, block, 0, stream,
-                               plan_dev, first, cnt, tiles);
-        else
-            hipLaunchKernelGGL((k_project_many<kManyProjBM, kManyProjBN, 32, 2, 2, kUnaligned, 2>), grid, block, 0,
-                               stream, plan_dev, first, cnt, tiles);
-        if (int e = check_launch()) return e;
+        const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
+            using C = decltype(c);
+            return with_mode(cls, [&](auto mode) {
+                hipLaunchKernelGGL(QG_PROJ(k_project_many, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream, plan_dev,
+                                   first, cnt, tiles);
+                return check_launch();
+            });
+        });
+        if (e) return e;
     }
     return QG_OK;
 }
@@ -219,27 +210,21 @@ int launch_backproject_many(const PlanHeader* plan_host, const PlanHeader* plan_
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
         const uint32_t tiles = plan_host->bp_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
-        const dim3 grid(grid8(tiles)), block(256);
-        if (plan_host->zero_points) {
-            if (cls == kExact)
-                hipLaunchKernelGGL((k_backproject_many<kManyBpBM, 32, 2, 2, kExact, false, kBpWgPerCu[kExact], true>), grid,
-                                   block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
-            else if (cls == kMasked)
-                hipLaunchKernelGGL((k_backproject_many<kManyBpBM, 32, 2, 2, kMasked, false, kBpWgPerCu[kMasked], true>), grid,
-                                   block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
-            else
-                hipLaunchKernelGGL((k_backproject_many<kManyBpBM, 32, 2, 2, kUnaligned, false, kBpWgPerCu[kUnaligned], true>),
-                                   grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
-        } else if (cls == kExact)
-            hipLaunchKernelGGL((k_backproject_many<kManyBpBM, 32, 2, 2, kExact, false, kBpWgPerCu[kExact]>), grid, block,
-                               0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
-        else if (cls == kMasked)
-            hipLaunchKernelGGL((k_backproject_many<kManyBpBM, 32, 2, 2, kMasked, false, kBpWgPerCu[kMasked]>), grid,
-                               block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
-        else
-            hipLaunchKernelGGL((k_backproject_many<kManyBpBM, 32, 2, 2, kUnaligned, false, kBpWgPerCu[kUnaligned]>),
-                               grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
-        if (int e = check_launch()) return e;
+        const int e = with_bp((int)plan_host->bp_cfg[cls], [&](auto c) {
+            using C = decltype(c);
+            return with_mode(cls, [&](auto mode) {
+                constexpr int MODE = mode();
+                const dim3 grid(grid8(tiles)), block(C::NT);
+                if (plan_host->zero_points)
+                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::PREF, C::kWg[MODE], true>),
+                                       grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
+                else
+                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::PREF, C::kWg[MODE]>),
+                                       grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
+                return check_launch();
+            });
+        });
+        if (e) return e;
     }
     return QG_OK;
 }

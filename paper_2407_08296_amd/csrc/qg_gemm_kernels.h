@@ -53,6 +53,7 @@ typedef u32x4 __attribute__((aligned(2))) u32x4_align2;
 typedef u32x4 __attribute__((aligned(1))) u32x4_align1;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef u32x2 __attribute__((aligned(4))) u32x2_align4;
+typedef u32x2 __attribute__((aligned(2))) u32x2_align2;
 typedef u32x4 __attribute__((aligned(4))) u32x4_align4;
 
 // How a kernel instance treats the matrix edges.
@@ -186,6 +187,33 @@ struct P_Task {
     static_assert(WORDS % (NT * WPT) == 0 && PER >= 1, "staging must divide evenly");
 };
 
+// Pipeline of the main loops: NS tiles of the direct-to-LDS operand (one LDS stage each) and NS register sets of P words,
+// so that the loads of a K step have NS - 1 steps to land.  Waves arrive here with their LDS stores issued; what the
+// next step reads has landed when all of them have left.  (Not __syncthreads: its fence may also wait for the loads
+// of later steps.)
+// The machine scheduler does not see the transpose reads as memory accesses and would move them across the barrier:
+// nothing is scheduled across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// A pointer whose origin the compiler does not know.  Loads through a pointer known to be read-only and unaliased may be
+// moved across the asm statements above and below; wait_loads counts on every load staying on its side of them.
+template <typename T>
+__device__ __forceinline__ T* opaque_ptr(T* p) {
+    asm volatile("" : "+s"(p));
+    return p;
+}
+
+// Wait until at most N of the wave's vector memory operations are outstanding (they complete in order).
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+    static_assert(N < 64, "vmcnt is a 6-bit counter");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
 // XCD-aware tile order: consecutive workgroup ids go round-robin over the 8 XCDs
 // (each with its own L2), so XCD x is handed the contiguous range of tiles
 // [x*per, (x+1)*per), and neighbouring tiles (which share operand panels) meet in
@@ -198,18 +226,104 @@ __device__ __forceinline__ uint32_t xcd_tile(uint32_t wg, uint32_t grid) {
 // ============================================================================
 // Projection: R[r0.., n0..] tile of BM x BN, K loop over m in steps of BK.
 // ============================================================================
-template <int BM, int BN, int BK, int WGM, int WGN>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS>
 struct ProjShape {
     static constexpr int NT = WGM * WGN * 64;
     static constexpr int PA = BM + kPadK, PB = BN;   // P tile padded, G tile swizzled (KMajorSwizzled)
     static constexpr int A_STAGE = BK * PA, B_STAGE = BK * PB;
-    static constexpr int SMEM = 2 * (A_STAGE + B_STAGE);  // uint16 elements
+    static constexpr int SMEM = 2 * A_STAGE + NS * B_STAGE;  // uint16 elements
+    static_assert(NS % 2 == 0, "the P tile has two LDS stages");
 };
+
+// Runs of four columns of a 32-row block of an r x ld array, as the projection's epilogue reads and writes them: run i
+// of a lane lies 8 i rows below its first one.  base: the block's first element of the tile's first column; `bytes`:
+// what is left of the (fp32) array from there; `rows`, `left`: rows and columns left from the lane's first run on.
+// DIRECT: through buffer resources, whose end is the row mask.  Otherwise rows start at arbitrary elements and every
+// access is checked.  A run that straddles the end of its row is written element by element (what lies past the end of
+// a row may be padding that is not ours to write); it is read whole only where the row pitch covers it.
+template <bool DIRECT, bool RAGGED>
+struct EpilogueAccess {
+    int ld;
+    bool straddles;   // the number of columns is not a multiple of 4
+    __device__ __forceinline__ f32x4 load(const float* base, int bytes, int rows, uint32_t voff, int left, int i) const {
+        if constexpr (DIRECT) {
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 32u * (uint32_t)(i * ld), kAuxStream));
+        } else {
+            f32x4 x = {0.f, 0.f, 0.f, 0.f};
+            if (8 * i >= rows || left <= 0) return x;
+            const float* p = base + (voff >> 2) + (int64_t)(8 * i) * ld;
+            if (left >= 4) return __builtin_bit_cast(f32x4, *reinterpret_cast<const u32x4_align4*>(p));
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                if (e < left) x[e] = p[e];
+            return x;
+        }
+    }
+    __device__ __forceinline__ void store(float* base, int bytes, int rows, uint32_t voff, int left, int i, f32x4 x) const {
+        if constexpr (DIRECT) {
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
+            const uint32_t so = 32u * (uint32_t)(i * ld);
+            const bool whole = !RAGGED || left >= 4;
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, whole ? voff : 0x80000000u, so, kAuxStream);
+            if (RAGGED && straddles) {   // wave-uniform
+                if (left > 0 && left < 4) {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e) {
+                        const float xe = x[e];
+                        if (e < left)
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, xe), rs, voff + 4u * e, so, 0);
+                    }
+                }
+            }
+        } else {
+            if (8 * i >= rows || left <= 0) return;
+            float* p = base + (voff >> 2) + (int64_t)(8 * i) * ld;
+            if (left >= 4) {
+                *reinterpret_cast<u32x4_align4*>(p) = __builtin_bit_cast(u32x4, x);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < left) p[e] = x[e];
+            }
+        }
+    }
+    // four bf16 in an array of half the element size (bytes and voff are those of the fp32 arrays)
+    __device__ __forceinline__ void store_bf16(uint16_t* base, int bytes, int rows, uint32_t voff, int left, int i, u32x2 x) const {
+        if constexpr (DIRECT) {
+            const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, RAGGED ? bytes / 2 : 0x7FFFFFFF);
+            const uint32_t so = 16u * (uint32_t)(i * ld);
+            const bool whole = !RAGGED || left >= 4;
+            __builtin_amdgcn_raw_buffer_store_b64(x, rs, whole ? voff >> 1 : 0x80000000u, so, kAuxStream);
+            if (RAGGED && straddles) {   // wave-uniform
+                if (left > 0 && left < 4) {
+#pragma unroll
+                    for (int e = 0; e < 3; ++e)
+                        if (e < left)
+                            __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(x[e >> 1] >> (16 * (e & 1))), rs,
+                                                                  (voff >> 1) + 2u * e, so, 0);
+                }
+            }
+        } else {
+            if (8 * i >= rows || left <= 0) return;
+            uint16_t* p = base + (voff >> 2) + (int64_t)(8 * i) * ld;
+            if (left >= 4) {
+                *reinterpret_cast<u32x2_align2*>(p) = x;
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < left) p[e] = (uint16_t)(x[e >> 1] >> (16 * (e & 1)));
+            }
+        }
+    }
+};
+constexpr int kTransposePitch = 40;                        // floats per row: rows 4 apart fall on the other half of the banks
+constexpr int kTransposeFloats = 32 * kTransposePitch;     // one wave's 32 x 32 block
 
 // With FUSE_ADAM the epilogue runs Adam on the tile while R is still in the accumulators: M and V are read and
 // written in place, N is stored as bf16 and R goes to memory only if the caller asked for it (R != nullptr), which
 // saves the 8 bytes per element of writing R and reading it back in a separate pass.
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, bool FUSE_ADAM = false>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS, int MODE, bool FUSE_ADAM = false>
 __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, const float* __restrict__ Ps,
                                              const uint16_t* __restrict__ G, float* __restrict__ R, int m, int n,
                                              int ld, int r, int r0, int n0, uint16_t* smem, float* __restrict__ Mo = nullptr,
@@ -218,7 +332,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     constexpr bool RAGGED = MODE != kExact;      // masked epilogue
     constexpr bool DIRECT = MODE != kUnaligned;  // buffer / direct-to-LDS loads; a P fetch (8*WPT codes) starts at a
                                                  // multiple of 8*WPT codes, so it lies in one block of 256
-    using S = ProjShape<BM, BN, BK, WGM, WGN>;
+    using S = ProjShape<BM, BN, BK, WGM, WGN, NS>;
     constexpr int NT = S::NT;
     constexpr int WM = BM / WGM, WN = BN / WGN, MB = WM / 32, NB = WN / 32;
     constexpr int PA = S::PA;
@@ -229,14 +343,21 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     constexpr int B_PER = BD::PER;
     static_assert(B_PER * NT * 8 == BK * BN, "staging must divide evenly");
     static_assert(BK % 16 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
+    if constexpr (DIRECT && NS > 2) {
+        Pq = opaque_ptr(Pq);
+        Ps = opaque_ptr(Ps);
+        G = opaque_ptr(G);
+    }
     uint16_t* As = smem;
     uint16_t* Bs = smem + 2 * S::A_STAGE;
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform: keeps everything derived from it scalar
     const int wm = wave / WGN, wn = wave % WGN;
-    uint32_t aw[A_PER][WPT];
-    float asc[A_PER][AT::NSC];
-    u32x4 bv[DIRECT ? 1 : B_PER];   // the unaligned kernels stage G through registers
+    uint32_t aw[NS][A_PER][WPT];
+    float asc[NS][A_PER][AT::NSC];
+    u32x4 bv[NS][DIRECT ? 1 : B_PER];   // the unaligned kernels stage G through registers
+    constexpr int TILE_LOADS = (DIRECT ? B_PER : 0) + A_PER * (1 + AT::NSC);   // vector memory operations of one gload
+    const int KT = (m + BK - 1) / BK;
 
     // Addresses are split into a part that is uniform over the workgroup and advances with the K step (scalar
     // registers, scalar arithmetic) and a 32-bit per-thread offset fixed for the whole loop; the kExact and kMasked kernels
@@ -261,8 +382,8 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
         }
     }
 
-    // Tile kt: P codes and scales into registers; G straight into LDS stage `stage` (kExact, kMasked) or into
-    // registers (kUnaligned, stored by sstore).
+    // Tile kt: P codes and scales into register set `stage`; G straight into LDS stage `stage` (kExact, kMasked) or into
+    // registers (kUnaligned, stored by sstore).  A tile past the end (kt >= KT) loads nothing: its resources are empty.
     auto gload = [&](int kt, int stage) {
         const int i0 = kt * BK;
         const int64_t e0 = (int64_t)i0 * r;
@@ -272,12 +393,14 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
         if constexpr (DIRECT) {
             __amdgpu_buffer_rsrc_t rq, rs, rg;
             if constexpr (MODE == kExact) {
-                rq = make_rsrc(pq); rs = make_rsrc(ps); rg = make_rsrc(g);
+                const int bytes = kt < KT ? 0x7FFFFFFF : 0;
+                rq = make_rsrc(pq, bytes); rs = make_rsrc(ps, bytes); rg = make_rsrc(g, bytes);
             } else {   // bounded by the end of each array: rows at or past m read as zero
                 const int64_t mr = (int64_t)m * r;
-                rq = make_rsrc(pq, bound_bytes((mr - e0) >> 1));
-                rs = make_rsrc(ps, bound_bytes((((mr + kGroup - 1) >> 8) - (e0 >> 8)) * 4));
-                rg = make_rsrc(g, bound_bytes(((int64_t)(m - i0) * ld - n0) * 2));
+                const bool in = kt < KT;
+                rq = make_rsrc(pq, in ? bound_bytes((mr - e0) >> 1) : 0);
+                rs = make_rsrc(ps, in ? bound_bytes((((mr + kGroup - 1) >> 8) - (e0 >> 8)) * 4) : 0);
+                rg = make_rsrc(g, in ? bound_bytes(((int64_t)(m - i0) * ld - n0) * 2) : 0);
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p)
@@ -285,10 +408,10 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
                                   2u * (uint32_t)(BD::load_row0(wave, p) * ld));
 #pragma unroll
             for (int p = 0; p < A_PER; ++p) {
-                buffer_load_words<WPT>(rq, a_el[p] >> 1, aw[p]);
+                buffer_load_words<WPT>(rq, a_el[p] >> 1, aw[stage][p]);
 #pragma unroll
                 for (int j = 0; j < AT::NSC; ++j)
-                    asc[p][j] = __builtin_bit_cast(
+                    asc[stage][p][j] = __builtin_bit_cast(
                         float, __builtin_amdgcn_raw_buffer_load_b32(rs, ((a_el[p] + 8 * j) >> 8) << 2, 0, 0));
             }
         } else {
@@ -296,19 +419,19 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
             for (int p = 0; p < A_PER; ++p) {
                 const int ti = t + p * NT;
                 const int row = ti / A_TPR, c = (ti % A_TPR) * (8 * WPT);
-                load_p_guarded<WPT>(pq, ps, a_el[p], i0 + row < m ? r - (r0 + c) : 0, aw[p], asc[p]);
+                load_p_guarded<WPT>(pq, ps, a_el[p], i0 + row < m ? r - (r0 + c) : 0, aw[stage][p],
+                                    asc[stage][p]);
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
                 const int ci = t + p * NT;
                 const int row = ci / BD::CPR, c8 = ci % BD::CPR;
                 const int valid = (i0 + row < m) ? (n - (n0 + c8 * 8)) : 0;
-                bv[p] = load8_bf16_guarded(reinterpret_cast<const uint16_t*>(g + b_byte[p]), valid);
+                bv[stage][p] = load8_bf16_guarded(reinterpret_cast<const uint16_t*>(g + b_byte[p]), valid);
             }
         }
     };
-    // Dequantized P tile (and, in the kUnaligned kernels, the G tile) into LDS stage `stage`; returns once the stage's
-    // direct loads have landed too, so that the barrier that follows publishes the whole stage.
+    // Dequantized P tile (and, in the kUnaligned kernels, the G tile) of register set `stage` into LDS.
     auto sstore = [&](int stage) {
 #pragma unroll
         for (int p = 0; p < A_PER; ++p) {
@@ -316,18 +439,22 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
             const int row = ti / A_TPR, c = (ti % A_TPR) * (8 * WPT);
 #pragma unroll
             for (int j = 0; j < WPT; ++j)
-                *reinterpret_cast<u32x4*>(As + stage * S::A_STAGE + row * PA + c + 8 * j) =
-                    dequant8_bf16(aw[p][j], asc[p][DIRECT ? 0 : j]);
+                *reinterpret_cast<u32x4*>(As + (stage & 1) * S::A_STAGE + row * PA + c + 8 * j) =
+                    dequant8_bf16(aw[stage][p][j], asc[stage][p][DIRECT ? 0 : j]);
         }
         if constexpr (!DIRECT) {
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
                 const int ci = t + p * NT;
-                *reinterpret_cast<u32x4*>(Bs + stage * S::B_STAGE + BD::chunk_offset(ci / BD::CPR, ci % BD::CPR)) = bv[p];
+                *reinterpret_cast<u32x4*>(Bs + stage * S::B_STAGE + BD::chunk_offset(ci / BD::CPR, ci % BD::CPR)) =
+                    bv[stage][p];
             }
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // direct loads are counted like any other load
         }
+    };
+    // The direct loads of the next tile have landed too (those of the NS - 2 tiles after it may be outstanding): the
+    // barrier that follows publishes the whole stage.
+    auto landed = [&]() {
+        if constexpr (DIRECT) wait_loads<(NS - 2) * TILE_LOADS>();
     };
 
     f32x16 acc[MB][NB];
@@ -338,18 +465,56 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
+    // The epilogue's accesses.  An accumulator lane holds single elements of 16 rows, and a 4-byte access takes the memory
+    // pipe's address unit as long as a 16-byte one (16 cycles a wave), so each 32 x 32 block goes through LDS and comes
+    // back as runs of four columns: lane l holds columns 4 (l % 8)..+3 of rows l / 8 + 8 i, i < 4, and a wave's access
+    // covers eight whole 128-byte row segments.
+    const int trow = lane >> 3, tcol = 4 * (lane & 7);
+    EpilogueAccess<DIRECT, RAGGED> ea;
+    ea.ld = ld;
+    ea.straddles = (n & 3) != 0;
+    uint32_t voff[NB];   // byte offset, in an fp32 array, of the lane's first run in each 32-column block; no resource
+                         // covers 2^31: runs past the end of a row
+    int left[NB];        // columns of the matrix from the lane's run on
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int col = wn * WN + b * 32 + tcol;   // inside the tile
+        left[b] = RAGGED ? n - (n0 + col) : 4;
+        voff[b] = left[b] > 0 ? 4u * (uint32_t)(trow * ld + col) : 0x80000000u;
+    }
+    // Rows at or past r lie past the end of every array: loads return 0, stores are dropped.
+    auto block_at = [&](int a) -> int64_t { return (int64_t)(r0 + wm * WM + a * 32) * ld + n0; };
+    auto block_rows = [&](int a) -> int { return r - (r0 + wm * WM + a * 32); };
+    auto block_bytes = [&](int a) -> int {   // what is left of an r x ld fp32 array from block a of the tile on
+        return RAGGED ? (block_rows(a) > 0 ? bound_bytes(((int64_t)block_rows(a) * ld - n0) * 4) : 0) : 0x7FFFFFFF;
+    };
+    // Few tiles (deep pipeline): the states are fetched ahead of the main loop, which hides their latency; many tiles:
+    // the registers are worth more as a third workgroup per CU, and the other workgroups cover the epilogue's loads.
+    constexpr bool PRELOAD = FUSE_ADAM && DIRECT && NS > 2 && MB * NB <= 2;
+    f32x4 pm[PRELOAD ? MB * NB * 4 : 1], pv[PRELOAD ? MB * NB * 4 : 1];
+    if constexpr (PRELOAD) {
+#pragma unroll
+        for (int a = 0; a < MB; ++a)
+#pragma unroll
+            for (int b = 0; b < NB; ++b)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    pm[(a * NB + b) * 4 + i] = ea.load(Mo + block_at(a), block_bytes(a), block_rows(a) - trow, voff[b], left[b], i);
+                    pv[(a * NB + b) * 4 + i] = ea.load(Vo + block_at(a), block_bytes(a), block_rows(a) - trow, voff[b], left[b], i);
+                }
+    }
+
     const int a_lane = kmajor_lane_offset(PA, lane) + wm * WM;
     int b_lane[NB];
 #pragma unroll
     for (int b = 0; b < NB; ++b) b_lane[b] = BD::lane_offset(lane) + ((wn * WN + b * 32) ^ BD::lane_swizzle(lane));
-    const int KT = (m + BK - 1) / BK;
 
     auto mfma_step = [&](int stage) {
-        const uint16_t* Ac = As + stage * S::A_STAGE + a_lane;
+        const uint16_t* Ac = As + (stage & 1) * S::A_STAGE + a_lane;
         const uint16_t* Bc = Bs + stage * S::B_STAGE;
         // With several workgroups per CU a SIMD holds several waves; the one in its MFMA phase gets issue priority so the
         // matrix pipe stays fed while the other waves' staging instructions fill the gaps.
-        __builtin_amdgcn_s_setprio(kMfmaPrio);
+        if constexpr (NS == 2) __builtin_amdgcn_s_setprio(kMfmaPrio);
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             bf16x8 af[MB], bf[NB];
@@ -363,170 +528,120 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
                 for (int b = 0; b < NB; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
             // fragments of one 16-wide sub-step at a time (keeps the register count within three workgroups per CU)
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (NS == 2) __builtin_amdgcn_sched_barrier(0);
         }
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (NS == 2) __builtin_amdgcn_s_setprio(0);
     };
 
-    // Unrolled by two so that the LDS stage of every access is a compile-time constant (no per-step address
-    // arithmetic).  Loads past the end re-read the last K slab (in bounds, never consumed), which keeps every load
-    // and store unconditional.
-    gload(0, 0);
+    // Unrolled by NS so that the LDS stage of every access is a compile-time constant (no per-step address
+    // arithmetic).  Every load and store is unconditional; steps past the end load nothing and multiply nothing.
+#pragma unroll
+    for (int u = 0; u < NS - 1; ++u) gload(u, u);
     sstore(0);
-    __syncthreads();
-    for (int kt = 0; kt < KT; kt += 2) {
-        gload(min(kt + 1, KT - 1), 1);
-        mfma_step(0);
-        sstore(1);
-        __syncthreads();
-        gload(min(kt + 2, KT - 1), 0);
-        if (kt + 1 < KT) mfma_step(1);
-        sstore(0);
-        __syncthreads();
+    if constexpr (DIRECT) wait_loads<0>();   // all of them: their order is not fixed here
+    lds_barrier();
+    for (int kt = 0; kt < KT; kt += NS) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            if constexpr (NS == 2) {
+                gload(kt + u + 1, u ^ 1);
+                if (u == 0 || kt + u < KT) mfma_step(u);
+                sstore(u ^ 1);
+            } else {
+                // one scheduling region: the fragment reads first, then the step's loads and the dequantization of the
+                // next P tile (its words were loaded NS - 2 steps ago) between the MFMAs
+                mfma_step(u);
+                gload(kt + u + NS - 1, (u + NS - 1) % NS);
+                sstore((u + 1) % NS);
+                __builtin_amdgcn_sched_group_barrier(0x100, BK / 16 * 2 * (MB + NB), 0);
+#pragma unroll
+                for (int i = 0; i < BK / 16 * MB * NB; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                }
+            }
+            landed();
+            lds_barrier();
+        }
+    }
+    if (NS > 2) {   // the direct loads of steps past the end, of every wave, have written their zeros
+        wait_loads<0>();
+        lds_barrier();
     }
 
-    const int lcol = lane & 31, lhalf = lane >> 5;
-    if (!FUSE_ADAM) {
-        // R through buffer stores: the base of each 32-row block and the row inside it are scalars, the lane supplies
-        // one byte offset per 32-column block, and stores past the resource's end are dropped by the hardware.  That
-        // is the whole row mask (rows at or past r lie past the end of R); a column at or past n gets an offset no
-        // resource covers.
-        uint32_t voff[NB];
+    float* tp = reinterpret_cast<float*>(smem) + wave * kTransposeFloats;   // the staging buffers are free now
+    static_assert(WGM * WGN * kTransposeFloats * 2 <= S::SMEM, "the transpose buffers fit in the staging buffers");
+    const bool write_R = !FUSE_ADAM || R != nullptr;
+#pragma unroll
+    for (int a = 0; a < MB; ++a) {
+        const int64_t at = block_at(a);
+        const int bytes = block_bytes(a), rows = block_rows(a) - trow;
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const int col = wn * WN + b * 32 + lcol;   // inside the tile
-            voff[b] = (!RAGGED || n0 + col < n) ? 4u * (uint32_t)(4 * lhalf * ld + col) : 0x80000000u;
-        }
 #pragma unroll
-        for (int a = 0; a < MB; ++a) {
-            const int row0 = r0 + wm * WM + a * 32;
-            float* base = R + (int64_t)row0 * ld + n0;
-            const __amdgpu_buffer_rsrc_t rr =
-                RAGGED ? make_rsrc(base, row0 < r ? bound_bytes(((int64_t)(r - row0) * ld - n0) * 4) : 0) : make_rsrc(base);
+            for (int v = 0; v < 16; ++v)
+                tp[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * kTransposePitch + (lane & 31)] = acc[a][b][v];
 #pragma unroll
-            for (int b = 0; b < NB; ++b)
+            for (int h = 0; h < 2; ++h) {   // two runs at a time: their states are fetched ahead of the arithmetic
+                f32x4 mm[2], vv[2], rr[2];
+                if constexpr (FUSE_ADAM) {
 #pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float x = acc[a][b][v];   // (a copy: bit_cast of a vector element lvalue reads element 0)
-                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), rr, voff[b],
-                                                          4u * (uint32_t)((8 * (v >> 2) + (v & 3)) * ld), kAuxStream);
-                }
-        }
-    } else if constexpr (DIRECT) {
-        // Adam on the tile while R is still in the accumulators.  M, V (and R, N) go through buffer resources like
-        // the R stores above: scalar base per 32-row block, scalar row offset, one per-lane offset per 32-column
-        // block; rows at or past r lie past the end of every array (loads return 0, stores are dropped), columns at
-        // or past n get an offset no resource covers.  Loads are issued eight rows at a time ahead of the
-        // arithmetic.  N: registers v and v+1 of a lane are rows i and i+1 of one column; even lanes store row i,
-        // odd lanes row i+1, each as one 4-byte bf16 pair with the value of the neighbouring column from lane ^ 1.
-        const AdamCoef c = *coef;
-        const bool odd = (lane & 1) != 0;
-        // v_perm_b32 selector over {nbr (bytes 4..7), own (bytes 0..3)}: even lanes (own.lo, nbr.lo), odd (nbr.hi, own.hi)
-        const uint32_t pair_sel = odd ? 0x03020706u : 0x05040100u;
-        uint32_t voff[NB], voffn[NB];
-#pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int col = wn * WN + b * 32 + lcol;   // inside the tile
-            const bool ok = !RAGGED || n0 + col < n;
-            voff[b] = ok ? 4u * (uint32_t)(4 * lhalf * ld + col) : 0x80000000u;
-            // a pair is stored if its first (even) column is a real one: with an odd n (possible only with a row pitch
-            // ld > n) the pair of column n - 1 also covers the first padding column
-            const bool okn = !RAGGED || n0 + (col & ~1) < n;
-            voffn[b] = okn ? 2u * (uint32_t)(4 * lhalf * ld + col + (odd ? ld - 1 : 0)) : 0x80000000u;
-        }
-#pragma unroll
-        for (int a = 0; a < MB; ++a) {
-            const int row0 = r0 + wm * WM + a * 32;
-            const int64_t e0 = (int64_t)row0 * ld + n0;
-            const int left4 = RAGGED ? (row0 < r ? bound_bytes(((int64_t)(r - row0) * ld - n0) * 4) : 0) : 0x7FFFFFFF;
-            const __amdgpu_buffer_rsrc_t rm = make_rsrc(Mo + e0, left4), rv = make_rsrc(Vo + e0, left4);
-            const bool write_R = R != nullptr;
-            const __amdgpu_buffer_rsrc_t rr = make_rsrc(write_R ? R + e0 : Mo + e0, write_R ? left4 : 0);
-            const __amdgpu_buffer_rsrc_t rn = make_rsrc(No + e0, RAGGED ? left4 / 2 : 0x7FFFFFFF);
-#pragma unroll
-            for (int b = 0; b < NB; ++b)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    float mm[8], vv[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) {
-                        const int v = 8 * h + q;
-                        const uint32_t so = 4u * (uint32_t)((8 * (v >> 2) + (v & 3)) * ld);
-                        mm[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rm, voff[b], so, kAuxStream));
-                        vv[q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rv, voff[b], so, kAuxStream));
+                    for (int q = 0; q < 2; ++q) {
+                        const int i = 2 * h + q;
+                        mm[q] = PRELOAD ? pm[PRELOAD ? (a * NB + b) * 4 + i : 0] : ea.load(Mo + at, bytes, rows, voff[b], left[b], i);
+                        vv[q] = PRELOAD ? pv[PRELOAD ? (a * NB + b) * 4 + i : 0] : ea.load(Vo + at, bytes, rows, voff[b], left[b], i);
                     }
+                }
 #pragma unroll
-                    for (int q = 0; q < 8; q += 2) {
-                        float nn[2];
+                for (int q = 0; q < 2; ++q)
+                    rr[q] = *reinterpret_cast<const f32x4*>(tp + (trow + 8 * (2 * h + q)) * kTransposePitch + tcol);
 #pragma unroll
-                        for (int e = 0; e < 2; ++e) {
-                            const int v = 8 * h + q + e;
-                            const uint32_t so = 4u * (uint32_t)((8 * (v >> 2) + (v & 3)) * ld);
-                            const float rr_ = acc[a][b][v];
-                            nn[e] = adam_one(rr_, mm[q + e], vv[q + e], c);
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, mm[q + e]), rm, voff[b], so, kAuxStream);
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, vv[q + e]), rv, voff[b], so, kAuxStream);
-                            if (write_R)
-                                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, rr_), rr, voff[b], so, kAuxStream);
+                for (int q = 0; q < 2; ++q) {
+                    const int i = 2 * h + q;
+                    if (write_R) ea.store(R + at, bytes, rows, voff[b], left[b], i, rr[q]);
+                    if constexpr (FUSE_ADAM) {
+                        float nn[4];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            float me = mm[q][e], ve = vv[q][e];
+                            nn[e] = adam_one(rr[q][e], me, ve, *coef);
+                            mm[q][e] = me;
+                            vv[q][e] = ve;
                         }
-                        const int v = 8 * h + q;   // rows i (v) and i + 1 (v + 1)
-                        // own column as (row i, row i+1), the neighbour lane's the same way (one DPP move), then one
-                        // byte permute picks (own row i, neighbour row i) in even lanes and (neighbour row i+1, own
-                        // row i+1) in odd lanes
-                        const uint32_t own = pack_bf16x2(nn[0], nn[1]);
-                        const uint32_t nbr = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)own, 0xB1, 0xF, 0xF, true);
-                        const uint32_t pk = __builtin_amdgcn_perm(nbr, own, pair_sel);
-                        __builtin_amdgcn_raw_buffer_store_b32(pk, rn, voffn[b],
-                                                              2u * (uint32_t)((8 * (v >> 2) + (v & 3)) * ld), kAuxStream);
-                    }
-                }
-        }
-    } else {
-        const AdamCoef c = *coef;
-#pragma unroll
-        for (int a = 0; a < MB; ++a)
-#pragma unroll
-            for (int b = 0; b < NB; ++b) {
-                const int col = n0 + wn * WN + b * 32 + lcol;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const int row = r0 + wm * WM + a * 32 + 8 * (v >> 2) + 4 * lhalf + (v & 3);
-                    const int64_t off = (int64_t)row * ld + col;
-                    if (row < r && col < n) {
-                        const float rr_ = acc[a][b][v];
-                        float mm = Mo[off], vv = Vo[off];
-                        const float nn = adam_one(rr_, mm, vv, c);
-                        if (R != nullptr) R[off] = rr_;
-                        Mo[off] = mm;
-                        Vo[off] = vv;
-                        No[off] = to_bf16(nn);
+                        ea.store(Mo + at, bytes, rows, voff[b], left[b], i, mm[q]);
+                        ea.store(Vo + at, bytes, rows, voff[b], left[b], i, vv[q]);
+                        const u32x2 nb = {pack_bf16x2(nn[0], nn[1]), pack_bf16x2(nn[2], nn[3])};
+                        ea.store_bf16(No + at, bytes, rows, voff[b], left[b], i, nb);
                     }
                 }
             }
+        }
     }
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int MIN_WG_PER_CU = 1>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS, int MODE, int MIN_WG_PER_CU = 1>
 __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project(const uint8_t* __restrict__ Pq,
                                                            const float* __restrict__ Ps,
                                                            const uint16_t* __restrict__ G, float* __restrict__ R,
                                                            int m, int n, int ld, int r, uint32_t tiles_r, uint32_t tiles) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN, NS>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
-    project_tile<BM, BN, BK, WGM, WGN, MODE>(Pq, Ps, G, R, m, n, ld, r, (int)(tile % tiles_r) * BM,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(Pq, Ps, G, R, m, n, ld, r, (int)(tile % tiles_r) * BM,
                                                (int)(tile / tiles_r) * BN, smem);
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int MIN_WG_PER_CU = 1>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS, int MODE, int MIN_WG_PER_CU = 1>
 __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam(
     const uint8_t* __restrict__ Pq, const float* __restrict__ Ps, const uint16_t* __restrict__ G,
     float* __restrict__ R, float* __restrict__ M, float* __restrict__ V, uint16_t* __restrict__ N, int m, int n, int ld,
     int r, uint32_t tiles_r, uint32_t tiles, AdamCoef coef) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN, NS>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
-    project_tile<BM, BN, BK, WGM, WGN, MODE, true>(Pq, Ps, G, R, m, n, ld, r, (int)(tile % tiles_r) * BM,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE, true>(Pq, Ps, G, R, m, n, ld, r, (int)(tile % tiles_r) * BM,
                                                      (int)(tile / tiles_r) * BN, smem, M, V, N, &coef);
 }
 
@@ -540,16 +655,16 @@ __device__ __forceinline__ int plan_find(const PlanMatrix* mats, int count, uint
     return lo;
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int MIN_WG_PER_CU = 1>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS, int MODE, int MIN_WG_PER_CU = 1>
 __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_many(const PlanHeader* __restrict__ plan, int first,
                                                                                int count, uint32_t tiles) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN, NS>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
     const PlanMatrix* mats = plan_matrices(plan) + first;
     const PlanMatrix& d = mats[plan_find(mats, count, tile, [](const PlanMatrix& x) { return x.proj_tile0; })];
     const uint32_t local = tile - d.proj_tile0;
-    project_tile<BM, BN, BK, WGM, WGN, MODE>(d.Pq, d.Ps, d.G, d.R, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(d.Pq, d.Ps, d.G, d.R, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
                                                (int)(local % d.proj_tiles_r) * BM,
                                                (int)(local / d.proj_tiles_r) * BN, smem);
 }
@@ -564,31 +679,31 @@ struct ProjBatch {
     const uint16_t* G[kProjBatchMax];
 };
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int MIN_WG_PER_CU = 1>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS, int MODE, int MIN_WG_PER_CU = 1>
 __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_batch(ProjBatch batch, float* __restrict__ R,
                                                                                 int64_t strideR, int m, int n, int ld,
                                                                                 int r, uint32_t tiles_r,
                                                                                 uint32_t tiles_per, uint32_t tiles) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN, NS>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
     const uint32_t z = tile / tiles_per, local = tile % tiles_per;
-    project_tile<BM, BN, BK, WGM, WGN, MODE>(batch.Pq[z], batch.Ps[z], batch.G[z], R + (int64_t)z * strideR, m, n, ld, r,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(batch.Pq[z], batch.Ps[z], batch.G[z], R + (int64_t)z * strideR, m, n, ld, r,
                                                (int)(local % tiles_r) * BM, (int)(local / tiles_r) * BN, smem);
 }
 
-template <int BM, int BN, int BK, int WGM, int WGN, int MODE, int MIN_WG_PER_CU = 1>
+template <int BM, int BN, int BK, int WGM, int WGN, int NS, int MODE, int MIN_WG_PER_CU = 1>
 __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam_many(const PlanHeader* __restrict__ plan,
                                                                                      int first, int count,
                                                                                      uint32_t tiles, int write_R,
                                                                                      AdamCoef coef) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[ProjShape<BM, BN, BK, WGM, WGN, NS>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
     const PlanMatrix* mats = plan_matrices(plan) + first;
     const PlanMatrix& d = mats[plan_find(mats, count, tile, [](const PlanMatrix& x) { return x.proj_tile0; })];
     const uint32_t local = tile - d.proj_tile0;
-    project_tile<BM, BN, BK, WGM, WGN, MODE, true>(d.Pq, d.Ps, d.G, write_R ? d.R : nullptr, (int)d.m, (int)d.n,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE, true>(d.Pq, d.Ps, d.G, write_R ? d.R : nullptr, (int)d.m, (int)d.n,
                                                      (int)d.ld, (int)d.r, (int)(local % d.proj_tiles_r) * BM,
                                                      (int)(local / d.proj_tiles_r) * BN, smem, d.M, d.V, d.N, &coef);
 }
@@ -604,14 +719,14 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam_m
 // W_PREFETCH: the weight tile has LDS of its own and is fetched before the main loop (one workgroup per CU);
 // otherwise it reuses the staging buffers after the main loop (smaller footprint, two workgroups per CU, whose
 // epilogue and main loop then overlap).
-template <int BMm, int BK, int WGn, int WGm, bool W_PREFETCH = true, bool ZP = false>
+template <int BMm, int BK, int WGn, int WGm, int NS, bool W_PREFETCH = true, bool ZP = false>
 struct BpShape {
     static constexpr int BNn = kGroup;
     static constexpr int NT = WGn * WGm * 64;
     static constexpr int PA = BNn;          // N tile, K-major, swizzled (KMajorSwizzled)
     static constexpr int PB = BK + kPadX;   // P tile, [m][k], padded
     static constexpr int A_STAGE = BK * PA, B_STAGE = BMm * PB;
-    static constexpr int STAGING = 2 * (A_STAGE + B_STAGE);   // uint16 elements
+    static constexpr int STAGING = NS * A_STAGE + 2 * B_STAGE;   // uint16 elements
     static constexpr int WTILE = BMm * BNn / 2;                // INT8 weight tile, in uint16 elements
     static constexpr int EXCH = (ZP ? 2 : 1) * WGn * BMm * 2;   // row-max (and, with zero points, row-min) exchange
     static constexpr int WOFF = W_PREFETCH ? STAGING : EXCH;    // after the exchange area if aliased
@@ -637,7 +752,7 @@ __device__ __forceinline__ constexpr int wtile_run_bits(int a, int v4) {
 // ZP: the weight carries a zero point per block (Sec. 3.1 eq.; Appendix A's `W_q - zeros`): x = (code - z)*s - lr*U,
 // the new block takes s' = (hi - lo)/255 over [min(0, min x), max(0, max x)], z' = -128 - round(lo/s'), and the
 // stochastically rounded code is floor(x/s' + u) + z'.
-template <int BMm, int BK, int WGn, int WGm, int MODE, bool DUMP_U, bool W_PREFETCH = true, bool ZP = false>
+template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool DUMP_U, bool W_PREFETCH = true, bool ZP = false>
 __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq, const float* __restrict__ Ps,
                                                  const uint16_t* __restrict__ N, int8_t* __restrict__ Wq,
                                                  float* __restrict__ Ws, float* __restrict__ Wz,
@@ -647,7 +762,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     constexpr bool RAGGED = MODE != kExact;      // masked epilogue
     constexpr bool DIRECT = MODE != kUnaligned;  // buffer / direct-to-LDS loads; a P fetch (8*WPT codes) starts at a
                                                  // multiple of 8*WPT codes, so it lies in one block of 256
-    using S = BpShape<BMm, BK, WGn, WGm, W_PREFETCH, ZP>;
+    using S = BpShape<BMm, BK, WGn, WGm, NS, W_PREFETCH, ZP>;
     constexpr int BNn = S::BNn, NT = S::NT, NW = WGn * WGm;
     constexpr int SN = BNn / WGn, SM = BMm / WGm, IB = SN / 32, JB = SM / 32;
     constexpr int PA = S::PA, PB = S::PB;
@@ -662,8 +777,13 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     static_assert(S::EXCH <= S::STAGING, "row-max exchange must fit in the staging buffers");
     static_assert((BMm / 4) % NW == 0, "weight tile rows must divide evenly over the waves");
     static_assert(SN % 32 == 0 && (SN & (SN - 1)) == 0, "a wave's column span must be a power of two (wtile_run_bits)");
+    if constexpr (DIRECT && NS > 2) {
+        Pq = opaque_ptr(Pq);
+        Ps = opaque_ptr(Ps);
+        N = opaque_ptr(N);
+    }
     uint16_t* As = smem;
-    uint16_t* Bs = smem + 2 * S::A_STAGE;
+    uint16_t* Bs = smem + NS * S::A_STAGE;
     uint8_t* wt = reinterpret_cast<uint8_t*>(smem + S::WOFF);
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform: keeps everything derived from it scalar
@@ -709,9 +829,11 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     };
     if (W_PREFETCH) load_wtile();   // lands while the GEMM main loop runs
 
-    u32x4 av[DIRECT ? 1 : A_PER];   // the unaligned kernels stage N through registers
-    uint32_t bw[B_PER][WPT];
-    float bsc[B_PER][BT::NSC];
+    u32x4 av[NS][DIRECT ? 1 : A_PER];   // the unaligned kernels stage N through registers
+    uint32_t bw[NS][B_PER][WPT];
+    float bsc[NS][B_PER][BT::NSC];
+    constexpr int TILE_LOADS = (DIRECT ? A_PER : 0) + B_PER * (1 + BT::NSC);   // vector memory operations of one gload
+    const int KT = (r + BK - 1) / BK;
 
     // Uniform bases that advance with the K step plus fixed 32-bit per-thread offsets, as in the projection.  The
     // tile's first code, m0*r, starts a block of 256 (m0 is a multiple of 128, r of 8); the K offset k0 does not,
@@ -735,7 +857,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     const int64_t e_tile = (int64_t)m0 * r;
 
     // Tile kt: N straight into LDS stage `stage` (kExact, kMasked) or into registers (kUnaligned); P codes and scales
-    // into registers.
+    // into register set `stage`.  A tile past the end (kt >= KT) loads nothing.
     auto gload = [&](int kt, int stage) {
         const int k0 = kt * BK;
         const uint8_t* nb = reinterpret_cast<const uint8_t*>(N + (int64_t)k0 * ld + n0);
@@ -744,12 +866,14 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
         if constexpr (DIRECT) {
             __amdgpu_buffer_rsrc_t rn, rq, rs;
             if constexpr (MODE == kExact) {
-                rn = make_rsrc(nb); rq = make_rsrc(pq); rs = make_rsrc(ps);
+                const int bytes = kt < KT ? 0x7FFFFFFF : 0;
+                rn = make_rsrc(nb, bytes); rq = make_rsrc(pq, bytes); rs = make_rsrc(ps, bytes);
             } else {   // bounded by the end of each array: rows of N at or past r read as zero (the K tail)
                 const int64_t mr = (int64_t)m * r;
-                rn = make_rsrc(nb, bound_bytes(((int64_t)(r - k0) * ld - n0) * 2));
-                rq = make_rsrc(pq, bound_bytes((mr - e_tile - k0) >> 1));
-                rs = make_rsrc(ps, bound_bytes((((mr + kGroup - 1) >> 8) - (e_tile >> 8)) * 4));
+                const bool in = kt < KT;
+                rn = make_rsrc(nb, in ? bound_bytes(((int64_t)(r - k0) * ld - n0) * 2) : 0);
+                rq = make_rsrc(pq, in ? bound_bytes((mr - e_tile - k0) >> 1) : 0);
+                rs = make_rsrc(ps, in ? bound_bytes((((mr + kGroup - 1) >> 8) - (e_tile >> 8)) * 4) : 0);
             }
 #pragma unroll
             for (int p = 0; p < A_PER; ++p)
@@ -757,10 +881,10 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                                   2u * (uint32_t)(AD::load_row0(wave, p) * ld));
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
-                buffer_load_words<WPT>(rq, b_el[p] >> 1, bw[p]);
+                buffer_load_words<WPT>(rq, b_el[p] >> 1, bw[stage][p]);
 #pragma unroll
                 for (int j = 0; j < BT::NSC; ++j)
-                    bsc[p][j] = __builtin_bit_cast(
+                    bsc[stage][p][j] = __builtin_bit_cast(
                         float, __builtin_amdgcn_raw_buffer_load_b32(rs, ((b_el[p] + (uint32_t)(k0 + 8 * j)) >> 8) << 2, 0, 0));
             }
         } else {
@@ -769,14 +893,14 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                 const int ci = t + p * NT;
                 const int row = ci / AD::CPR, c8 = ci % AD::CPR;
                 const int valid = (k0 + row < r) ? (n - (n0 + c8 * 8)) : 0;
-                av[p] = load8_bf16_guarded(reinterpret_cast<const uint16_t*>(nb + a_byte[p]), valid);
+                av[stage][p] = load8_bf16_guarded(reinterpret_cast<const uint16_t*>(nb + a_byte[p]), valid);
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
                 const int ti = t + p * NT;
                 const int row = ti / B_TPR, c = (ti % B_TPR) * (8 * WPT);
                 load_p_guarded<WPT>(Pq + (e_tile >> 1), ps, b_el[p] + (uint32_t)k0, m0 + row < m ? r - (k0 + c) : 0,
-                                    bw[p], bsc[p]);
+                                    bw[stage][p], bsc[stage][p]);
             }
         }
     };
@@ -787,18 +911,20 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
             const int row = ti / B_TPR, c = (ti % B_TPR) * (8 * WPT);
 #pragma unroll
             for (int j = 0; j < WPT; ++j)
-                *reinterpret_cast<u32x4*>(Bs + stage * S::B_STAGE + row * PB + c + 8 * j) =
-                    dequant8_bf16(bw[p][j], bsc[p][DIRECT ? 0 : j]);
+                *reinterpret_cast<u32x4*>(Bs + (stage & 1) * S::B_STAGE + row * PB + c + 8 * j) =
+                    dequant8_bf16(bw[stage][p][j], bsc[stage][p][DIRECT ? 0 : j]);
         }
         if constexpr (!DIRECT) {
 #pragma unroll
             for (int p = 0; p < A_PER; ++p) {
                 const int ci = t + p * NT;
-                *reinterpret_cast<u32x4*>(As + stage * S::A_STAGE + AD::chunk_offset(ci / AD::CPR, ci % AD::CPR)) = av[p];
+                *reinterpret_cast<u32x4*>(As + stage * S::A_STAGE + AD::chunk_offset(ci / AD::CPR, ci % AD::CPR)) =
+                    av[stage][p];
             }
-        } else {
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the stage's direct loads have landed
         }
+    };
+    auto landed = [&]() {   // the next stage's direct loads, see the projection
+        if constexpr (DIRECT) wait_loads<(NS - 2) * TILE_LOADS>();
     };
 
     f32x16 acc[IB][JB];
@@ -814,12 +940,11 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
 #pragma unroll
     for (int a = 0; a < IB; ++a) a_lane[a] = AD::lane_offset(lane) + ((wn * SN + a * 32) ^ AD::lane_swizzle(lane));
     const int b_lane = (wm * SM + lrow) * PB + 8 * lhalf;
-    const int KT = (r + BK - 1) / BK;
 
     auto mfma_step = [&](int stage) {
         const uint16_t* Ac = As + stage * S::A_STAGE;
-        const uint16_t* Bc = Bs + stage * S::B_STAGE + b_lane;
-        __builtin_amdgcn_s_setprio(kMfmaPrio);
+        const uint16_t* Bc = Bs + (stage & 1) * S::B_STAGE + b_lane;
+        if constexpr (NS == 2) __builtin_amdgcn_s_setprio(kMfmaPrio);
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             bf16x8 af[IB], bf[JB];
@@ -834,22 +959,42 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                 for (int b = 0; b < JB; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
         }
-        __builtin_amdgcn_s_setprio(0);
+        if constexpr (NS == 2) __builtin_amdgcn_s_setprio(0);
     };
 
-    // unrolled by two (constant LDS stages); loads past the end re-read the last K slab, see the projection
-    gload(0, 0);
+    // unrolled by NS (constant LDS stages), see the projection
+#pragma unroll
+    for (int u = 0; u < NS - 1; ++u) gload(u, u);
     sstore(0);
-    __syncthreads();
-    for (int kt = 0; kt < KT; kt += 2) {
-        gload(min(kt + 1, KT - 1), 1);
-        mfma_step(0);
-        sstore(1);
-        __syncthreads();
-        gload(min(kt + 2, KT - 1), 0);
-        if (kt + 1 < KT) mfma_step(1);
-        sstore(0);
-        __syncthreads();
+    if constexpr (DIRECT) wait_loads<0>();   // all of them: their order is not fixed here
+    lds_barrier();
+    for (int kt = 0; kt < KT; kt += NS) {
+#pragma unroll
+        for (int u = 0; u < NS; ++u) {
+            if constexpr (NS == 2) {
+                gload(kt + u + 1, u ^ 1);
+                if (u == 0 || kt + u < KT) mfma_step(u);
+                sstore(u ^ 1);
+            } else {
+                mfma_step(u);
+                gload(kt + u + NS - 1, (u + NS - 1) % NS);
+                sstore((u + 1) % NS);
+                __builtin_amdgcn_sched_group_barrier(0x100, BK / 16 * (2 * IB + JB), 0);
+#pragma unroll
+                for (int i = 0; i < BK / 16 * IB * JB; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                }
+            }
+            landed();
+            lds_barrier();
+        }
+    }
+    if (NS > 2) {   // the direct loads of steps past the end have written their zeros into the staging buffers
+        wait_loads<0>();
+        lds_barrier();
     }
 
     if (!W_PREFETCH) load_wtile();    // the staging buffers are free now (the main loop ends with a barrier)
@@ -1002,7 +1147,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     }
 }
 
-template <int BMm, int BK, int WGn, int WGm, int MODE, bool DUMP_U, bool W_PREFETCH = true, int MIN_WG_PER_CU = 1,
+template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool DUMP_U, bool W_PREFETCH = true, int MIN_WG_PER_CU = 1,
           bool ZP = false>
 __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject(const uint8_t* __restrict__ Pq,
                                                                const float* __restrict__ Ps,
@@ -1012,22 +1157,22 @@ __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject(co
                                                                float* __restrict__ Udbg, int m, int n, int ld, int r,
                                                                float alpha, float lr, uint32_t key, uint32_t tiles_m,
                                                                uint32_t tiles) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, W_PREFETCH, ZP>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, NS, W_PREFETCH, ZP>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
-    backproject_tile<BMm, BK, WGn, WGm, MODE, DUMP_U, W_PREFETCH, ZP>(Pq, Ps, N, Wq, Ws, Wz, Udbg, m, n, ld, r, (int)(tile % tiles_m) * BMm,
+    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, DUMP_U, W_PREFETCH, ZP>(Pq, Ps, N, Wq, Ws, Wz, Udbg, m, n, ld, r, (int)(tile % tiles_m) * BMm,
                                                 (int)(tile / tiles_m), alpha, lr, key, smem);
 }
 
 constexpr int kBpStrip = 16;   // row tiles per strip of the grouped back-projection's tile numbering (8: the same
                                // time; 32: 2 % slower; whole columns of tiles, as before: 1 % slower)
 
-template <int BMm, int BK, int WGn, int WGm, int MODE, bool W_PREFETCH = true, int MIN_WG_PER_CU = 1, bool ZP = false>
+template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool W_PREFETCH = true, int MIN_WG_PER_CU = 1, bool ZP = false>
 __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject_many(const PlanHeader* __restrict__ plan, int first,
                                                                                    int count, uint32_t tiles,
                                                                                    float alpha, float lr,
                                                                                    uint64_t seed, uint64_t step) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, W_PREFETCH, ZP>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, NS, W_PREFETCH, ZP>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
     const PlanMatrix* mats = plan_matrices(plan) + first;
@@ -1042,7 +1187,7 @@ __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject_ma
     const uint32_t strip = local / (kBpStrip * tiles_n), in_strip = local % (kBpStrip * tiles_n);
     const uint32_t strip_rows = min((uint32_t)kBpStrip, d.bp_tiles_m - strip * kBpStrip);
     const uint32_t tile_m = strip * kBpStrip + in_strip % strip_rows, tile_n = in_strip / strip_rows;
-    backproject_tile<BMm, BK, WGn, WGm, MODE, false, W_PREFETCH, ZP>(d.Pq, d.Ps, d.N, d.Wq, d.Ws, d.Wz, nullptr, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
+    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, false, W_PREFETCH, ZP>(d.Pq, d.Ps, d.N, d.Wq, d.Ws, d.Wz, nullptr, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
                                                 (int)tile_m * BMm, (int)tile_n, alpha, lr, key, smem);
 }
 

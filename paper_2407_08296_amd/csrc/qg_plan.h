@@ -10,11 +10,16 @@ namespace qg {
 
 constexpr uint32_t kPlanMagic = 0x51474C50u;  // "QGLP"
 
-// Tile shapes of the grouped GEMM launches (must match the kernel instantiations).
+// Largest tile shapes of the GEMM launches: they decide a matrix's edge class.
 constexpr int kManyProjBM = 128;  // rows of R (r) per tile
 constexpr int kManyProjBN = 256;  // columns of R (n) per tile
 constexpr int kManyBpBM = 128;    // rows of W (m) per tile
 constexpr int kManyBpBN = 256;    // columns of W (n) per tile = one quantization block per row
+
+// Tile configurations of a launch (qg_gemm.hip), by rows per projection or back-projection tile and, for the largest
+// projection tile, by its columns.
+enum : int { kProj64 = 0, kProj128 = 1, kProj256 = 2 };
+enum : int { kBp64 = 0, kBp128 = 1 };
 
 struct PlanMatrix {
     int64_t m, n, r;
@@ -51,7 +56,8 @@ struct PlanHeader {
     uint32_t proj_tiles[kPlanClasses];
     uint32_t bp_tiles[kPlanClasses];
     uint32_t zero_points;                 // 1 if the weights carry zero points (all of them or none)
-    uint32_t pad_[2];
+    uint32_t proj_cfg[kPlanClasses];      // tile configuration of each class (kProj*, kBp*)
+    uint32_t bp_cfg[kPlanClasses];
 };
 static_assert(sizeof(PlanHeader) % 16 == 0, "records must stay 16-byte aligned");
 

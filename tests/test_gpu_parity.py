@@ -347,6 +347,32 @@ def test_step_many_matches_oracle(shapes):
         check_scales_step(host(s.Ws), o["Ws"])
 
 
+@pytest.mark.parametrize("count", [60, 270])
+@pytest.mark.parametrize("m,n,r", [(256, 512, 256), (200, 520, 144), (200, 521, 136), (130, 517, 128)])
+def test_every_tile_configuration_gives_the_single_step(m, n, r, count):
+    """The tiles of a launch depend on how many there are: one matrix, 60 and 270 of them run in three configurations of
+    the projection and two of the back-projection, exact, masked and unaligned.  The order of every sum is the same, so
+    matrix 0 comes out bit for bit as from the single call."""
+    d = make_inputs(m, n, r)
+
+    def fresh():
+        return qg.MatrixState(m, n, r, dev(d["Pq"]), dev(d["Ps"]), dev(d["Gb"]), dev(d["Wq"]), dev(d["Ws"]),
+                              torch.full((r, n), 1e-4, device=DEV), torch.full((r, n), 1e-7, device=DEV),
+                              torch.empty((r, n), device=DEV), torch.empty((r, n), dtype=torch.bfloat16, device=DEV))
+    s, mats = fresh(), [fresh() for _ in range(count)]
+    qg.step(s.Pq, s.Ps, s.G, s.Wq, s.Ws, s.M, s.V, s.R, s.N, m, n, r, qg.hparams(), 11, 2)
+    qg.step_many(qg.StepPlan(mats), qg.hparams(), 11, 2)
+    torch.cuda.synchronize()
+    for i in (0, 1, count - 1):
+        x = mats[i]
+        assert torch.equal(x.R, s.R) and torch.equal(x.M, s.M) and torch.equal(x.V, s.V)
+        assert torch.equal(x.N.view(torch.int16), s.N.view(torch.int16))
+        if i == 0:   # the other matrices round with seeds of their own
+            assert torch.equal(x.Wq, s.Wq)
+        assert torch.equal(x.Ws, s.Ws)
+    assert rel_fro(host(s.R), Q.project(d["Pq"], d["Ps"], d["Gb"], m, n, r)) <= 2e-5
+
+
 def test_step_many_without_R_buffers_gives_the_same_state():
     """The grouped step writes R only if every matrix supplies a buffer; everything else must not depend on it."""
     import dataclasses
