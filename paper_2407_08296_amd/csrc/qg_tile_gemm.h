@@ -10,6 +10,8 @@
 #include "qg_common.h"
 #include "qg_gemm_kernels.h"
 
+#include <type_traits>
+
 namespace qg {
 
 // (the Z layouts: INT8 with a zero point per block, dequantized as (code - zero) * scale)
@@ -65,9 +67,12 @@ struct LinBatch {
     int64_t ldc = 0;   // row pitch of C in elements (0: N, dense rows)
 };
 
-// Staging of one operand tile: global -> registers (fetch) -> LDS (commit; INT8 is dequantized here).  EXACT: the
-// tile lies inside the matrix, K is a whole number of steps and rows are 16-byte aligned - no checks.
-template <int LAYOUT, int XT, int BK, bool EXACT, int NT = 256>
+// What a fetch may take for granted: the chunk lies inside the matrix and is 16-byte aligned; it lies inside the matrix;
+// nothing.
+enum : int { kFetchAligned = 0, kFetchInside = 1, kFetchGuarded = 2 };
+
+// Staging of one operand tile: global -> registers (fetch) -> LDS (commit; INT8 is dequantized here).
+template <int LAYOUT, int XT, int BK, int NT = 256>
 struct LinStage {
     static constexpr bool kFast = LAYOUT == kBf16KFast || LAYOUT == kInt8KFast || LAYOUT == kInt8ZKFast;
     static constexpr bool kZero = LAYOUT == kInt8ZKFast || LAYOUT == kInt8ZKSlow;
@@ -82,6 +87,7 @@ struct LinStage {
     float s[kInt8 ? PER : 1];
     float z[kZero ? PER : 1];
 
+    template <int FETCH>
     __device__ __forceinline__ void fetch(const LinOperand& op, int x0, int X, int k0, int K) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
@@ -90,16 +96,18 @@ struct LinStage {
             const int row = kFast ? x0 + tr : k0 + tr;               // ... and inside the matrix
             const int col = kFast ? k0 + tc : x0 + tc;
             const int rows = kFast ? X : K, cols = kFast ? K : X;
-            const int valid = EXACT ? CH : (row < rows ? cols - col : 0);
+            const int valid = FETCH != kFetchGuarded ? CH : (row < rows ? cols - col : 0);
             const int64_t off = (int64_t)row * op.ld + col;
             if constexpr (kInt8) {
                 const int8_t* src = static_cast<const int8_t*>(op.base) + off;
-                if constexpr (EXACT) v[q] = *reinterpret_cast<const u32x4*>(src); else v[q] = load16_i8_guarded(src, valid);
+                if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
+                else v[q] = load16_i8_guarded(src, valid);
                 s[q] = valid > 0 ? op.scales[(int64_t)row * op.sgroups + (col >> 8)] : 0.f;
                 if constexpr (kZero) z[q] = valid > 0 ? op.zeros[(int64_t)row * op.sgroups + (col >> 8)] : 0.f;
             } else {
                 const uint16_t* src = static_cast<const uint16_t*>(op.base) + off;
-                if constexpr (EXACT) v[q] = *reinterpret_cast<const u32x4*>(src); else v[q] = load8_bf16_guarded(src, valid);
+                if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
+                else v[q] = load8_bf16_guarded(src, valid);
             }
         }
     }
@@ -125,27 +133,70 @@ struct LinStage {
     }
 };
 
+// A wave's 32 x 32 block of C, rows from row0 and columns from col0 on: through LDS (tp: kTransposeFloats floats of the
+// wave's own), so that C is written in 16-byte runs of a row.  A lane of the accumulator holds single elements of 16
+// rows, and the memory pipe's address unit takes 16 cycles per wave-wide access whatever its width: as 2-byte stores a
+// 256 x 256 bf16 tile spent 7 us there.  Rows of C may start at any element; EXACT: the block lies inside C.
+// bj: added to the lane's column (lane % 32).
+template <bool EXACT, typename OUT>
+__device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* tp, OUT* __restrict__ C, int64_t ldc, int row0,
+                                            int col0, int M, int N, int lane) {
+#pragma unroll
+    for (int v = 0; v < 16; ++v)
+        tp[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * kTransposePitch + (lane & 31)] = acc[v] + bj;
+    constexpr int RUN = 16 / sizeof(OUT), LPR = 32 / RUN, RPI = 64 / LPR;   // elements per run, lanes per row, rows per access
+#pragma unroll
+    for (int i = 0; i < 32 / RPI; ++i) {
+        const int row = RPI * i + lane / LPR, col = RUN * (lane % LPR);
+        const float* src = tp + row * kTransposePitch + col;
+        const f32x4 lo = *reinterpret_cast<const f32x4*>(src);
+        u32x4 o;
+        if constexpr (sizeof(OUT) == 4) {
+            o = __builtin_bit_cast(u32x4, lo);
+        } else {
+            const f32x4 hi = *reinterpret_cast<const f32x4*>(src + 4);
+            o = u32x4{pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]), pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3])};
+        }
+        OUT* dst = C + (int64_t)(row0 + row) * ldc + col0 + col;
+        const int left = EXACT ? RUN : (row0 + row < M ? N - (col0 + col) : 0);
+        if (left >= RUN) {
+            if constexpr (sizeof(OUT) == 4) *reinterpret_cast<u32x4_align4*>(dst) = o;
+            else *reinterpret_cast<u32x4_align2*>(dst) = o;
+        } else {
+#pragma unroll
+            for (int e = 0; e < RUN - 1; ++e)
+                if (e < left) {
+                    if constexpr (sizeof(OUT) == 4) dst[e] = __builtin_bit_cast(float, (uint32_t)o[e & 3]);
+                    else dst[e] = (OUT)(o[e >> 1] >> (16 * (e & 1)));
+                }
+        }
+    }
+}
+
 // C[M][N] (bf16 or fp32) = sum_k A(i, k) B(k, j) (+ bias[j]); A's x index runs over the rows of C, B's over its
-// columns.
-// Two LDS stages: while the MFMAs of step kt read stage kt & 1, the operands of step kt + 1 (fetched into registers
-// before those MFMAs) are written to the other stage; one barrier per step.
-// WM: wave rows of the workgroup (2: 128-row tile, 256 threads, two workgroups per CU; 4: 256-row tile, 512 threads,
-// one workgroup per CU - the B tile, and with it the dequantization of an INT8 B operand, is then shared by twice as
-// many MFMAs).
-template <int AL, int BL, bool EXACT, typename OUT, int TN, int BK, int WM = 2>
+// columns.  Tile TM = 32 MB WM rows x TN columns, a wave computes 32 MB x TN / 2.
+// Two LDS stages and two register sets: while the MFMAs of step kt read stage kt & 1, the operands of step kt + 1 are
+// written to the other stage and those of step kt + 2 are fetched; one barrier per step.
+// WM: wave rows of the workgroup (2: 256 threads, several workgroups per CU; 4: 512 threads, one workgroup per CU - the
+// B tile, and with it the dequantization of an INT8 B operand, is then shared by twice as many MFMAs).
+// EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a
+// workgroup whose tile lies inside runs unchecked too, but for the last, partial step.
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM = 2>
 __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOperand A, LinOperand B,
                                                       const uint16_t* __restrict__ bias,
                                                       OUT* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
                                                       LinBatch batch) {
-    constexpr int TM = 64 * WM, NT = 128 * WM;
-    using SA = LinStage<AL, TM, BK, EXACT, NT>;
-    using SB = LinStage<BL, TN, BK, EXACT, NT>;
+    constexpr int TM = 32 * MB * WM, NT = 128 * WM;
+    using SA = LinStage<AL, TM, BK, NT>;
+    using SB = LinStage<BL, TN, BK, NT>;
     A.base = batch.a[blockIdx.y];
     B.base = static_cast<const char*>(B.base) + batch.strideB_bytes * blockIdx.y;
     C += batch.strideC * blockIdx.y;
     const int64_t ldc = batch.ldc ? batch.ldc : N;
-    __shared__ __attribute__((aligned(16))) uint16_t At[2][SA::ELEMS];
-    __shared__ __attribute__((aligned(16))) uint16_t Bt[2][SB::ELEMS];
+    constexpr int STAGING = 2 * (SA::ELEMS + SB::ELEMS), TRANSPOSE = 2 * WM * kTransposeFloats * 2;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[STAGING > TRANSPOSE ? STAGING : TRANSPOSE];
+    auto At = [&](int stage) { return smem + stage * SA::ELEMS; };
+    auto Bt = [&](int stage) { return smem + 2 * SA::ELEMS + stage * SB::ELEMS; };
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
     // Each XCD (own L2) takes a contiguous range of tiles, and tiles are numbered in strips eight row tiles tall,
@@ -155,9 +206,9 @@ __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOper
     const int strip = (int)(tile / (uint32_t)(kLinStrip * tiles_n)), in_strip = (int)(tile % (uint32_t)(kLinStrip * tiles_n));
     const int strip_rows = min(kLinStrip, tiles_m - strip * kLinStrip);
     const int i0 = (strip * kLinStrip + in_strip % strip_rows) * TM, j0 = (in_strip / strip_rows) * TN;
-    SA sa;
-    SB sb;
-    constexpr int MB = 2, NB = TN / 64;        // 32 x 32 blocks of the wave's 64 x TN/2
+    SA sa[2];
+    SB sb[2];
+    constexpr int NB = TN / 64;                // 32 x 32 blocks of a wave: MB x NB
     f32x16 acc[MB][NB];
 #pragma unroll
     for (int a = 0; a < MB; ++a)
@@ -165,58 +216,91 @@ __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOper
         for (int b = 0; b < NB; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-    const int KT = (K + BK - 1) / BK;
-    sa.fetch(A, i0, M, 0, K);
-    sb.fetch(B, j0, N, 0, K);
-    sa.commit(At[0]);
-    sb.commit(Bt[0]);
-    __syncthreads();
-    for (int kt = 0; kt < KT; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < KT;
-        if (more) {
-            sa.fetch(A, i0, M, (kt + 1) * BK, K);
-            sb.fetch(B, j0, N, (kt + 1) * BK, K);
-        }
-        __builtin_amdgcn_s_setprio(kMfmaPrio);     // the wave in its MFMA phase goes first (two workgroups per CU)
+    auto mfma_step = [&](int stage) {
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             bf16x8 af[MB], bf[NB];
 #pragma unroll
-            for (int a = 0; a < MB; ++a) af[a] = SA::frag(At[cur], wm * 64 + a * 32, kk, lane);
+            for (int a = 0; a < MB; ++a) af[a] = SA::frag(At(stage), wm * 32 * MB + a * 32, kk, lane);
 #pragma unroll
-            for (int b = 0; b < NB; ++b) bf[b] = SB::frag(Bt[cur], wn * (TN / 2) + b * 32, kk, lane);
+            for (int b = 0; b < NB; ++b) bf[b] = SB::frag(Bt(stage), wn * (TN / 2) + b * 32, kk, lane);
 #pragma unroll
             for (int a = 0; a < MB; ++a)
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);     // fragments of one sub-step at a time
         }
-        __builtin_amdgcn_s_setprio(0);
-        if (more) {
-            sa.commit(At[cur ^ 1]);
-            sb.commit(Bt[cur ^ 1]);
+    };
+    // The KT steps from k = 0 on, every chunk of them fetched under FETCH's terms.
+    auto steps = [&](auto fetch_mode, int KT) {
+        constexpr int FETCH = decltype(fetch_mode)::value;
+        auto fetch = [&](int kt, int set) {
+            const int k0 = min(kt, KT - 1) * BK;   // past the end: the last slab again, never consumed
+            sa[set].template fetch<FETCH>(A, i0, M, k0, K);
+            sb[set].template fetch<FETCH>(B, j0, N, k0, K);
+        };
+        fetch(0, 0);
+        fetch(1, 1);
+        sa[0].commit(At(0));
+        sb[0].commit(Bt(0));
+        lds_barrier();
+        for (int kt = 0; kt + 1 < KT; kt += 2) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                // one scheduling region: fragment reads, the fetches of step kt + u + 2 and the commit of step kt + u + 1
+                // between the MFMAs
+                mfma_step(u);
+                fetch(kt + u + 2, u);
+                sa[u ^ 1].commit(At(u ^ 1));
+                sb[u ^ 1].commit(Bt(u ^ 1));
+                constexpr int READS = MB * (SA::kFast ? 1 : 2) + NB * (SB::kFast ? 1 : 2), MFMAS = MB * NB;
+                __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
+#pragma unroll
+                for (int i = 0; i < BK / 16 * MFMAS; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x100, (READS + MFMAS - 1) / MFMAS, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                }
+                lds_barrier();
+            }
         }
-        __syncthreads();
+        if (KT & 1) {
+            mfma_step(0);
+            lds_barrier();
+        }
+    };
+    bool inside = true;
+    if constexpr (EXACT) {
+        steps(std::integral_constant<int, kFetchAligned>(), K / BK);
+    } else {
+        inside = i0 + TM <= M && j0 + TN <= N;
+        const int whole = K / BK;
+        if (!inside) {
+            steps(std::integral_constant<int, kFetchGuarded>(), (K + BK - 1) / BK);
+        } else {
+            if (whole > 0) steps(std::integral_constant<int, kFetchInside>(), whole);
+            if (whole * BK < K) {
+                sa[0].template fetch<kFetchGuarded>(A, i0, M, whole * BK, K);
+                sb[0].template fetch<kFetchGuarded>(B, j0, N, whole * BK, K);
+                sa[0].commit(At(0));
+                sb[0].commit(Bt(0));
+                lds_barrier();
+                mfma_step(0);
+                lds_barrier();
+            }
+        }
     }
-    // register v of a 32 x 32 block: row 8 (v / 4) + 4 (l / 32) + v % 4 (A's index), column l % 32 (B's index)
+    float* tp = reinterpret_cast<float*>(smem) + wave * kTransposeFloats;
 #pragma unroll
     for (int a = 0; a < MB; ++a)
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const int col = j0 + wn * (TN / 2) + b * 32 + (lane & 31);
-            const bool col_ok = EXACT || col < N;
-            const float bj = (bias != nullptr && col_ok) ? __builtin_bit_cast(float, (uint32_t)bias[col] << 16) : 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = i0 + wm * 64 + a * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const float x = acc[a][b][v];
-                if (EXACT || (row < M && col_ok)) {
-                    if constexpr (sizeof(OUT) == 4) C[(int64_t)row * ldc + col] = x + bj;
-                    else C[(int64_t)row * ldc + col] = to_bf16(x + bj);
-                }
-            }
+            const int row0 = i0 + wm * 32 * MB + a * 32, col0 = j0 + wn * (TN / 2) + b * 32, col = col0 + (lane & 31);
+            const float bj = (bias != nullptr && (EXACT || col < N)) ? __builtin_bit_cast(float, (uint32_t)bias[col] << 16) : 0.f;
+            if (EXACT || inside) store_block<true>(acc[a][b], bj, tp, C, ldc, row0, col0, M, N, lane);
+            else store_block<false>(acc[a][b], bj, tp, C, ldc, row0, col0, M, N, lane);
         }
 }
 
@@ -301,19 +385,13 @@ __global__ __launch_bounds__(256, 3) void k_gemm_kslow_direct(const uint16_t* __
         landed();
         __syncthreads();
     }
+    float* tp = reinterpret_cast<float*>(wave < 2 ? As[0] : Bs[0]) + (wave & 1) * kTransposeFloats;
+    static_assert(2 * AD::STAGE >= 2 * kTransposeFloats * 2, "two waves' transpose buffers fit in the A stages");
 #pragma unroll
     for (int a = 0; a < MB; ++a)
 #pragma unroll
-        for (int b = 0; b < NB; ++b) {
-            const int col = j0 + wn * 128 + b * 32 + (lane & 31);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = i0 + wm * 64 + a * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const float x = acc[a][b][v];
-                if constexpr (sizeof(OUT) == 4) C[(int64_t)row * ldc + col] = x;
-                else C[(int64_t)row * ldc + col] = to_bf16(x);
-            }
-        }
+        for (int b = 0; b < NB; ++b)
+            store_block<true>(acc[a][b], 0.f, tp, C, ldc, i0 + wm * 64 + a * 32, j0 + wn * 128 + b * 32, M, N, lane);
 }
 
 // bf16 [X][64] operand tile (rows along the contraction index, 128 bytes each) filled by direct global -> LDS loads:
@@ -354,7 +432,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_kfast_direct(LinOperand A, LinO
     constexpr int TM = 256, TN = 256, BK = 64, NW = 8;
     static_assert(BL == kInt8KFast || BL == kInt8ZKFast, "B: INT8 with the contraction index fast");
     using AD = KFastDirect<TM, NW>;
-    using SB = LinStage<BL, TN, BK, true, 512>;
+    using SB = LinStage<BL, TN, BK, 512>;
     __shared__ __attribute__((aligned(16))) uint16_t As[2][AD::ELEMS];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[2][SB::ELEMS];
     A.base = batch.a[blockIdx.y];
@@ -378,7 +456,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_kfast_direct(LinOperand A, LinO
             const int row0 = (wave * AD::PER + p) * 8;
             buffer_load_lds16(ra, As[stage] + row0 * AD::ROW, a_byte, 2u * (uint32_t)(row0 * A.ld));
         }
-        sb.fetch(B, j0, N, kt * BK, K);
+        sb.template fetch<kFetchAligned>(B, j0, N, kt * BK, K);
     };
     constexpr int MB = 2, NB = 4;
     f32x16 acc[MB][NB];
@@ -423,26 +501,22 @@ __global__ __launch_bounds__(512, 1) void k_gemm_kfast_direct(LinOperand A, LinO
         landed();
         __syncthreads();
     }
+    float* tp = reinterpret_cast<float*>(As[0]) + wave * kTransposeFloats;
+    static_assert(2 * AD::ELEMS >= NW * kTransposeFloats * 2, "the transpose buffers fit in the A stages");
 #pragma unroll
     for (int a = 0; a < MB; ++a)
 #pragma unroll
         for (int b = 0; b < NB; ++b) {
-            const int col = j0 + wn * 128 + b * 32 + (lane & 31);
-            const float bj = bias != nullptr ? __builtin_bit_cast(float, (uint32_t)bias[col] << 16) : 0.f;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int row = i0 + wm * 64 + a * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-                const float x = acc[a][b][v] + bj;
-                if constexpr (sizeof(OUT) == 4) C[(int64_t)row * ldc + col] = x;
-                else C[(int64_t)row * ldc + col] = to_bf16(x);
-            }
+            const int col0 = j0 + wn * 128 + b * 32;
+            const float bj = bias != nullptr ? __builtin_bit_cast(float, (uint32_t)bias[col0 + (lane & 31)] << 16) : 0.f;
+            store_block<true>(acc[a][b], bj, tp, C, ldc, i0 + wm * 64 + a * 32, col0, M, N, lane);
         }
 }
 
-template <int AL, int BL, typename OUT, int TN, int BK, int WM = 2>
+template <int AL, int BL, typename OUT, int MB, int TN, int BK, int WM = 2>
 static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M,
                                    int64_t N, int64_t K, hipStream_t st, const LinBatch* many, int count, int64_t ldc) {
-    constexpr int TM = 64 * WM;
+    constexpr int TM = 32 * MB * WM;
     const int64_t tiles_m = (M + TM - 1) / TM, tiles_n = (N + TN - 1) / TN;
     const dim3 grid((unsigned)((tiles_m * tiles_n + 7) / 8 * 8), (unsigned)count);   // x: a multiple of the 8 XCDs
     LinBatch batch;
@@ -457,10 +531,10 @@ static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, con
     // no checks at all when every tile and every step is whole and rows start 16-byte aligned
     const bool exact = M % TM == 0 && N % TN == 0 && K % BK == 0 && A.ld % 8 == 0 && B.ld % 16 == 0;
     if (exact)
-        hipLaunchKernelGGL((k_tile_gemm<AL, BL, true, OUT, TN, BK, WM>), grid, dim3(128 * WM), 0, st, A, B, bias, C, (int)M,
+        hipLaunchKernelGGL((k_tile_gemm<AL, BL, true, OUT, MB, TN, BK, WM>), grid, dim3(128 * WM), 0, st, A, B, bias, C, (int)M,
                            (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
     else
-        hipLaunchKernelGGL((k_tile_gemm<AL, BL, false, OUT, TN, BK, WM>), grid, dim3(128 * WM), 0, st, A, B, bias, C, (int)M,
+        hipLaunchKernelGGL((k_tile_gemm<AL, BL, false, OUT, MB, TN, BK, WM>), grid, dim3(128 * WM), 0, st, A, B, bias, C, (int)M,
                            (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
 }
 
@@ -470,9 +544,16 @@ static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, con
 //    INT8 B - is shared by twice as many MFMAs as in a 128-row tile, global traffic per MFMA halves, and 64-deep
 //    steps fetch whole cache lines of operands whose rows run along k.  Forward pass 2.24 -> 1.87, grad_input
 //    1.82 -> 1.66 (256 x 256 x 32 with eight waves: 1.72; 256 x 128 x 64: forward unchanged at 2.24).
-//  * otherwise two workgroups of four waves per CU: 128 x 128 x 64 when both operands have k fast (2.28 against 2.37
-//    for 128 x 256 x 32 and 2.80 for 128 x 128 x 32 on the forward pass), 128 x 256 x 32 when that fills the chip,
-//    128 x 128 x 32 for small outputs.
+//  * otherwise four waves: 128 x 128 x 64 when an operand is INT8 or both have k fast, 128 x 256 x 32 (when that fills
+//    the chip twice) or 128 x 128 x 32 for grad_W;
+//  * 64 x 64 x 64, four waves of one 32 x 32 block each, where 128 x 128 tiles would leave CUs idle: a K step of a lone
+//    workgroup is a serial chain (fragments, MFMAs, commit, barrier), 1.2 us for 128 x 128 x 64 before the commit and the
+//    fetches went between the MFMAs.  Measured (us, 64 / 128): forward, 256 tokens, 768 -> 2048 (32 tiles of 128 x 128)
+//    13.6 / 16.6, 256 x 4096 -> 11008 (172) 48 / 51, 1024 x 4096 -> 4096 (256) 65 / 54; grad_input, 1000 x 2048 -> 2048
+//    (128) 29 / 41, 256 x 4096 -> 11008 (172) 53 / 47; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 2736 x 1024 (176)
+//    40 / 62, 1000 tokens, 2048 x 2048 (256) 21 / 17.
+// One decoder layer, forward and backward: 256 tokens of the 130M model 331 -> 189 us, 1000 of the 1B model 1430 -> 982,
+// 4096 of the 7B model 5155 -> 4790 (that by the 16-byte stores of C).
 template <int AL, int BL, typename OUT>
 // ldc: row pitch of C in elements (0: N).
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
@@ -511,16 +592,19 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
                     return check_launch();
                 }
             }
-            launch_tile_gemm_shape<AL, BL, OUT, 256, 64, 4>(A, B, bias, C, M, N, K, st, many, count, ldc);
+            launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 64, 4>(A, B, bias, C, M, N, K, st, many, count, ldc);
             return check_launch();
         }
     }
-    if constexpr (both_fast)
-        launch_tile_gemm_shape<AL, BL, OUT, 128, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128) * count;
+    if (tiles128 < (int8_b && !both_fast ? 160 : 256))
+        launch_tile_gemm_shape<AL, BL, OUT, 1, 64, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    else if constexpr (both_fast || int8_b)
+        launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
     else if (((M + kLinTM - 1) / kLinTM) * ((N + 255) / 256) * count >= 512)
-        launch_tile_gemm_shape<AL, BL, OUT, 256, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
+        launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
     else
-        launch_tile_gemm_shape<AL, BL, OUT, 128, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
+        launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
     return check_launch();
 }
 

@@ -83,6 +83,16 @@ def test_backward(tokens, m, n):
     assert torch.equal(dx2.view(torch.int16), dx.view(torch.int16)) and torch.equal(G2.view(torch.int16), G.view(torch.int16))
 
 
+@pytest.mark.parametrize("tokens,m,n", [
+    (63, 65, 130), (65, 127, 63), (64, 192, 128),              # around one 64 x 64 tile and one 64-deep step
+    (2100, 2190, 200), (2180, 200, 2111), (200, 2180, 2112),   # 128-row tiles of the three products, edges everywhere
+    (4100, 4110, 72), (4096, 72, 4111),                        # 256 x 256 tiles that are not whole
+])
+def test_tile_configurations(tokens, m, n):
+    test_forward(tokens, m, n)
+    test_backward(tokens, m, n)
+
+
 def test_gradient_feeds_the_optimizer_step():
     """The layer's grad_W, as stored, is a valid gradient input of the step: projecting it gives what the oracle
     gives for the same bits."""
