@@ -93,7 +93,8 @@ int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, f
         using C = decltype(c);
         return with_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), [&](auto mode) {
             const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles = tr * (uint32_t)((n + C::BN - 1) / C::BN);
-            hipLaunchKernelGGL(QG_PROJ(k_project_adam, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream, Pq, Ps, G, R, M,
+            // (for three workgroups per CU the 128 x 256 instance of this kernel spills)
+            hipLaunchKernelGGL((k_project_adam<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, mode(), C::NS == 2 ? 2 : C::kWg[mode()]>), dim3(grid8(tiles)), dim3(C::NT), 0, stream, Pq, Ps, G, R, M,
                                V, N, (int)m, (int)n, (int)ld, (int)r, tr, tiles, coef);
             return check_launch();
         });

@@ -645,6 +645,13 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam(
                                                      (int)(tile / tiles_r) * BN, smem, M, V, N, &coef);
 }
 
+// A pointer read from the plan is a generic one to the compiler, which then emits flat accesses: slower than global ones,
+// and they count as LDS accesses too, so every wait for a fragment read also waits for them.
+template <typename T>
+__device__ __forceinline__ T* as_global(T* p) {
+    return (T*)(__attribute__((address_space(1))) T*)reinterpret_cast<uintptr_t>(p);
+}
+
 template <typename F>
 __device__ __forceinline__ int plan_find(const PlanMatrix* mats, int count, uint32_t tile, F first_tile) {
     int lo = 0, hi = count - 1;
@@ -664,7 +671,7 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_many(c
     const PlanMatrix* mats = plan_matrices(plan) + first;
     const PlanMatrix& d = mats[plan_find(mats, count, tile, [](const PlanMatrix& x) { return x.proj_tile0; })];
     const uint32_t local = tile - d.proj_tile0;
-    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(d.Pq, d.Ps, d.G, d.R, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(as_global(d.Pq), as_global(d.Ps), as_global(d.G), as_global(d.R), (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
                                                (int)(local % d.proj_tiles_r) * BM,
                                                (int)(local / d.proj_tiles_r) * BN, smem);
 }
@@ -703,9 +710,10 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam_m
     const PlanMatrix* mats = plan_matrices(plan) + first;
     const PlanMatrix& d = mats[plan_find(mats, count, tile, [](const PlanMatrix& x) { return x.proj_tile0; })];
     const uint32_t local = tile - d.proj_tile0;
-    project_tile<BM, BN, BK, WGM, WGN, NS, MODE, true>(d.Pq, d.Ps, d.G, write_R ? d.R : nullptr, (int)d.m, (int)d.n,
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE, true>(as_global(d.Pq), as_global(d.Ps), as_global(d.G), write_R ? as_global(d.R) : nullptr, (int)d.m, (int)d.n,
                                                      (int)d.ld, (int)d.r, (int)(local % d.proj_tiles_r) * BM,
-                                                     (int)(local / d.proj_tiles_r) * BN, smem, d.M, d.V, d.N, &coef);
+                                                     (int)(local / d.proj_tiles_r) * BN, smem, as_global(d.M), as_global(d.V),
+                                                         as_global(d.N), &coef);
 }
 
 // ============================================================================
@@ -1187,7 +1195,8 @@ __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject_ma
     const uint32_t strip = local / (kBpStrip * tiles_n), in_strip = local % (kBpStrip * tiles_n);
     const uint32_t strip_rows = min((uint32_t)kBpStrip, d.bp_tiles_m - strip * kBpStrip);
     const uint32_t tile_m = strip * kBpStrip + in_strip % strip_rows, tile_n = in_strip / strip_rows;
-    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, false, W_PREFETCH, ZP>(d.Pq, d.Ps, d.N, d.Wq, d.Ws, d.Wz, nullptr, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
+    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, false, W_PREFETCH, ZP>(
+        as_global(d.Pq), as_global(d.Ps), as_global(d.N), as_global(d.Wq), as_global(d.Ws), as_global(d.Wz), nullptr, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
                                                 (int)tile_m * BMm, (int)tile_n, alpha, lr, key, smem);
 }
 
