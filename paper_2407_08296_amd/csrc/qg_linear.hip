@@ -65,19 +65,10 @@ extern "C" int qg_int8_linear_backward_ld(const uint16_t* dy_bf16, const uint16_
         (dx_bf16 && !aligned16(dx_bf16)) || (G_bf16 && !aligned16(G_bf16)))
         return QG_ERR_ALIGN;
     const int sg = (int)((n + kGroup - 1) / kGroup);
-    if (dx_bf16) {   // dx[t][i] = sum_o dy[t][o] W[o][i]
-        const LinOperand A = {dy_bf16, nullptr, ld_m, 0}, B = {Wq, Ws, ld_n, sg};
-        if (int e = launch_tile_gemm<kBf16KFast, kInt8KSlow, uint16_t>(A, B, nullptr, dx_bf16, tokens, n, m, (hipStream_t)stream,
-                                                                       nullptr, 1, ld_n))
-            return e;
-    }
-    if (G_bf16) {    // G[o][i] = sum_t dy[t][o] x[t][i]
-        const LinOperand A = {dy_bf16, nullptr, ld_m, 0}, B = {x_bf16, nullptr, ld_n, 0};
-        if (int e = launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A, B, nullptr, G_bf16, m, n, tokens, (hipStream_t)stream,
-                                                                       nullptr, 1, ld_n))
-            return e;
-    }
-    return QG_OK;
+    // dx[t][i] = sum_o dy[t][o] W[o][i],  G[o][i] = sum_t dy[t][o] x[t][i]
+    const LinOperand dy = {dy_bf16, nullptr, ld_m, 0}, W = {Wq, Ws, ld_n, sg}, x = {x_bf16, nullptr, ld_n, 0};
+    return launch_linear_backward<kInt8KSlow>(dy, W, dx_bf16, tokens, n, m, ld_n, dy, x, G_bf16, m, n, tokens, ld_n,
+                                              (hipStream_t)stream);
 }
 
 extern "C" int qg_int8_linear_backward(const uint16_t* dy_bf16, const uint16_t* x_bf16, const int8_t* Wq, const float* Ws,
@@ -113,15 +104,10 @@ extern "C" int qg_int8_linear_t_backward(const uint16_t* dy_bf16, const uint16_t
         (dx_bf16 && !aligned16(dx_bf16)) || (GS_bf16 && !aligned16(GS_bf16)))
         return QG_ERR_ALIGN;
     const int sg = (int)((m + kGroup - 1) / kGroup);
-    if (dx_bf16) {   // dx[t][i] = sum_o dy[t][o] S[i][o]
-        const LinOperand A = {dy_bf16, nullptr, m, 0}, B = {Sq, Ss, m, sg};
-        if (int e = launch_tile_gemm<kBf16KFast, kInt8KFast, uint16_t>(A, B, nullptr, dx_bf16, tokens, n, m, (hipStream_t)stream)) return e;
-    }
-    if (GS_bf16) {   // G_S[i][o] = sum_t x[t][i] dy[t][o]
-        const LinOperand A = {x_bf16, nullptr, n, 0}, B = {dy_bf16, nullptr, m, 0};
-        if (int e = launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A, B, nullptr, GS_bf16, n, m, tokens, (hipStream_t)stream)) return e;
-    }
-    return QG_OK;
+    // dx[t][i] = sum_o dy[t][o] S[i][o],  G_S[i][o] = sum_t x[t][i] dy[t][o]
+    const LinOperand dy = {dy_bf16, nullptr, m, 0}, S = {Sq, Ss, m, sg}, x = {x_bf16, nullptr, n, 0};
+    return launch_linear_backward<kInt8KFast>(dy, S, dx_bf16, tokens, n, m, n, x, dy, GS_bf16, n, m, tokens, m,
+                                              (hipStream_t)stream);
 }
 
 // The layer on a zero-point weight (Sec. 3.1 eq. with z; Appendix A: W = (W_q - zeros) * scales): the same products,
@@ -149,15 +135,9 @@ extern "C" int qg_int8_linear_zp_backward(const uint16_t* dy_bf16, const uint16_
         (Wz && !aligned16(Wz)) || (dx_bf16 && !aligned16(dx_bf16)) || (G_bf16 && !aligned16(G_bf16)))
         return QG_ERR_ALIGN;
     const int sg = (int)((n + kGroup - 1) / kGroup);
-    if (dx_bf16) {
-        const LinOperand A = {dy_bf16, nullptr, m, 0}, B = {Wq, Ws, n, sg, Wz};
-        if (int e = launch_tile_gemm<kBf16KFast, kInt8ZKSlow, uint16_t>(A, B, nullptr, dx_bf16, tokens, n, m, (hipStream_t)stream)) return e;
-    }
-    if (G_bf16) {
-        const LinOperand A = {dy_bf16, nullptr, m, 0}, B = {x_bf16, nullptr, n, 0};
-        if (int e = launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A, B, nullptr, G_bf16, m, n, tokens, (hipStream_t)stream)) return e;
-    }
-    return QG_OK;
+    const LinOperand dy = {dy_bf16, nullptr, m, 0}, W = {Wq, Ws, n, sg, Wz}, x = {x_bf16, nullptr, n, 0};
+    return launch_linear_backward<kInt8ZKSlow>(dy, W, dx_bf16, tokens, n, m, n, dy, x, G_bf16, m, n, tokens, n,
+                                               (hipStream_t)stream);
 }
 
 // Zero-point weight stored transposed (S = W^T with zero points along each row of S): the two variants combined.
@@ -184,13 +164,7 @@ extern "C" int qg_int8_linear_t_zp_backward(const uint16_t* dy_bf16, const uint1
         (Sz && !aligned16(Sz)) || (dx_bf16 && !aligned16(dx_bf16)) || (GS_bf16 && !aligned16(GS_bf16)))
         return QG_ERR_ALIGN;
     const int sg = (int)((m + kGroup - 1) / kGroup);
-    if (dx_bf16) {
-        const LinOperand A = {dy_bf16, nullptr, m, 0}, B = {Sq, Ss, m, sg, Sz};
-        if (int e = launch_tile_gemm<kBf16KFast, kInt8ZKFast, uint16_t>(A, B, nullptr, dx_bf16, tokens, n, m, (hipStream_t)stream)) return e;
-    }
-    if (GS_bf16) {
-        const LinOperand A = {x_bf16, nullptr, n, 0}, B = {dy_bf16, nullptr, m, 0};
-        if (int e = launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A, B, nullptr, GS_bf16, n, m, tokens, (hipStream_t)stream)) return e;
-    }
-    return QG_OK;
+    const LinOperand dy = {dy_bf16, nullptr, m, 0}, S = {Sq, Ss, m, sg, Sz}, x = {x_bf16, nullptr, n, 0};
+    return launch_linear_backward<kInt8ZKFast>(dy, S, dx_bf16, tokens, n, m, n, x, dy, GS_bf16, n, m, tokens, m,
+                                               (hipStream_t)stream);
 }

@@ -181,28 +181,29 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* 
 // B tile, and with it the dequantization of an INT8 B operand, is then shared by twice as many MFMAs).
 // EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a
 // workgroup whose tile lies inside runs unchecked too, but for the last, partial step.
-template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM = 2>
-__global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOperand A, LinOperand B,
-                                                      const uint16_t* __restrict__ bias,
-                                                      OUT* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
-                                                      LinBatch batch) {
-    constexpr int TM = 32 * MB * WM, NT = 128 * WM;
+template <int AL, int BL, int MB, int TN, int BK, int WM>
+struct TileGemm {
+    static constexpr int TM = 32 * MB * WM, NT = 128 * WM;
     using SA = LinStage<AL, TM, BK, NT>;
     using SB = LinStage<BL, TN, BK, NT>;
-    A.base = batch.a[blockIdx.y];
-    B.base = static_cast<const char*>(B.base) + batch.strideB_bytes * blockIdx.y;
-    C += batch.strideC * blockIdx.y;
-    const int64_t ldc = batch.ldc ? batch.ldc : N;
-    constexpr int STAGING = 2 * (SA::ELEMS + SB::ELEMS), TRANSPOSE = 2 * WM * kTransposeFloats * 2;
-    __shared__ __attribute__((aligned(16))) uint16_t smem[STAGING > TRANSPOSE ? STAGING : TRANSPOSE];
+    static constexpr int STAGING = 2 * (SA::ELEMS + SB::ELEMS), TRANSPOSE = 2 * WM * kTransposeFloats * 2;
+    static constexpr int SMEM = STAGING > TRANSPOSE ? STAGING : TRANSPOSE;   // uint16 elements
+};
+
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM>
+__device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* __restrict__ bias,
+                                          OUT* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n,
+                                          uint32_t tile, uint16_t* smem) {
+    using T = TileGemm<AL, BL, MB, TN, BK, WM>;
+    using SA = typename T::SA;
+    using SB = typename T::SB;
+    constexpr int TM = T::TM;
     auto At = [&](int stage) { return smem + stage * SA::ELEMS; };
     auto Bt = [&](int stage) { return smem + 2 * SA::ELEMS + stage * SB::ELEMS; };
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
-    // Each XCD (own L2) takes a contiguous range of tiles, and tiles are numbered in strips eight row tiles tall,
-    // column tile by column tile: the tiles in flight on an XCD share eight A panels and a few B panels.
-    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
-    if (tile >= (uint32_t)(tiles_m * tiles_n)) return;
+    // Tiles are numbered in strips eight row tiles tall, column tile by column tile: the tiles in flight on an XCD share
+    // eight A panels and a few B panels.
     const int strip = (int)(tile / (uint32_t)(kLinStrip * tiles_n)), in_strip = (int)(tile % (uint32_t)(kLinStrip * tiles_n));
     const int strip_rows = min(kLinStrip, tiles_m - strip * kLinStrip);
     const int i0 = (strip * kLinStrip + in_strip % strip_rows) * TM, j0 = (in_strip / strip_rows) * TN;
@@ -302,6 +303,48 @@ __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOper
             if (EXACT || inside) store_block<true>(acc[a][b], bj, tp, C, ldc, row0, col0, M, N, lane);
             else store_block<false>(acc[a][b], bj, tp, C, ldc, row0, col0, M, N, lane);
         }
+}
+
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM = 2>
+__global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOperand A, LinOperand B,
+                                                      const uint16_t* __restrict__ bias,
+                                                      OUT* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
+                                                      LinBatch batch) {
+    __shared__ __attribute__((aligned(16))) uint16_t smem[TileGemm<AL, BL, MB, TN, BK, WM>::SMEM];
+    A.base = batch.a[blockIdx.y];
+    B.base = static_cast<const char*>(B.base) + batch.strideB_bytes * blockIdx.y;
+    // each XCD (own L2) takes a contiguous range of tiles
+    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    if (tile >= (uint32_t)(tiles_m * tiles_n)) return;
+    tile_gemm<AL, BL, EXACT, OUT, MB, TN, BK, WM>(A, B, bias, C + batch.strideC * blockIdx.y, batch.ldc ? batch.ldc : N, M, N, K,
+                                                  tiles_m, tiles_n, tile, smem);
+}
+
+// Two products in one launch, 64 x 64 tiles: the two of a backward pass, which do not depend on each other, where each
+// alone leaves most of the chip idle (one after the other their times add up).  The first grid0 workgroups run the
+// first (A bf16 with k fast, B the weight), the others the second (both bf16 with k slow).
+struct LinProduct {
+    LinOperand A, B;
+    uint16_t* C;
+    int64_t ldc;
+    int M, N, K, tiles_m, tiles_n;
+};
+template <int BL, bool EXACT>
+__global__ __launch_bounds__(256, 2) void k_tile_gemm_pair(LinProduct p0, LinProduct p1, uint32_t grid0) {
+    using T0 = TileGemm<kBf16KFast, BL, 1, 64, 64, 2>;
+    using T1 = TileGemm<kBf16KSlow, kBf16KSlow, 1, 64, 64, 2>;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[T0::SMEM > T1::SMEM ? T0::SMEM : T1::SMEM];
+    if (blockIdx.x < grid0) {
+        const uint32_t tile = xcd_tile(blockIdx.x, grid0);
+        if (tile >= (uint32_t)(p0.tiles_m * p0.tiles_n)) return;
+        tile_gemm<kBf16KFast, BL, EXACT, uint16_t, 1, 64, 64, 2>(p0.A, p0.B, nullptr, p0.C, p0.ldc, p0.M, p0.N, p0.K, p0.tiles_m,
+                                                               p0.tiles_n, tile, smem);
+    } else {
+        const uint32_t tile = xcd_tile(blockIdx.x - grid0, gridDim.x - grid0);
+        if (tile >= (uint32_t)(p1.tiles_m * p1.tiles_n)) return;
+        tile_gemm<kBf16KSlow, kBf16KSlow, EXACT, uint16_t, 1, 64, 64, 2>(p1.A, p1.B, nullptr, p1.C, p1.ldc, p1.M, p1.N, p1.K,
+                                                                       p1.tiles_m, p1.tiles_n, tile, smem);
+    }
 }
 
 // Both operands bf16 with the contraction index as their slow index, whole tiles and aligned rows (grad_W at the
@@ -538,6 +581,13 @@ static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, con
                            (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
 }
 
+// Whether a product runs 64 x 64 tiles (see launch_tile_gemm).
+template <int AL, int BL>
+static bool lin_small(int64_t M, int64_t N, int count) {
+    constexpr bool slow_weight = BL == kInt8KSlow || BL == kInt8ZKSlow;
+    return ((M + 127) / 128) * ((N + 127) / 128) * count < (slow_weight ? 160 : 256);
+}
+
 // Tile shape, from measurements on the linear layer of the LLaMA-7B shapes (ms per decoder layer at 4096 tokens):
 //  * large outputs with an INT8 B operand, or with the contraction index fast in both operands: 256 x 256 tiles with
 //    64-deep steps, eight waves, one workgroup per CU (144 KB of LDS).  The B tile - and the dequantization of an
@@ -552,7 +602,7 @@ static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, con
 //    13.6 / 16.6, 256 x 4096 -> 11008 (172) 48 / 51, 1024 x 4096 -> 4096 (256) 65 / 54; grad_input, 1000 x 2048 -> 2048
 //    (128) 29 / 41, 256 x 4096 -> 11008 (172) 53 / 47; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 2736 x 1024 (176)
 //    40 / 62, 1000 tokens, 2048 x 2048 (256) 21 / 17.
-// One decoder layer, forward and backward: 256 tokens of the 130M model 331 -> 189 us, 1000 of the 1B model 1430 -> 982,
+// One decoder layer, forward and backward: 256 tokens of the 130M model 331 -> 181 us, 1000 of the 1B model 1430 -> 982,
 // 4096 of the 7B model 5155 -> 4790 (that by the 16-byte stores of C).
 template <int AL, int BL, typename OUT>
 // ldc: row pitch of C in elements (0: N).
@@ -596,8 +646,7 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
             return check_launch();
         }
     }
-    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128) * count;
-    if (tiles128 < (int8_b && !both_fast ? 160 : 256))
+    if (lin_small<AL, BL>(M, N, count))
         launch_tile_gemm_shape<AL, BL, OUT, 1, 64, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
     else if constexpr (both_fast || int8_b)
         launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
@@ -606,6 +655,35 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
     else
         launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
     return check_launch();
+}
+
+// dx (tokens x n_in = dy W, W with layout BL) and grad_W (rows x cols = A1^T B1 over the tokens): one launch where both
+// products run 64 x 64 tiles, otherwise one after the other.  Either output may be missing.  One 130M decoder layer on 256
+// tokens, forward and backward: 181 us with two launches per backward call, 151 with one.
+template <int BL>
+static int launch_linear_backward(const LinOperand& A0, const LinOperand& B0, uint16_t* dx, int64_t M0, int64_t N0, int64_t K0,
+                                  int64_t ldc0, const LinOperand& A1, const LinOperand& B1, uint16_t* G, int64_t M1, int64_t N1,
+                                  int64_t K1, int64_t ldc1, hipStream_t st) {
+    if (dx && G && lin_small<kBf16KFast, BL>(M0, N0, 1) && lin_small<kBf16KSlow, kBf16KSlow>(M1, N1, 1)) {
+        auto product = [](const LinOperand& A, const LinOperand& B, uint16_t* C, int64_t M, int64_t N, int64_t K, int64_t ldc) {
+            return LinProduct{A, B, C, ldc, (int)M, (int)N, (int)K, (int)((M + 63) / 64), (int)((N + 63) / 64)};
+        };
+        auto whole = [](const LinOperand& A, const LinOperand& B, int64_t M, int64_t N, int64_t K) {
+            return M % 64 == 0 && N % 64 == 0 && K % 64 == 0 && A.ld % 8 == 0 && B.ld % 16 == 0;
+        };
+        const LinProduct p0 = product(A0, B0, dx, M0, N0, K0, ldc0), p1 = product(A1, B1, G, M1, N1, K1, ldc1);
+        auto grid8 = [](const LinProduct& p) { return (unsigned)((p.tiles_m * p.tiles_n + 7) / 8 * 8); };   // the 8 XCDs
+        const unsigned grid0 = grid8(p0), grid = grid0 + grid8(p1);
+        if (whole(A0, B0, M0, N0, K0) && whole(A1, B1, M1, N1, K1))
+            hipLaunchKernelGGL((k_tile_gemm_pair<BL, true>), dim3(grid), dim3(256), 0, st, p0, p1, grid0);
+        else
+            hipLaunchKernelGGL((k_tile_gemm_pair<BL, false>), dim3(grid), dim3(256), 0, st, p0, p1, grid0);
+        return check_launch();
+    }
+    if (dx)
+        if (int e = launch_tile_gemm<kBf16KFast, BL, uint16_t>(A0, B0, nullptr, dx, M0, N0, K0, st, nullptr, 1, ldc0)) return e;
+    if (G) return launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A1, B1, nullptr, G, M1, N1, K1, st, nullptr, 1, ldc1);
+    return QG_OK;
 }
 
 }  // namespace qg
