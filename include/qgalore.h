@@ -86,9 +86,8 @@ typedef struct {
                              0 or n: dense rows.  Otherwise >= n and a multiple of 16: rows then start 16-byte aligned
                              whatever n is, which takes a matrix with n % 8 != 0 (n = 5461 in the LLaMA-1B shapes) off
                              the slow under-aligned path.  Every array holds rows * ld elements.  Padding columns are never read for a
-                             result; they are not written either, with two exceptions: N goes out as pairs of columns (an
-                             odd n overwrites the first padding column of N), and the unfused qg_lowrank_adam_many runs
-                             over the padding of M, V, N as well. */
+                             result; they are not written either, except that the unfused
+                             qg_lowrank_adam_many runs over the padding of M, V, N as well. */
     float*          Wz;   /* zero points of W, [m][ceil(n/256)], in/out, or NULL: the symmetric format.  Either every
                              matrix of a plan has them or none (QG_ERR_NULL otherwise). */
 } qg_matrix_desc;
@@ -371,7 +370,7 @@ int qg_step(const uint8_t* Pq, const float* Ps, const uint16_t* G_bf16,
  * elements apart (ld >= n and a multiple of 16, or ld == n / 0 for dense rows; m*ld < 2^32), as in the `ld` field of
  * qg_matrix_desc: a matrix whose n is not a multiple of 8 then runs in the kernels for 16-byte aligned rows.  Scales
  * stay [m][ceil(n/256)]; the stochastic-rounding index stays i*n + j, so the n real columns get the dense layout's
- * result.  Padding is never read for a result and not written, except that N is stored in pairs of columns. */
+ * result.  Padding is never read for a result and not written. */
 int qg_step_ld(const uint8_t* Pq, const float* Ps, const uint16_t* G_bf16,
                int8_t* Wq, float* Ws, float* M, float* V, float* R, uint16_t* N_bf16,
                int64_t m, int64_t n, int64_t ld, int64_t r, int group,
