@@ -235,9 +235,24 @@ struct ProjShape {
     static_assert(NS % 2 == 0, "the P tile has two LDS stages");
 };
 
+// Element (row, col) of a block whose rows lie ld elements apart, counted from the block's first element.  As an unsigned
+// 32-bit number it is exact for every element inside a matrix (rows * ld < 2^32); its byte offset, or the product as an
+// int, is so only up to ld = 2^24, the limit of the buffer-resource kernels.
+constexpr __host__ __device__ uint32_t element_offset(int row, int ld, int col) {
+    return (uint32_t)row * (uint32_t)ld + (uint32_t)col;
+}
+constexpr bool element_offset_exact(int ld) {   // over the rows of the widest matrices (8 rows at least, rows * ld < 2^32)
+    for (int64_t row = 0; (row + 1) * ld < (int64_t(1) << 32) && row < 32; ++row)
+        if ((int64_t)element_offset((int)row, ld, 252) != row * ld + 252) return false;
+    return true;
+}
+static_assert(element_offset_exact(1 << 24) && element_offset_exact(138547332) && element_offset_exact(153391691) &&
+              element_offset_exact(306783379) && element_offset_exact(536870911), "rows of the widest matrices");
+
 // Runs of four columns of a 32-row block of an r x ld array, as the projection's epilogue reads and writes them: run i
 // of a lane lies 8 i rows below its first one.  base: the block's first element of the tile's first column; `bytes`:
-// what is left of the (fp32) array from there; `rows`, `left`: rows and columns left from the lane's first run on.
+// what is left of the (fp32) array from there; `rows`, `left`: rows and columns left from the lane's first run on;
+// `off`: that run's offset from base, in bytes of the fp32 array (DIRECT) or in elements (otherwise: ld may exceed 2^24).
 // DIRECT: through buffer resources, whose end is the row mask.  Otherwise rows start at arbitrary elements and every
 // access is checked.  A run that straddles the end of its row is written element by element (what lies past the end of
 // a row may be padding that is not ours to write); it is read whole only where the row pitch covers it.
@@ -245,14 +260,14 @@ template <bool DIRECT, bool RAGGED>
 struct EpilogueAccess {
     int ld;
     bool straddles;   // the number of columns is not a multiple of 4
-    __device__ __forceinline__ f32x4 load(const float* base, int bytes, int rows, uint32_t voff, int left, int i) const {
+    __device__ __forceinline__ f32x4 load(const float* base, int bytes, int rows, uint32_t off, int left, int i) const {
         if constexpr (DIRECT) {
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
-            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, voff, 32u * (uint32_t)(i * ld), kAuxStream));
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 32u * (uint32_t)(i * ld), kAuxStream));
         } else {
             f32x4 x = {0.f, 0.f, 0.f, 0.f};
             if (8 * i >= rows || left <= 0) return x;
-            const float* p = base + (voff >> 2) + (int64_t)(8 * i) * ld;
+            const float* p = base + off + (int64_t)(8 * i) * ld;
             if (left >= 4) return __builtin_bit_cast(f32x4, *reinterpret_cast<const u32x4_align4*>(p));
 #pragma unroll
             for (int e = 0; e < 3; ++e)
@@ -260,25 +275,25 @@ struct EpilogueAccess {
             return x;
         }
     }
-    __device__ __forceinline__ void store(float* base, int bytes, int rows, uint32_t voff, int left, int i, f32x4 x) const {
+    __device__ __forceinline__ void store(float* base, int bytes, int rows, uint32_t off, int left, int i, f32x4 x) const {
         if constexpr (DIRECT) {
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
             const uint32_t so = 32u * (uint32_t)(i * ld);
             const bool whole = !RAGGED || left >= 4;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, whole ? voff : 0x80000000u, so, kAuxStream);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, whole ? off : 0x80000000u, so, kAuxStream);
             if (RAGGED && straddles) {   // wave-uniform
                 if (left > 0 && left < 4) {
 #pragma unroll
                     for (int e = 0; e < 3; ++e) {
                         const float xe = x[e];
                         if (e < left)
-                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, xe), rs, voff + 4u * e, so, 0);
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, xe), rs, off + 4u * e, so, 0);
                     }
                 }
             }
         } else {
             if (8 * i >= rows || left <= 0) return;
-            float* p = base + (voff >> 2) + (int64_t)(8 * i) * ld;
+            float* p = base + off + (int64_t)(8 * i) * ld;
             if (left >= 4) {
                 *reinterpret_cast<u32x4_align4*>(p) = __builtin_bit_cast(u32x4, x);
             } else {
@@ -288,25 +303,25 @@ struct EpilogueAccess {
             }
         }
     }
-    // four bf16 in an array of half the element size (bytes and voff are those of the fp32 arrays)
-    __device__ __forceinline__ void store_bf16(uint16_t* base, int bytes, int rows, uint32_t voff, int left, int i, u32x2 x) const {
+    // four bf16 in an array of half the element size (bytes, and off in bytes, are those of the fp32 arrays)
+    __device__ __forceinline__ void store_bf16(uint16_t* base, int bytes, int rows, uint32_t off, int left, int i, u32x2 x) const {
         if constexpr (DIRECT) {
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, RAGGED ? bytes / 2 : 0x7FFFFFFF);
             const uint32_t so = 16u * (uint32_t)(i * ld);
             const bool whole = !RAGGED || left >= 4;
-            __builtin_amdgcn_raw_buffer_store_b64(x, rs, whole ? voff >> 1 : 0x80000000u, so, kAuxStream);
+            __builtin_amdgcn_raw_buffer_store_b64(x, rs, whole ? off >> 1 : 0x80000000u, so, kAuxStream);
             if (RAGGED && straddles) {   // wave-uniform
                 if (left > 0 && left < 4) {
 #pragma unroll
                     for (int e = 0; e < 3; ++e)
                         if (e < left)
                             __builtin_amdgcn_raw_buffer_store_b16((uint16_t)(x[e >> 1] >> (16 * (e & 1))), rs,
-                                                                  (voff >> 1) + 2u * e, so, 0);
+                                                                  (off >> 1) + 2u * e, so, 0);
                 }
             }
         } else {
             if (8 * i >= rows || left <= 0) return;
-            uint16_t* p = base + (voff >> 2) + (int64_t)(8 * i) * ld;
+            uint16_t* p = base + off + (int64_t)(8 * i) * ld;
             if (left >= 4) {
                 *reinterpret_cast<u32x2_align2*>(p) = x;
             } else {
@@ -473,14 +488,15 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     EpilogueAccess<DIRECT, RAGGED> ea;
     ea.ld = ld;
     ea.straddles = (n & 3) != 0;
-    uint32_t voff[NB];   // byte offset, in an fp32 array, of the lane's first run in each 32-column block; no resource
-                         // covers 2^31: runs past the end of a row
+    uint32_t off[NB];    // offset of the lane's first run in each 32-column block (see EpilogueAccess); no resource covers
+                         // 2^31: runs past the end of a row
     int left[NB];        // columns of the matrix from the lane's run on
 #pragma unroll
     for (int b = 0; b < NB; ++b) {
         const int col = wn * WN + b * 32 + tcol;   // inside the tile
         left[b] = RAGGED ? n - (n0 + col) : 4;
-        voff[b] = left[b] > 0 ? 4u * (uint32_t)(trow * ld + col) : 0x80000000u;
+        off[b] = element_offset(trow, ld, col);
+        if constexpr (DIRECT) off[b] = left[b] > 0 ? 4u * off[b] : 0x80000000u;
     }
     // Rows at or past r lie past the end of every array: loads return 0, stores are dropped.
     auto block_at = [&](int a) -> int64_t { return (int64_t)(r0 + wm * WM + a * 32) * ld + n0; };
@@ -499,8 +515,8 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
             for (int b = 0; b < NB; ++b)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    pm[(a * NB + b) * 4 + i] = ea.load(Mo + block_at(a), block_bytes(a), block_rows(a) - trow, voff[b], left[b], i);
-                    pv[(a * NB + b) * 4 + i] = ea.load(Vo + block_at(a), block_bytes(a), block_rows(a) - trow, voff[b], left[b], i);
+                    pm[(a * NB + b) * 4 + i] = ea.load(Mo + block_at(a), block_bytes(a), block_rows(a) - trow, off[b], left[b], i);
+                    pv[(a * NB + b) * 4 + i] = ea.load(Vo + block_at(a), block_bytes(a), block_rows(a) - trow, off[b], left[b], i);
                 }
     }
 
@@ -590,8 +606,8 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
 #pragma unroll
                     for (int q = 0; q < 2; ++q) {
                         const int i = 2 * h + q;
-                        mm[q] = PRELOAD ? pm[PRELOAD ? (a * NB + b) * 4 + i : 0] : ea.load(Mo + at, bytes, rows, voff[b], left[b], i);
-                        vv[q] = PRELOAD ? pv[PRELOAD ? (a * NB + b) * 4 + i : 0] : ea.load(Vo + at, bytes, rows, voff[b], left[b], i);
+                        mm[q] = PRELOAD ? pm[PRELOAD ? (a * NB + b) * 4 + i : 0] : ea.load(Mo + at, bytes, rows, off[b], left[b], i);
+                        vv[q] = PRELOAD ? pv[PRELOAD ? (a * NB + b) * 4 + i : 0] : ea.load(Vo + at, bytes, rows, off[b], left[b], i);
                     }
                 }
 #pragma unroll
@@ -600,7 +616,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
                     const int i = 2 * h + q;
-                    if (write_R) ea.store(R + at, bytes, rows, voff[b], left[b], i, rr[q]);
+                    if (write_R) ea.store(R + at, bytes, rows, off[b], left[b], i, rr[q]);
                     if constexpr (FUSE_ADAM) {
                         float nn[4];
 #pragma unroll
@@ -610,10 +626,10 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
                             mm[q][e] = me;
                             vv[q][e] = ve;
                         }
-                        ea.store(Mo + at, bytes, rows, voff[b], left[b], i, mm[q]);
-                        ea.store(Vo + at, bytes, rows, voff[b], left[b], i, vv[q]);
+                        ea.store(Mo + at, bytes, rows, off[b], left[b], i, mm[q]);
+                        ea.store(Vo + at, bytes, rows, off[b], left[b], i, vv[q]);
                         const u32x2 nb = {pack_bf16x2(nn[0], nn[1]), pack_bf16x2(nn[2], nn[3])};
-                        ea.store_bf16(No + at, bytes, rows, voff[b], left[b], i, nb);
+                        ea.store_bf16(No + at, bytes, rows, off[b], left[b], i, nb);
                     }
                 }
             }

@@ -85,6 +85,54 @@ def test_step_just_below_the_index_limit():
         print(f"block {g}: R {eR:.2e} N {eN:.2e} identical codes {same:.6f}", flush=True)
 
 
+def check_wide_step(m, n, r):
+    """One warm step (t = 3) on a matrix of few rows and up to 2^32 / m columns, generated on the device in column chunks;
+    the first, middle and last (ragged) column block, all rows of each, against the oracle."""
+    t, seed = 3, 0x0FED_CBA9_8765_4321
+    assert m * n < 2 ** 32
+    gen = torch.Generator(device=DEV); gen.manual_seed(m + n)
+    Pq_h, Ps_h = Q.quant_int4(I.projection_f32(m, r))
+    ng = (n + 255) // 256
+    G = torch.empty((m, n), dtype=torch.bfloat16, device=DEV)
+    Wq = torch.empty((m, n), dtype=torch.int8, device=DEV)
+    M = torch.empty((r, n), dtype=torch.float32, device=DEV)
+    V = torch.empty((r, n), dtype=torch.float32, device=DEV)
+    chunk = 1 << 24
+    for c in range(0, n, chunk):
+        w = min(chunk, n - c)
+        G[:, c:c + w] = torch.randn((m, w), generator=gen, device=DEV) * 1e-2
+        Wq[:, c:c + w] = torch.randint(-127, 128, (m, w), generator=gen, device=DEV, dtype=torch.int8)
+        M[:, c:c + w] = torch.randn((r, w), generator=gen, device=DEV) * 5e-3
+        V[:, c:c + w] = (torch.randn((r, w), generator=gen, device=DEV) * 5e-3) ** 2 + 1e-8
+    Ws = torch.rand((m, ng), generator=gen, device=DEV) * 1e-4 + 1e-4
+    R = torch.empty((r, n), dtype=torch.float32, device=DEV)
+    N = torch.empty((r, n), dtype=torch.bfloat16, device=DEV)
+    blocks = [(g, slice(g * 256, min((g + 1) * 256, n))) for g in (0, ng // 2, ng - 1)]
+    cut = lambda x, sl: host(x[:, sl].contiguous())
+    before = [dict(G=bits(G[:, sl]), Wq=cut(Wq, sl), Ws=host(Ws[:, g:g + 1].contiguous()), M=cut(M, sl), V=cut(V, sl))
+              for g, sl in blocks]
+    print("launching the step on", m, "x", n, flush=True)
+    qg.step(dev(Pq_h), dev(Ps_h), G, Wq, Ws, M, V, R, N, m, n, r, qg.hparams(), seed, t)
+    torch.cuda.synchronize()
+    for (g, sl), b in zip(blocks, before):
+        o = Q.step(b["Wq"], b["Ws"], b["G"], Pq_h, Ps_h, b["M"], b["V"], t, HP, seed=seed, r=r, n_total=n, col0=g * 256)
+        for i in range(r):                                       # row by row: an error in one must not be averaged away
+            row = slice(i, i + 1)
+            assert rel_fro(cut(R, sl)[row], o["R"][row]) <= 2e-5, (g, i)
+            assert rel_fro(cut(M, sl)[row], o["M"][row]) <= 2e-5 and rel_fro(cut(V, sl)[row], o["V"][row]) <= 4e-5, (g, i)
+            assert rel_fro(Q.bf16_bits_to_f64(bits(N[:, sl]))[row], Q.bf16_rne(o["N"])[row]) <= 1e-3, (g, i)
+        d = cut(Wq, sl).astype(np.int32) - o["Wq"].astype(np.int32)
+        assert np.abs(d).max() <= 1 and np.mean(d != 0) <= 1e-2, g   # few elements: one differing code is a large share
+        assert np.allclose(host(Ws[:, g:g + 1].contiguous()), o["Ws"], rtol=1e-5, atol=0), g
+
+
+@pytest.mark.parametrize("m,n,r", [(8, 153391691, 8), (8, 300000001, 8)])
+def test_rows_far_apart(m, n, r):
+    """Rows so long that the byte offset between the first and the last row of an epilogue run of M, V, R no longer fits
+    32 bits (4 * 7 * n >= 2^32)."""
+    check_wide_step(m, n, r)
+
+
 @pytest.mark.parametrize("m,n,r", [(8, 8, 8), (8, 1, 8), (9, 257, 8), (256, 256, 256)])
 def test_smallest_shapes(m, n, r):
     """The smallest shapes the step accepts (r a multiple of 8, r <= m; any n >= 1), r = m included: one workgroup,
