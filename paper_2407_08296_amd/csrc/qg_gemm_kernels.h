@@ -381,7 +381,8 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     // so code bytes and block scales split the same way.
     static_assert(BK % 32 == 0, "a K step must cover whole blocks of 256 codes");
     constexpr int B_OFFS = DIRECT ? BD::VARIANTS : B_PER;
-    uint32_t a_el[A_PER], b_byte[B_OFFS];   // P: element offset; G: byte offset
+    uint32_t a_el[A_PER], b_off[B_OFFS];   // P: element offset; G: byte offset (kUnaligned: element offset, ld may
+                                           // exceed 2^24)
 #pragma unroll
     for (int p = 0; p < A_PER; ++p) {
         const int ti = t + p * NT;
@@ -390,10 +391,10 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
 #pragma unroll
     for (int p = 0; p < B_OFFS; ++p) {
         if constexpr (DIRECT) {
-            b_byte[p] = BD::lane_src_bytes(lane, ld, p);
+            b_off[p] = BD::lane_src_bytes(lane, ld, p);
         } else {
             const int ci = t + p * NT;
-            b_byte[p] = 2u * (uint32_t)((ci / BD::CPR) * ld + (ci % BD::CPR) * 8);
+            b_off[p] = element_offset(ci / BD::CPR, ld, (ci % BD::CPR) * 8);
         }
     }
 
@@ -404,7 +405,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
         const int64_t e0 = (int64_t)i0 * r;
         const uint8_t* pq = Pq + (e0 >> 1);
         const float* ps = Ps + (e0 >> 8);
-        const uint8_t* g = reinterpret_cast<const uint8_t*>(G + (int64_t)i0 * ld + n0);
+        const uint16_t* g = G + (int64_t)i0 * ld + n0;
         if constexpr (DIRECT) {
             __amdgpu_buffer_rsrc_t rq, rs, rg;
             if constexpr (MODE == kExact) {
@@ -419,7 +420,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p)
-                buffer_load_lds16(rg, Bs + stage * S::B_STAGE + BD::load_row0(wave, p) * BN, b_byte[p % BD::VARIANTS],
+                buffer_load_lds16(rg, Bs + stage * S::B_STAGE + BD::load_row0(wave, p) * BN, b_off[p % BD::VARIANTS],
                                   2u * (uint32_t)(BD::load_row0(wave, p) * ld));
 #pragma unroll
             for (int p = 0; p < A_PER; ++p) {
@@ -442,7 +443,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
                 const int ci = t + p * NT;
                 const int row = ci / BD::CPR, c8 = ci % BD::CPR;
                 const int valid = (i0 + row < m) ? (n - (n0 + c8 * 8)) : 0;
-                bv[stage][p] = load8_bf16_guarded(reinterpret_cast<const uint16_t*>(g + b_byte[p]), valid);
+                bv[stage][p] = load8_bf16_guarded(g + b_off[p], valid);
             }
         }
     };
@@ -863,14 +864,15 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     // tile's first code, m0*r, starts a block of 256 (m0 is a multiple of 128, r of 8); the K offset k0 does not,
     // so the index of a code's block scale takes one add and two shifts per step.
     constexpr int A_OFFS = DIRECT ? AD::VARIANTS : A_PER;
-    uint32_t a_byte[A_OFFS], b_el[B_PER];   // N: byte offset; P: element offset inside the tile's rows
+    uint32_t a_off[A_OFFS], b_el[B_PER];   // N: byte or element offset, as G's in the projection; P: element offset inside
+                                           // the tile's rows
 #pragma unroll
     for (int p = 0; p < A_OFFS; ++p) {
         if constexpr (DIRECT) {
-            a_byte[p] = AD::lane_src_bytes(lane, ld, p);
+            a_off[p] = AD::lane_src_bytes(lane, ld, p);
         } else {
             const int ci = t + p * NT;
-            a_byte[p] = 2u * (uint32_t)((ci / AD::CPR) * ld + (ci % AD::CPR) * 8);
+            a_off[p] = element_offset(ci / AD::CPR, ld, (ci % AD::CPR) * 8);
         }
     }
 #pragma unroll
@@ -884,7 +886,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     // into register set `stage`.  A tile past the end (kt >= KT) loads nothing.
     auto gload = [&](int kt, int stage) {
         const int k0 = kt * BK;
-        const uint8_t* nb = reinterpret_cast<const uint8_t*>(N + (int64_t)k0 * ld + n0);
+        const uint16_t* nb = N + (int64_t)k0 * ld + n0;
         const uint8_t* pq = Pq + ((e_tile + k0) >> 1);
         const float* ps = Ps + (e_tile >> 8);
         if constexpr (DIRECT) {
@@ -901,7 +903,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
             }
 #pragma unroll
             for (int p = 0; p < A_PER; ++p)
-                buffer_load_lds16(rn, As + stage * S::A_STAGE + AD::load_row0(wave, p) * BNn, a_byte[p % AD::VARIANTS],
+                buffer_load_lds16(rn, As + stage * S::A_STAGE + AD::load_row0(wave, p) * BNn, a_off[p % AD::VARIANTS],
                                   2u * (uint32_t)(AD::load_row0(wave, p) * ld));
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
@@ -917,7 +919,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                 const int ci = t + p * NT;
                 const int row = ci / AD::CPR, c8 = ci % AD::CPR;
                 const int valid = (k0 + row < r) ? (n - (n0 + c8 * 8)) : 0;
-                av[stage][p] = load8_bf16_guarded(reinterpret_cast<const uint16_t*>(nb + a_byte[p]), valid);
+                av[stage][p] = load8_bf16_guarded(nb + a_off[p], valid);
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
