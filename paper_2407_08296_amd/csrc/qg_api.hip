@@ -208,9 +208,6 @@ extern "C" int qg_plan_build(int count, const qg_matrix_desc* descs, void* plan_
             t256 += proj_tiles(kProj256, d.n, d.r);
             b128 += bp_tiles_m(kBp128, d.m) * ((d.n + kManyBpBN - 1) / kManyBpBN);
         }
-        if (t256 > 0x7FFFFFF0ll || b128 > 0x7FFFFFF0ll) return QG_ERR_SHAPE;
-        h.proj_tiles[cls] = (uint32_t)t256;
-        h.bp_tiles[cls] = (uint32_t)b128;
         h.proj_cfg[cls] = (uint32_t)proj_config(cls, t128, t256);
         h.bp_cfg[cls] = (uint32_t)bp_config(b128);
     }
@@ -243,8 +240,8 @@ extern "C" int qg_plan_build(int count, const qg_matrix_desc* descs, void* plan_
     h.adam_chunks = (uint32_t)adam;
     for (int cls = 0; cls < kPlanClasses; ++cls) {
         if (proj[cls] > 0x7FFFFFF0ull || bp[cls] > 0x7FFFFFF0ull) return QG_ERR_SHAPE;
-        h.proj_launch[cls] = (uint32_t)proj[cls];
-        h.bp_launch[cls] = (uint32_t)bp[cls];
+        h.proj_tiles[cls] = (uint32_t)proj[cls];
+        h.bp_tiles[cls] = (uint32_t)bp[cls];
     }
     std::memcpy(plan_host, &h, sizeof h);
     return QG_OK;

@@ -115,7 +115,7 @@ int launch_project_adam_many(const PlanHeader* plan_host, const PlanHeader* plan
     const AdamCoef coef = make_adam_coef(hp, step);
     for (int cls = 0; cls < kPlanClasses; ++cls) {
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
-        const uint32_t tiles = plan_host->proj_launch[cls];
+        const uint32_t tiles = plan_host->proj_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
         const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
             using C = decltype(c);
@@ -190,7 +190,7 @@ int launch_backproject(const uint8_t* Pq, const float* Ps, const uint16_t* N, in
 int launch_project_many(const PlanHeader* plan_host, const PlanHeader* plan_dev, hipStream_t stream) {
     for (int cls = 0; cls < kPlanClasses; ++cls) {
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
-        const uint32_t tiles = plan_host->proj_launch[cls];
+        const uint32_t tiles = plan_host->proj_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
         const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
             using C = decltype(c);
@@ -209,7 +209,7 @@ int launch_backproject_many(const PlanHeader* plan_host, const PlanHeader* plan_
                             uint64_t seed, int64_t step, hipStream_t stream) {
     for (int cls = 0; cls < kPlanClasses; ++cls) {
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
-        const uint32_t tiles = plan_host->bp_launch[cls];
+        const uint32_t tiles = plan_host->bp_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
         const int e = with_bp((int)plan_host->bp_cfg[cls], [&](auto c) {
             using C = decltype(c);

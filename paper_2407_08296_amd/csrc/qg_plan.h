@@ -53,14 +53,11 @@ struct PlanHeader {
     uint32_t adam_chunks;
     uint32_t no_R;                        // 1 if some matrix has no R buffer
     int32_t class_count[kPlanClasses];    // matrices per class, in storage order
-    uint32_t proj_tiles[kPlanClasses];    // size of a class: its largest (kProj256, kBp128) tiles
+    uint32_t proj_tiles[kPlanClasses];    // tiles of each class's launch, in its configuration
     uint32_t bp_tiles[kPlanClasses];
     uint32_t zero_points;                 // 1 if the weights carry zero points (all of them or none)
     uint32_t proj_cfg[kPlanClasses];      // tile configuration of each class (kProj*, kBp*)
     uint32_t bp_cfg[kPlanClasses];
-    uint32_t proj_launch[kPlanClasses];   // tiles of each launch in its configuration
-    uint32_t bp_launch[kPlanClasses];
-    uint32_t pad_[2];
 };
 static_assert(sizeof(PlanHeader) % 16 == 0, "records must stay 16-byte aligned");
 

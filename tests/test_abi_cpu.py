@@ -206,31 +206,36 @@ def test_plan_build_on_host(L):
     buf = C.create_string_buffer(nbytes)
     assert L.qg_plan_build(2, descs, buf, nbytes - 1) == 5
     assert L.qg_plan_build(2, descs, buf, nbytes) == 0
-    # header: magic, count, Adam chunks, no_R, then per class (exact, masked, unaligned): matrices, projection
-    # tiles, back-projection tiles
-    hdr = (C.c_uint32 * 16).from_buffer(buf)
+    # header: magic, count, Adam chunks, no_R, then per class (exact, masked, unaligned): matrices, projection tiles and
+    # back-projection tiles that are launched; zero points; per class the configurations of the two
+    hdr = (C.c_uint32 * 20).from_buffer(buf)
     assert hdr[1] == 2                                       # count
     assert hdr[2] == 2 * (1024 * 4096) // 4096               # Adam chunks of 4096 elements
     assert hdr[3] == 0                                       # every matrix has an R buffer
     assert list(hdr[4:7]) == [2, 0, 0]                       # both matrices need no edge checks
-    assert list(hdr[7:10]) == [2 * 8 * 16, 0, 0]             # projection tiles 128 x 256 over r x n
+    assert list(hdr[7:10]) == [2 * 8 * 32, 0, 0]             # projection tiles 128 x 128 over r x n
     assert list(hdr[10:13]) == [32 * 16 + 86 * 16, 0, 0]     # back-projection tiles 128 x 256 over m x n
+    assert list(hdr[13:20]) == [0, PROJ128, PROJ64, PROJ64, BP128, BP64, BP64]
     descs[1].n = 5461                                        # odd row length: rows not 16-byte aligned
     assert L.qg_plan_build(2, descs, buf, nbytes) == 0
-    hdr = (C.c_uint32 * 16).from_buffer(buf)
+    hdr = (C.c_uint32 * 20).from_buffer(buf)
     assert list(hdr[4:7]) == [1, 0, 1]
-    assert list(hdr[7:10]) == [8 * 16, 0, 8 * 22] and list(hdr[10:13]) == [32 * 16, 0, 86 * 22]
+    # 8 * 32 and 8 * 43 tiles of 128 x 128: 64 x 128 for the one, 128 x 128 for the other
+    assert list(hdr[7:10]) == [16 * 32, 0, 8 * 43] and list(hdr[10:13]) == [32 * 16, 0, 86 * 22]
+    assert list(hdr[14:20]) == [PROJ64, PROJ64, PROJ128, BP128, BP64, BP128]
     descs[1].n = 2736                                        # ragged but aligned rows; m = 11008 = 86 x 128
     assert L.qg_plan_build(2, descs, buf, nbytes) == 0
-    hdr = (C.c_uint32 * 16).from_buffer(buf)
+    hdr = (C.c_uint32 * 20).from_buffer(buf)
     assert list(hdr[4:7]) == [1, 1, 0]
-    assert list(hdr[7:10]) == [8 * 16, 8 * 11, 0] and list(hdr[10:13]) == [32 * 16, 86 * 11, 0]
+    assert list(hdr[7:10]) == [16 * 32, 16 * 22, 0] and list(hdr[10:13]) == [32 * 16, 86 * 11, 0]
+    assert list(hdr[14:20]) == [PROJ64, PROJ64, PROJ64, BP128, BP128, BP64]
     descs[1].n, descs[1].ld = 5461, 5472                     # the same odd n with a row pitch: aligned rows, masked class
     assert L.qg_plan_build(2, descs, buf, nbytes) == 0
-    hdr = (C.c_uint32 * 16).from_buffer(buf)
+    hdr = (C.c_uint32 * 20).from_buffer(buf)
     assert list(hdr[4:7]) == [1, 1, 0]
     assert hdr[2] == (1024 * 4096 + 1024 * 5472) // 4096     # the unfused Adam runs over the padding too
-    assert list(hdr[7:10]) == [8 * 16, 8 * 22, 0] and list(hdr[10:13]) == [32 * 16, 86 * 22, 0]
+    assert list(hdr[7:10]) == [16 * 32, 8 * 43, 0] and list(hdr[10:13]) == [32 * 16, 86 * 22, 0]
+    assert list(hdr[14:20]) == [PROJ64, PROJ128, PROJ64, BP128, BP128, BP64]
     for bad in (5460, 5464, 5461 + 7):                       # below n; not a multiple of 16 (twice)
         descs[1].ld = bad
         assert L.qg_plan_build(2, descs, buf, nbytes) == 2
@@ -246,6 +251,57 @@ def test_plan_build_on_host(L):
     hp = qg.hparams()
     assert L.qg_step_many(2, None, FAKE, nbytes, C.byref(hp), 0, 1, None) == 1
     assert L.qg_step_many(3, buf, FAKE, nbytes, C.byref(hp), 0, 1, None) == 5
+
+
+# tile configurations in the plan header: rows x columns of a projection tile, rows of a back-projection tile
+PROJ64, PROJ128, PROJ256 = 0, 1, 2
+BP64, BP128 = 0, 1
+PROJ_TILE = {PROJ64: (64, 128), PROJ128: (128, 128), PROJ256: (128, 256)}
+BP_ROWS = {BP64: 64, BP128: 128}
+
+
+@pytest.mark.parametrize("count,m,n,r,cls,proj,bp", [
+    # exact class: one tile of 128 x 128 and one 128-row back-projection tile per matrix and 128 or 256 columns
+    (40, 128, 1024, 128, 0, PROJ64, BP64),          # 320 tiles of 128 x 128, 160 of the back-projection
+    (1, 128, 320 * 128, 128, 0, PROJ64, BP64),
+    (321, 128, 256, 128, 0, PROJ128, BP64),         # 642; 321
+    (383, 128, 256, 128, 0, PROJ128, BP64),
+    (384, 128, 256, 128, 0, PROJ128, BP128),
+    (1023, 128, 256, 128, 0, PROJ128, BP128),       # of 128 x 256
+    (1024, 128, 256, 128, 0, PROJ256, BP128),
+    (160, 140, 200, 136, 2, PROJ128, BP64),         # r % 16 != 0: unaligned; 640 tiles of 128 x 128, 320
+    (80, 140, 200, 136, 2, PROJ64, BP64),           # 320
+    (81, 140, 200, 136, 2, PROJ128, BP64),
+    (192, 140, 200, 136, 2, PROJ128, BP128),
+    (1100, 140, 200, 136, 2, PROJ128, BP128),       # 2200 of 128 x 256: still 128 x 128
+    (1024, 120, 200, 48, 1, PROJ256, BP128),        # masked
+    (1023, 120, 200, 48, 1, PROJ128, BP128),
+])
+def test_plan_tiles_on_both_sides_of_every_rule(L, count, m, n, r, cls, proj, bp):
+    """The configuration of a class follows from its number of tiles (320 of 128 x 128 at most: 64 x 128; 1024 of 128 x
+    256 at least, rows aligned: 128 x 256; 384 back-projection tiles of 128 rows at least: 128 rows), and the tiles of
+    each launch and every matrix's first tiles are those of that configuration."""
+    descs = (qg.MatrixDesc * count)()
+    for d in descs:
+        d.m, d.n, d.r = m, n, r
+        for f in ("Pq", "Ps", "G", "Wq", "Ws", "M", "V", "R", "N"):
+            setattr(d, f, FAKE)
+    nbytes = L.qg_plan_bytes(count, descs)
+    buf = C.create_string_buffer(nbytes)
+    assert L.qg_plan_build(count, descs, buf, nbytes) == 0
+    hdr = (C.c_uint32 * 20).from_buffer(buf)
+    assert hdr[4 + cls] == count and hdr[14 + cls] == proj and hdr[17 + cls] == bp
+    up = lambda a, b: -(-a // b)
+    tr, tn = up(r, PROJ_TILE[proj][0]), up(n, PROJ_TILE[proj][1])
+    tm, tc = up(m, BP_ROWS[bp]), up(n, 256)
+    assert hdr[7 + cls] == count * tr * tn and hdr[10 + cls] == count * tm * tc
+    others = [c for c in range(3) if c != cls]
+    assert all(hdr[4 + c] == hdr[7 + c] == hdr[10 + c] == 0 for c in others)
+    size = (nbytes - 80) // count                            # record: 4 sizes, 10 pointers, then 6 words
+    assert size == 136
+    for i in (0, count // 2, count - 1):
+        w = (C.c_uint32 * 6).from_buffer(buf, 80 + i * size + 112)
+        assert list(w) == [i * up(r * n, 4096), i * tr * tn, i * tm * tc, tr, tm, i]
 
 
 def test_policy_matches_oracle_tables(L):
