@@ -596,12 +596,13 @@ def _pitched_state(shapes_ld):
     [(333, 261, 144, 272), (512, 1365, 128, 1376)],      # odd n: the pitch moves them to the aligned, masked class
     [(768, 768, 256, 800), (333, 264, 144, 288)],        # whole tiles with a pitch; aligned rows, a wider pitch
     [(300, 700, 40, 704), (200, 517, 48, 528)],          # r % 16 != 0 keeps the general path; edges everywhere
+    [(333, 262, 144, 272), (512, 1367, 128, 1376)],      # n % 4 = 2 and 3: a row's last run is stored element by element
+    [(300, 702, 40, 704), (300, 703, 40, 704)],          # the same in the general path
 ])
 def test_step_many_with_row_pitch(shapes_ld):
     """A row pitch ld > n (the descriptor's `ld`): results equal the oracle's on the n real columns, the padding of the
     weight, the moments and the outputs keeps its fill (whatever the gradient's padding holds: NaN here), and where the
-    dense layout runs in the same kernel class the two are bit-identical.  (N is stored as pairs of columns: with an
-    odd n the first padding column of N is overwritten.)"""
+    dense layout runs in the same kernel class the two are bit-identical."""
     mats, data = _pitched_state(shapes_ld)
     dense, _ = _state_for([(m, n, r) for m, n, r, _ in shapes_ld])
     seed = 33
@@ -619,7 +620,7 @@ def test_step_many_with_row_pitch(shapes_ld):
         check_scales_step(host(s.Ws), o["Ws"], rel=5e-4)     # a first step from zero moments
         # padding untouched
         assert torch.all(s.Wq[:, n:] == 85) and torch.all(s.M[:, n:] == 777.0) and torch.all(s.V[:, n:] == 777.0)
-        assert torch.all(s.N[:, n + n % 2:] == 0x1234) and torch.all(torch.isnan(s.R[:, n:]))   # N goes out in pairs
+        assert torch.all(s.N[:, n:] == 0x1234) and torch.all(torch.isnan(s.R[:, n:]))
         if n % 8 == 0:   # same edge class with and without the pitch: same kernels, same arithmetic
             assert torch.equal(s.Wq[:, :n], dn.Wq.view(s.m, n)) and torch.equal(s.Ws, dn.Ws)
             assert torch.equal(s.M[:, :n], dn.M) and torch.equal(s.R[:, :n], dn.R)
@@ -678,7 +679,8 @@ def test_llama1b_down_shape_with_row_pitch_sampled_columns():
     assert np.all(gWq[:, n:] == 85)
 
 
-@pytest.mark.parametrize("m,n,r,ld", [(333, 261, 144, 272), (512, 1365, 128, 1376), (768, 768, 256, 800), (300, 700, 40, 704)])
+@pytest.mark.parametrize("m,n,r,ld", [(333, 261, 144, 272), (512, 1365, 128, 1376), (768, 768, 256, 800), (300, 700, 40, 704),
+                                      (333, 262, 144, 272), (333, 263, 144, 272), (300, 703, 40, 704)])
 def test_single_matrix_step_with_row_pitch(m, n, r, ld):
     """qg_step_ld: the single-matrix step on arrays with rows ld elements apart.  The n real columns get the oracle's
     result and, bit for bit, the grouped step's on the same pitched arrays; the padding (NaN in the gradient) is neither
@@ -697,6 +699,6 @@ def test_single_matrix_step_with_row_pitch(m, n, r, ld):
     check_codes(host(s.Wq[:, :n]), o["Wq"].reshape(m, n))
     check_scales_step(host(s.Ws), o["Ws"], rel=5e-4)
     assert torch.all(s.Wq[:, n:] == 85) and torch.all(s.M[:, n:] == 777.0) and torch.all(s.V[:, n:] == 777.0)
-    assert torch.all(s.N[:, n + n % 2:] == 0x1234) and torch.all(torch.isnan(s.R[:, n:]))
+    assert torch.all(s.N[:, n:] == 0x1234) and torch.all(torch.isnan(s.R[:, n:]))
     assert torch.equal(s.Wq, g.Wq) and torch.equal(s.Ws, g.Ws) and torch.equal(s.M[:, :n], g.M[:, :n])
     assert torch.equal(s.R[:, :n], g.R[:, :n]) and torch.equal(s.N[:, :n], g.N[:, :n])
