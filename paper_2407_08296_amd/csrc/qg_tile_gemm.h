@@ -87,16 +87,22 @@ struct LinStage {
     float s[kInt8 ? PER : 1];
     float z[kZero ? PER : 1];
 
-    template <int FETCH>
-    __device__ __forceinline__ void fetch(const LinOperand& op, int x0, int X, int k0, int K) {
+    // KI: int or int64_t.  Over a 64-bit k0 the compiler turns the addresses of a loop into running pointers; over a 32-bit
+    // one it recomputes a 64-bit product per chunk and step (grad_W with 128 x 128 x 32 tiles, 2048 tokens, 2560 x 2048:
+    // 36.2 against 38.6 us), which takes fewer registers.
+    template <int FETCH, typename KI>
+    __device__ __forceinline__ void fetch(const LinOperand& op, int x0, int X, KI k0, int K) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int idx = threadIdx.x + NT * q;
             const int tr = idx / CPR, tc = (idx % CPR) * CH;         // row and first column inside the tile
-            const int row = kFast ? x0 + tr : k0 + tr;               // ... and inside the matrix
-            const int col = kFast ? k0 + tc : x0 + tc;
-            const int rows = kFast ? X : K, cols = kFast ? K : X;
-            const int valid = FETCH != kFetchGuarded ? CH : (row < rows ? cols - col : 0);
+            const auto row = kFast ? x0 + tr : k0 + tr;              // ... and inside the matrix
+            const auto col = kFast ? k0 + tc : x0 + tc;
+            int valid = CH;
+            if constexpr (FETCH == kFetchGuarded) {
+                const int k = (int)k0;
+                valid = kFast ? (x0 + tr < X ? K - (k + tc) : 0) : (k + tr < K ? X - (x0 + tc) : 0);
+            }
             const int64_t off = (int64_t)row * op.ld + col;
             if constexpr (kInt8) {
                 const int8_t* src = static_cast<const int8_t*>(op.base) + off;
@@ -175,12 +181,16 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* 
 
 // C[M][N] (bf16 or fp32) = sum_k A(i, k) B(k, j) (+ bias[j]); A's x index runs over the rows of C, B's over its
 // columns.  Tile TM = 32 MB WM rows x TN columns, a wave computes 32 MB x TN / 2.
-// Two LDS stages and two register sets: while the MFMAs of step kt read stage kt & 1, the operands of step kt + 1 are
-// written to the other stage and those of step kt + 2 are fetched; one barrier per step.
+// Two LDS stages, one barrier per step.  DEEP: two register sets - while the MFMAs of step kt read stage kt & 1, the
+// operands of step kt + 1 are written to the other stage and those of step kt + 2 are fetched, all of it between the
+// MFMAs: for workgroups that have a CU to themselves.  Otherwise one set - the operands of step kt + 1 are fetched before
+// the MFMAs of step kt and written to the other stage after them: fewer registers, and workgroups that share a CU cover for
+// each other.
 // WM: wave rows of the workgroup (2: 256 threads, several workgroups per CU; 4: 512 threads, one workgroup per CU - the
 // B tile, and with it the dequantization of an INT8 B operand, is then shared by twice as many MFMAs).
 // EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a
-// workgroup whose tile lies inside runs unchecked too, but for the last, partial step.
+// workgroup whose tile lies inside runs unchecked too, but for the last, partial step - except with one register set and an
+// INT8 B with k slow, where that measured slower than checking (grad_input, 1000 tokens, 4096 -> 11008: 140 against 136 us).
 template <int AL, int BL, int MB, int TN, int BK, int WM>
 struct TileGemm {
     static constexpr int TM = 32 * MB * WM, NT = 128 * WM;
@@ -190,7 +200,7 @@ struct TileGemm {
     static constexpr int SMEM = STAGING > TRANSPOSE ? STAGING : TRANSPOSE;   // uint16 elements
 };
 
-template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM>
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM, bool DEEP>
 __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* __restrict__ bias,
                                           OUT* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n,
                                           uint32_t tile, uint16_t* smem) {
@@ -207,8 +217,8 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
     const int strip = (int)(tile / (uint32_t)(kLinStrip * tiles_n)), in_strip = (int)(tile % (uint32_t)(kLinStrip * tiles_n));
     const int strip_rows = min(kLinStrip, tiles_m - strip * kLinStrip);
     const int i0 = (strip * kLinStrip + in_strip % strip_rows) * TM, j0 = (in_strip / strip_rows) * TN;
-    SA sa[2];
-    SB sb[2];
+    SA sa[DEEP ? 2 : 1];
+    SB sb[DEEP ? 2 : 1];
     constexpr int NB = TN / 64;                // 32 x 32 blocks of a wave: MB x NB
     f32x16 acc[MB][NB];
 #pragma unroll
@@ -218,6 +228,7 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
     auto mfma_step = [&](int stage) {
+        if constexpr (!DEEP) __builtin_amdgcn_s_setprio(kMfmaPrio);   // the wave in its MFMA phase goes first
 #pragma unroll
         for (int kk = 0; kk < BK / 16; ++kk) {
             bf16x8 af[MB], bf[NB];
@@ -230,20 +241,43 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
 #pragma unroll
                 for (int b = 0; b < NB; ++b)
                     acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
+            if constexpr (!DEEP) __builtin_amdgcn_sched_barrier(0);   // fragments of one sub-step at a time
         }
+        if constexpr (!DEEP) __builtin_amdgcn_s_setprio(0);
     };
     // The KT steps from k = 0 on, every chunk of them fetched under FETCH's terms.
+    // (64-deep steps with two register sets have no registers left for running pointers.)
+    using KI = std::conditional_t<DEEP && BK == 64, int, int64_t>;
     auto steps = [&](auto fetch_mode, int KT) {
         constexpr int FETCH = decltype(fetch_mode)::value;
-        auto fetch = [&](int kt, int set) {
-            const int k0 = min(kt, KT - 1) * BK;   // past the end: the last slab again, never consumed
+        auto fetch = [&](KI k0, int set) {
             sa[set].template fetch<FETCH>(A, i0, M, k0, K);
             sb[set].template fetch<FETCH>(B, j0, N, k0, K);
         };
-        fetch(0, 0);
-        fetch(1, 1);
-        sa[0].commit(At(0));
-        sb[0].commit(Bt(0));
+        auto commit = [&](int set, int stage) {
+            sa[set].commit(At(stage));
+            sb[set].commit(Bt(stage));
+        };
+        if constexpr (!DEEP) {
+            KI k0 = 0;
+            fetch(k0, 0);
+            commit(0, 0);
+            __syncthreads();   // (lds_barrier, across which nothing is scheduled: grad_input of the 7B layer 143 against 134 us)
+            for (int kt = 0; kt < KT; ++kt) {
+                const int cur = kt & 1;
+                const bool more = kt + 1 < KT;
+                k0 += BK;
+                if (more) fetch(k0, 0);
+                mfma_step(cur);
+                if (more) commit(0, cur ^ 1);
+                __syncthreads();
+            }
+            return;
+        }
+        auto slab = [&](int kt) { return (KI)min(kt, KT - 1) * BK; };   // past the end: the last slab again, never consumed
+        fetch(slab(0), 0);
+        fetch(slab(1), DEEP);
+        commit(0, 0);
         lds_barrier();
         for (int kt = 0; kt + 1 < KT; kt += 2) {
 #pragma unroll
@@ -251,9 +285,8 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
                 // one scheduling region: fragment reads, the fetches of step kt + u + 2 and the commit of step kt + u + 1
                 // between the MFMAs
                 mfma_step(u);
-                fetch(kt + u + 2, u);
-                sa[u ^ 1].commit(At(u ^ 1));
-                sb[u ^ 1].commit(Bt(u ^ 1));
+                fetch(slab(kt + u + 2), DEEP ? u : 0);
+                commit(DEEP ? u ^ 1 : 0, u ^ 1);
                 constexpr int READS = MB * (SA::kFast ? 1 : 2) + NB * (SB::kFast ? 1 : 2), MFMAS = MB * NB;
                 __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
 #pragma unroll
@@ -278,7 +311,8 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
     } else {
         inside = i0 + TM <= M && j0 + TN <= N;
         const int whole = K / BK;
-        if (!inside) {
+        constexpr bool CHECK_ALL = !DEEP && (BL == kInt8KSlow || BL == kInt8ZKSlow);
+        if (CHECK_ALL || !inside) {
             steps(std::integral_constant<int, kFetchGuarded>(), (K + BK - 1) / BK);
         } else {
             if (whole > 0) steps(std::integral_constant<int, kFetchInside>(), whole);
@@ -305,7 +339,7 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
         }
 }
 
-template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM = 2>
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM, bool DEEP>
 __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOperand A, LinOperand B,
                                                       const uint16_t* __restrict__ bias,
                                                       OUT* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
@@ -316,7 +350,7 @@ __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOper
     // each XCD (own L2) takes a contiguous range of tiles
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= (uint32_t)(tiles_m * tiles_n)) return;
-    tile_gemm<AL, BL, EXACT, OUT, MB, TN, BK, WM>(A, B, bias, C + batch.strideC * blockIdx.y, batch.ldc ? batch.ldc : N, M, N, K,
+    tile_gemm<AL, BL, EXACT, OUT, MB, TN, BK, WM, DEEP>(A, B, bias, C + batch.strideC * blockIdx.y, batch.ldc ? batch.ldc : N, M, N, K,
                                                   tiles_m, tiles_n, tile, smem);
 }
 
@@ -337,12 +371,12 @@ __global__ __launch_bounds__(256, 2) void k_tile_gemm_pair(LinProduct p0, LinPro
     if (blockIdx.x < grid0) {
         const uint32_t tile = xcd_tile(blockIdx.x, grid0);
         if (tile >= (uint32_t)(p0.tiles_m * p0.tiles_n)) return;
-        tile_gemm<kBf16KFast, BL, EXACT, uint16_t, 1, 64, 64, 2>(p0.A, p0.B, nullptr, p0.C, p0.ldc, p0.M, p0.N, p0.K, p0.tiles_m,
+        tile_gemm<kBf16KFast, BL, EXACT, uint16_t, 1, 64, 64, 2, true>(p0.A, p0.B, nullptr, p0.C, p0.ldc, p0.M, p0.N, p0.K, p0.tiles_m,
                                                                p0.tiles_n, tile, smem);
     } else {
         const uint32_t tile = xcd_tile(blockIdx.x - grid0, gridDim.x - grid0);
         if (tile >= (uint32_t)(p1.tiles_m * p1.tiles_n)) return;
-        tile_gemm<kBf16KSlow, kBf16KSlow, EXACT, uint16_t, 1, 64, 64, 2>(p1.A, p1.B, nullptr, p1.C, p1.ldc, p1.M, p1.N, p1.K,
+        tile_gemm<kBf16KSlow, kBf16KSlow, EXACT, uint16_t, 1, 64, 64, 2, true>(p1.A, p1.B, nullptr, p1.C, p1.ldc, p1.M, p1.N, p1.K,
                                                                        p1.tiles_m, p1.tiles_n, tile, smem);
     }
 }
@@ -428,13 +462,21 @@ __global__ __launch_bounds__(256, 3) void k_gemm_kslow_direct(const uint16_t* __
         landed();
         __syncthreads();
     }
-    float* tp = reinterpret_cast<float*>(wave < 2 ? As[0] : Bs[0]) + (wave & 1) * kTransposeFloats;
-    static_assert(2 * AD::STAGE >= 2 * kTransposeFloats * 2, "two waves' transpose buffers fit in the A stages");
+    // Straight from the accumulators: three workgroups per CU cover for each other's stores here (64 tokens, 4096 x 11008:
+    // 20.8 us, as 16-byte runs through LDS 23.0; 4096 tokens 329 and 331).
 #pragma unroll
     for (int a = 0; a < MB; ++a)
 #pragma unroll
-        for (int b = 0; b < NB; ++b)
-            store_block<true>(acc[a][b], 0.f, tp, C, ldc, i0 + wm * 64 + a * 32, j0 + wn * 128 + b * 32, M, N, lane);
+        for (int b = 0; b < NB; ++b) {
+            const int col = j0 + wn * 128 + b * 32 + (lane & 31);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int row = i0 + wm * 64 + a * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+                const float x = acc[a][b][v];
+                if constexpr (sizeof(OUT) == 4) C[(int64_t)row * ldc + col] = x;
+                else C[(int64_t)row * ldc + col] = to_bf16(x);
+            }
+        }
 }
 
 // bf16 [X][64] operand tile (rows along the contraction index, 128 bytes each) filled by direct global -> LDS loads:
@@ -556,7 +598,8 @@ __global__ __launch_bounds__(512, 1) void k_gemm_kfast_direct(LinOperand A, LinO
         }
 }
 
-template <int AL, int BL, typename OUT, int MB, int TN, int BK, int WM = 2>
+// DEEP_EXACT, DEEP_RAGGED: two register sets where every tile and step is whole, and where not.
+template <int AL, int BL, typename OUT, int MB, int TN, int BK, int WM, bool DEEP_EXACT, bool DEEP_RAGGED>
 static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M,
                                    int64_t N, int64_t K, hipStream_t st, const LinBatch* many, int count, int64_t ldc) {
     constexpr int TM = 32 * MB * WM;
@@ -574,38 +617,50 @@ static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, con
     // no checks at all when every tile and every step is whole and rows start 16-byte aligned
     const bool exact = M % TM == 0 && N % TN == 0 && K % BK == 0 && A.ld % 8 == 0 && B.ld % 16 == 0;
     if (exact)
-        hipLaunchKernelGGL((k_tile_gemm<AL, BL, true, OUT, MB, TN, BK, WM>), grid, dim3(128 * WM), 0, st, A, B, bias, C, (int)M,
-                           (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
+        hipLaunchKernelGGL((k_tile_gemm<AL, BL, true, OUT, MB, TN, BK, WM, DEEP_EXACT>), grid, dim3(128 * WM), 0, st, A, B, bias,
+                           C, (int)M, (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
     else
-        hipLaunchKernelGGL((k_tile_gemm<AL, BL, false, OUT, MB, TN, BK, WM>), grid, dim3(128 * WM), 0, st, A, B, bias, C, (int)M,
-                           (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
+        hipLaunchKernelGGL((k_tile_gemm<AL, BL, false, OUT, MB, TN, BK, WM, DEEP_RAGGED>), grid, dim3(128 * WM), 0, st, A, B, bias,
+                           C, (int)M, (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
 }
 
 // Whether a product runs 64 x 64 tiles (see launch_tile_gemm).
 template <int AL, int BL>
 static bool lin_small(int64_t M, int64_t N, int count) {
-    constexpr bool slow_weight = BL == kInt8KSlow || BL == kInt8ZKSlow;
-    return ((M + 127) / 128) * ((N + 127) / 128) * count < (slow_weight ? 160 : 256);
+    constexpr bool slow_weight = BL == kInt8KSlow || BL == kInt8ZKSlow, grad_w = AL == kBf16KSlow && BL == kBf16KSlow;
+    return ((M + 127) / 128) * ((N + 127) / 128) * count < (slow_weight ? 160 : grad_w ? 200 : 256);
 }
 
-// Tile shape, from measurements on the linear layer of the LLaMA-7B shapes (ms per decoder layer at 4096 tokens):
+// Tile shape, from measurements on the linear layer (us unless said otherwise; T: 128 x 128 tiles of the product):
 //  * large outputs with an INT8 B operand, or with the contraction index fast in both operands: 256 x 256 tiles with
 //    64-deep steps, eight waves, one workgroup per CU (144 KB of LDS).  The B tile - and the dequantization of an
 //    INT8 B - is shared by twice as many MFMAs as in a 128-row tile, global traffic per MFMA halves, and 64-deep
-//    steps fetch whole cache lines of operands whose rows run along k.  Forward pass 2.24 -> 1.87, grad_input
-//    1.82 -> 1.66 (256 x 256 x 32 with eight waves: 1.72; 256 x 128 x 64: forward unchanged at 2.24).
-//  * otherwise four waves: 128 x 128 x 64 when an operand is INT8 or both have k fast, 128 x 256 x 32 (when that fills
-//    the chip twice) or 128 x 128 x 32 for grad_W;
+//    steps fetch whole cache lines of operands whose rows run along k.  7B shapes, ms per decoder layer at 4096 tokens:
+//    forward 2.24 -> 1.87, grad_input 1.82 -> 1.66 (256 x 256 x 32 with eight waves: 1.72; 256 x 128 x 64: forward
+//    unchanged at 2.24).  Two register sets where all tiles are whole (grad_input, 4096 tokens, 4096 -> 4096: 134 against
+//    137 with one; 8192 tokens 253 / 260); with ragged edges only where the last round of tiles leaves most CUs idle and the
+//    columns are whole (forward, 3000 tokens, 4096 -> 11008, 516 tiles: 334 / 371, but 5000 tokens, 2048 -> 5461, 440 tiles:
+//    161 / 158; 3000 tokens, 2048 -> 5461, 264 tiles with ragged columns: 160 / 145).
+//  * otherwise four waves: 128 x 128 x 64 when an operand is INT8 or both have k fast, with one register set where the
+//    tiles make one round of two workgroups per CU (256 < T <= 512) and two sets below and above: forward, 2048 tokens,
+//    2048 -> 2048 (T = 256) 26.7 with two against 31.3, 4096 tokens, 2048 -> 1280 (320) 40.0 / 36.0, 512 tokens, 4096 ->
+//    11008 (344) 75 / 67, 6000 tokens, 2048 -> 1920 (705) 74 / 77, 1024 tokens, 4096 -> 11008 (688) 124 / 135.  An INT8 B
+//    with k slow: two sets up to T = 256 only where rows and columns are whole (grad_input, 1024 tokens, 4096 -> 4096 45 /
+//    58, but 1000 tokens 80 / 77 and 4100 tokens, 768 -> 768 25.4 / 23.4), and beyond T = 512 128 x 128 x 32 with four
+//    workgroups per CU (4096 tokens, 2048 -> 2048 (512): 64-deep 42, 32-deep 44.5; 4100 tokens (528) 90 / 74; 3000 tokens,
+//    4096 -> 4096 (768) 179 / 150).
+//    grad_W: 128 x 256 x 32 when that fills the chip twice, 128 x 128 x 32 below, with two register sets up to T = 256
+//    (1000 tokens, 2048 x 2048: 16.0 against 19.7) and where everything is whole (2048 tokens, 3072 x 2048, T = 384: 37.1 /
+//    38.7; ragged, 2000 tokens, 3000 x 3000, T = 576: 91 / 85).
 //  * 64 x 64 x 64, four waves of one 32 x 32 block each, where 128 x 128 tiles would leave CUs idle: a K step of a lone
 //    workgroup is a serial chain (fragments, MFMAs, commit, barrier), 1.2 us for 128 x 128 x 64 before the commit and the
-//    fetches went between the MFMAs.  Measured (us, 64 / 128): forward, 256 tokens, 768 -> 2048 (32 tiles of 128 x 128)
-//    13.6 / 16.6, 256 x 4096 -> 11008 (172) 48 / 51, 1024 x 4096 -> 4096 (256) 65 / 54; grad_input, 1000 x 2048 -> 2048
-//    (128) 29 / 41, 256 x 4096 -> 11008 (172) 53 / 47; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 2736 x 1024 (176)
-//    40 / 62, 1000 tokens, 2048 x 2048 (256) 21 / 17.
-// One decoder layer, forward and backward: 256 tokens of the 130M model 331 -> 181 us, 1000 of the 1B model 1430 -> 982,
-// 4096 of the 7B model 5155 -> 4790 (that by the 16-byte stores of C).
-template <int AL, int BL, typename OUT>
+//    fetches went between the MFMAs.  64 / 128: forward, 256 tokens, 768 -> 2048 (T = 32) 13.6 / 16.6, 256 x 4096 -> 11008
+//    (172) 46.5 / 46.3, 2048 tokens, 2048 -> 1664 (208) 30.9 / 25.4, but ragged, 3000 tokens, 2048 -> 1280 (240) 38.5 / 48.4
+//    and 300 tokens, 4096 -> 11008 (258) 70 / 103; grad_input, 1000 x 2048 -> 2048 (128) 29 / 41, 256 x 4096 -> 11008 (172)
+//    53 / 43; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 1024 tokens, 1536 x 2048 (192) 15.7 / 15.9, 1664 x 2048 (208)
+//    20.8 / 15.9.
 // ldc: row pitch of C in elements (0: N).
+template <int AL, int BL, typename OUT>
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
                             int64_t K, hipStream_t st, const LinBatch* many = nullptr, int count = 1, int64_t ldc = 0) {
     constexpr bool both_fast = (AL == kBf16KFast || AL == kInt8KFast || AL == kInt8ZKFast) &&
@@ -642,29 +697,49 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
                     return check_launch();
                 }
             }
-            launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 64, 4>(A, B, bias, C, M, N, K, st, many, count, ldc);
+            const int64_t last = (((M + 255) / 256) * ((N + 255) / 256) * count - 1) % 256 + 1;   // tiles of the last round
+            if (last <= 64 && N % 256 == 0)
+                launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 64, 4, true, true>(A, B, bias, C, M, N, K, st, many, count, ldc);
+            else
+                launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 64, 4, true, false>(A, B, bias, C, M, N, K, st, many, count, ldc);
             return check_launch();
         }
     }
-    if (lin_small<AL, BL>(M, N, count))
-        launch_tile_gemm_shape<AL, BL, OUT, 1, 64, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
-    else if constexpr (both_fast || int8_b)
-        launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 64>(A, B, bias, C, M, N, K, st, many, count, ldc);
-    else if (((M + kLinTM - 1) / kLinTM) * ((N + 255) / 256) * count >= 512)
-        launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
-    else
-        launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 32>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    const int64_t tiles128 = ((M + 127) / 128) * ((N + 127) / 128) * count;
+    if (lin_small<AL, BL>(M, N, count)) {
+        launch_tile_gemm_shape<AL, BL, OUT, 1, 64, 64, 2, true, true>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    } else if constexpr (both_fast || int8_b) {
+        if constexpr (!both_fast) {
+            if (tiles128 > 512) {
+                launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 32, 2, true, false>(A, B, bias, C, M, N, K, st, many, count, ldc);
+                return check_launch();
+            }
+        }
+        const bool two = tiles128 > 256 ? tiles128 > 512 : both_fast || (M % 128 == 0 && N % 128 == 0);
+        if (two)
+            launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 64, 2, true, true>(A, B, bias, C, M, N, K, st, many, count, ldc);
+        else
+            launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 64, 2, false, false>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    } else if (((M + kLinTM - 1) / kLinTM) * ((N + 255) / 256) * count >= 512) {
+        launch_tile_gemm_shape<AL, BL, OUT, 2, 256, 32, 2, true, true>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    } else if (tiles128 <= 256) {
+        launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 32, 2, true, true>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    } else {
+        launch_tile_gemm_shape<AL, BL, OUT, 2, 128, 32, 2, true, false>(A, B, bias, C, M, N, K, st, many, count, ldc);
+    }
     return check_launch();
 }
 
 // dx (tokens x n_in = dy W, W with layout BL) and grad_W (rows x cols = A1^T B1 over the tokens): one launch where both
-// products run 64 x 64 tiles, otherwise one after the other.  Either output may be missing.  One 130M decoder layer on 256
-// tokens, forward and backward: 181 us with two launches per backward call, 151 with one.
+// products fit 64 x 64 tiles, otherwise one after the other.  Either output may be missing.  One 130M decoder layer on 256
+// tokens, forward and backward: 181 us with two launches per backward call, 151 with one.  grad_W comes along up to the
+// chip's 256 tiles of 128 x 128, further than it runs 64 x 64 tiles alone: 256 tokens, 2048 -> 1664 (208) 13.8 us, two
+// launches 18.8; 1024 tokens, 2048 -> 1920 (240) 33.1 / 36.4.
 template <int BL>
 static int launch_linear_backward(const LinOperand& A0, const LinOperand& B0, uint16_t* dx, int64_t M0, int64_t N0, int64_t K0,
                                   int64_t ldc0, const LinOperand& A1, const LinOperand& B1, uint16_t* G, int64_t M1, int64_t N1,
                                   int64_t K1, int64_t ldc1, hipStream_t st) {
-    if (dx && G && lin_small<kBf16KFast, BL>(M0, N0, 1) && lin_small<kBf16KSlow, kBf16KSlow>(M1, N1, 1)) {
+    if (dx && G && lin_small<kBf16KFast, BL>(M0, N0, 1) && ((M1 + 127) / 128) * ((N1 + 127) / 128) < 256) {
         auto product = [](const LinOperand& A, const LinOperand& B, uint16_t* C, int64_t M, int64_t N, int64_t K, int64_t ldc) {
             return LinProduct{A, B, C, ldc, (int)M, (int)N, (int)K, (int)((M + 63) / 64), (int)((N + 63) / 64)};
         };

@@ -93,6 +93,20 @@ def test_tile_configurations(tokens, m, n):
     test_backward(tokens, m, n)
 
 
+@pytest.mark.parametrize("tokens,m,n", [
+    (4096, 1280, 128), (2304, 64, 2304),     # one round of whole 128-row tiles: forward, grad_input
+    (1536, 100, 2048), (1500, 72, 2050),     # below it, grad_input: a ragged contraction index, ragged rows and columns
+    (4096, 64, 2176), (4100, 72, 2050),      # above it, grad_input: whole and ragged
+    (6000, 1290, 72),                        # above it, forward: ragged
+    (4100, 4096, 72), (4100, 72, 4096),      # 256 x 256 tiles, a second round of a few ragged rows
+    (96, 1792, 2048), (100, 1800, 2050),     # grad_W: 224 and 255 tiles of 128 x 128, whole and ragged,
+    (128, 2560, 2048), (68, 2570, 2050),     # 320 and 357
+])
+def test_loop_and_tile_of_every_size_class(tokens, m, n):
+    test_forward(tokens, m, n)
+    test_backward(tokens, m, n)
+
+
 def test_gradient_feeds_the_optimizer_step():
     """The layer's grad_W, as stored, is a valid gradient input of the step: projecting it gives what the oracle
     gives for the same bits."""
