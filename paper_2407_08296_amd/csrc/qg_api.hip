@@ -34,10 +34,10 @@ int launch_project_adam(const uint8_t*, const float*, const uint16_t*, float*, f
 int launch_project_adam_many(const PlanHeader*, const PlanHeader*, int, int64_t, const qg_hparams*, hipStream_t);
 int project_mode(int64_t m, int64_t n, int64_t ld, int64_t r);       // edge class the grouped projection needs for a matrix
 int backproject_mode(int64_t m, int64_t n, int64_t ld, int64_t r);   // ... and the grouped back-projection
-// tile configuration of a launch (edge class, 128 x 128 and 128 x 256 tiles of the projection; 128-row tiles of the
-// back-projection) and the tiles of a matrix in it
-int proj_config(int mode, int64_t tiles128, int64_t tiles256);
-int bp_config(int64_t tiles128);
+// tile configuration of a launch (edge class; largest r, 128 x 128 and 128 x 256 tiles of the projection; 128-row tiles of
+// the back-projection) and the tiles of a matrix in it
+int proj_config(int mode, int64_t r, int64_t tiles128, int64_t tiles256);
+int bp_config(int mode, int64_t tiles128);
 int64_t proj_tiles(int cfg, int64_t n, int64_t r);
 int64_t proj_tiles_r(int cfg, int64_t r);
 int64_t bp_tiles_m(int cfg, int64_t m);
@@ -200,16 +200,17 @@ extern "C" int qg_plan_build(int count, const qg_matrix_desc* descs, void* plan_
         return a > b ? a : b;
     };
     for (int cls = 0; cls < kPlanClasses; ++cls) {
-        int64_t t128 = 0, t256 = 0, b128 = 0;
+        int64_t r = 0, t128 = 0, t256 = 0, b128 = 0;
         for (int i = 0; i < count; ++i) {
             const qg_matrix_desc& d = descs[i];
             if (matrix_class(d) != cls) continue;
+            r = d.r > r ? d.r : r;
             t128 += proj_tiles(kProj128, d.n, d.r);
             t256 += proj_tiles(kProj256, d.n, d.r);
             b128 += bp_tiles_m(kBp128, d.m) * ((d.n + kManyBpBN - 1) / kManyBpBN);
         }
-        h.proj_cfg[cls] = (uint32_t)proj_config(cls, t128, t256);
-        h.bp_cfg[cls] = (uint32_t)bp_config(b128);
+        h.proj_cfg[cls] = (uint32_t)proj_config(cls, r, t128, t256);
+        h.bp_cfg[cls] = (uint32_t)bp_config(cls, b128);
     }
     uint64_t adam = 0, proj[kPlanClasses] = {0, 0, 0}, bp[kPlanClasses] = {0, 0, 0};
     int out = 0;

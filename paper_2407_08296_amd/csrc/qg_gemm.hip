@@ -13,8 +13,9 @@ static inline unsigned grid8(uint32_t tiles) { return ((tiles + 7u) / 8u) * 8u; 
 // Edge mode of a matrix for tiles of TM (along r for the projection, along m for the back-projection) x TN and K
 // steps of BK over `kdim`; ld is the row pitch of the n-wide arrays.  The direct loads need 16-byte aligned rows
 // (ld % 8, and r % 16 for the 8-byte P fetches) and 32-bit per-lane offsets.
+static inline bool unaligned(int64_t ld, int64_t r) { return ld > (int64_t(1) << 24) || (ld % 8) != 0 || (r % 16) != 0; }
 static inline int edge_mode(int64_t tiled, int TM, int64_t n, int64_t ld, int TN, int64_t kdim, int BK, int64_t r) {
-    if (ld > (int64_t(1) << 24) || (ld % 8) != 0 || (r % 16) != 0) return kUnaligned;
+    if (unaligned(ld, r)) return kUnaligned;
     if ((tiled % TM) == 0 && (n % TN) == 0 && (kdim % BK) == 0) return kExact;
     return kMasked;
 }
@@ -46,20 +47,23 @@ static auto with_mode(int mode, F f) {
 // its CU is bound by its own serial chain (fragment reads, MFMAs, dequantization, barrier): 0.31 us for 128 x 128, 0.23 us
 // for 64 x 128, against 0.11 and 0.05 us of MFMA time, so a launch with few tiles takes the smaller ones, with four tiles
 // in flight and the dequantization between the MFMAs; a launch with 128 x 256 workgroups enough (three fit a CU) lets
-// the workgroups cover for each other and takes the tile with the least staging per MFMA.  Measured (us per step, tiles
-// 64 x 128 / 128 x 128 / 128 x 256): one 2048 x 2048 matrix, r = 512, 37 / 48 / 53; 28 matrices of the 350M layer,
-// r = 256 (256 + 304 tiles of 128 x 128) 155 / 172 / 208; 84 of the 130M layer (624 of 128 x 256) 229 / 219 / 233;
-// 7 of the 7B layer (1112) 1585 / 1268 / 1258.  Unaligned rows are staged through registers, which leaves the
-// 128 x 256 instance two workgroups per CU: 1.09 ms with 128 x 128 against 1.29 for the 1B model's 24 odd matrices.
+// the workgroups cover for each other and takes the tile with the least staging per MFMA.  Measured with Adam (us, tiles
+// 64 x 128 / 128 x 128, at the number T of 128 x 128 tiles): 1024 x 1024, r = 256: T = 256 26 / 31, 320 32 / 41, 384 35 / 41,
+// 448 46 / 45; 2048 x 2048, r = 512: 320 45 / 53, 384 51 / 57, 512 66 / 66; 4096 rows, r = 1024: 320 73 / 83, 376 86 / 87,
+// 448 102 / 92: they cross between 384 and 448.  128 x 128 / 128 x 256, at the number of the latter: r = 256: 512 90 / 96,
+// 1024 175 / 188, 1536 278 / 280; r = 512: 768 170 / 172, 1152 261 / 264, 1536 348 / 338; r = 1024: 768 269 / 250, 896
+// 307 / 317, 1024 367 / 356, 1536 541 / 502.  Unaligned rows are staged through registers, which leaves the 128 x 256 instance two
+// workgroups per CU: 1.09 ms with 128 x 128 against 1.29 for the 1B model's 24 odd matrices.  A matrix of 64 rows of R or
+// fewer would leave half of every 128-row tile empty (64 x 100000, r = 64: 26 us; 128 x 128 34, 128 x 256 30).
 template <typename F>
 static auto with_proj(int cfg, F f) {
     if (cfg == kProj64) return f(ProjCfg<64, 128, 32, 2, 2, 4, 2, 2, 2>());
     if (cfg == kProj128) return f(ProjCfg<128, 128, 32, 2, 2, 4, 3, 3, 3>());
     return f(ProjCfg<kManyProjBM, kManyProjBN, 32, 2, 2, 2, 3, 3, 2>());
 }
-// tiles128: 128 x 128 tiles of the launch, tiles256: 128 x 256 tiles
-int proj_config(int mode, int64_t tiles128, int64_t tiles256) {
-    if (tiles128 <= 320) return kProj64;
+// r: the largest of the launch; tiles128: its 128 x 128 tiles, tiles256: its 128 x 256 tiles
+int proj_config(int mode, int64_t r, int64_t tiles128, int64_t tiles256) {
+    if (r <= 64 || tiles128 <= 320) return kProj64;
     return mode == kUnaligned || tiles256 < 1024 ? kProj128 : kProj256;
 }
 int64_t proj_tiles(int cfg, int64_t n, int64_t r) {
@@ -67,20 +71,23 @@ int64_t proj_tiles(int cfg, int64_t n, int64_t r) {
 }
 int64_t proj_tiles_r(int cfg, int64_t r) { return with_proj(cfg, [&](auto c) { return (r + c.BM - 1) / c.BM; }); }
 static int proj_config_of(int64_t n, int64_t ld, int64_t r, int64_t count) {
-    return proj_config((ld % 8) != 0 || (r % 16) != 0 ? kUnaligned : kExact, proj_tiles(kProj128, n, r) * count,
+    return proj_config(unaligned(ld, r) ? kUnaligned : kExact, r, proj_tiles(kProj128, n, r) * count,
                        proj_tiles(kProj256, n, r) * count);
 }
 
 // Back-projection: 128 rows x one block of 256 columns, three workgroups per CU, once that gives every CU a workgroup and
-// a half; below that 64 rows with four tiles in flight (us per step, 64 / 128 rows: 512 x 512, r = 128, 18.9 / 23.5;
-// 2048 x 2048, r = 512 (128 tiles) 46 / 53; 4096 x 4096, r = 1024 (512 tiles) 143 / 141; the weight tile shares the
-// staging LDS, the VALU-heavy update epilogue of one workgroup overlaps the main loops of the others).
+// a half; below that 64 rows with four tiles in flight (us, 64 / 128 rows, at the number of the latter: 1024 x 1024, r = 256:
+// 128 9.1 / 13.4, 256 13.1 / 14.5, 320 18.9 / 19.8, 384 19.3 / 20.1, 448 22.1 / 20.5; 2048 x 2048, r = 512: 128 11.8 / 17.6,
+// 256 16.9 / 18.8, 384 25.1 / 25.7, 512 30.6 / 26.5; the weight tile shares the staging LDS, the VALU-heavy update epilogue of
+// one workgroup overlaps the main loops of the others).  Unaligned rows: as long as the 64-row tiles make about one round
+// of two workgroups per CU (1024 x 1021, r = 256: 256 38 / 46, 288 54 / 59; 20000 x 300, r = 64, 314: 48 / 40; 2048 x 5461,
+// r = 512, 352: 77 / 72).
 template <typename F>
 static auto with_bp(int cfg, F f) {
     if (cfg == kBp64) return f(BpCfg<64, 32, 2, 2, 4, false, 2, 2, 2>());
     return f(BpCfg<kManyBpBM, 32, 2, 2, 2, false, 3, 3, 2>());   // the checked variant needs more registers
 }
-int bp_config(int64_t tiles128) { return tiles128 < 384 ? kBp64 : kBp128; }
+int bp_config(int mode, int64_t tiles128) { return tiles128 < (mode == kUnaligned ? 300 : 384) ? kBp64 : kBp128; }
 int64_t bp_tiles_m(int cfg, int64_t m) { return with_bp(cfg, [&](auto c) { return (m + c.BM - 1) / c.BM; }); }
 
 #define QG_PROJ(KERNEL, C, M, ...) (KERNEL<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, M, C::kWg[M]>)
@@ -93,9 +100,9 @@ int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, f
         using C = decltype(c);
         return with_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), [&](auto mode) {
             const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles = tr * (uint32_t)((n + C::BN - 1) / C::BN);
-            // (for three workgroups per CU the 128 x 256 instance of this kernel spills)
-            hipLaunchKernelGGL((k_project_adam<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, mode(), C::NS == 2 ? 2 : C::kWg[mode()]>), dim3(grid8(tiles)), dim3(C::NT), 0, stream, Pq, Ps, G, R, M,
-                               V, N, (int)m, (int)n, (int)ld, (int)r, tr, tiles, coef);
+            constexpr int WG = C::NS == 2 ? 2 : C::kWg[mode()];   // (for three the 128 x 256 instance of this kernel spills)
+            hipLaunchKernelGGL((k_project_adam<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, mode(), WG>), dim3(grid8(tiles)),
+                               dim3(C::NT), 0, stream, Pq, Ps, G, R, M, V, N, (int)m, (int)n, (int)ld, (int)r, tr, tiles, coef);
             return check_launch();
         });
     });
@@ -143,8 +150,8 @@ int launch_project(const uint8_t* Pq, const float* Ps, const uint16_t* G, float*
     });
 }
 
-// R_z = dequant(P_z)^T G_z for `count` (<= kProjBatchMax) matrices of one shape in one launch (same arithmetic per element as launch_project: the order of the sum over m does not depend on the
-// tile shape).
+// R_z = dequant(P_z)^T G_z for `count` (<= kProjBatchMax) matrices of one shape in one launch (same arithmetic per element
+// as launch_project: the order of the sum over m does not depend on the tile shape).
 int launch_project_batch(const ProjBatch& batch, int count, float* R, int64_t strideR, int64_t m, int64_t n, int64_t ld,
                          int64_t r, hipStream_t stream) {
     return with_proj(proj_config_of(n, ld, r, count), [&](auto c) {
@@ -164,7 +171,8 @@ int launch_backproject(const uint8_t* Pq, const float* Ps, const uint16_t* N, in
                        float* Udbg, int64_t m, int64_t n, int64_t ld, int64_t r, float alpha, float lr, uint64_t seed,
                        int64_t step, hipStream_t stream) {
     const uint32_t key = sr_key(seed, (uint64_t)step, 0u);
-    return with_bp(bp_config(bp_tiles_m(kBp128, m) * ((n + kGroup - 1) / kGroup)), [&](auto c) {
+    const int cfg = bp_config(unaligned(ld, r) ? kUnaligned : kExact, bp_tiles_m(kBp128, m) * ((n + kGroup - 1) / kGroup));
+    return with_bp(cfg, [&](auto c) {
         using C = decltype(c);
         return with_mode(edge_mode(m, C::BM, n, ld, kGroup, r, C::BK, r), [&](auto mode) {
             constexpr int MODE = mode();

@@ -269,18 +269,20 @@ BP_ROWS = {BP64: 64, BP128: 128}
     (384, 128, 256, 128, 0, PROJ128, BP128),
     (1023, 128, 256, 128, 0, PROJ128, BP128),       # of 128 x 256
     (1024, 128, 256, 128, 0, PROJ256, BP128),
-    (160, 140, 200, 136, 2, PROJ128, BP64),         # r % 16 != 0: unaligned; 640 tiles of 128 x 128, 320
-    (80, 140, 200, 136, 2, PROJ64, BP64),           # 320
+    (80, 140, 200, 136, 2, PROJ64, BP64),           # r % 16 != 0: unaligned; 320 tiles of 128 x 128, 160
     (81, 140, 200, 136, 2, PROJ128, BP64),
-    (192, 140, 200, 136, 2, PROJ128, BP128),
+    (149, 140, 200, 136, 2, PROJ128, BP64),         # 298 of the back-projection
+    (150, 140, 200, 136, 2, PROJ128, BP128),
     (1100, 140, 200, 136, 2, PROJ128, BP128),       # 2200 of 128 x 256: still 128 x 128
-    (1024, 120, 200, 48, 1, PROJ256, BP128),        # masked
-    (1023, 120, 200, 48, 1, PROJ128, BP128),
+    (1024, 120, 200, 112, 1, PROJ256, BP128),       # masked
+    (1023, 120, 200, 112, 1, PROJ128, BP128),
+    (1100, 120, 200, 64, 1, PROJ64, BP128),         # r <= 64: half of a 128-row tile would be empty
+    (1100, 120, 200, 40, 2, PROJ64, BP128),
 ])
 def test_plan_tiles_on_both_sides_of_every_rule(L, count, m, n, r, cls, proj, bp):
-    """The configuration of a class follows from its number of tiles (320 of 128 x 128 at most: 64 x 128; 1024 of 128 x
-    256 at least, rows aligned: 128 x 256; 384 back-projection tiles of 128 rows at least: 128 rows), and the tiles of
-    each launch and every matrix's first tiles are those of that configuration."""
+    """The configuration of a class follows from its number of tiles (320 of 128 x 128 at most, or r <= 64: 64 x 128; 1024
+    of 128 x 256 at least, rows aligned: 128 x 256; 384 back-projection tiles of 128 rows at least, 300 for unaligned rows:
+    128 rows), and the tiles of each launch and every matrix's first tiles are those of that configuration."""
     descs = (qg.MatrixDesc * count)()
     for d in descs:
         d.m, d.n, d.r = m, n, r

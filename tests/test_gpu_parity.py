@@ -348,7 +348,8 @@ def test_step_many_matches_oracle(shapes):
 
 
 @pytest.mark.parametrize("count", [60, 270])
-@pytest.mark.parametrize("m,n,r", [(256, 512, 256), (200, 520, 144), (200, 521, 136), (130, 517, 128)])
+@pytest.mark.parametrize("m,n,r", [(256, 512, 256), (200, 520, 144), (200, 521, 136), (130, 517, 128),
+                                   (130, 520, 64), (64, 517, 40), (96, 521, 88)])   # 64 rows of R or fewer, two and three K steps
 def test_every_tile_configuration_gives_the_single_step(m, n, r, count):
     """The tiles of a launch depend on how many there are: one matrix, 60 and 270 of them run in three configurations of
     the projection and two of the back-projection, exact, masked and unaligned.  The order of every sum is the same, so
