@@ -214,8 +214,8 @@ def other_configs(device):
         rows.append({"config": config, "workload": WORKLOADS[config], "row_layout": "pitch 16" if pad else "dense",
                      "ms_per_step": ms, "mfma_bound_ms": mfma_ms, "hbm_bound_ms": hbm_ms,
                      "bound": "mfma" if mfma_ms >= hbm_ms else "hbm", "frac_of_bound": bound / ms,
-                     "note": ("latency-bound: two dependent launches of four tiles each; a tile's K loop and epilogue set the time "
-                              "(replayed from a captured graph the step takes the same 35-39 us)") if config == 0 else None})
+                     "note": ("latency-bound: two dependent launches of 8 and 16 tiles; a tile's K loop and epilogue set the time"
+                              if config == 0 else None)})
         del plan, mats
         torch.cuda.empty_cache()
     return rows

@@ -31,10 +31,9 @@ struct ProjCfg {
     static constexpr int BM = BM_, BN = BN_, BK = BK_, WGM = WGM_, WGN = WGN_, NS = NS_, NT = WGM_ * WGN_ * 64;
     static constexpr int kWg[3] = {W0, W1, W2};
 };
-template <int BM_, int BK_, int WGn_, int WGm_, int NS_, bool PREF_, int W0, int W1, int W2>
+template <int BM_, int BK_, int WGn_, int WGm_, int NS_, int W0, int W1, int W2>
 struct BpCfg {
     static constexpr int BM = BM_, BN = kGroup, BK = BK_, WGn = WGn_, WGm = WGm_, NS = NS_, NT = WGn_ * WGm_ * 64;
-    static constexpr bool PREF = PREF_;
     static constexpr int kWg[3] = {W0, W1, W2};
 };
 template <typename F>
@@ -84,8 +83,8 @@ static int proj_config_of(int64_t n, int64_t ld, int64_t r, int64_t count) {
 // r = 512, 352: 77 / 72).
 template <typename F>
 static auto with_bp(int cfg, F f) {
-    if (cfg == kBp64) return f(BpCfg<64, 32, 2, 2, 4, false, 2, 2, 2>());
-    return f(BpCfg<kManyBpBM, 32, 2, 2, 2, false, 3, 3, 2>());   // the checked variant needs more registers
+    if (cfg == kBp64) return f(BpCfg<64, 32, 2, 2, 4, 2, 2, 2>());
+    return f(BpCfg<kManyBpBM, 32, 2, 2, 2, 3, 3, 2>());   // the checked variant needs more registers
 }
 int bp_config(int mode, int64_t tiles128) { return tiles128 < (mode == kUnaligned ? 300 : 384) ? kBp64 : kBp128; }
 int64_t bp_tiles_m(int cfg, int64_t m) { return with_bp(cfg, [&](auto c) { return (m + c.BM - 1) / c.BM; }); }
@@ -179,15 +178,15 @@ int launch_backproject(const uint8_t* Pq, const float* Ps, const uint16_t* N, in
             const uint32_t tm = (uint32_t)((m + C::BM - 1) / C::BM), tiles = tm * (uint32_t)((n + kGroup - 1) / kGroup);
             const dim3 grid(grid8(tiles)), block(C::NT);
             if (Wz != nullptr)   // zero-point weights (no U dump)
-                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::PREF, C::kWg[MODE], true>),
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::kWg[MODE], true>),
                                    grid, block, 0, stream, Pq, Ps, N, Wq, Ws, Wz, nullptr, (int)m, (int)n, (int)ld, (int)r,
                                    alpha, lr, key, tm, tiles);
             else if (Udbg != nullptr)
-                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, true, C::PREF, C::kWg[MODE]>), grid,
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, true, C::kWg[MODE]>), grid,
                                    block, 0, stream, Pq, Ps, N, Wq, Ws, nullptr, Udbg, (int)m, (int)n, (int)ld, (int)r, alpha,
                                    lr, key, tm, tiles);
             else
-                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::PREF, C::kWg[MODE]>), grid,
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::kWg[MODE]>), grid,
                                    block, 0, stream, Pq, Ps, N, Wq, Ws, nullptr, nullptr, (int)m, (int)n, (int)ld, (int)r,
                                    alpha, lr, key, tm, tiles);
             return check_launch();
@@ -225,10 +224,10 @@ int launch_backproject_many(const PlanHeader* plan_host, const PlanHeader* plan_
                 constexpr int MODE = mode();
                 const dim3 grid(grid8(tiles)), block(C::NT);
                 if (plan_host->zero_points)
-                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::PREF, C::kWg[MODE], true>),
+                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::kWg[MODE], true>),
                                        grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
                 else
-                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::PREF, C::kWg[MODE]>),
+                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::kWg[MODE]>),
                                        grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
                 return check_launch();
             });

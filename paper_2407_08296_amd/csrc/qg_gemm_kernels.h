@@ -692,9 +692,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_many(c
     const PlanMatrix* mats = plan_matrices(plan) + first;
     const PlanMatrix& d = mats[plan_find(mats, count, tile, [](const PlanMatrix& x) { return x.proj_tile0; })];
     const uint32_t local = tile - d.proj_tile0;
-    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(as_global(d.Pq), as_global(d.Ps), as_global(d.G), as_global(d.R), (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
-                                               (int)(local % d.proj_tiles_r) * BM,
-                                               (int)(local / d.proj_tiles_r) * BN, smem);
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE>(as_global(d.Pq), as_global(d.Ps), as_global(d.G), as_global(d.R), (int)d.m,
+                                                 (int)d.n, (int)d.ld, (int)d.r, (int)(local % d.proj_tiles_r) * BM,
+                                                 (int)(local / d.proj_tiles_r) * BN, smem);
 }
 
 // Up to kProjBatchMax matrices of one shape in one launch, their pointers passed by value (no plan in device memory:
@@ -731,10 +731,11 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam_m
     const PlanMatrix* mats = plan_matrices(plan) + first;
     const PlanMatrix& d = mats[plan_find(mats, count, tile, [](const PlanMatrix& x) { return x.proj_tile0; })];
     const uint32_t local = tile - d.proj_tile0;
-    project_tile<BM, BN, BK, WGM, WGN, NS, MODE, true>(as_global(d.Pq), as_global(d.Ps), as_global(d.G), write_R ? as_global(d.R) : nullptr, (int)d.m, (int)d.n,
-                                                     (int)d.ld, (int)d.r, (int)(local % d.proj_tiles_r) * BM,
-                                                     (int)(local / d.proj_tiles_r) * BN, smem, as_global(d.M), as_global(d.V),
-                                                         as_global(d.N), &coef);
+    project_tile<BM, BN, BK, WGM, WGN, NS, MODE, true>(as_global(d.Pq), as_global(d.Ps), as_global(d.G),
+                                                       write_R ? as_global(d.R) : nullptr, (int)d.m, (int)d.n, (int)d.ld,
+                                                       (int)d.r, (int)(local % d.proj_tiles_r) * BM,
+                                                       (int)(local / d.proj_tiles_r) * BN, smem, as_global(d.M),
+                                                       as_global(d.V), as_global(d.N), &coef);
 }
 
 // ============================================================================
@@ -745,10 +746,9 @@ __global__ __launch_bounds__(WGM* WGN * 64, MIN_WG_PER_CU) void k_project_adam_m
 // in-lane reduction plus one cross-half shuffle and one LDS exchange.
 // Tile: 256 columns of W (exactly one quantization block per row) x BMm rows.
 // ============================================================================
-// W_PREFETCH: the weight tile has LDS of its own and is fetched before the main loop (one workgroup per CU);
-// otherwise it reuses the staging buffers after the main loop (smaller footprint, two workgroups per CU, whose
-// epilogue and main loop then overlap).
-template <int BMm, int BK, int WGn, int WGm, int NS, bool W_PREFETCH = true, bool ZP = false>
+// The weight tile reuses the staging buffers after the main loop: with LDS of its own, fetched before the loop, only one
+// workgroup would fit a CU, and the epilogue of one overlaps the main loop of another.
+template <int BMm, int BK, int WGn, int WGm, int NS, bool ZP = false>
 struct BpShape {
     static constexpr int BNn = kGroup;
     static constexpr int NT = WGn * WGm * 64;
@@ -758,8 +758,8 @@ struct BpShape {
     static constexpr int STAGING = NS * A_STAGE + 2 * B_STAGE;   // uint16 elements
     static constexpr int WTILE = BMm * BNn / 2;                // INT8 weight tile, in uint16 elements
     static constexpr int EXCH = (ZP ? 2 : 1) * WGn * BMm * 2;   // row-max (and, with zero points, row-min) exchange
-    static constexpr int WOFF = W_PREFETCH ? STAGING : EXCH;    // after the exchange area if aliased
-    static constexpr int SMEM = W_PREFETCH ? STAGING + WTILE : (STAGING > WOFF + WTILE ? STAGING : WOFF + WTILE);
+    static constexpr int WOFF = EXCH;                           // the weight tile lies after the exchange area
+    static constexpr int SMEM = STAGING > WOFF + WTILE ? STAGING : WOFF + WTILE;
 };
 
 // Byte offset of weight-tile element (row, col) in LDS.  Rows are 256 bytes (one quantization block); the 16
@@ -781,7 +781,7 @@ __device__ __forceinline__ constexpr int wtile_run_bits(int a, int v4) {
 // ZP: the weight carries a zero point per block (Sec. 3.1 eq.; Appendix A's `W_q - zeros`): x = (code - z)*s - lr*U,
 // the new block takes s' = (hi - lo)/255 over [min(0, min x), max(0, max x)], z' = -128 - round(lo/s'), and the
 // stochastically rounded code is floor(x/s' + u) + z'.
-template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool DUMP_U, bool W_PREFETCH = true, bool ZP = false>
+template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool DUMP_U, bool ZP = false>
 __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq, const float* __restrict__ Ps,
                                                  const uint16_t* __restrict__ N, int8_t* __restrict__ Wq,
                                                  float* __restrict__ Ws, float* __restrict__ Wz,
@@ -791,7 +791,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     constexpr bool RAGGED = MODE != kExact;      // masked epilogue
     constexpr bool DIRECT = MODE != kUnaligned;  // buffer / direct-to-LDS loads; a P fetch (8*WPT codes) starts at a
                                                  // multiple of 8*WPT codes, so it lies in one block of 256
-    using S = BpShape<BMm, BK, WGn, WGm, NS, W_PREFETCH, ZP>;
+    using S = BpShape<BMm, BK, WGn, WGm, NS, ZP>;
     constexpr int BNn = S::BNn, NT = S::NT, NW = WGn * WGm;
     constexpr int SN = BNn / WGn, SM = BMm / WGm, IB = SN / 32, JB = SM / 32;
     constexpr int PA = S::PA, PB = S::PB;
@@ -824,40 +824,38 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     // whole tile inside the matrix and rows 16-byte aligned: the direct loads work in the edge-checking kernels too
     const bool w_fast = !RAGGED || (m0 + BMm <= m && n0 + BNn <= n && (ld & 15) == 0);
     auto load_wtile = [&]() {
-    if (w_fast) {
+        if (w_fast) {
 #pragma unroll
-        for (int i = 0; i < W_ROUNDS; ++i) {
-            const int rb = (wave * W_ROUNDS + i) * 4;             // first of the 4 rows this wave access covers
-            const int row = rb + (lane >> 4), chunk = (lane ^ row) & 15;
-            const int8_t* src = Wq + (int64_t)(m0 + row) * ld + n0 + chunk * 16;
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
-                                             (__attribute__((address_space(3))) void*)(wt + rb * kGroup), 16, 0, 0);
-        }
-    } else {
-        // same lane -> (row, chunk) map through registers: rows may start at any byte offset, and the chunk that
-        // straddles the matrix edge is fetched byte by byte
-#pragma unroll
-        for (int i = 0; i < W_ROUNDS; ++i) {
-            const int rb = (wave * W_ROUNDS + i) * 4;
-            const int row = rb + (lane >> 4), chunk = (lane ^ row) & 15;
-            const int8_t* src = Wq + (int64_t)(m0 + row) * ld + n0 + chunk * 16;
-            const int valid = m0 + row < m ? n - (n0 + chunk * 16) : 0;
-            u32x4 v = {0u, 0u, 0u, 0u};
-            if (valid >= 16) {
-                v = *reinterpret_cast<const u32x4_align1*>(src);
-            } else {
-                uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-                for (int j = 0; j < 16; ++j)
-                    if (j < valid) w[j >> 2] |= (uint32_t)(uint8_t)src[j] << (8 * (j & 3));
-                v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3];
+            for (int i = 0; i < W_ROUNDS; ++i) {
+                const int rb = (wave * W_ROUNDS + i) * 4;             // first of the 4 rows this wave access covers
+                const int row = rb + (lane >> 4), chunk = (lane ^ row) & 15;
+                const int8_t* src = Wq + (int64_t)(m0 + row) * ld + n0 + chunk * 16;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                                 (__attribute__((address_space(3))) void*)(wt + rb * kGroup), 16, 0, 0);
             }
-            *reinterpret_cast<u32x4*>(wt + rb * kGroup + lane * 16) = v;
+        } else {
+            // same lane -> (row, chunk) map through registers: rows may start at any byte offset, and the chunk that
+            // straddles the matrix edge is fetched byte by byte
+#pragma unroll
+            for (int i = 0; i < W_ROUNDS; ++i) {
+                const int rb = (wave * W_ROUNDS + i) * 4;
+                const int row = rb + (lane >> 4), chunk = (lane ^ row) & 15;
+                const int8_t* src = Wq + (int64_t)(m0 + row) * ld + n0 + chunk * 16;
+                const int valid = m0 + row < m ? n - (n0 + chunk * 16) : 0;
+                u32x4 v = {0u, 0u, 0u, 0u};
+                if (valid >= 16) {
+                    v = *reinterpret_cast<const u32x4_align1*>(src);
+                } else {
+                    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+                    for (int j = 0; j < 16; ++j)
+                        if (j < valid) w[j >> 2] |= (uint32_t)(uint8_t)src[j] << (8 * (j & 3));
+                    v[0] = w[0]; v[1] = w[1]; v[2] = w[2]; v[3] = w[3];
+                }
+                *reinterpret_cast<u32x4*>(wt + rb * kGroup + lane * 16) = v;
+            }
         }
-    }
     };
-    if (W_PREFETCH) load_wtile();   // lands while the GEMM main loop runs
-
     u32x4 av[NS][DIRECT ? 1 : A_PER];   // the unaligned kernels stage N through registers
     uint32_t bw[NS][B_PER][WPT];
     float bsc[NS][B_PER][BT::NSC];
@@ -865,7 +863,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     const int KT = (r + BK - 1) / BK;
 
     // Uniform bases that advance with the K step plus fixed 32-bit per-thread offsets, as in the projection.  The
-    // tile's first code, m0*r, starts a block of 256 (m0 is a multiple of 128, r of 8); the K offset k0 does not,
+    // tile's first code, m0*r, starts a block of 256 (m0 is a multiple of 64, r of 8); the K offset k0 does not,
     // so the index of a code's block scale takes one add and two shifts per step.
     constexpr int A_OFFS = DIRECT ? AD::VARIANTS : A_PER;
     uint32_t a_off[A_OFFS], b_el[B_PER];   // N: byte or element offset, as G's in the projection; P: element offset inside
@@ -1027,7 +1025,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
         lds_barrier();
     }
 
-    if (!W_PREFETCH) load_wtile();    // the staging buffers are free now (the main loop ends with a barrier)
+    load_wtile();    // the staging buffers are free now (the main loop ends with a barrier)
     // The rows' old scales (and zero points) are fetched together with the weight tile: one wait covers both, where
     // loading them inside the epilogue exposed a second memory latency per tile.
     float s_old_row[JB], z_old_row[ZP ? JB : 1];
@@ -1177,8 +1175,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     }
 }
 
-template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool DUMP_U, bool W_PREFETCH = true, int MIN_WG_PER_CU = 1,
-          bool ZP = false>
+template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool DUMP_U, int MIN_WG_PER_CU = 1, bool ZP = false>
 __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject(const uint8_t* __restrict__ Pq,
                                                                const float* __restrict__ Ps,
                                                                const uint16_t* __restrict__ N,
@@ -1187,22 +1184,23 @@ __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject(co
                                                                float* __restrict__ Udbg, int m, int n, int ld, int r,
                                                                float alpha, float lr, uint32_t key, uint32_t tiles_m,
                                                                uint32_t tiles) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, NS, W_PREFETCH, ZP>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, NS, ZP>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
-    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, DUMP_U, W_PREFETCH, ZP>(Pq, Ps, N, Wq, Ws, Wz, Udbg, m, n, ld, r, (int)(tile % tiles_m) * BMm,
-                                                (int)(tile / tiles_m), alpha, lr, key, smem);
+    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, DUMP_U, ZP>(Pq, Ps, N, Wq, Ws, Wz, Udbg, m, n, ld, r,
+                                                              (int)(tile % tiles_m) * BMm, (int)(tile / tiles_m), alpha, lr,
+                                                              key, smem);
 }
 
 constexpr int kBpStrip = 16;   // row tiles per strip of the grouped back-projection's tile numbering (8: the same
                                // time; 32: 2 % slower; whole columns of tiles, as before: 1 % slower)
 
-template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, bool W_PREFETCH = true, int MIN_WG_PER_CU = 1, bool ZP = false>
+template <int BMm, int BK, int WGn, int WGm, int NS, int MODE, int MIN_WG_PER_CU = 1, bool ZP = false>
 __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject_many(const PlanHeader* __restrict__ plan, int first,
                                                                                    int count, uint32_t tiles,
                                                                                    float alpha, float lr,
                                                                                    uint64_t seed, uint64_t step) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, NS, W_PREFETCH, ZP>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[BpShape<BMm, BK, WGn, WGm, NS, ZP>::SMEM];
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= tiles) return;
     const PlanMatrix* mats = plan_matrices(plan) + first;
@@ -1217,9 +1215,10 @@ __global__ __launch_bounds__(WGn* WGm * 64, MIN_WG_PER_CU) void k_backproject_ma
     const uint32_t strip = local / (kBpStrip * tiles_n), in_strip = local % (kBpStrip * tiles_n);
     const uint32_t strip_rows = min((uint32_t)kBpStrip, d.bp_tiles_m - strip * kBpStrip);
     const uint32_t tile_m = strip * kBpStrip + in_strip % strip_rows, tile_n = in_strip / strip_rows;
-    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, false, W_PREFETCH, ZP>(
-        as_global(d.Pq), as_global(d.Ps), as_global(d.N), as_global(d.Wq), as_global(d.Ws), as_global(d.Wz), nullptr, (int)d.m, (int)d.n, (int)d.ld, (int)d.r,
-                                                (int)tile_m * BMm, (int)tile_n, alpha, lr, key, smem);
+    backproject_tile<BMm, BK, WGn, WGm, NS, MODE, false, ZP>(as_global(d.Pq), as_global(d.Ps), as_global(d.N), as_global(d.Wq),
+                                                             as_global(d.Ws), as_global(d.Wz), nullptr, (int)d.m, (int)d.n,
+                                                             (int)d.ld, (int)d.r, (int)tile_m * BMm, (int)tile_n, alpha, lr,
+                                                             key, smem);
 }
 
 }  // namespace qg
