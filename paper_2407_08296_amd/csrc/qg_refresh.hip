@@ -278,8 +278,9 @@ __device__ __forceinline__ double trace_of(const double* __restrict__ S, int r, 
 // around its latency: one wave holds 16 columns of all 64 rows in registers (lane = row) and takes pivot and
 // multipliers from other lanes with v_readlane (no LDS round trip or barrier per column); the four waves then update
 // what is right of the 16 columns with fp64 MFMAs.  The inverse is built from the four 16 x 16 diagonal inverses
-// (one wave each) and three block diagonals of MFMA products.  One barrier pair per 16 columns; with the matrix in LDS
-// and two barriers per column (the form before) a 64 x 64 block took 91 us, this one about 12 us.
+// (one wave each) and three block diagonals of MFMA products.  One barrier pair per 16 columns.  With the matrix in LDS
+// and two barriers per column (the form before) the launch of one 64 x 64 block took 91 us, with this one (k_chol_diag, the
+// trace of S included) it takes 28.
 __device__ __forceinline__ void chol_diag_block(double* T, double* rdg, double* __restrict__ S, int r, int kb,
                                                 double* __restrict__ Dinv, double* __restrict__ X, int32_t* __restrict__ info,
                                                 double sigma, double flag_factor) {
@@ -384,21 +385,29 @@ __device__ __forceinline__ void chol_diag_block(double* T, double* rdg, double* 
     }
 }
 
-// The first diagonal block: also forms sigma, kept for the later ones.
-__global__ __launch_bounds__(256) void k_chol_first(double* __restrict__ S, int r, double* __restrict__ Dinv,
-                                                    double* __restrict__ X, int32_t* __restrict__ info,
-                                                    double* __restrict__ shift, double flag_factor, BatchStride st) {
+// Diagonal block kb; the first one (FIRST: kb is 0) also forms sigma, kept for the later ones.
+template <bool FIRST>
+__global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ S, int r, int kb, double* __restrict__ Dinv,
+                                                   double* __restrict__ X, int32_t* __restrict__ info,
+                                                   double* __restrict__ shift, double flag_factor, BatchStride st) {
     S += blockIdx.z * st.S;
     __shared__ double T[kNB * kPitchD];
     __shared__ double rdg[kNB], red[4];
+    const int base = FIRST ? 0 : kb * kNB;
     for (int e = threadIdx.x; e < kNB * kNB; e += 256) {     // consecutive threads along a row
         const int i = e >> 6, c = e & 63;
-        T[i * kPitchD + c] = (i < r && c < r) ? S[(int64_t)i * r + c] : (i == c ? 1.0 : 0.0);
+        T[i * kPitchD + c] = (base + i < r && base + c < r) ? S[(int64_t)(base + i) * r + base + c] : (i == c ? 1.0 : 0.0);
     }
-    const double tr = trace_of(S, r, red);
-    const double sigma = tr > 0.0 ? 0x1p-46 * tr : 0.0;
-    if (threadIdx.x == 0) shift[blockIdx.z * st.shift] = sigma;
-    chol_diag_block(T, rdg, S, r, 0, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma, flag_factor);
+    double sigma;
+    if constexpr (FIRST) {
+        const double tr = trace_of(S, r, red);
+        sigma = tr > 0.0 ? 0x1p-46 * tr : 0.0;
+        if (threadIdx.x == 0) shift[blockIdx.z * st.shift] = sigma;
+    } else {
+        sigma = shift[blockIdx.z * st.shift];
+        __syncthreads();
+    }
+    chol_diag_block(T, rdg, S, r, FIRST ? 0 : kb, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma, flag_factor);
 }
 
 __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int r, int kb, const double* __restrict__ Dinv,
@@ -485,9 +494,11 @@ __global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S,
     trinv_block(S + blockIdx.z * st.S, X + blockIdx.z * st.X, Dinv + blockIdx.z * st.D, r, ib, blockIdx.x, At, Bt);
 }
 
-// Workgroups 0 .. pairs-1: the trailing blocks of step kb, block (kb+1, kb+1) first, which goes on to be factored;
-// workgroups pairs .. pairs+kb-1: block row kb of X (L's row kb and X_kk are final, X's rows above too).  In one
-// launch the three fill the chip together, and a block column costs two launches where it took four.
+// Workgroups 0 .. pairs-1: the trailing blocks of step kb.  FUSED: block (kb+1, kb+1) goes on to be factored, and workgroups
+// pairs .. pairs+kb-1 take block row kb of X (L's row kb and X_kk are final, X's rows above too): in one launch the three
+// fill the chip together, and a block column costs two launches where it takes four.  But every workgroup then holds the
+// diagonal block's 302 registers and the inverse's 43 KB of LDS, one on a CU; on its own the trailing update fits five.
+template <bool FUSED>
 __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int r, int kb, int pairs,
                                                      double* __restrict__ Dinv, double* __restrict__ X,
                                                      int32_t* __restrict__ info, const double* __restrict__ shift,
@@ -495,14 +506,16 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
     S += blockIdx.z * st.S;
     X += blockIdx.z * st.X;
     Dinv += blockIdx.z * st.D;
-    constexpr int A_LEN = kNB * kPitchKF, B_LEN = kNB * kPitchT;
-    static_assert(A_LEN + B_LEN >= kNB * kPitchD && B_LEN >= kNB * kPitchKF, "one buffer serves the three roles");
+    constexpr int A_LEN = kNB * kPitchKF, B_LEN = FUSED ? kNB * kPitchT : A_LEN;
+    static_assert(!FUSED || (A_LEN + B_LEN >= kNB * kPitchD && B_LEN >= A_LEN), "one buffer serves the three roles");
     __shared__ double buf[A_LEN + B_LEN];
-    __shared__ double rdg[kNB];
+    __shared__ double rdg[FUSED ? kNB : 1];
     double *At = buf, *Bt = buf + A_LEN;
-    if ((int)blockIdx.x >= pairs) {
-        trinv_block(S, X, Dinv, r, kb, blockIdx.x - pairs, At, Bt);
-        return;
+    if constexpr (FUSED) {
+        if ((int)blockIdx.x >= pairs) {
+            trinv_block(S, X, Dinv, r, kb, blockIdx.x - pairs, At, Bt);
+            return;
+        }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
     int pi, pj;
@@ -524,19 +537,21 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
         mma_chunk(At, kPitchKF, 1, Bt, kPitchKF, 1, acc, lane, wi, wj);
         __syncthreads();
     }
-    if (blockIdx.x != 0) {
+    if (!FUSED || blockIdx.x != 0) {
         for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
             const int gi = ib * kNB + row, gj = jb * kNB + col;
             if (gi < r && gj < r) S[(int64_t)gi * r + gj] -= x;
         });
         return;
     }
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = ib * kNB + row, gj = ib * kNB + col;
-        buf[row * kPitchD + col] = (gi < r && gj < r) ? S[(int64_t)gi * r + gj] - x : (row == col ? 1.0 : 0.0);
-    });
-    __syncthreads();
-    chol_diag_block(buf, rdg, S, r, kb + 1, Dinv, X, info + blockIdx.z, shift[blockIdx.z * st.shift], flag_factor);
+    if constexpr (FUSED) {
+        for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
+            const int gi = ib * kNB + row, gj = ib * kNB + col;
+            buf[row * kPitchD + col] = (gi < r && gj < r) ? S[(int64_t)gi * r + gj] - x : (row == col ? 1.0 : 0.0);
+        });
+        __syncthreads();
+        chol_diag_block(buf, rdg, S, r, kb + 1, Dinv, X, info + blockIdx.z, shift[blockIdx.z * st.shift], flag_factor);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -680,14 +695,26 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     const unsigned B = (unsigned)batch;
     hipLaunchKernelGGL(k_gram, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
-    hipLaunchKernelGGL(k_chol_first, dim3(1, 1, B), blk, 0, stream, S, (int)r, Dinv, X, info, shift, flag_factor, st);
+    // One launch per block column while its workgroups, one on a CU, are few (ms per refresh, fused / separate: one 4096 x
+    // 4096, r = 1024, 2.36 / 3.16, 16 of them 10.9 / 11.2, 32 20.8 / 19.9, 128 80.0 / 72.6; r = 512: 32 matrices 3.62 / 3.76, 96
+    // 9.74 / 9.32; r = 256: 32 0.85 / 0.91, 84 1.81 / 1.79).  The arithmetic is the same, and with it every bit.
+    const bool fused = batch * nt <= 384;
+    hipLaunchKernelGGL(k_chol_diag<true>, dim3(1, 1, B), blk, 0, stream, S, (int)r, 0, Dinv, X, info, shift, flag_factor, st);
     for (int kb = 0; kb + 1 < nt; ++kb) {
         const int below = nt - kb - 1, left = below * (below + 1) / 2;
         hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
-        hipLaunchKernelGGL(k_chol_update, dim3(left + kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
-                           flag_factor, st);
+        if (fused) {
+            hipLaunchKernelGGL(k_chol_update<true>, dim3(left + kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info,
+                               shift, flag_factor, st);
+        } else {
+            hipLaunchKernelGGL(k_chol_update<false>, dim3(left, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
+                               flag_factor, st);
+            hipLaunchKernelGGL(k_chol_diag<false>, dim3(1, 1, B), blk, 0, stream, S, (int)r, kb + 1, Dinv, X, info, shift,
+                               flag_factor, st);
+        }
     }
-    if (nt > 1) hipLaunchKernelGGL(k_trinv_row, dim3(nt - 1, 1, B), blk, 0, stream, S, X, Dinv, (int)r, nt - 1, st);
+    for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
+        if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
     hipLaunchKernelGGL(k_apply, dim3((unsigned)((m + kNB - 1) / kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
 }
 

@@ -252,6 +252,23 @@ def test_batched_refresh_across_launch_groups(count):
         assert float(host(cos)[i]) == float(host(one[2])[0])
 
 
+@pytest.mark.parametrize("m,n,r,count", [(256, 264, 200, 96), (256, 264, 200, 97), (160, 200, 136, 129), (72, 96, 64, 385)])
+def test_large_batches_equal_the_single_matrix_calls(m, n, r, count):
+    """Up to 384 block rows of 64 in a batch (96 matrices of r = 200) a block column of the factorization is one launch,
+    beyond that its parts are launches of their own: bit for bit the single call's result either way."""
+    ins = [start(m, n, r, seed=s) for s in range(3)]
+    up = [(bits_t(Gb), dev(Pq), dev(Ps)) for Gb, Pq, Ps in ins]
+    single = [qg.subspace_refresh(Pq, Ps, G, m, n, r, 1) for G, Pq, Ps in up]
+    pick = [up[i % 3] for i in range(count)]
+    pq, ps, cos, info, _ = qg.subspace_refresh_many([p for _, p, _ in pick], [s for _, _, s in pick], [g for g, _, _ in pick],
+                                                    m, n, r, 1)
+    assert host(info).tolist() == [0] * count
+    c = host(cos)
+    for i in range(count):
+        one = single[i % 3]
+        assert torch.equal(pq[i], one[0]) and torch.equal(ps[i], one[1]) and float(c[i]) == float(host(one[2])[0]), i
+
+
 def test_refresh_at_llama7b_shapes_by_properties():
     """Full-size matrices of the 7B configuration (r = 1024): sampled entries of Y against fp64 dot products, Q
     orthonormal and spanning Y, the new P capturing more of G than the start."""
