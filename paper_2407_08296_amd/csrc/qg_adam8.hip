@@ -23,7 +23,7 @@ constexpr int kS8SignedZero = 127;    // index of 0 in the signed table
 
 // Bucket table of the encoder: the positive floats up to 1 are cut into buckets by their top 15 bits (exponent and 7
 // mantissa bits); lut[bucket] = number of midpoints below the bucket's lower edge.  Buckets are narrower than the
-// spacing of the midpoints everywhere (at most one midpoint per bucket, which s8_build relies on and the bit-exact
+// spacing of the midpoints everywhere (at most one midpoint per bucket, which s8_encode4 relies on and the bit-exact
 // tests of the quantizer cover), so the code of a value is lut[bucket] plus one comparison with the next midpoint.
 constexpr int kS8KeyShift = 16;
 constexpr int kS8KeyOne = 0x3F800000 >> kS8KeyShift;     // bucket of 1.0
@@ -41,40 +41,51 @@ struct S8Tables {
 };
 
 // Entry p >= 1 of the positive half of a table with levels 0..top.
-__device__ inline double s8_positive(int p, int top) {
+constexpr double s8_positive(int p, int top) {
     const double pow10neg[8] = {1e0, 1e-1, 1e-2, 1e-3, 1e-4, 1e-5, 1e-6, 1e-7};
-    const int L = 31 - __clz(p), k = p - (1 << L);
-    return pow10neg[top - L] * (0.1 + 0.9 * (double)(k + 1) / (double)(1 << L));
+    int L = 0;
+    while ((2 << L) <= p) ++L;
+    return pow10neg[top - L] * (0.1 + 0.9 * (double)(p - (1 << L) + 1) / (double)(1 << L));
 }
 
-// Number of the `count` ascending midpoints mid[0..count) that lie below x.
-__device__ inline int s8_count_below(const float* mid, int count, float x) {
-    int lo = 0, hi = count;   // answer in [lo, hi]
-    while (lo < hi) {
-        const int m = (lo + hi) >> 1;
-        if (mid[m] < x) lo = m + 1; else hi = m;
+// lut[i] = number of the `count` ascending midpoints below the lower edge of bucket key0 + i.
+constexpr void s8_fill_lut(uint8_t* lut, int size, int key0, const float* mid, int count) {
+    int below = 0;
+    for (int i = 0; i < size; ++i) {
+        const float edge = __builtin_bit_cast(float, (uint32_t)(key0 + i) << kS8KeyShift);
+        while (below < count && mid[below] < edge) ++below;
+        lut[i] = (uint8_t)below;
     }
-    return lo;
 }
 
-// Every workgroup (256 threads) builds the tables from the definition; thread p makes entry p.
-__device__ inline void s8_build(S8Tables& T) {
-    const int p = threadIdx.x;
-    T.uval[p] = p == 0 ? 0.f : (float)s8_positive(p, 7);
-    float s;
-    if (p < kS8SignedZero) s = -(float)s8_positive(kS8SignedZero - p, 6);
-    else if (p == kS8SignedZero) s = 0.f;
-    else s = (float)s8_positive((p < 255 ? p : 254) - kS8SignedZero, 6);
-    T.sval[p] = s;
-    __syncthreads();
-    T.umid[p] = p < 255 ? (float)(0.5 * ((double)T.uval[p] + (double)T.uval[p + 1])) : INFINITY;
-    T.smid[p] = p < 254 ? (float)(0.5 * ((double)T.sval[p] + (double)T.sval[p + 1])) : INFINITY;
-    __syncthreads();
-    for (int i = p; i < kS8ULut; i += 256)
-        T.ulut[i] = (uint8_t)s8_count_below(T.umid, 255, __builtin_bit_cast(float, (uint32_t)(kS8UKey0 + i) << kS8KeyShift));
-    for (int i = p; i < kS8SLut; i += 256)
-        T.slut[i] = (uint8_t)s8_count_below(T.smid + kS8SignedZero, 127,
-                                            __builtin_bit_cast(float, (uint32_t)(kS8SKey0 + i) << kS8KeyShift));
+// The tables from their definition, at compile time.
+constexpr S8Tables s8_make() {
+    S8Tables T{};
+    for (int p = 0; p < 256; ++p) {
+        T.uval[p] = p == 0 ? 0.f : (float)s8_positive(p, 7);
+        if (p < kS8SignedZero) T.sval[p] = -(float)s8_positive(kS8SignedZero - p, 6);
+        else if (p > kS8SignedZero) T.sval[p] = (float)s8_positive((p < 255 ? p : 254) - kS8SignedZero, 6);
+    }
+    for (int p = 0; p < 256; ++p) {
+        T.umid[p] = p < 255 ? (float)(0.5 * ((double)T.uval[p] + (double)T.uval[p + 1])) : __builtin_inff();
+        T.smid[p] = p < 254 ? (float)(0.5 * ((double)T.sval[p] + (double)T.sval[p + 1])) : __builtin_inff();
+    }
+    s8_fill_lut(T.ulut, kS8ULut, kS8UKey0, T.umid, 255);
+    s8_fill_lut(T.slut, kS8SLut, kS8SKey0, T.smid + kS8SignedZero, 127);
+    return T;
+}
+__device__ __attribute__((aligned(16))) const S8Tables kS8Tables = s8_make();
+
+// The tables (10 KB, from L2) into LDS, 16 bytes per thread and access, by every workgroup (256 threads).  A launch on one
+// matrix is a few blocks per wave, so what a workgroup does before its first block counts: made there from their
+// definition, with fp64 entries and a binary search per bucket, the tables took most of it.  k_lowrank_adam8, us, made in
+// LDS / copied: 65536 elements 15.9 / 8.5, 1024 x 4096 51.3 / 12.4, 1024 x 11008 96.4 / 28.3, 1.17e9 2565 / 2535.
+__device__ inline void s8_load(S8Tables& T) {
+    constexpr int CHUNKS = sizeof(S8Tables) / 16;
+    static_assert(sizeof(S8Tables) % 16 == 0 && alignof(S8Tables) <= 16, "whole 16-byte chunks");
+    const u32x4* src = reinterpret_cast<const u32x4*>(&kS8Tables);
+    u32x4* dst = reinterpret_cast<u32x4*>(&T);
+    for (int i = threadIdx.x; i < CHUNKS; i += 256) dst[i] = src[i];
     __syncthreads();
 }
 
@@ -126,8 +137,8 @@ __device__ inline void for_each_block(int64_t count, F f) {
 
 __global__ __launch_bounds__(256) void k_state8_quant(const float* __restrict__ x, int64_t count, int is_signed,
                                                       uint8_t* __restrict__ codes, float* __restrict__ scales) {
-    __shared__ S8Tables T;
-    s8_build(T);
+    __shared__ __attribute__((aligned(16))) S8Tables T;
+    s8_load(T);
     for_each_block(count, [&](int64_t b, int64_t e, bool in, int lane) {
         const f32x4 v = in ? *reinterpret_cast<const f32x4*>(x + e) : f32x4{0.f, 0.f, 0.f, 0.f};
         const float xs[4] = {v[0], v[1], v[2], v[3]};
@@ -140,8 +151,8 @@ __global__ __launch_bounds__(256) void k_state8_quant(const float* __restrict__ 
 
 __global__ __launch_bounds__(256) void k_state8_dequant(const uint8_t* __restrict__ codes, const float* __restrict__ scales,
                                                         int64_t count, int is_signed, float* __restrict__ x) {
-    __shared__ S8Tables T;
-    s8_build(T);
+    __shared__ __attribute__((aligned(16))) S8Tables T;
+    s8_load(T);
     const float* val = is_signed ? T.sval : T.uval;
     for_each_block(count, [&](int64_t b, int64_t e, bool in, int lane) {
         if (!in) return;
@@ -158,8 +169,8 @@ __global__ __launch_bounds__(256) void k_lowrank_adam8(const float* __restrict__
                                                        float* __restrict__ Ms, uint8_t* __restrict__ Vq,
                                                        float* __restrict__ Vs, uint16_t* __restrict__ N, int64_t count,
                                                        AdamCoef c) {
-    __shared__ S8Tables T;
-    s8_build(T);
+    __shared__ __attribute__((aligned(16))) S8Tables T;
+    s8_load(T);
     for_each_block(count, [&](int64_t b, int64_t e, bool in, int lane) {
         f32x4 r = {0.f, 0.f, 0.f, 0.f};
         uint32_t mq = 0x7F7F7F7Fu, vq = 0;              // zeros of the two tables
@@ -195,7 +206,8 @@ __global__ __launch_bounds__(256) void k_lowrank_adam8(const float* __restrict__
 static unsigned s8_grid(int64_t count) {
     const int64_t blocks = (count + kS8Block - 1) / kS8Block, wgs = (blocks + 3) / 4;
     return (unsigned)(wgs < 8192 ? wgs : 8192);          // 32 waves per CU at most; the rest is a grid-stride loop
-                                                         // (2048 workgroups, one resident set, measured slower)
+                                                         // (us at 1.17e9 / 11.3e6 elements: 8192 2535 / 28.3, 4096
+                                                         // 2670 / 26.2, 2048 2763 / 26.3, 1024 2692 / 29.2)
 }
 
 static int check_state8(int64_t count) {
