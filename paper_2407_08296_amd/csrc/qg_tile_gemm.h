@@ -67,9 +67,10 @@ struct LinBatch {
     int64_t ldc = 0;   // row pitch of C in elements (0: N, dense rows)
 };
 
-// What a fetch may take for granted: the chunk lies inside the matrix and is 16-byte aligned; it lies inside the matrix;
-// nothing.
-enum : int { kFetchAligned = 0, kFetchInside = 1, kFetchGuarded = 2 };
+// What a fetch may take for granted: the chunk lies inside the matrix and is 16-byte aligned; the step lies inside the
+// contraction and no chunk straddles the end of the x indices (those past it read the last row or chunk again, for results
+// that are never stored); nothing.
+enum : int { kFetchAligned = 0, kFetchClamped = 1, kFetchGuarded = 2 };
 
 // Staging of one operand tile: global -> registers (fetch) -> LDS (commit; INT8 is dequantized here).
 template <int LAYOUT, int XT, int BK, int NT = 256>
@@ -96,20 +97,21 @@ struct LinStage {
         for (int q = 0; q < PER; ++q) {
             const int idx = threadIdx.x + NT * q;
             const int tr = idx / CPR, tc = (idx % CPR) * CH;         // row and first column inside the tile
-            const auto row = kFast ? x0 + tr : k0 + tr;              // ... and inside the matrix
-            const auto col = kFast ? k0 + tc : x0 + tc;
+            int x = x0 + (kFast ? tr : tc);                          // ... and inside the matrix
+            if constexpr (FETCH == kFetchClamped) x = min(x, kFast ? X - 1 : X - CH);
+            const KI k = k0 + (kFast ? tc : tr);
+            const int64_t row = kFast ? x : k, col = kFast ? k : x;
             int valid = CH;
             if constexpr (FETCH == kFetchGuarded) {
-                const int k = (int)k0;
-                valid = kFast ? (x0 + tr < X ? K - (k + tc) : 0) : (k + tr < K ? X - (x0 + tc) : 0);
+                valid = kFast ? (x < X ? K - (int)k : 0) : ((int)k < K ? X - x : 0);
             }
-            const int64_t off = (int64_t)row * op.ld + col;
+            const int64_t off = row * op.ld + col;
             if constexpr (kInt8) {
                 const int8_t* src = static_cast<const int8_t*>(op.base) + off;
                 if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
                 else v[q] = load16_i8_guarded(src, valid);
-                s[q] = valid > 0 ? op.scales[(int64_t)row * op.sgroups + (col >> 8)] : 0.f;
-                if constexpr (kZero) z[q] = valid > 0 ? op.zeros[(int64_t)row * op.sgroups + (col >> 8)] : 0.f;
+                s[q] = valid > 0 ? op.scales[row * op.sgroups + (col >> 8)] : 0.f;
+                if constexpr (kZero) z[q] = valid > 0 ? op.zeros[row * op.sgroups + (col >> 8)] : 0.f;
             } else {
                 const uint16_t* src = static_cast<const uint16_t*>(op.base) + off;
                 if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
@@ -130,6 +132,8 @@ struct LinStage {
             }
         }
     }
+    // Whether the tile of the XT x indices from x0 on can be fetched clamped (chunks along x: whole ones, or all inside).
+    __device__ static __forceinline__ bool clampable(int x0, int X) { return kFast || X % CH == 0 || x0 + XT <= X; }
     // MFMA operand fragment of the 32 x indices starting at xb for the 16-deep sub-step kk
     __device__ static __forceinline__ bf16x8 frag(const uint16_t* tile, int xb, int kk, int lane) {
         if constexpr (kFast)
@@ -188,9 +192,12 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* 
 // each other.
 // WM: wave rows of the workgroup (2: 256 threads, several workgroups per CU; 4: 512 threads, one workgroup per CU - the
 // B tile, and with it the dequantization of an INT8 B operand, is then shared by twice as many MFMAs).
-// EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a
-// workgroup whose tile lies inside runs unchecked too, but for the last, partial step - except with one register set and an
-// INT8 B with k slow, where that measured slower than checking (grad_input, 1000 tokens, 4096 -> 11008: 140 against 136 us).
+// EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a workgroup
+// runs unchecked too, but for the last, partial step, with its x indices clamped to the operand's last row or chunk: the
+// checks cost a wave three branches per chunk, and the workgroups at the edge, which took them, were the last to end (1000
+// tokens, 2048 -> 2048: forward 28.5 -> 20.9 us, grad_input 29.4 -> 21.7; 1024 tokens 20.4 and 22.0).  Checked are tiles at
+// the edge of an operand with k slow whose last chunk is not whole, and all tiles with one register set, an INT8 B with k slow
+// and such a last chunk, where checking measured faster (grad_input, 1000 tokens, 2048 -> 5461: 98.6 against 102.5).
 template <int AL, int BL, int MB, int TN, int BK, int WM>
 struct TileGemm {
     static constexpr int TM = 32 * MB * WM, NT = 128 * WM;
@@ -311,11 +318,11 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
     } else {
         inside = i0 + TM <= M && j0 + TN <= N;
         const int whole = K / BK;
-        constexpr bool CHECK_ALL = !DEEP && (BL == kInt8KSlow || BL == kInt8ZKSlow);
-        if (CHECK_ALL || !inside) {
+        const bool check_all = !DEEP && (BL == kInt8KSlow || BL == kInt8ZKSlow) && N % SB::CH != 0;
+        if (check_all || !SA::clampable(i0, M) || !SB::clampable(j0, N)) {
             steps(std::integral_constant<int, kFetchGuarded>(), (K + BK - 1) / BK);
         } else {
-            if (whole > 0) steps(std::integral_constant<int, kFetchInside>(), whole);
+            if (whole > 0) steps(std::integral_constant<int, kFetchClamped>(), whole);
             if (whole * BK < K) {
                 sa[0].template fetch<kFetchGuarded>(A, i0, M, whole * BK, K);
                 sb[0].template fetch<kFetchGuarded>(B, j0, N, whole * BK, K);

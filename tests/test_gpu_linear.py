@@ -107,6 +107,15 @@ def test_loop_and_tile_of_every_size_class(tokens, m, n):
     test_backward(tokens, m, n)
 
 
+@pytest.mark.parametrize("tokens,m,n", [
+    (65, 80, 144), (1, 16, 48), (130, 2064, 528),   # ragged tiles of whole 16-element chunks: clamped, also with k slow
+    (127, 264, 72),                                  # whole chunks of bf16, not of INT8 codes
+])
+def test_ragged_tiles_of_whole_chunks(tokens, m, n):
+    test_forward(tokens, m, n)
+    test_backward(tokens, m, n)
+
+
 def test_gradient_feeds_the_optimizer_step():
     """The layer's grad_W, as stored, is a valid gradient input of the step: projecting it gives what the oracle
     gives for the same bits."""
