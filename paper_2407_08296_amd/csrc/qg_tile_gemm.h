@@ -87,6 +87,8 @@ struct LinStage {
     u32x4 v[PER];
     float s[kInt8 ? PER : 1];
     float z[kZero ? PER : 1];
+    // NT = 64: every wave of the workgroup stages a tile of its own
+    __device__ static __forceinline__ int thread() { return NT == 64 ? threadIdx.x & 63 : threadIdx.x; }
 
     // KI: int or int64_t.  Over a 64-bit k0 the compiler turns the addresses of a loop into running pointers; over a 32-bit
     // one it recomputes a 64-bit product per chunk and step (grad_W with 128 x 128 x 32 tiles, 2048 tokens, 2560 x 2048:
@@ -95,7 +97,7 @@ struct LinStage {
     __device__ __forceinline__ void fetch(const LinOperand& op, int x0, int X, KI k0, int K) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            const int idx = threadIdx.x + NT * q;
+            const int idx = thread() + NT * q;
             const int tr = idx / CPR, tc = (idx % CPR) * CH;         // row and first column inside the tile
             int x = x0 + (kFast ? tr : tc);                          // ... and inside the matrix
             if constexpr (FETCH == kFetchClamped) x = min(x, kFast ? X - 1 : X - CH);
@@ -122,7 +124,7 @@ struct LinStage {
     __device__ __forceinline__ void commit(uint16_t* tile) const {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
-            const int idx = threadIdx.x + NT * q;
+            const int idx = thread() + NT * q;
             uint16_t* dst = tile + (idx / CPR) * PITCH + (idx % CPR) * CH;
             if constexpr (kInt8) {
                 *reinterpret_cast<u32x4*>(dst) = dequant8_i8_bf16<kZero>(v[q][0], v[q][1], s[q], kZero ? z[q] : 0.f);
@@ -361,31 +363,159 @@ __global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOper
                                                   tiles_m, tiles_n, tile, smem);
 }
 
-// Two products in one launch, 64 x 64 tiles: the two of a backward pass, which do not depend on each other, where each
-// alone leaves most of the chip idle (one after the other their times add up).  The first grid0 workgroups run the
-// first (A bf16 with k fast, B the weight), the others the second (both bf16 with k slow).
+// A product as a kernel argument.
 struct LinProduct {
     LinOperand A, B;
     uint16_t* C;
     int64_t ldc;
     int M, N, K, tiles_m, tiles_n;
 };
-template <int BL, bool EXACT>
-__global__ __launch_bounds__(256, 2) void k_tile_gemm_pair(LinProduct p0, LinProduct p1, uint32_t grid0) {
-    using T0 = TileGemm<kBf16KFast, BL, 1, 64, 64, 2>;
-    using T1 = TileGemm<kBf16KSlow, kBf16KSlow, 1, 64, 64, 2>;
-    __shared__ __attribute__((aligned(16))) uint16_t smem[T0::SMEM > T1::SMEM ? T0::SMEM : T1::SMEM];
-    if (blockIdx.x < grid0) {
-        const uint32_t tile = xcd_tile(blockIdx.x, grid0);
-        if (tile >= (uint32_t)(p0.tiles_m * p0.tiles_n)) return;
-        tile_gemm<kBf16KFast, BL, EXACT, uint16_t, 1, 64, 64, 2, true>(p0.A, p0.B, nullptr, p0.C, p0.ldc, p0.M, p0.N, p0.K, p0.tiles_m,
-                                                               p0.tiles_n, tile, smem);
+
+// The contraction split over the KW waves of a workgroup: 32 x 32 tiles, wave w takes the 64-deep steps w, w + KW, ... of
+// the whole tile, and the KW partial tiles are added through LDS in a fixed order.  For products of few tiles, where what
+// counts is the length of a workgroup's serial chain (fetch, commit, fragments, MFMAs per step): it is KW times shorter than
+// with the tile split over the waves, there are four times as many workgroups as with 64 x 64 tiles, and since a wave stages
+// its own operands (its LDS accesses complete in order) there is no barrier before the final sum.
+template <int AL, int BL, int KW>
+struct KSplit {
+    static constexpr int BK = 64, NT = 64 * KW;
+    using SA = LinStage<AL, 32, BK, 64>;
+    using SB = LinStage<BL, 32, BK, 64>;
+    static constexpr int WAVE = SA::ELEMS + SB::ELEMS;   // uint16 elements of a wave's operands, then of its partial tile
+    static_assert(2 * kTransposeFloats <= WAVE, "the partial tile fits where the operands were");
+    static constexpr int SMEM = KW * WAVE;
+};
+
+template <int AL, int BL, bool EXACT, int KW>
+__device__ __forceinline__ void ksplit_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* __restrict__ bias,
+                                            uint16_t* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n,
+                                            uint32_t tile, uint16_t* smem) {
+    using T = KSplit<AL, BL, KW>;
+    using SA = typename T::SA;
+    using SB = typename T::SB;
+    constexpr int BK = T::BK;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    uint16_t *At = smem + wave * T::WAVE, *Bt = At + SA::ELEMS;
+    const int strip = (int)(tile / (uint32_t)(kLinStrip * tiles_n)), in_strip = (int)(tile % (uint32_t)(kLinStrip * tiles_n));
+    const int strip_rows = min(kLinStrip, tiles_m - strip * kLinStrip);
+    const int i0 = (strip * kLinStrip + in_strip % strip_rows) * 32, j0 = (in_strip / strip_rows) * 32;
+    auto steps_below = [&](int n) { return n > wave ? (n - wave + KW - 1) / KW : 0; };   // of this wave, below step n
+    SA sa[2];
+    SB sb[2];
+    f32x16 acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+    // between a wave's writes of its tiles and its reads, and back: its LDS instructions complete in order, so what has to
+    // be kept is the order in which they are issued (the scheduler does not see the transposing reads as accesses)
+    auto in_order = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto compute = [&](int set, auto fetch_next) {
+        sa[set].commit(At);
+        sb[set].commit(Bt);
+        in_order();
+        bf16x8 af[BK / 16], bf[BK / 16];
+#pragma unroll
+        for (int kk = 0; kk < BK / 16; ++kk) {
+            af[kk] = SA::frag(At, 0, kk, lane);
+            bf[kk] = SB::frag(Bt, 0, kk, lane);
+        }
+        in_order();
+        fetch_next();
+#pragma unroll
+        for (int kk = 0; kk < BK / 16; ++kk) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[kk], bf[kk], acc, 0, 0, 0);
+    };
+    // this wave's steps first, first + KW, ... (`count` of them), fetched two ahead under FETCH's terms
+    auto run = [&](auto fetch_mode, int first, int count) {
+        constexpr int FETCH = decltype(fetch_mode)::value;
+        auto fetch = [&](int i, int set) {
+            if (i >= count) return;
+            const int k0 = (first + KW * i) * BK;
+            sa[set].template fetch<FETCH>(A, i0, M, k0, K);
+            sb[set].template fetch<FETCH>(B, j0, N, k0, K);
+        };
+        fetch(0, 0);
+        fetch(1, 1);
+        for (int i = 0; i < count; i += 2) {
+            compute(0, [&] { fetch(i + 2, 0); });
+            if (i + 1 < count) compute(1, [&] { fetch(i + 3, 1); });
+        }
+    };
+    using Guarded = std::integral_constant<int, kFetchGuarded>;
+    const int total = (K + BK - 1) / BK, whole = K / BK;
+    if constexpr (EXACT) {
+        run(std::integral_constant<int, kFetchAligned>(), wave, steps_below(total));
+    } else if (SA::clampable(i0, M) && SB::clampable(j0, N)) {
+        const int n = steps_below(whole);
+        run(std::integral_constant<int, kFetchClamped>(), wave, n);
+        if (steps_below(total) > n) run(Guarded(), wave + KW * n, 1);   // the last, partial step
     } else {
-        const uint32_t tile = xcd_tile(blockIdx.x - grid0, gridDim.x - grid0);
-        if (tile >= (uint32_t)(p1.tiles_m * p1.tiles_n)) return;
-        tile_gemm<kBf16KSlow, kBf16KSlow, EXACT, uint16_t, 1, 64, 64, 2, true>(p1.A, p1.B, nullptr, p1.C, p1.ldc, p1.M, p1.N, p1.K,
-                                                                       p1.tiles_m, p1.tiles_n, tile, smem);
+        run(Guarded(), wave, steps_below(total));
     }
+    float* tp = reinterpret_cast<float*>(At);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) tp[(8 * (v >> 2) + 4 * (lane >> 5) + (v & 3)) * kTransposePitch + (lane & 31)] = acc[v];
+    __syncthreads();
+    if (threadIdx.x >= 256) return;
+    const int row = threadIdx.x / 8, col = (threadIdx.x % 8) * 4;        // four columns of a row per thread
+    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int w = 0; w < KW; ++w) {
+        const f32x4 x = *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(smem + w * T::WAVE) +
+                                                        row * kTransposePitch + col);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sum[e] += x[e];
+    }
+    const int left = EXACT ? 4 : (i0 + row < M ? N - (j0 + col) : 0);
+    if (bias != nullptr) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < left) sum[e] += __builtin_bit_cast(float, (uint32_t)bias[j0 + col + e] << 16);
+    }
+    const u32x2 o = {pack_bf16x2(sum[0], sum[1]), pack_bf16x2(sum[2], sum[3])};
+    uint16_t* dst = C + (int64_t)(i0 + row) * ldc + j0 + col;
+    if (left >= 4) {
+        *reinterpret_cast<u32x2_align2*>(dst) = o;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 3; ++e)
+            if (e < left) dst[e] = (uint16_t)(o[e >> 1] >> (16 * (e & 1)));
+    }
+}
+
+template <int BL, bool EXACT, int KW>
+__global__ __launch_bounds__(64 * KW) void k_ksplit_gemm(LinProduct p, const uint16_t* __restrict__ bias) {
+    __shared__ __attribute__((aligned(16))) uint16_t smem[KSplit<kBf16KFast, BL, KW>::SMEM];
+    const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
+    if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
+    ksplit_gemm<kBf16KFast, BL, EXACT, KW>(p.A, p.B, bias, p.C, p.ldc, p.M, p.N, p.K, p.tiles_m, p.tiles_n, tile, smem);
+}
+
+// The two products of a backward pass in one launch: they do not depend on each other, and each alone leaves most of the chip
+// idle (one after the other their times add up).  The first grid0 workgroups run the first (A bf16 with k fast, B the
+// weight), the others the second (both bf16 with k slow).  SPLIT: 32 x 32 tiles with the contraction split over the waves,
+// otherwise 64 x 64 tiles.
+template <int AL, int BL, bool SPLIT>
+constexpr int kPairSmem = SPLIT ? KSplit<AL, BL, 4>::SMEM : TileGemm<AL, BL, 1, 64, 64, 2>::SMEM;
+template <int AL, int BL, bool EXACT, bool SPLIT>
+__device__ __forceinline__ void pair_product(const LinProduct& p, uint32_t block, uint32_t blocks, uint16_t* smem) {
+    const uint32_t tile = xcd_tile(block, blocks);
+    if (tile >= (uint32_t)(p.tiles_m * p.tiles_n)) return;
+    if constexpr (SPLIT)
+        ksplit_gemm<AL, BL, EXACT, 4>(p.A, p.B, nullptr, p.C, p.ldc, p.M, p.N, p.K, p.tiles_m, p.tiles_n, tile, smem);
+    else
+        tile_gemm<AL, BL, EXACT, uint16_t, 1, 64, 64, 2, true>(p.A, p.B, nullptr, p.C, p.ldc, p.M, p.N, p.K, p.tiles_m, p.tiles_n,
+                                                               tile, smem);
+}
+template <int BL, bool EXACT, bool SPLIT0, bool SPLIT1>
+__global__ __launch_bounds__(256, 2) void k_gemm_pair(LinProduct p0, LinProduct p1, uint32_t grid0) {
+    constexpr int S0 = kPairSmem<kBf16KFast, BL, SPLIT0>, S1 = kPairSmem<kBf16KSlow, kBf16KSlow, SPLIT1>;
+    __shared__ __attribute__((aligned(16))) uint16_t smem[S0 > S1 ? S0 : S1];
+    if (blockIdx.x < grid0) pair_product<kBf16KFast, BL, EXACT, SPLIT0>(p0, blockIdx.x, grid0, smem);
+    else pair_product<kBf16KSlow, kBf16KSlow, EXACT, SPLIT1>(p1, blockIdx.x - grid0, gridDim.x - grid0, smem);
 }
 
 // Both operands bf16 with the contraction index as their slow index, whole tiles and aligned rows (grad_W at the
@@ -638,6 +768,31 @@ static bool lin_small(int64_t M, int64_t N, int count) {
     return ((M + 127) / 128) * ((N + 127) / 128) * count < (slow_weight ? 160 : grad_w ? 200 : 256);
 }
 
+// Whether a product of the linear layer splits its contraction over the waves of a workgroup (T: its 32 x 32 tiles).  Against
+// the tiles of launch_tile_gemm, us, split / not: forward, 256 tokens, 768 -> 768 (T = 192) 4.0 / 6.6, 2048 -> 2048 (512) 9.2 /
+// 13.4, 1000 tokens, 2048 -> 768 (768) 11.3 / 13.3, 768 -> 768 6.4 / 6.9, but 1024 -> 1024 (1024) 9.0 / 8.2.  A weight with k
+// slow (grad_input) needs twice the LDS per wave, and a chain that is long for the number of tiles: 256 tokens, 2048 -> 2048
+// (512) 11.7 / 13.9, 500 tokens, K = 3001, 1007 columns (512) 55 / 95, but with grad_W in the same launch 256 tokens, K = 768,
+// 2048 columns (512) 9.4 / 8.0, K = 1024, 2736 columns (688) 14.3 / 11.0.  grad_W: 512 x 512 (256), 1024 tokens 4.8 / 7.1, 4096
+// tokens 10.9 / 30, but 256 tokens with grad_input in the same launch 4.2 / 3.7, and 768 x 768 (576), 1024 tokens 9.5 / 7.4.
+template <int AL, int BL>
+static bool lin_ksplit(int64_t M, int64_t N, int64_t K) {
+    const int64_t T = ((M + 31) / 32) * ((N + 31) / 32);
+    if (AL == kBf16KSlow && BL == kBf16KSlow) return T <= 320 && K >= 512;
+    if (BL == kInt8KSlow || BL == kInt8ZKSlow) return T <= 512 && K >= 3 * T;
+    return T <= 768;
+}
+
+static LinProduct lin_product(const LinOperand& A, const LinOperand& B, uint16_t* C, int64_t M, int64_t N, int64_t K, int64_t ldc,
+                              int tile) {
+    return LinProduct{A, B, C, ldc, (int)M, (int)N, (int)K, (int)((M + tile - 1) / tile), (int)((N + tile - 1) / tile)};
+}
+// Whether every tile and every 64-deep step is whole and every row of the operands starts 16-byte aligned.
+static bool lin_whole(const LinProduct& p, int tile) {
+    return p.M % tile == 0 && p.N % tile == 0 && p.K % 64 == 0 && p.A.ld % 8 == 0 && p.B.ld % 16 == 0;
+}
+static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p.tiles_n + 7) / 8 * 8); }   // the 8 XCDs
+
 // Tile shape, from measurements on the linear layer (us unless said otherwise; T: 128 x 128 tiles of the product):
 //  * large outputs with an INT8 B operand, or with the contraction index fast in both operands: 256 x 256 tiles with
 //    64-deep steps, eight waves, one workgroup per CU (144 KB of LDS).  The B tile - and the dequantization of an
@@ -670,6 +825,23 @@ static bool lin_small(int64_t M, int64_t N, int count) {
 template <int AL, int BL, typename OUT>
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
                             int64_t K, hipStream_t st, const LinBatch* many = nullptr, int count = 1, int64_t ldc = 0) {
+    if constexpr (AL == kBf16KFast && BL != kBf16KFast && BL != kBf16KSlow && std::is_same_v<OUT, uint16_t>) {
+        if (many == nullptr && lin_ksplit<AL, BL>(M, N, K)) {
+            const LinProduct p = lin_product(A, B, C, M, N, K, ldc ? ldc : N, 32);
+            auto launch = [&](auto exact, auto waves) {
+                hipLaunchKernelGGL((k_ksplit_gemm<BL, exact.value, waves.value>), dim3(lin_grid(p)), dim3(64 * waves.value), 0, st,
+                                   p, bias);
+            };
+            using Four = std::integral_constant<int, 4>;
+            using Eight = std::integral_constant<int, 8>;
+            // eight waves up to one workgroup per CU (256 tokens, 2736 -> 1024 (T = 256) 7.5 us, with four 9.3; 64 tokens, 2048 ->
+            // 5461 (342) 10.3 / 9.2)
+            const bool eight = p.tiles_m * p.tiles_n <= 256;
+            if (lin_whole(p, 32)) eight ? launch(std::true_type(), Eight()) : launch(std::true_type(), Four());
+            else eight ? launch(std::false_type(), Eight()) : launch(std::false_type(), Four());
+            return check_launch();
+        }
+    }
     constexpr bool both_fast = (AL == kBf16KFast || AL == kInt8KFast || AL == kInt8ZKFast) &&
                                (BL == kBf16KFast || BL == kInt8KFast || BL == kInt8ZKFast);
     if constexpr (AL == kBf16KSlow && BL == kBf16KSlow) {
@@ -738,34 +910,45 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
 }
 
 // dx (tokens x n_in = dy W, W with layout BL) and grad_W (rows x cols = A1^T B1 over the tokens): one launch where both
-// products fit 64 x 64 tiles, otherwise one after the other.  Either output may be missing.  One 130M decoder layer on 256
-// tokens, forward and backward: 181 us with two launches per backward call, 151 with one.  grad_W comes along up to the
-// chip's 256 tiles of 128 x 128, further than it runs 64 x 64 tiles alone: 256 tokens, 2048 -> 1664 (208) 13.8 us, two
+// products fit 64 x 64 tiles or are split over waves, otherwise one after the other.  Either output may be missing.  One 130M
+// decoder layer on 256 tokens, forward and backward: 181 us with two launches per backward call, 151 with one; its backward
+// calls alone, with the chain of grad_input split, 768 -> 768 7.0 -> 5.9, 2048 -> 768 14.7 -> 9.5.  grad_W comes along up to
+// the chip's 256 tiles of 128 x 128, further than it runs 64 x 64 tiles alone: 256 tokens, 2048 -> 1664 (208) 13.8 us, two
 // launches 18.8; 1024 tokens, 2048 -> 1920 (240) 33.1 / 36.4.
 template <int BL>
 static int launch_linear_backward(const LinOperand& A0, const LinOperand& B0, uint16_t* dx, int64_t M0, int64_t N0, int64_t K0,
                                   int64_t ldc0, const LinOperand& A1, const LinOperand& B1, uint16_t* G, int64_t M1, int64_t N1,
                                   int64_t K1, int64_t ldc1, hipStream_t st) {
-    if (dx && G && lin_small<kBf16KFast, BL>(M0, N0, 1) && ((M1 + 127) / 128) * ((N1 + 127) / 128) < 256) {
-        auto product = [](const LinOperand& A, const LinOperand& B, uint16_t* C, int64_t M, int64_t N, int64_t K, int64_t ldc) {
-            return LinProduct{A, B, C, ldc, (int)M, (int)N, (int)K, (int)((M + 63) / 64), (int)((N + 63) / 64)};
+    const bool split0 = lin_ksplit<kBf16KFast, BL>(M0, N0, K0), split1 = lin_ksplit<kBf16KSlow, kBf16KSlow>(M1, N1, K1);
+    const bool pair0 = split0 || lin_small<kBf16KFast, BL>(M0, N0, 1), pair1 = split1 || ((M1 + 127) / 128) * ((N1 + 127) / 128) < 256;
+    const int tile0 = split0 ? 32 : 64, tile1 = split1 ? 32 : 64;
+    const LinProduct p0 = lin_product(A0, B0, dx, M0, N0, K0, ldc0, tile0), p1 = lin_product(A1, B1, G, M1, N1, K1, ldc1, tile1);
+    // `with0` of the first product's workgroups, `with1` of the second's
+    auto launch_pair = [&](bool with0, bool with1) {
+        const unsigned grid0 = with0 ? lin_grid(p0) : 0, grid = grid0 + (with1 ? lin_grid(p1) : 0);
+        const bool exact = (!with0 || lin_whole(p0, tile0)) && (!with1 || lin_whole(p1, tile1));
+        auto launch = [&](auto e, auto s0, auto s1) {
+            hipLaunchKernelGGL((k_gemm_pair<BL, e.value, s0.value, s1.value>), dim3(grid), dim3(256), 0, st, p0, p1, grid0);
         };
-        auto whole = [](const LinOperand& A, const LinOperand& B, int64_t M, int64_t N, int64_t K) {
-            return M % 64 == 0 && N % 64 == 0 && K % 64 == 0 && A.ld % 8 == 0 && B.ld % 16 == 0;
+        auto pick = [&](auto e) {
+            if (split0) split1 ? launch(e, std::true_type(), std::true_type()) : launch(e, std::true_type(), std::false_type());
+            else split1 ? launch(e, std::false_type(), std::true_type()) : launch(e, std::false_type(), std::false_type());
         };
-        const LinProduct p0 = product(A0, B0, dx, M0, N0, K0, ldc0), p1 = product(A1, B1, G, M1, N1, K1, ldc1);
-        auto grid8 = [](const LinProduct& p) { return (unsigned)((p.tiles_m * p.tiles_n + 7) / 8 * 8); };   // the 8 XCDs
-        const unsigned grid0 = grid8(p0), grid = grid0 + grid8(p1);
-        if (whole(A0, B0, M0, N0, K0) && whole(A1, B1, M1, N1, K1))
-            hipLaunchKernelGGL((k_tile_gemm_pair<BL, true>), dim3(grid), dim3(256), 0, st, p0, p1, grid0);
-        else
-            hipLaunchKernelGGL((k_tile_gemm_pair<BL, false>), dim3(grid), dim3(256), 0, st, p0, p1, grid0);
+        exact ? pick(std::true_type()) : pick(std::false_type());
         return check_launch();
+    };
+    if (dx && G && pair0 && pair1) return launch_pair(true, true);
+    // (a product whose contraction is split runs in this kernel alone too: the same bits whether the other is asked for or not)
+    if (dx) {
+        if (split0) {
+            if (int e = launch_pair(true, false)) return e;
+        } else if (int e = launch_tile_gemm<kBf16KFast, BL, uint16_t>(A0, B0, nullptr, dx, M0, N0, K0, st, nullptr, 1, ldc0)) {
+            return e;
+        }
     }
-    if (dx)
-        if (int e = launch_tile_gemm<kBf16KFast, BL, uint16_t>(A0, B0, nullptr, dx, M0, N0, K0, st, nullptr, 1, ldc0)) return e;
-    if (G) return launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A1, B1, nullptr, G, M1, N1, K1, st, nullptr, 1, ldc1);
-    return QG_OK;
+    if (!G) return QG_OK;
+    if (split1) return launch_pair(false, true);
+    return launch_tile_gemm<kBf16KSlow, kBf16KSlow, uint16_t>(A1, B1, nullptr, G, M1, N1, K1, st, nullptr, 1, ldc1);
 }
 
 }  // namespace qg

@@ -116,6 +116,18 @@ def test_ragged_tiles_of_whole_chunks(tokens, m, n):
     test_backward(tokens, m, n)
 
 
+@pytest.mark.parametrize("tokens,m,n", [
+    (512, 64, 64), (64, 512, 64), (32, 32, 32),      # whole 32 x 32 tiles, fewer steps than waves, one step
+    (33, 31, 577), (100, 130, 1000),                 # ragged edges; 10 steps over 8 waves, the last one partial
+    (544, 530, 70),                                  # four waves in the forward pass
+    (544, 200, 33), (600, 100, 130), (96, 300, 40),  # grad_input and grad_W split, only grad_W, only grad_input
+    (200, 1500, 600), (64, 2048, 512),               # a long chain in grad_input
+])
+def test_contraction_split_over_waves(tokens, m, n):
+    test_forward(tokens, m, n)
+    test_backward(tokens, m, n)
+
+
 def test_gradient_feeds_the_optimizer_step():
     """The layer's grad_W, as stored, is a valid gradient input of the step: projecting it gives what the oracle
     gives for the same bits."""
