@@ -165,7 +165,8 @@ def _ptr(t: torch.Tensor | None, dtypes=None) -> int | None:
 
 
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    # (without the Stream object of torch.cuda.current_stream(): 0.3 us instead of 2.8 of the 10 a small call takes)
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
