@@ -37,7 +37,6 @@ constexpr int kKC = 16;               // K extent staged in LDS per barrier pair
 constexpr int kPitchKF = kKC + 1;     // LDS pitch of a [64][k] chunk (k fastest): odd, so that the 16 rows a fragment
                                       // read touches at one k fall on 16 different bank pairs (36 gave 4-way conflicts)
 constexpr int kPitchKS = kNB + 16;    // LDS pitch of a [k][64] chunk (k slowest)
-constexpr int kPitchT = kNB + 2;      // LDS pitch of a 64 x 64 intermediate
 
 // ROWS x COLS block at (row0, col0) of a row-major matrix (fp32 or fp64) -> registers -> LDS doubles.  Elements
 // outside [0, rows) x [0, cols) read as zero.  col0 and cols are even, so an element pair never straddles the edge.
@@ -128,6 +127,12 @@ __device__ __forceinline__ double rsqrt_f64(double d) {
         y = fma(0.5 * y, e, y);
     }
     return y;
+}
+
+// 1 / d for d > 0: the hardware estimate and one step of third order.
+__device__ __forceinline__ double rcp_f64(double d) {
+    const double y = __builtin_amdgcn_rcp(d), e = fma(-d, y, 1.0);
+    return fma(y, fma(e, e, e), y);
 }
 
 // (bi, bj) with bi >= bj of the idx-th block of a lower block triangle, rows first.
@@ -245,11 +250,22 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
 constexpr int kSB = 16;               // sub-block of the diagonal block: one fp64 MFMA tile
 constexpr int kPitchD = kNB + 1;      // LDS pitch of the diagonal block (odd: 16 rows of a fragment on 16 bank pairs)
 
-__device__ __forceinline__ double readlane_f64(double x, int lane) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, x);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+constexpr int kPitchX = kSB + 1;      // ... of the inverses of its 16 x 16 diagonal blocks
+
+// x of lane L of each row of 16 lanes, in all 16.
+template <int L>
+__device__ __forceinline__ double row_bcast_f64(double x) {
+    const long long b = __builtin_bit_cast(long long, x);
+    return __builtin_bit_cast(double, __builtin_amdgcn_update_dpp(b, b, 0x150 + L, 0xf, 0xf, false));   // row_newbcast:L
+}
+
+// f(0), ..., f(N - 1) with the index as a compile-time constant.
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F f) {
+    if constexpr (I < N) {
+        f(std::integral_constant<int, I>());
+        static_for<N, I + 1>(f);
+    }
 }
 
 // acc += A B for 16 x 16 blocks in LDS: element (i, k) of A at a[i * a_pi + k * a_pk], (k, j) of B at b[k * b_pk + j * b_pj].
@@ -265,7 +281,13 @@ __device__ __forceinline__ f64x4 mma16(const double* a, int a_pi, int a_pk, cons
 // Sum of the diagonal of S (r x r), the same value in every thread; red: 4 doubles of LDS.
 __device__ __forceinline__ double trace_of(const double* __restrict__ S, int r, double* red) {
     double acc = 0.0;
-    for (int i = threadIdx.x; i < r; i += 256) acc += S[(int64_t)i * r + i];
+    for (int i0 = threadIdx.x; i0 < r; i0 += 1024) {
+        double x[4];                                  // four loads in flight
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = i0 + 256 * q < r ? S[(int64_t)(i0 + 256 * q) * (r + 1)] : 0.0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc += x[q];
+    }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
@@ -274,18 +296,19 @@ __device__ __forceinline__ double trace_of(const double* __restrict__ S, int r, 
 }
 
 // Factors the 64 x 64 block in T (pitch kPitchD, lower triangle, complete when called: no barrier needed before) and
-// inverts the factor; writes L_kk to S and X_kk to Dinv and X.  A serial chain of 64 pivots, so everything is arranged
-// around its latency: one wave holds 16 columns of all 64 rows in registers (lane = row) and takes pivot and
-// multipliers from other lanes with v_readlane (no LDS round trip or barrier per column); the four waves then update
-// what is right of the 16 columns with fp64 MFMAs.  The inverse is built from the four 16 x 16 diagonal inverses
-// (one wave each) and three block diagonals of MFMA products.  One barrier pair per 16 columns.  With the matrix in LDS
-// and two barriers per column (the form before) the launch of one 64 x 64 block took 91 us, with this one (k_chol_diag, the
-// trace of S included) it takes 28.
-__device__ __forceinline__ void chol_diag_block(double* T, double* rdg, double* __restrict__ S, int r, int kb,
-                                                double* __restrict__ Dinv, double* __restrict__ X, int32_t* __restrict__ info,
-                                                double sigma, double flag_factor) {
-    constexpr int P = kPitchD, NSB = kNB / kSB;
-    const int t = threadIdx.x, lane = t & 63;
+// inverts the factor; writes X_kk to Dinv and X (nothing reads L_kk).  D: 4 * kSB * kPitchX doubles of LDS.  A serial chain
+// of 64 pivots, so everything is arranged around its latency.  Per 16 columns: one wave eliminates the 16 x 16 diagonal block
+// (lane % 16 = row) and, with the same multipliers, the identity beside it (lane % 16 = column of X_pp), which fills the
+// chain's idle cycles; the pivot and the multipliers come from other lanes by DPP row broadcasts (all four rows of 16 lanes
+// do the same, a broadcast does not leave its row).  Then L_ip = S_ip X_pp^T for the blocks below, and what is right of the 16
+// columns together with block row p of X, from 16 x 16 fp64 MFMAs spread over the four waves.  k_chol_diag on one matrix, cycles:
+// 34000, 3900 of them per 16 pivots (14 us); with all 64 rows in the chain and v_readlane, whose scalar registers spilled,
+// 7000 per 16 pivots, the inverse afterwards 12500 and the load of T, one element at a time, 18000: 75000 (31 us).
+__device__ __forceinline__ void chol_diag_block(double* T, double* D, int r, int kb, double* __restrict__ Dinv,
+                                                double* __restrict__ X, int32_t* __restrict__ info, double sigma,
+                                                double flag_factor) {
+    constexpr int P = kPitchD, PX = kPitchX, NSB = kNB / kSB;
+    const int t = threadIdx.x, lane = t & 63, l16 = lane & 15, l4 = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int base = kb * kNB;
     // a pivot at or below flag_factor * sigma is reported: 0 in the first round (only pivots that are not positive),
@@ -295,93 +318,86 @@ __device__ __forceinline__ void chol_diag_block(double* T, double* rdg, double* 
     __syncthreads();
     for (int p = 0; p < NSB; ++p) {
         const int c0 = p * kSB;
+        double* Dp = D + p * kSB * PX;
         if (wave == 0) {
-            double a[kSB];
+            double b[kSB], x[kSB];
 #pragma unroll
-            for (int c = 0; c < kSB; ++c) a[c] = T[lane * P + c0 + c];
-#pragma unroll
-            for (int j = 0; j < kSB; ++j) {
-                double d = readlane_f64(a[j], c0 + j);
-                if (!(d > floor_d)) {                   // too small, not positive, or NaN
-                    if (lane == 0 && base + c0 + j < r) atomicCAS(info, 0, base + c0 + j + 1);
-                    if (!(d > 0.0)) d = 1.0;
-                }
-                const double rs = rsqrt_f64(d);         // column j is scaled by 1 / L_jj, kept for the inverse below
-                if (lane == 0) rdg[c0 + j] = rs;
-                a[j] = lane == c0 + j ? d * rs : a[j] * rs;
-#pragma unroll
-                for (int c = j + 1; c < kSB; ++c) a[c] = fma(-a[j], readlane_f64(a[j], c0 + c), a[c]);
+            for (int c = 0; c < kSB; ++c) {
+                b[c] = T[(c0 + l16) * P + c0 + c];
+                x[c] = c == l16 ? 1.0 : 0.0;
             }
+            // U D U^T form: a reciprocal of the pivot is all that the chain from one pivot to the next needs; the square
+            // roots are taken at the end, of all sixteen pivots at once (dv: lane % 16 = pivot)
+            int bad = kSB;                              // first pivot that is too small, not positive, or NaN
+            double dv = 1.0;
+            static_for<kSB>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const double d = row_bcast_f64<j>(b[j]);
+                const bool positive = d > 0.0;
+                const double inv = positive ? rcp_f64(d) : 1.0;
+                if constexpr (j + 1 < kSB) {            // the next pivot's column first
+                    const double l = row_bcast_f64<j + 1>(b[j]) * b[j];
+                    b[j + 1] = fma(-l, inv, b[j + 1]);
+                }
+                const double u = b[j] * inv;
+                static_for<kSB - 1 - j>([&](auto ic) {
+                    constexpr int c = j + 1 + decltype(ic)::value;
+                    const double l = row_bcast_f64<c>(u);
+                    if constexpr (c > j + 1) b[c] = fma(-l, b[j], b[c]);
+                    x[c] = fma(-l, x[j], x[c]);
+                });
+                bad = !(d > floor_d) && bad == kSB ? j : bad;
+                dv = l16 == j && positive ? d : dv;
+            });
+            const double rs = rsqrt_f64(dv);
+            static_for<kSB>([&](auto cc) { x[decltype(cc)::value] *= row_bcast_f64<decltype(cc)::value>(rs); });
+            if (lane == 0 && bad < kSB && base + c0 + bad < r) atomicCAS(info, 0, base + c0 + bad + 1);
+            if (lane < kSB) {
 #pragma unroll
-            for (int c = 0; c < kSB; ++c)
-                if (lane >= c0 + c) T[lane * P + c0 + c] = a[c];
+                for (int c = 0; c < kSB; ++c) Dp[c * PX + lane] = c >= lane ? x[c] : 0.0;
+            }
         }
         __syncthreads();
-        // what is right of the 16 columns: block (i, j) -= L_ip L_jp^T, p < j <= i
-        const int left = NSB - 1 - p;
-        for (int b = wave; b < left * (left + 1) / 2; b += 4) {
-            int bi, bj;
-            lower_pair(b, bi, bj);
-            const int ri = (p + 1 + bi) * kSB, rj = (p + 1 + bj) * kSB;
-            const f64x4 u = mma16(T + ri * P + c0, P, 1, T + rj * P + c0, 1, P, f64x4{0.0, 0.0, 0.0, 0.0}, lane);
+        if (p + 1 + wave < NSB) {                       // L_ip = S_ip X_pp^T
+            double* Tip = T + (p + 1 + wave) * kSB * P + c0;
+            const f64x4 u = mma16(Tip, P, 1, Dp, 1, PX, f64x4{0.0, 0.0, 0.0, 0.0}, lane);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) T[(ri + 4 * v + (lane >> 4)) * P + rj + (lane & 15)] -= u[v];
+            for (int v = 0; v < 4; ++v) Tip[(4 * v + l4) * P + l16] = u[v];
+        }
+        __syncthreads();
+        // X_pj = -X_pp sum_{k=j}^{p-1} L_pk X_kj for j < p, element (i, c) kept at T[column][row] of the strict upper
+        // triangle, which holds nothing else; block (i, j) -= L_ip L_jp^T for p < j <= i.
+        const int left = NSB - 1 - p, trailing = left * (left + 1) / 2;
+        for (int task = wave; task < p + trailing; task += 4) {
+            if (task < p) {
+                const int j = task;
+                const double* Lp = T + c0 * P;
+                f64x4 w = mma16(Lp + j * kSB, P, 1, D + j * kSB * PX, PX, 1, f64x4{0.0, 0.0, 0.0, 0.0}, lane);
+                for (int k = j + 1; k < p; ++k) w = mma16(Lp + k * kSB, P, 1, T + j * kSB * P + k * kSB, 1, P, w, lane);
+                // W's accumulator layout (row 4 v + l / 16, column l % 16) is the B operand layout of k = 4 v + l / 16
+                f64x4 u{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    u = __builtin_amdgcn_mfma_f64_16x16x4f64(Dp[l16 * PX + 4 * v + l4], w[v], u, 0, 0, 0);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) T[(j * kSB + l16) * P + c0 + 4 * v + l4] = -u[v];
+            } else {
+                int bi, bj;
+                lower_pair(task - p, bi, bj);
+                const int ri = (p + 1 + bi) * kSB, rj = (p + 1 + bj) * kSB;
+                const f64x4 u = mma16(T + ri * P + c0, P, 1, T + rj * P + c0, 1, P, f64x4{0.0, 0.0, 0.0, 0.0}, lane);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) T[(ri + 4 * v + l4) * P + rj + l16] -= u[v];
+            }
         }
         __syncthreads();
     }
-    // L out; the strict upper triangle, which nothing reads as a factor, then receives X^T: X[i][c] at T[c][i], c < i;
-    // the diagonal of X is rdg.
-    for (int e = t; e < kNB * kNB; e += 256) {
-        const int ii = e >> 6, c = e & 63;
-        if (c <= ii && base + ii < r) S[(int64_t)(base + ii) * r + base + c] = T[ii * P + c];
-    }
-    // diagonal blocks: lane c of wave w owns column c of X_ww (forward substitution in registers)
-    {
-        const int c0 = wave * kSB, c = lane & 15;
-        double x[kSB];
 #pragma unroll
-        for (int i = 0; i < kSB; ++i) {
-            double s = i == c ? 1.0 : 0.0;
-#pragma unroll
-            for (int k = 0; k < i; ++k) s = fma(-T[(c0 + i) * P + c0 + k], x[k], s);
-            x[i] = s * rdg[c0 + i];
-        }
-        if (lane < kSB) {
-#pragma unroll
-            for (int i = 1; i < kSB; ++i)
-                if (i > c) T[(c0 + c) * P + c0 + i] = x[i];
-        }
-    }
-    __syncthreads();
-    // element (i, c) of X inside a diagonal block of X, and of its transpose, as MFMA operands
-    auto xd = [&](int row, int col) { return col < row ? T[col * P + row] : (col == row ? rdg[row] : 0.0); };
-    for (int d = 1; d < NSB; ++d) {                     // block diagonal d: X_ij = -X_ii sum_{k=j}^{i-1} L_ik X_kj, i = j + d
-        const int j = wave, i = wave + d;
-        const int ri = i * kSB, rj = j * kSB;
-        const bool on = i < NSB;                        // wave-uniform
-        f64x4 w{0.0, 0.0, 0.0, 0.0};
-        if (on) {
-            const int row = lane & 15, kq = lane >> 4;
-#pragma unroll
-            for (int k = 0; k < kSB; k += 4)            // k = j: X_jj is triangular, its upper triangle holds other things
-                w = __builtin_amdgcn_mfma_f64_16x16x4f64(T[(ri + row) * P + rj + k + kq], xd(rj + k + kq, rj + row), w, 0, 0, 0);
-            for (int kb2 = j + 1; kb2 < i; ++kb2)       // X_kj at T[rj + column][kk + row]
-                w = mma16(T + ri * P + kb2 * kSB, P, 1, T + rj * P + kb2 * kSB, 1, P, w, lane);
-            // -X_ii W: W's accumulator layout (row 4 v + l / 16, column l % 16) is the B operand layout of k = 4 v + l / 16
-            f64x4 x{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                x = __builtin_amdgcn_mfma_f64_16x16x4f64(xd(ri + row, ri + 4 * v + kq), w[v], x, 0, 0, 0);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) T[(rj + row) * P + ri + 4 * v + kq] = -x[v];
-        }
-        __syncthreads();
-    }
-    for (int e = t; e < kNB * kNB; e += 256) {
-        const int ii = e >> 6, c = e & 63;
-        const double x = xd(ii, c);
-        Dinv[(int64_t)kb * kNB * kNB + e] = x;
-        if (base + ii < r && base + c < r) X[(int64_t)(base + ii) * r + base + c] = x;
+    for (int q = 0; q < kNB * kNB / 256; ++q) {         // (row i of X: lane = column)
+        const int i = 4 * q + wave, c = lane, ib = i / kSB, cb = c / kSB;
+        const double y = *(cb == ib ? D + i * PX + c % kSB : T + c * P + i), x = cb <= ib ? y : 0.0;
+        Dinv[(int64_t)kb * kNB * kNB + i * kNB + c] = x;
+        if (base + i < r && base + c < r) X[(int64_t)(base + i) * r + base + c] = x;
     }
 }
 
@@ -392,11 +408,14 @@ __global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ S, int r
                                                    double* __restrict__ shift, double flag_factor, BatchStride st) {
     S += blockIdx.z * st.S;
     __shared__ double T[kNB * kPitchD];
-    __shared__ double rdg[kNB], red[4];
+    __shared__ double D[kNB * kPitchX];
+    __shared__ double red[4];
     const int base = FIRST ? 0 : kb * kNB;
-    for (int e = threadIdx.x; e < kNB * kNB; e += 256) {     // consecutive threads along a row
-        const int i = e >> 6, c = e & 63;
-        T[i * kPitchD + c] = (base + i < r && base + c < r) ? S[(int64_t)(base + i) * r + base + c] : (i == c ? 1.0 : 0.0);
+    double v[kNB * kNB / 256];                               // all loads in flight at once
+#pragma unroll
+    for (int q = 0; q < kNB * kNB / 256; ++q) {
+        const int i = 4 * q + (threadIdx.x >> 6), c = threadIdx.x & 63;
+        v[q] = (base + i < r && base + c < r) ? S[(int64_t)(base + i) * r + base + c] : (i == c ? 1.0 : 0.0);
     }
     double sigma;
     if constexpr (FIRST) {
@@ -405,9 +424,11 @@ __global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ S, int r
         if (threadIdx.x == 0) shift[blockIdx.z * st.shift] = sigma;
     } else {
         sigma = shift[blockIdx.z * st.shift];
-        __syncthreads();
     }
-    chol_diag_block(T, rdg, S, r, FIRST ? 0 : kb, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma, flag_factor);
+#pragma unroll
+    for (int q = 0; q < kNB * kNB / 256; ++q) T[(4 * q + (threadIdx.x >> 6)) * kPitchD + (threadIdx.x & 63)] = v[q];
+    __syncthreads();
+    chol_diag_block(T, D, r, FIRST ? 0 : kb, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma, flag_factor);
 }
 
 __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int r, int kb, const double* __restrict__ Dinv,
@@ -442,62 +463,70 @@ __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// X = L^-1, block (ib, kb) with kb < ib (all block rows above are complete):  X_ik = -X_ii (sum_{j=k}^{i-1} L_ij X_jk).
-// At, Bt: kNB * kPitchKF and kNB * kPitchT doubles of LDS.
+// X = L^-1, block (ib, kb) with kb < ib (all block rows above are complete):  X_ik = -X_ii (sum_{j=k}^{i-1} L_ij X_jk).  A
+// workgroup takes 16 columns of the block (strip 0 .. 3), a wave 16 rows of them, and whole 64-deep blocks of the sum, the
+// next one in registers meanwhile: with 64 columns and 16-deep chunks a workgroup was a chain of up to 60 chunks of 16 MFMAs,
+// two barriers and a load each (last block row at r = 1024: 60 us, now 24).
+// At, Bt: kNB * kPitchD and kNB * kPitchX doubles of LDS.
 // ---------------------------------------------------------------------------------------------------------------
-__device__ __forceinline__ void trinv_block(const double* __restrict__ S, double* __restrict__ X,
-                                            const double* __restrict__ Dinv, int r, int ib, int kb, double* At, double* Bt) {
-    // phase 1: At (L chunk, k fast) and Bt (X chunk, k slow); phase 2: Tm (the sum) and At (X_ii chunk)
-    static_assert(kNB * kPitchT >= kKC * kPitchKS, "the intermediate reuses the X chunk's buffer");
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
-    f64x4 acc[2][2];
-    zero_acc(acc);
-    BlockStage<kNB, kKC, kPitchKF, double> sa;
-    BlockStage<kKC, kNB, kPitchKS, double> sb;
-    const double* D = Dinv + (int64_t)ib * kNB * kNB;
-    const int k_end = ib * kNB;
+constexpr int kStrips = kNB / kSB;    // strips of a block of X
+
+__device__ __forceinline__ void trinv_strip(const double* __restrict__ S, double* __restrict__ X,
+                                            const double* __restrict__ Dinv, int r, int ib, int kb, int strip, double* At,
+                                            double* Bt) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, l4 = lane >> 4;
+    const int c0 = kb * kNB + strip * kSB;
+    if (c0 >= r) return;
+    BlockStage<kNB, kNB, kPitchD, double> sa;
+    BlockStage<kNB, kSB, kPitchX, double> sb;
+    auto product = [&] {
+        f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
+        const double *ap = At + (wave * kSB + l16) * kPitchD + l4, *bp = Bt + l4 * kPitchX + l16;
+#pragma unroll
+        for (int k = 0; k < kNB; k += 4)
+            acc[(k / 4) & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[k], bp[k * kPitchX], acc[(k / 4) & 1], 0, 0, 0);
+        return acc[0] + acc[1];
+    };
+    f64x4 sum{0.0, 0.0, 0.0, 0.0};
     sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
-    sb.fetch(X, r, kb * kNB, kb * kNB, r, r);
-    for (int kc = kb * kNB; kc < k_end; kc += kKC) {
+    sb.fetch(X, r, kb * kNB, c0, r, r);
+    for (int j = kb; j < ib; ++j) {
         sa.commit(At);
         sb.commit(Bt);
         __syncthreads();
-        if (kc + kKC < k_end) {
-            sa.fetch(S, r, ib * kNB, kc + kKC, r, r);
-            sb.fetch(X, r, kc + kKC, kb * kNB, r, r);
+        if (j + 1 < ib) {
+            sa.fetch(S, r, ib * kNB, (j + 1) * kNB, r, r);
+            sb.fetch(X, r, (j + 1) * kNB, c0, r, r);
         } else {
-            sa.fetch(D, kNB, 0, 0, kNB, kNB);     // first chunk of the second product
+            sa.fetch(Dinv + (int64_t)ib * kNB * kNB, kNB, 0, 0, kNB, kNB);
         }
-        mma_chunk(At, kPitchKF, 1, Bt, 1, kPitchKS, acc, lane, wi, wj);
+        sum += product();
         __syncthreads();
     }
-    double* Tm = Bt;
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) { Tm[row * kPitchT + col] = x; });
-    zero_acc(acc);
-    for (int kc = 0; kc < kNB; kc += kKC) {
-        sa.commit(At);
-        __syncthreads();       // also publishes Tm on the first pass
-        if (kc + kKC < kNB) sa.fetch(D, kNB, 0, kc + kKC, kNB, kNB);
-        mma_chunk(At, kPitchKF, 1, Tm + kc * kPitchT, 1, kPitchT, acc, lane, wi, wj);
-        __syncthreads();
+    sa.commit(At);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) Bt[(wave * kSB + 4 * v + l4) * kPitchX + l16] = sum[v];
+    __syncthreads();
+    const f64x4 x = product();
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const int i = ib * kNB + wave * kSB + 4 * v + l4, c = c0 + l16;
+        if (i < r && c < r) X[(int64_t)i * r + c] = -x[v];
     }
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = ib * kNB + row, gj = kb * kNB + col;
-        if (gi < r && gj < r) X[(int64_t)gi * r + gj] = -x;
-    });
 }
 
 __global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S, double* __restrict__ X,
                                                    const double* __restrict__ Dinv, int r, int ib, BatchStride st) {
-    __shared__ double At[kNB * kPitchKF];
-    __shared__ double Bt[kNB * kPitchT];
-    trinv_block(S + blockIdx.z * st.S, X + blockIdx.z * st.X, Dinv + blockIdx.z * st.D, r, ib, blockIdx.x, At, Bt);
+    __shared__ double At[kNB * kPitchD];
+    __shared__ double Bt[kNB * kPitchX];
+    trinv_strip(S + blockIdx.z * st.S, X + blockIdx.z * st.X, Dinv + blockIdx.z * st.D, r, ib, blockIdx.x / kStrips,
+                blockIdx.x % kStrips, At, Bt);
 }
 
 // Workgroups 0 .. pairs-1: the trailing blocks of step kb.  FUSED: block (kb+1, kb+1) goes on to be factored, and workgroups
-// pairs .. pairs+kb-1 take block row kb of X (L's row kb and X_kk are final, X's rows above too): in one launch the three
-// fill the chip together, and a block column costs two launches where it takes four.  But every workgroup then holds the
-// diagonal block's 302 registers and the inverse's 43 KB of LDS, one on a CU; on its own the trailing update fits five.
+// the kStrips * kb after them take block row kb of X (L's row kb and X_kk are final, X's rows above too): in one launch the
+// three fill the chip together, and a block column costs two launches where it takes four.  But every workgroup then holds the
+// diagonal block's 156 registers and 42 KB of LDS, three on a CU; on its own the trailing update fits five.
 template <bool FUSED>
 __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int r, int kb, int pairs,
                                                      double* __restrict__ Dinv, double* __restrict__ X,
@@ -506,14 +535,13 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
     S += blockIdx.z * st.S;
     X += blockIdx.z * st.X;
     Dinv += blockIdx.z * st.D;
-    constexpr int A_LEN = kNB * kPitchKF, B_LEN = FUSED ? kNB * kPitchT : A_LEN;
-    static_assert(!FUSED || (A_LEN + B_LEN >= kNB * kPitchD && B_LEN >= A_LEN), "one buffer serves the three roles");
-    __shared__ double buf[A_LEN + B_LEN];
-    __shared__ double rdg[FUSED ? kNB : 1];
-    double *At = buf, *Bt = buf + A_LEN;
+    constexpr int UPDATE = 2 * kNB * kPitchKF, BLOCK = kNB * (kPitchD + kPitchX);
+    __shared__ double buf[FUSED && BLOCK > UPDATE ? BLOCK : UPDATE];
+    double *At = buf, *Bt = buf + kNB * kPitchKF;
     if constexpr (FUSED) {
-        if ((int)blockIdx.x >= pairs) {
-            trinv_block(S, X, Dinv, r, kb, blockIdx.x - pairs, At, Bt);
+        const int strip = (int)blockIdx.x - pairs;
+        if (strip >= 0) {
+            trinv_strip(S, X, Dinv, r, kb, strip / kStrips, strip % kStrips, buf, buf + kNB * kPitchD);
             return;
         }
     }
@@ -550,7 +578,7 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
             buf[row * kPitchD + col] = (gi < r && gj < r) ? S[(int64_t)gi * r + gj] - x : (row == col ? 1.0 : 0.0);
         });
         __syncthreads();
-        chol_diag_block(buf, rdg, S, r, kb + 1, Dinv, X, info + blockIdx.z, shift[blockIdx.z * st.shift], flag_factor);
+        chol_diag_block(buf, buf + kNB * kPitchD, r, kb + 1, Dinv, X, info + blockIdx.z, shift[blockIdx.z * st.shift], flag_factor);
     }
 }
 
@@ -704,7 +732,7 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
         const int below = nt - kb - 1, left = below * (below + 1) / 2;
         hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
         if (fused) {
-            hipLaunchKernelGGL(k_chol_update<true>, dim3(left + kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info,
+            hipLaunchKernelGGL(k_chol_update<true>, dim3(left + kStrips * kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info,
                                shift, flag_factor, st);
         } else {
             hipLaunchKernelGGL(k_chol_update<false>, dim3(left, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
@@ -714,7 +742,7 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
         }
     }
     for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
-        if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
+        if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(kStrips * ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
     hipLaunchKernelGGL(k_apply, dim3((unsigned)((m + kNB - 1) / kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
 }
 
