@@ -70,44 +70,47 @@ struct BlockStage {
     }
 };
 
-// One K chunk of the workgroup's 64 x 64 product on the fp64 matrix cores.  Wave (wi, wj) owns the 32 x 32 quadrant
-// as 2 x 2 blocks of v_mfma_f64_16x16x4: lane l supplies A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16];
-// register v of the result is element (i = 4 v + l / 16, j = l % 16).  Operand element (i, k) of A sits at
-// At[i * a_pi + k * a_pk], element (k, j) of B at Bt[j * b_pj + k * b_pk].
+// One K chunk (KC deep) of the workgroup's product on the fp64 matrix cores.  Wave (wi, wj) owns a quadrant of W x W blocks
+// of v_mfma_f64_16x16x4: lane l supplies A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16]; register v of the
+// result is element (i = 4 v + l / 16, j = l % 16).  Operand element (i, k) of A sits at At[i * a_pi + k * a_pk], element
+// (k, j) of B at Bt[j * b_pj + k * b_pk].
+template <int KC = kKC, int W>
 __device__ __forceinline__ void mma_chunk(const double* At, int a_pi, int a_pk, const double* Bt, int b_pj, int b_pk,
-                                          f64x4 (&acc)[2][2], int lane, int wi, int wj) {
-    const double* ap = At + (wi * 32 + (lane & 15)) * a_pi + (lane >> 4) * a_pk;
-    const double* bp = Bt + (wj * 32 + (lane & 15)) * b_pj + (lane >> 4) * b_pk;
+                                          f64x4 (&acc)[W][W], int lane, int wi, int wj) {
+    const double* ap = At + (wi * 16 * W + (lane & 15)) * a_pi + (lane >> 4) * a_pk;
+    const double* bp = Bt + (wj * 16 * W + (lane & 15)) * b_pj + (lane >> 4) * b_pk;
 #pragma unroll
-    for (int k0 = 0; k0 < kKC; k0 += 4) {
-        double af[2], bf[2];
+    for (int k0 = 0; k0 < KC; k0 += 4) {
+        double af[W], bf[W];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) af[a] = ap[a * 16 * a_pi + k0 * a_pk];
+        for (int a = 0; a < W; ++a) af[a] = ap[a * 16 * a_pi + k0 * a_pk];
 #pragma unroll
-        for (int b = 0; b < 2; ++b) bf[b] = bp[b * 16 * b_pj + k0 * b_pk];
+        for (int b = 0; b < W; ++b) bf[b] = bp[b * 16 * b_pj + k0 * b_pk];
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < W; ++a)
 #pragma unroll
-            for (int b = 0; b < 2; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
+            for (int b = 0; b < W; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(af[a], bf[b], acc[a][b], 0, 0, 0);
     }
 }
 
-__device__ __forceinline__ void zero_acc(f64x4 (&acc)[2][2]) {
+template <int W>
+__device__ __forceinline__ void zero_acc(f64x4 (&acc)[W][W]) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < W; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+        for (int b = 0; b < W; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
 }
 
-// f(row, col, value) for every element of the wave's quadrant, row and col inside the 64 x 64 block.
-template <typename F>
-__device__ __forceinline__ void for_each_acc(const f64x4 (&acc)[2][2], int lane, int wi, int wj, F f) {
+// f(row, col, value) for every element of the wave's quadrant, row and col inside the workgroup's block.
+template <int W, typename F>
+__device__ __forceinline__ void for_each_acc(const f64x4 (&acc)[W][W], int lane, int wi, int wj, F f) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < W; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
+        for (int b = 0; b < W; ++b)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) f(wi * 32 + a * 16 + 4 * v + (lane >> 4), wj * 32 + b * 16 + (lane & 15), acc[a][b][v]);
+            for (int v = 0; v < 4; ++v)
+                f((wi * W + a) * 16 + 4 * v + (lane >> 4), (wj * W + b) * 16 + (lane & 15), acc[a][b][v]);
 }
 
 // A batch of matrices with the same m and r runs through the fp64 kernels in one launch each, matrix b =
@@ -186,36 +189,49 @@ __global__ void k_set_i32(int32_t* p, int32_t v, int count) {
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int kGramMaxSlices = 8;
 
+// The two products over m rows come with 64 x 64 blocks (TB) and 16-deep chunks for many workgroups, and with 32 x 32 blocks
+// and 64-deep chunks for few, where a workgroup's chain of chunks is what counts: a quarter of the MFMAs per chunk row, four
+// times the workgroups, a quarter of the barriers (768 x 256: k_gram 31 -> 15 us, k_apply 21 -> 9).  The order of every
+// sum is the same in both.
+template <int TB>
+struct F64Tile {
+    static constexpr int W = TB / 32, KC = TB == kNB ? kKC : 64;
+    static constexpr int PITCH_KF = KC + 1;                  // [x][k] chunk, k fastest
+    static constexpr int PITCH_KS = TB + 16;                 // [k][x] chunk, k slowest
+};
+
+template <int TB>
 __global__ __launch_bounds__(256) void k_gram(const float* __restrict__ Y, double* __restrict__ part, int m, int r,
                                               int slice_rows, BatchStride st) {
+    using F = F64Tile<TB>;
     Y += blockIdx.z * st.Y;
     part += blockIdx.z * st.part;
-    __shared__ double At[kKC * kPitchKS];
-    __shared__ double Bt[kKC * kPitchKS];
+    __shared__ double At[F::KC * F::PITCH_KS];
+    __shared__ double Bt[F::KC * F::PITCH_KS];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
     int bi, bj;
     lower_pair(blockIdx.x, bi, bj);
     const bool diag = bi == bj;
     const int k_begin = blockIdx.y * slice_rows, k_end = min(m, k_begin + slice_rows);
     double* S = part + (int64_t)blockIdx.y * r * r;
-    BlockStage<kKC, kNB, kPitchKS, float> sa, sb;
-    f64x4 acc[2][2];
+    BlockStage<F::KC, TB, F::PITCH_KS, float> sa, sb;
+    f64x4 acc[F::W][F::W];
     zero_acc(acc);
-    sa.fetch(Y, r, k_begin, bi * kNB, k_end, r);
-    if (!diag) sb.fetch(Y, r, k_begin, bj * kNB, k_end, r);
-    for (int k0 = k_begin; k0 < k_end; k0 += kKC) {
+    sa.fetch(Y, r, k_begin, bi * TB, k_end, r);
+    if (!diag) sb.fetch(Y, r, k_begin, bj * TB, k_end, r);
+    for (int k0 = k_begin; k0 < k_end; k0 += F::KC) {
         sa.commit(At);
         if (!diag) sb.commit(Bt);
         __syncthreads();
-        if (k0 + kKC < k_end) {
-            sa.fetch(Y, r, k0 + kKC, bi * kNB, k_end, r);
-            if (!diag) sb.fetch(Y, r, k0 + kKC, bj * kNB, k_end, r);
+        if (k0 + F::KC < k_end) {
+            sa.fetch(Y, r, k0 + F::KC, bi * TB, k_end, r);
+            if (!diag) sb.fetch(Y, r, k0 + F::KC, bj * TB, k_end, r);
         }
-        mma_chunk(At, 1, kPitchKS, diag ? At : Bt, 1, kPitchKS, acc, lane, wi, wj);
+        mma_chunk<F::KC>(At, 1, F::PITCH_KS, diag ? At : Bt, 1, F::PITCH_KS, acc, lane, wi, wj);
         __syncthreads();
     }
     for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = bi * kNB + row, gj = bj * kNB + col;
+        const int gi = bi * TB + row, gj = bj * TB + col;
         if (gi < r && gj < r) S[(int64_t)gi * r + gj] = x;
     });
 }
@@ -255,8 +271,9 @@ constexpr int kPitchX = kSB + 1;      // ... of the inverses of its 16 x 16 diag
 // x of lane L of each row of 16 lanes, in all 16.
 template <int L>
 __device__ __forceinline__ double row_bcast_f64(double x) {
-    const long long b = __builtin_bit_cast(long long, x);
-    return __builtin_bit_cast(double, __builtin_amdgcn_update_dpp(b, b, 0x150 + L, 0xf, 0xf, false));   // row_newbcast:L
+    long long b = __builtin_bit_cast(long long, x);
+    b = __builtin_amdgcn_mov_dpp(b, 0x150 + L, 0xf, 0xf, true);   // row_newbcast:L
+    return __builtin_bit_cast(double, b);
 }
 
 // f(0), ..., f(N - 1) with the index as a compile-time constant.
@@ -330,24 +347,30 @@ __device__ __forceinline__ void chol_diag_block(double* T, double* D, int r, int
             // roots are taken at the end, of all sixteen pivots at once (dv: lane % 16 = pivot)
             int bad = kSB;                              // first pivot that is too small, not positive, or NaN
             double dv = 1.0;
-            static_for<kSB>([&](auto jc) {
+            double u = 0.0;                             // column j of U D over the pivot, of the pivot before
+            static_for<kSB + 1>([&](auto jc) {          // per scheduling region: pivot j's chain, the rest of pivot j - 1
                 constexpr int j = decltype(jc)::value;
-                const double d = row_bcast_f64<j>(b[j]);
-                const bool positive = d > 0.0;
-                const double inv = positive ? rcp_f64(d) : 1.0;
-                if constexpr (j + 1 < kSB) {            // the next pivot's column first
-                    const double l = row_bcast_f64<j + 1>(b[j]) * b[j];
-                    b[j + 1] = fma(-l, inv, b[j + 1]);
+                double u1 = 0.0;
+                if constexpr (j > 0 && j + 1 < kSB) b[j + 1] = fma(-row_bcast_f64<j + 1>(u), b[j - 1], b[j + 1]);
+                if constexpr (j < kSB) {
+                    const double d = row_bcast_f64<j>(b[j]);
+                    const bool positive = d > 0.0;
+                    const double inv = positive ? rcp_f64(d) : 1.0;
+                    if constexpr (j + 1 < kSB) b[j + 1] = fma(-(row_bcast_f64<j + 1>(b[j]) * b[j]), inv, b[j + 1]);
+                    u1 = b[j] * inv;
+                    bad = !(d > floor_d) && bad == kSB ? j : bad;
+                    dv = l16 == j && positive ? d : dv;
                 }
-                const double u = b[j] * inv;
-                static_for<kSB - 1 - j>([&](auto ic) {
-                    constexpr int c = j + 1 + decltype(ic)::value;
-                    const double l = row_bcast_f64<c>(u);
-                    if constexpr (c > j + 1) b[c] = fma(-l, b[j], b[c]);
-                    x[c] = fma(-l, x[j], x[c]);
-                });
-                bad = !(d > floor_d) && bad == kSB ? j : bad;
-                dv = l16 == j && positive ? d : dv;
+                if constexpr (j > 0)
+                    static_for<kSB - j>([&](auto ic) {
+                        constexpr int c = j + decltype(ic)::value;
+                        const double l = row_bcast_f64<c>(u);
+                        if constexpr (c > j + 1) b[c] = fma(-l, b[j - 1], b[c]);
+                        x[c] = fma(-l, x[j - 1], x[c]);
+                        asm volatile("" : "+v"(x[c]));   // (here, not where X_pp is stored, with every l kept until then)
+                    });
+                u = u1;
+                __builtin_amdgcn_sched_barrier(0);
             });
             const double rs = rsqrt_f64(dv);
             static_for<kSB>([&](auto cc) { x[decltype(cc)::value] *= row_bcast_f64<decltype(cc)::value>(rs); });
@@ -585,35 +608,37 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
 // ---------------------------------------------------------------------------------------------------------------
 // Q = Y X^T (X lower triangular: column block jb needs the contraction index up to the end of that block only)
 // ---------------------------------------------------------------------------------------------------------------
+template <int TB>
 __global__ __launch_bounds__(256) void k_apply(const float* __restrict__ Y, const double* __restrict__ X,
                                                float* __restrict__ Q, int m, int r, BatchStride st) {
+    using F = F64Tile<TB>;
     Y += blockIdx.z * st.Y;
     X += blockIdx.z * st.X;
     Q += blockIdx.z * st.Q;
-    __shared__ double At[kNB * kPitchKF];
-    __shared__ double Bt[kNB * kPitchKF];
+    __shared__ double At[TB * F::PITCH_KF];
+    __shared__ double Bt[TB * F::PITCH_KF];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
-    const int a0 = blockIdx.x * kNB, jb = blockIdx.y;
-    const int kend = min(r, (jb + 1) * kNB);
-    BlockStage<kNB, kKC, kPitchKF, float> sa;
-    BlockStage<kNB, kKC, kPitchKF, double> sb;
-    f64x4 acc[2][2];
+    const int a0 = blockIdx.x * TB, b0 = blockIdx.y * TB;
+    const int kend = min(r, (b0 / kNB + 1) * kNB);           // X is zero above its diagonal blocks
+    BlockStage<TB, F::KC, F::PITCH_KF, float> sa;
+    BlockStage<TB, F::KC, F::PITCH_KF, double> sb;
+    f64x4 acc[F::W][F::W];
     zero_acc(acc);
     sa.fetch(Y, r, a0, 0, m, r);
-    sb.fetch(X, r, jb * kNB, 0, r, r);
-    for (int kc = 0; kc < kend; kc += kKC) {
+    sb.fetch(X, r, b0, 0, r, r);
+    for (int kc = 0; kc < kend; kc += F::KC) {
         sa.commit(At);
         sb.commit(Bt);
         __syncthreads();
-        if (kc + kKC < kend) {
-            sa.fetch(Y, r, a0, kc + kKC, m, r);
-            sb.fetch(X, r, jb * kNB, kc + kKC, r, r);
+        if (kc + F::KC < kend) {
+            sa.fetch(Y, r, a0, kc + F::KC, m, r);
+            sb.fetch(X, r, b0, kc + F::KC, r, r);
         }
-        mma_chunk(At, kPitchKF, 1, Bt, kPitchKF, 1, acc, lane, wi, wj);
+        mma_chunk<F::KC>(At, F::PITCH_KF, 1, Bt, F::PITCH_KF, 1, acc, lane, wi, wj);
         __syncthreads();
     }
     for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = a0 + row, gj = jb * kNB + col;
+        const int gi = a0 + row, gj = b0 + col;
         if (gi < m && gj < r) Q[(int64_t)gi * r + gj] = (float)x;
     });
 }
@@ -721,7 +746,16 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     const int slices = gram_slices(m, r, &slice_rows);
     const dim3 blk(256);
     const unsigned B = (unsigned)batch;
-    hipLaunchKernelGGL(k_gram, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
+    auto blocks = [](int64_t n, int size) { return (unsigned)((n + size - 1) / size); };
+    const unsigned nt32 = blocks(r, 32);
+    // 32 x 32 blocks while 64 x 64 ones are about a workgroup per CU or fewer (us per refresh, always 64 / this line / up to
+    // 1000 / 9000 workgroups: 2048 x 2048, r = 512 705 / 652 / 653 / 651, 3000 x 700, r = 128, eight of them 552 / 507 / 515 /
+    // 517, 2048 x 2048, r = 512, sixteen 1982 / 1956 / 1984 / 2274)
+    constexpr int64_t kFewBlocks = 300;
+    if ((int64_t)pairs * slices * batch < kFewBlocks)
+        hipLaunchKernelGGL(k_gram<32>, dim3(nt32 * (nt32 + 1) / 2, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
+    else
+        hipLaunchKernelGGL(k_gram<kNB>, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
     // One launch per block column while its workgroups, one on a CU, are few (ms per refresh, fused / separate: one 4096 x
     // 4096, r = 1024, 2.36 / 3.16, 16 of them 10.9 / 11.2, 32 20.8 / 19.9, 128 80.0 / 72.6; r = 512: 32 matrices 3.62 / 3.76, 96
@@ -743,7 +777,10 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     }
     for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
         if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(kStrips * ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
-    hipLaunchKernelGGL(k_apply, dim3((unsigned)((m + kNB - 1) / kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
+    if ((int64_t)blocks(m, kNB) * nt * batch < kFewBlocks)
+        hipLaunchKernelGGL(k_apply<32>, dim3(blocks(m, 32), nt32, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
+    else
+        hipLaunchKernelGGL(k_apply<kNB>, dim3(blocks(m, kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
 }
 
 // Cholesky QR twice: Y -> T -> Q.  info: `batch` consecutive device ints.
