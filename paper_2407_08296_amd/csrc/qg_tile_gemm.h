@@ -69,8 +69,17 @@ struct LinBatch {
 
 // What a fetch may take for granted: the chunk lies inside the matrix and is 16-byte aligned; the step lies inside the
 // contraction and no chunk straddles the end of the x indices (those past it read the last row or chunk again, for results
-// that are never stored); nothing.
-enum : int { kFetchAligned = 0, kFetchClamped = 1, kFetchGuarded = 2 };
+// that are never stored); the same, but the chunk that straddles the end is the last whole one shifted; nothing.
+enum : int { kFetchAligned = 0, kFetchClamped = 1, kFetchShifted = 2, kFetchGuarded = 3 };
+
+// The 128 bits of v shifted right by `bits` < 128.
+__device__ __forceinline__ u32x4 shift_right_128(u32x4 v, int bits) {
+    const uint64_t lo = (uint64_t)v[1] << 32 | v[0], hi = (uint64_t)v[3] << 32 | v[2];
+    const int b = bits & 63;
+    const uint64_t h = hi >> b, l = (lo >> b) | ((hi << 1) << (63 - b));
+    const uint64_t rl = bits < 64 ? l : h, rh = bits < 64 ? h : 0;
+    return u32x4{(uint32_t)rl, (uint32_t)(rl >> 32), (uint32_t)rh, (uint32_t)(rh >> 32)};
+}
 
 // Staging of one operand tile: global -> registers (fetch) -> LDS (commit; INT8 is dequantized here).
 template <int LAYOUT, int XT, int BK, int NT = 256>
@@ -100,7 +109,9 @@ struct LinStage {
             const int idx = thread() + NT * q;
             const int tr = idx / CPR, tc = (idx % CPR) * CH;         // row and first column inside the tile
             int x = x0 + (kFast ? tr : tc);                          // ... and inside the matrix
-            if constexpr (FETCH == kFetchClamped) x = min(x, kFast ? X - 1 : X - CH);
+            const int xs = min(x, X - 1);                            // for the block scale: the chunk's own block
+            const int past = FETCH == kFetchShifted && !kFast ? min(max(x - (X - CH), 0), CH - 1) : 0;
+            if constexpr (FETCH == kFetchClamped || FETCH == kFetchShifted) x = min(x, kFast ? X - 1 : X - CH);
             const KI k = k0 + (kFast ? tc : tr);
             const int64_t row = kFast ? x : k, col = kFast ? k : x;
             int valid = CH;
@@ -112,13 +123,15 @@ struct LinStage {
                 const int8_t* src = static_cast<const int8_t*>(op.base) + off;
                 if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
                 else v[q] = load16_i8_guarded(src, valid);
-                s[q] = valid > 0 ? op.scales[row * op.sgroups + (col >> 8)] : 0.f;
-                if constexpr (kZero) z[q] = valid > 0 ? op.zeros[row * op.sgroups + (col >> 8)] : 0.f;
+                const int64_t block = (!kFast && FETCH == kFetchShifted ? xs : col) >> 8;
+                s[q] = valid > 0 ? op.scales[row * op.sgroups + block] : 0.f;
+                if constexpr (kZero) z[q] = valid > 0 ? op.zeros[row * op.sgroups + block] : 0.f;
             } else {
                 const uint16_t* src = static_cast<const uint16_t*>(op.base) + off;
                 if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
                 else v[q] = load8_bf16_guarded(src, valid);
             }
+            if constexpr (FETCH == kFetchShifted && !kFast) v[q] = shift_right_128(v[q], past * (128 / CH));
         }
     }
     __device__ __forceinline__ void commit(uint16_t* tile) const {
@@ -136,6 +149,8 @@ struct LinStage {
     }
     // Whether the tile of the XT x indices from x0 on can be fetched clamped (chunks along x: whole ones, or all inside).
     __device__ static __forceinline__ bool clampable(int x0, int X) { return kFast || X % CH == 0 || x0 + XT <= X; }
+    // ... shifted (at least one whole chunk along x).
+    __device__ static __forceinline__ bool shiftable(int X) { return kFast || X >= CH; }
     // MFMA operand fragment of the 32 x indices starting at xb for the 16-deep sub-step kk
     __device__ static __forceinline__ bf16x8 frag(const uint16_t* tile, int xb, int kk, int lane) {
         if constexpr (kFast)
@@ -197,9 +212,10 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* 
 // EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a workgroup
 // runs unchecked too, but for the last, partial step, with its x indices clamped to the operand's last row or chunk: the
 // checks cost a wave three branches per chunk, and the workgroups at the edge, which took them, were the last to end (1000
-// tokens, 2048 -> 2048: forward 28.5 -> 20.9 us, grad_input 29.4 -> 21.7; 1024 tokens 20.4 and 22.0).  Checked are tiles at
-// the edge of an operand with k slow whose last chunk is not whole, and all tiles with one register set, an INT8 B with k slow
-// and such a last chunk, where checking measured faster (grad_input, 1000 tokens, 2048 -> 5461: 98.6 against 102.5).
+// tokens, 2048 -> 2048: forward 28.5 -> 20.9 us, grad_input 29.4 -> 21.7; 1024 tokens 20.4 and 22.0).  Where the last chunk of
+// an operand with k slow is not whole, the tile at its edge takes the last whole chunk and shifts it (1000 tokens, 2048 ->
+// 5461: grad_input 98.6 -> 50.9, grad_W 80.1 -> 48.1; with every element of that chunk checked and loaded alone, the few
+// workgroups of that edge took longer than all others together).  Checked are operands of less than a chunk.
 template <int AL, int BL, int MB, int TN, int BK, int WM>
 struct TileGemm {
     static constexpr int TM = 32 * MB * WM, NT = 128 * WM;
@@ -320,11 +336,14 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
     } else {
         inside = i0 + TM <= M && j0 + TN <= N;
         const int whole = K / BK;
-        const bool check_all = !DEEP && (BL == kInt8KSlow || BL == kInt8ZKSlow) && N % SB::CH != 0;
-        if (check_all || !SA::clampable(i0, M) || !SB::clampable(j0, N)) {
+        const bool shiftable = SA::shiftable(M) && SB::shiftable(N);
+        if (!shiftable) {
             steps(std::integral_constant<int, kFetchGuarded>(), (K + BK - 1) / BK);
         } else {
-            if (whole > 0) steps(std::integral_constant<int, kFetchClamped>(), whole);
+            if (whole > 0) {
+                if (SA::clampable(i0, M) && SB::clampable(j0, N)) steps(std::integral_constant<int, kFetchClamped>(), whole);
+                else steps(std::integral_constant<int, kFetchShifted>(), whole);
+            }
             if (whole * BK < K) {
                 sa[0].template fetch<kFetchGuarded>(A, i0, M, whole * BK, K);
                 sb[0].template fetch<kFetchGuarded>(B, j0, N, whole * BK, K);
@@ -448,9 +467,10 @@ __device__ __forceinline__ void ksplit_gemm(const LinOperand& A, const LinOperan
     const int total = (K + BK - 1) / BK, whole = K / BK;
     if constexpr (EXACT) {
         run(std::integral_constant<int, kFetchAligned>(), wave, steps_below(total));
-    } else if (SA::clampable(i0, M) && SB::clampable(j0, N)) {
+    } else if (SA::shiftable(M) && SB::shiftable(N)) {
         const int n = steps_below(whole);
-        run(std::integral_constant<int, kFetchClamped>(), wave, n);
+        if (SA::clampable(i0, M) && SB::clampable(j0, N)) run(std::integral_constant<int, kFetchClamped>(), wave, n);
+        else run(std::integral_constant<int, kFetchShifted>(), wave, n);
         if (steps_below(total) > n) run(Guarded(), wave + KW * n, 1);   // the last, partial step
     } else {
         run(Guarded(), wave, steps_below(total));

@@ -95,6 +95,16 @@ def test_orthonormalize_around_the_block_sizes(r):
     assert np.abs(got.T @ got - np.eye(r)).max() <= 1e-6
 
 
+@pytest.mark.parametrize("r,column", [(72, 20), (72, 70), (136, 0), (136, 79)])
+def test_orthonormalize_reports_a_column_with_a_nan(r, column):
+    """The first pivot that is not a number is the column's own, whatever 16- or 64-wide block it lies in."""
+    Y = np.random.default_rng(r).standard_normal((300, r)).astype(np.float32)
+    Y[5, column] = np.nan
+    Qd, info = qg.orthonormalize(dev(Y))
+    assert int(host(info)[0]) == column + 1
+    assert not np.isfinite(host(Qd)[:, column]).any()
+
+
 def test_orthonormalize_graded_columns():
     """Column norms spread over four decades and strong correlation: cond(Y) ~ 1e5."""
     m, r = 777, 200
