@@ -89,7 +89,15 @@ static auto with_bp(int cfg, F f) {
 int bp_config(int mode, int64_t tiles128) { return tiles128 < (mode == kUnaligned ? 300 : 384) ? kBp64 : kBp128; }
 int64_t bp_tiles_m(int cfg, int64_t m) { return with_bp(cfg, [&](auto c) { return (m + c.BM - 1) / c.BM; }); }
 
-#define QG_PROJ(KERNEL, C, M, ...) (KERNEL<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, M, C::kWg[M]>)
+// The projection with Adam: a masked launch whose rows share cache lines has instances of its own (see kAuxStream).
+template <typename F>
+static auto with_adam_mode(int mode, bool lines, F f) {
+    if (mode == kMasked && !lines) return f(std::integral_constant<int, kMaskedShared>());
+    return with_mode(mode, f);
+}
+constexpr int wg_index(int mode) { return mode == kMaskedShared ? kMasked : mode; }
+
+#define QG_PROJ(KERNEL, C, M, ...) (KERNEL<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, M, C::kWg[wg_index(M)]>)
 // ld: row pitch in elements of G, R, M, V, N (n for dense rows).
 int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, float* R, float* M, float* V,
                         uint16_t* N, int64_t m, int64_t n, int64_t ld, int64_t r, int64_t step, const qg_hparams* hp,
@@ -97,9 +105,9 @@ int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, f
     const AdamCoef coef = make_adam_coef(hp, step);
     return with_proj(proj_config_of(n, ld, r, 1), [&](auto c) {
         using C = decltype(c);
-        return with_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), [&](auto mode) {
+        return with_adam_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), whole_lines(ld), [&](auto mode) {
             const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles = tr * (uint32_t)((n + C::BN - 1) / C::BN);
-            constexpr int WG = C::NS == 2 ? 2 : C::kWg[mode()];   // (for three the 128 x 256 instance of this kernel spills)
+            constexpr int WG = C::NS == 2 ? 2 : C::kWg[wg_index(mode())];   // (for three the 128 x 256 instance of this kernel spills)
             hipLaunchKernelGGL((k_project_adam<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, mode(), WG>), dim3(grid8(tiles)),
                                dim3(C::NT), 0, stream, Pq, Ps, G, R, M, V, N, (int)m, (int)n, (int)ld, (int)r, tr, tiles, coef);
             return check_launch();
@@ -123,9 +131,11 @@ int launch_project_adam_many(const PlanHeader* plan_host, const PlanHeader* plan
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
         const uint32_t tiles = plan_host->proj_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
+        bool lines = true;
+        for (int i = first; i < first + cnt; ++i) lines = lines && whole_lines(plan_matrices(plan_host)[i].ld);
         const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
             using C = decltype(c);
-            return with_mode(cls, [&](auto mode) {
+            return with_adam_mode(cls, lines, [&](auto mode) {
                 hipLaunchKernelGGL(QG_PROJ(k_project_adam_many, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream,
                                    plan_dev, first, cnt, tiles, write_R, coef);
                 return check_launch();

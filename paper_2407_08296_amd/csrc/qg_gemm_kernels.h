@@ -24,8 +24,12 @@ namespace qg {
 constexpr int kPadK = 32;  // bf16 of padding per row of a K-major tile (64 B: rows k..k+3 hit distinct bank groups)
 // Cache policy of the R stores: non-temporal.  R is written once and read by a later kernel; kept out of the L2 it
 // leaves the operand panels there for the tiles that share them (+13 % on one large matrix alone, neutral inside
-// the full 7B step).
+// the full 7B step).  So are the accesses to M, V and N - but only where rows of fp32 start at whole 128-byte lines: a line that
+// two tiles share would go to memory in two parts, and come from there twice (us, non-temporal / not: projection with Adam, 24
+// matrices of 2048 rows, r = 512: n = 5464 798 / 600, 48 of 1024 x 2736, r = 256: 268 / 248, 24 of 2048 x 1000: 92 / 60; whole
+// lines: n = 5472 481 / 498, 5504 478 / 487; R alone, 48 of 1024 x 2736, 114 / 122).
 constexpr int kAuxStream = 2;
+inline bool whole_lines(int64_t ld) { return (ld & 31) == 0; }
 constexpr int kMfmaPrio = 1;   // wave priority during the MFMA phase of a K step (0 outside)
 constexpr int kPadX = 8;   // bf16 of padding per row of a K-contiguous tile (16 B)
 
@@ -64,7 +68,8 @@ typedef u32x4 __attribute__((aligned(4))) u32x4_align4;
 //               only reach output elements the masked epilogue never stores).
 //   kUnaligned: rows start at arbitrary element offsets (n not a multiple of 8): operands go through registers with
 //               per-chunk checks.
-enum : int { kExact = 0, kMasked = 1, kUnaligned = 2 };
+//   kMaskedShared: kMasked where rows share cache lines (the projection with Adam only, see kAuxStream).
+enum : int { kExact = 0, kMasked = 1, kUnaligned = 2, kMaskedShared = 3 };
 
 // Number of bytes a bounded buffer resource may cover: `bytes` (not negative, a multiple of 4, below 2^34) clamped
 // to what the 32-bit field holds; per-lane offsets stay far below that clamp.  Written with a shift and a 32-bit
@@ -255,15 +260,16 @@ static_assert(element_offset_exact(1 << 24) && element_offset_exact(138547332) &
 // `off`: that run's offset from base, in bytes of the fp32 array (DIRECT) or in elements (otherwise: ld may exceed 2^24).
 // DIRECT: through buffer resources, whose end is the row mask.  Otherwise rows start at arbitrary elements and every
 // access is checked.  A run that straddles the end of its row is written element by element (what lies past the end of
-// a row may be padding that is not ours to write); it is read whole only where the row pitch covers it.
-template <bool DIRECT, bool RAGGED>
+// a row may be padding that is not ours to write); it is read whole only where the row pitch covers it.  AUX: cache
+// policy (see kAuxStream).
+template <bool DIRECT, bool RAGGED, int AUX>
 struct EpilogueAccess {
     int ld;
     bool straddles;   // the number of columns is not a multiple of 4
     __device__ __forceinline__ f32x4 load(const float* base, int bytes, int rows, uint32_t off, int left, int i) const {
         if constexpr (DIRECT) {
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
-            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 32u * (uint32_t)(i * ld), kAuxStream));
+            return __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 32u * (uint32_t)(i * ld), AUX));
         } else {
             f32x4 x = {0.f, 0.f, 0.f, 0.f};
             if (8 * i >= rows || left <= 0) return x;
@@ -280,7 +286,7 @@ struct EpilogueAccess {
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, bytes);
             const uint32_t so = 32u * (uint32_t)(i * ld);
             const bool whole = !RAGGED || left >= 4;
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, whole ? off : 0x80000000u, so, kAuxStream);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, x), rs, whole ? off : 0x80000000u, so, AUX);
             if (RAGGED && straddles) {   // wave-uniform
                 if (left > 0 && left < 4) {
 #pragma unroll
@@ -309,7 +315,7 @@ struct EpilogueAccess {
             const __amdgpu_buffer_rsrc_t rs = make_rsrc(base, RAGGED ? bytes / 2 : 0x7FFFFFFF);
             const uint32_t so = 16u * (uint32_t)(i * ld);
             const bool whole = !RAGGED || left >= 4;
-            __builtin_amdgcn_raw_buffer_store_b64(x, rs, whole ? off >> 1 : 0x80000000u, so, kAuxStream);
+            __builtin_amdgcn_raw_buffer_store_b64(x, rs, whole ? off >> 1 : 0x80000000u, so, AUX);
             if (RAGGED && straddles) {   // wave-uniform
                 if (left > 0 && left < 4) {
 #pragma unroll
@@ -486,7 +492,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     // back as runs of four columns: lane l holds columns 4 (l % 8)..+3 of rows l / 8 + 8 i, i < 4, and a wave's access
     // covers eight whole 128-byte row segments.
     const int trow = lane >> 3, tcol = 4 * (lane & 7);
-    EpilogueAccess<DIRECT, RAGGED> ea;
+    EpilogueAccess<DIRECT, RAGGED, MODE == kMaskedShared ? 0 : kAuxStream> ea;
     ea.ld = ld;
     ea.straddles = (n & 3) != 0;
     uint32_t off[NB];    // offset of the lane's first run in each 32-column block (see EpilogueAccess); no resource covers
