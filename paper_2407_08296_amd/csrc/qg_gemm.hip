@@ -97,7 +97,12 @@ static auto with_adam_mode(int mode, bool lines, F f) {
 }
 constexpr int wg_index(int mode) { return mode == kMaskedShared ? kMasked : mode; }
 
-#define QG_PROJ(KERNEL, C, M, ...) (KERNEL<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, M, C::kWg[wg_index(M)]>)
+
+// Tiles in flight: two in the unaligned kernels.  Their operands pass through registers, and those of four tiles spilled (with
+// the checks that kept the compiler from it, and from one K step to the next a load at a time at the edge, 2048 x 5461, r =
+// 512, with Adam took 139 us instead of 50, the back-projection 76 instead of 46; 24 of them 812 / 688 and 808 / 676).
+constexpr int stages(int mode, int ns) { return mode == kUnaligned ? 2 : ns; }
+#define QG_PROJ(KERNEL, C, M, ...) (KERNEL<C::BM, C::BN, C::BK, C::WGM, C::WGN, stages(M, C::NS), M, C::kWg[wg_index(M)]>)
 // ld: row pitch in elements of G, R, M, V, N (n for dense rows).
 int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, float* R, float* M, float* V,
                         uint16_t* N, int64_t m, int64_t n, int64_t ld, int64_t r, int64_t step, const qg_hparams* hp,
@@ -107,9 +112,10 @@ int launch_project_adam(const uint8_t* Pq, const float* Ps, const uint16_t* G, f
         using C = decltype(c);
         return with_adam_mode(edge_mode(r, C::BM, n, ld, C::BN, m, C::BK, r), whole_lines(ld), [&](auto mode) {
             const uint32_t tr = (uint32_t)((r + C::BM - 1) / C::BM), tiles = tr * (uint32_t)((n + C::BN - 1) / C::BN);
-            constexpr int WG = C::NS == 2 ? 2 : C::kWg[wg_index(mode())];   // (for three the 128 x 256 instance of this kernel spills)
-            hipLaunchKernelGGL((k_project_adam<C::BM, C::BN, C::BK, C::WGM, C::WGN, C::NS, mode(), WG>), dim3(grid8(tiles)),
-                               dim3(C::NT), 0, stream, Pq, Ps, G, R, M, V, N, (int)m, (int)n, (int)ld, (int)r, tr, tiles, coef);
+            constexpr int WG = C::NS == 2 ? 2 : C::kWg[wg_index(mode())];   // (for three the 128 x 256 instance spills)
+            hipLaunchKernelGGL((k_project_adam<C::BM, C::BN, C::BK, C::WGM, C::WGN, stages(mode(), C::NS), mode(), WG>),
+                               dim3(grid8(tiles)), dim3(C::NT), 0, stream, Pq, Ps, G, R, M, V, N, (int)m, (int)n, (int)ld, (int)r,
+                               tr, tiles, coef);
             return check_launch();
         });
     });
@@ -136,8 +142,10 @@ int launch_project_adam_many(const PlanHeader* plan_host, const PlanHeader* plan
         const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
             using C = decltype(c);
             return with_adam_mode(cls, lines, [&](auto mode) {
-                hipLaunchKernelGGL(QG_PROJ(k_project_adam_many, C, mode()), dim3(grid8(tiles)), dim3(C::NT), 0, stream,
-                                   plan_dev, first, cnt, tiles, write_R, coef);
+                // (unaligned 128 x 128 tiles: four workgroups per CU, 24 of 2048 x 5461, r = 512, 713 -> 688 us)
+                constexpr int WG = mode() == kUnaligned && C::BM == 128 && C::BN == 128 ? 4 : C::kWg[wg_index(mode())];
+                hipLaunchKernelGGL((k_project_adam_many<C::BM, C::BN, C::BK, C::WGM, C::WGN, stages(mode(), C::NS), mode(), WG>),
+                                   dim3(grid8(tiles)), dim3(C::NT), 0, stream, plan_dev, first, cnt, tiles, write_R, coef);
                 return check_launch();
             });
         });
@@ -188,15 +196,15 @@ int launch_backproject(const uint8_t* Pq, const float* Ps, const uint16_t* N, in
             const uint32_t tm = (uint32_t)((m + C::BM - 1) / C::BM), tiles = tm * (uint32_t)((n + kGroup - 1) / kGroup);
             const dim3 grid(grid8(tiles)), block(C::NT);
             if (Wz != nullptr)   // zero-point weights (no U dump)
-                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::kWg[MODE], true>),
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, stages(MODE, C::NS), MODE, false, C::kWg[MODE], true>),
                                    grid, block, 0, stream, Pq, Ps, N, Wq, Ws, Wz, nullptr, (int)m, (int)n, (int)ld, (int)r,
                                    alpha, lr, key, tm, tiles);
             else if (Udbg != nullptr)
-                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, true, C::kWg[MODE]>), grid,
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, stages(MODE, C::NS), MODE, true, C::kWg[MODE]>), grid,
                                    block, 0, stream, Pq, Ps, N, Wq, Ws, nullptr, Udbg, (int)m, (int)n, (int)ld, (int)r, alpha,
                                    lr, key, tm, tiles);
             else
-                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, false, C::kWg[MODE]>), grid,
+                hipLaunchKernelGGL((k_backproject<C::BM, C::BK, C::WGn, C::WGm, stages(MODE, C::NS), MODE, false, C::kWg[MODE]>), grid,
                                    block, 0, stream, Pq, Ps, N, Wq, Ws, nullptr, nullptr, (int)m, (int)n, (int)ld, (int)r,
                                    alpha, lr, key, tm, tiles);
             return check_launch();
@@ -234,10 +242,10 @@ int launch_backproject_many(const PlanHeader* plan_host, const PlanHeader* plan_
                 constexpr int MODE = mode();
                 const dim3 grid(grid8(tiles)), block(C::NT);
                 if (plan_host->zero_points)
-                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::kWg[MODE], true>),
+                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, stages(MODE, C::NS), MODE, C::kWg[MODE], true>),
                                        grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
                 else
-                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, C::NS, MODE, C::kWg[MODE]>),
+                    hipLaunchKernelGGL((k_backproject_many<C::BM, C::BK, C::WGn, C::WGm, stages(MODE, C::NS), MODE, C::kWg[MODE]>),
                                        grid, block, 0, stream, plan_dev, first, cnt, tiles, alpha, lr, seed, (uint64_t)step);
                 return check_launch();
             });

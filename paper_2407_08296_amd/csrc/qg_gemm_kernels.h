@@ -16,6 +16,8 @@
 // row k+j, so lane i ends up with column i of rows k..k+3.
 #pragma once
 
+#include <type_traits>
+
 #include "qg_common.h"
 #include "qg_plan.h"
 
@@ -66,8 +68,7 @@ typedef u32x4 __attribute__((aligned(4))) u32x4_align4;
 //               direct-to-LDS loads as kExact, bounded by the end of the matrix: what lies past the end reads as
 //               zero, which is all the K tail needs; columns past a row's end read the next row (finite values that
 //               only reach output elements the masked epilogue never stores).
-//   kUnaligned: rows start at arbitrary element offsets (n not a multiple of 8): operands go through registers with
-//               per-chunk checks.
+//   kUnaligned: rows start at arbitrary element offsets (n not a multiple of 8): operands go through registers.
 //   kMaskedShared: kMasked where rows share cache lines (the projection with Adam only, see kAuxStream).
 enum : int { kExact = 0, kMasked = 1, kUnaligned = 2, kMaskedShared = 3 };
 
@@ -150,6 +151,46 @@ __device__ __forceinline__ u32x4 load8_bf16_guarded(const uint16_t* src, int val
         if (j < valid) w[j >> 1] |= (uint32_t)src[j] << (16 * (j & 1));
     const u32x4 o = {w[0], w[1], w[2], w[3]};
     return o;
+}
+
+// The 128 bits of v shifted right by `bits` < 128.
+__device__ __forceinline__ u32x4 shift_right_128(u32x4 v, int bits) {
+    const uint64_t lo = (uint64_t)v[1] << 32 | v[0], hi = (uint64_t)v[3] << 32 | v[2];
+    const int b = bits & 63;
+    const uint64_t h = hi >> b, l = (lo >> b) | ((hi << 1) << (63 - b));
+    const uint64_t rl = bits < 64 ? l : h, rh = bits < 64 ? h : 0;
+    return u32x4{(uint32_t)rl, (uint32_t)(rl >> 32), (uint32_t)rh, (uint32_t)(rh >> 32)};
+}
+
+// The unaligned kernels load without checks: the K steps that lie inside the matrices run in a pipeline of their own (the last,
+// partial one after it, checked), and a tile at the edge of the columns loads the last whole chunk of a row and shifts it when
+// it is stored (EDGE).  Addresses are a scalar base and a 32-bit byte offset per chunk that is fixed for the whole loop (as
+// running 64-bit pointers they took the registers of four tiles in flight and spilled), which covers row pitches up to 2^24;
+// beyond it, and for less than a chunk of columns, every step is a checked one.
+__device__ __forceinline__ bool pipelined(int n, int ld) { return n >= 8 && ld <= (1 << 24); }
+
+// Chunk of eight columns from col on: first column loaded, and the shift in bits; columns at or past n give anything, for
+// results that are never stored.  n >= 8.
+__device__ __forceinline__ int edge_column(int col, int n, int& shift) {
+    const int c = min(col, n - 8);
+    shift = 16 * min(col - c, 7);
+    return c;
+}
+
+// Unchecked fetch of WPT words of INT4 codes from element e (a multiple of 8) on, a scale per word.
+template <int WPT>
+__device__ __forceinline__ void load_p_words(const uint8_t* Pq, const float* Ps, uint32_t e, uint32_t (&w)[WPT], float (&sc)[WPT]) {
+    static_assert(WPT <= 2, "one or two words");
+    const uint8_t* p = Pq + (e >> 1);   // (e < 2^31)
+    if constexpr (WPT == 2) {
+        const u32x2 v = *reinterpret_cast<const u32x2_align4*>(p);
+        w[0] = v[0]; w[1] = v[1];
+    } else {
+        w[0] = *reinterpret_cast<const uint32_t*>(p);
+    }
+#pragma unroll
+    for (int j = 0; j < WPT; ++j)
+        sc[j] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(Ps) + (((e + 8 * j) >> 8) << 2));
 }
 
 // Guarded fetch of WPT words of INT4 codes starting at flat element index e (a multiple of 8), of which the first
@@ -387,12 +428,20 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     // so code bytes and block scales split the same way.
     static_assert(BK % 32 == 0, "a K step must cover whole blocks of 256 codes");
     constexpr int B_OFFS = DIRECT ? BD::VARIANTS : B_PER;
-    uint32_t a_el[A_PER], b_off[B_OFFS];   // P: element offset; G: byte offset (kUnaligned: element offset, ld may
-                                           // exceed 2^24)
+    uint32_t a_el[A_PER], b_off[B_OFFS];   // P: element offset; G: byte offset from the tile's first element (kUnaligned:
+                                           // from the first row's)
+    bool a_next[DIRECT ? 1 : A_PER];       // kUnaligned, at the edge: the wanted word is the second one loaded
+    int b_shift[DIRECT ? 1 : B_PER];       // ... see edge_column
+    const bool edge = !DIRECT && (r0 + BM > r || n0 + BN > n);
 #pragma unroll
     for (int p = 0; p < A_PER; ++p) {
         const int ti = t + p * NT;
-        a_el[p] = (uint32_t)((ti / A_TPR) * r + r0 + (ti % A_TPR) * (8 * WPT));
+        int c = r0 + (ti % A_TPR) * (8 * WPT);
+        if constexpr (!DIRECT) {
+            a_next[p] = c > r - 8 * WPT;
+            c = min(c, r - 8 * WPT);       // (tiles of two words per fetch are for r > 64)
+        }
+        a_el[p] = (uint32_t)((ti / A_TPR) * r + c);
     }
 #pragma unroll
     for (int p = 0; p < B_OFFS; ++p) {
@@ -400,12 +449,14 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
             b_off[p] = BD::lane_src_bytes(lane, ld, p);
         } else {
             const int ci = t + p * NT;
-            b_off[p] = element_offset(ci / BD::CPR, ld, (ci % BD::CPR) * 8);
+            b_off[p] = 2u * element_offset(ci / BD::CPR, ld, edge_column(n0 + (ci % BD::CPR) * 8, max(n, 8), b_shift[p]));
         }
     }
 
     // Tile kt: P codes and scales into register set `stage`; G straight into LDS stage `stage` (kExact, kMasked) or into
-    // registers (kUnaligned, stored by sstore).  A tile past the end (kt >= KT) loads nothing: its resources are empty.
+    // registers (kUnaligned, stored by sstore).  A tile past the end (kt >= KT) loads nothing: its resources are empty (or,
+    // kUnaligned, the last tile again).
+    const int KT_WHOLE = pipelined(n, ld) ? m / BK : 0;   // kUnaligned: steps of the pipeline
     auto gload = [&](int kt, int stage) {
         const int i0 = kt * BK;
         const int64_t e0 = (int64_t)i0 * r;
@@ -436,21 +487,49 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
                     asc[stage][p][j] = __builtin_bit_cast(
                         float, __builtin_amdgcn_raw_buffer_load_b32(rs, ((a_el[p] + 8 * j) >> 8) << 2, 0, 0));
             }
-        } else {
+        }
+    };
+    auto gload_unaligned = [&](int kt, int stage) {
+        if constexpr (!DIRECT) {
+            const int i0 = min(kt, KT_WHOLE - 1) * BK;
+            const int64_t e0 = (int64_t)i0 * r;
+#pragma unroll
+            for (int p = 0; p < A_PER; ++p) load_p_words<WPT>(Pq + (e0 >> 1), Ps + (e0 >> 8), a_el[p], aw[stage][p], asc[stage][p]);
+#pragma unroll
+            for (int p = 0; p < B_PER; ++p)
+                bv[stage][p] =
+                    *reinterpret_cast<const u32x4_align2*>(reinterpret_cast<const char*>(G + (int64_t)i0 * ld) + b_off[p]);
+        }
+    };
+    auto gload_checked = [&](int kt) {   // into register set 0
+        if constexpr (!DIRECT) {
+            const int i0 = kt * BK;
+            const int64_t e0 = (int64_t)i0 * r;
 #pragma unroll
             for (int p = 0; p < A_PER; ++p) {
                 const int ti = t + p * NT;
-                const int row = ti / A_TPR, c = (ti % A_TPR) * (8 * WPT);
-                load_p_guarded<WPT>(pq, ps, a_el[p], i0 + row < m ? r - (r0 + c) : 0, aw[stage][p],
-                                    asc[stage][p]);
+                const int row = ti / A_TPR, c = r0 + (ti % A_TPR) * (8 * WPT);
+                load_p_guarded<WPT>(Pq + (e0 >> 1), Ps + (e0 >> 8), (uint32_t)(row * r + c), i0 + row < m ? r - c : 0, aw[0][p],
+                                    asc[0][p]);
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
                 const int ci = t + p * NT;
-                const int row = ci / BD::CPR, c8 = ci % BD::CPR;
-                const int valid = (i0 + row < m) ? (n - (n0 + c8 * 8)) : 0;
-                bv[stage][p] = load8_bf16_guarded(g + b_off[p], valid);
+                const int row = ci / BD::CPR, c = n0 + (ci % BD::CPR) * 8;
+                bv[0][p] = load8_bf16_guarded(G + (int64_t)i0 * ld + element_offset(row, ld, c), i0 + row < m ? n - c : 0);
             }
+        }
+    };
+    auto shift_edge = [&](int stage) {   // kUnaligned, tiles at the edge: see edge_column
+        if constexpr (!DIRECT) {
+#pragma unroll
+            for (int p = 0; p < A_PER; ++p)
+                if constexpr (WPT == 2) {
+                    aw[stage][p][0] = a_next[p] ? aw[stage][p][WPT - 1] : aw[stage][p][0];
+                    asc[stage][p][0] = a_next[p] ? asc[stage][p][AT::NSC - 1] : asc[stage][p][0];
+                }
+#pragma unroll
+            for (int p = 0; p < B_PER; ++p) bv[stage][p] = shift_right_128(bv[stage][p], b_shift[p]);
         }
     };
     // Dequantized P tile (and, in the kUnaligned kernels, the G tile) of register set `stage` into LDS.
@@ -558,38 +637,70 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
 
     // Unrolled by NS so that the LDS stage of every access is a compile-time constant (no per-step address
     // arithmetic).  Every load and store is unconditional; steps past the end load nothing and multiply nothing.
+    if constexpr (DIRECT) {
 #pragma unroll
-    for (int u = 0; u < NS - 1; ++u) gload(u, u);
-    sstore(0);
-    if constexpr (DIRECT) wait_loads<0>();   // all of them: their order is not fixed here
-    lds_barrier();
-    for (int kt = 0; kt < KT; kt += NS) {
+        for (int u = 0; u < NS - 1; ++u) gload(u, u);
+        sstore(0);
+        wait_loads<0>();   // all of them: their order is not fixed here
+        lds_barrier();
+        for (int kt = 0; kt < KT; kt += NS) {
 #pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            if constexpr (NS == 2) {
-                gload(kt + u + 1, u ^ 1);
-                if (u == 0 || kt + u < KT) mfma_step(u);
-                sstore(u ^ 1);
-            } else {
-                // one scheduling region: the fragment reads first, then the step's loads and the dequantization of the
-                // next P tile (its words were loaded NS - 2 steps ago) between the MFMAs
-                mfma_step(u);
-                gload(kt + u + NS - 1, (u + NS - 1) % NS);
-                sstore((u + 1) % NS);
-                __builtin_amdgcn_sched_group_barrier(0x100, BK / 16 * 2 * (MB + NB), 0);
+            for (int u = 0; u < NS; ++u) {
+                if constexpr (NS == 2) {
+                    gload(kt + u + 1, u ^ 1);
+                    if (u == 0 || kt + u < KT) mfma_step(u);
+                    sstore(u ^ 1);
+                } else {
+                    // one scheduling region: the fragment reads first, then the step's loads and the dequantization of the
+                    // next P tile (its words were loaded NS - 2 steps ago) between the MFMAs
+                    mfma_step(u);
+                    gload(kt + u + NS - 1, (u + NS - 1) % NS);
+                    sstore((u + 1) % NS);
+                    __builtin_amdgcn_sched_group_barrier(0x100, BK / 16 * 2 * (MB + NB), 0);
 #pragma unroll
-                for (int i = 0; i < BK / 16 * MB * NB; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                    for (int i = 0; i < BK / 16 * MB * NB; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                    }
+                }
+                landed();
+                lds_barrier();
+            }
+        }
+    } else {
+        static_assert(DIRECT || NS == 2, "two register sets");
+        auto pipeline = [&](auto at_edge) {
+            constexpr bool EDGE = decltype(at_edge)::value;
+            auto store = [&](int stage) {
+                if constexpr (EDGE) shift_edge(stage);
+                sstore(stage);
+            };
+            gload_unaligned(0, 0);
+            store(0);
+            lds_barrier();
+            for (int kt = 0; kt < KT_WHOLE; kt += 2) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    gload_unaligned(kt + u + 1, u ^ 1);
+                    mfma_step(u);
+                    store(u ^ 1);
+                    lds_barrier();
+                    if (u == 0 && kt + 1 >= KT_WHOLE) break;
                 }
             }
-            landed();
+        };
+        if (KT_WHOLE > 0) {
+            if (edge) pipeline(std::true_type());
+            else pipeline(std::false_type());
+        }
+        for (int kt = KT_WHOLE; kt < KT; ++kt) {
+            gload_checked(kt);
+            sstore(0);
             lds_barrier();
-            // (the kernels with direct loads run to a whole number of NS steps: 2048 x 2048, r = 512, with this exit 21.6 us,
-            // without 20.6; 8 x 10^6 columns, r = 8, unaligned, 58 against 82)
-            if (!DIRECT && u < NS - 1 && kt + u + 1 >= KT) break;
+            mfma_step(0);
+            lds_barrier();
         }
     }
     if (NS > 2) {   // the direct loads of steps past the end, of every wave, have written their zeros
@@ -873,20 +984,24 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     // so the index of a code's block scale takes one add and two shifts per step.
     constexpr int A_OFFS = DIRECT ? AD::VARIANTS : A_PER;
     uint32_t a_off[A_OFFS], b_el[B_PER];   // N: byte or element offset, as G's in the projection; P: element offset inside
-                                           // the tile's rows
+                                           // the tile's rows (kUnaligned: rows past the last one are the last one again)
+    int a_shift[DIRECT ? 1 : A_PER];       // kUnaligned, at the edge: see edge_column
+    const bool edge = !DIRECT && n0 + BNn > n;
+    const int KT_WHOLE = pipelined(n, ld) ? r / BK : 0;   // kUnaligned: steps of the pipeline, as in the projection
 #pragma unroll
     for (int p = 0; p < A_OFFS; ++p) {
         if constexpr (DIRECT) {
             a_off[p] = AD::lane_src_bytes(lane, ld, p);
         } else {
             const int ci = t + p * NT;
-            a_off[p] = element_offset(ci / AD::CPR, ld, (ci % AD::CPR) * 8);
+            a_off[p] = 2u * element_offset(ci / AD::CPR, ld, edge_column(n0 + (ci % AD::CPR) * 8, max(n, 8), a_shift[p]));
         }
     }
 #pragma unroll
     for (int p = 0; p < B_PER; ++p) {
         const int ti = t + p * NT;
-        b_el[p] = (uint32_t)((ti / B_TPR) * r + (ti % B_TPR) * (8 * WPT));
+        const int row = DIRECT ? ti / B_TPR : min(ti / B_TPR, m - 1 - m0);
+        b_el[p] = (uint32_t)(row * r + (ti % B_TPR) * (8 * WPT));
     }
     const int64_t e_tile = (int64_t)m0 * r;
 
@@ -921,21 +1036,42 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                     bsc[stage][p][j] = __builtin_bit_cast(
                         float, __builtin_amdgcn_raw_buffer_load_b32(rs, ((b_el[p] + (uint32_t)(k0 + 8 * j)) >> 8) << 2, 0, 0));
             }
-        } else {
+        }
+    };
+    auto gload_unaligned = [&](int kt, int stage) {
+        if constexpr (!DIRECT) {
+            const int k0 = min(kt, KT_WHOLE - 1) * BK;
+#pragma unroll
+            for (int p = 0; p < A_PER; ++p)
+                av[stage][p] =
+                    *reinterpret_cast<const u32x4_align2*>(reinterpret_cast<const char*>(N + (int64_t)k0 * ld) + a_off[p]);
+#pragma unroll
+            for (int p = 0; p < B_PER; ++p)
+                load_p_words<WPT>(Pq + (e_tile >> 1), Ps + (e_tile >> 8), b_el[p] + (uint32_t)k0, bw[stage][p], bsc[stage][p]);
+        }
+    };
+    auto gload_checked = [&](int kt) {   // into register set 0
+        if constexpr (!DIRECT) {
+            const int k0 = kt * BK;
 #pragma unroll
             for (int p = 0; p < A_PER; ++p) {
                 const int ci = t + p * NT;
-                const int row = ci / AD::CPR, c8 = ci % AD::CPR;
-                const int valid = (k0 + row < r) ? (n - (n0 + c8 * 8)) : 0;
-                av[stage][p] = load8_bf16_guarded(nb + a_off[p], valid);
+                const int row = ci / AD::CPR, c = n0 + (ci % AD::CPR) * 8;
+                av[0][p] = load8_bf16_guarded(N + (int64_t)k0 * ld + element_offset(row, ld, c), k0 + row < r ? n - c : 0);
             }
 #pragma unroll
             for (int p = 0; p < B_PER; ++p) {
                 const int ti = t + p * NT;
-                const int row = ti / B_TPR, c = (ti % B_TPR) * (8 * WPT);
-                load_p_guarded<WPT>(Pq + (e_tile >> 1), ps, b_el[p] + (uint32_t)k0, m0 + row < m ? r - (k0 + c) : 0,
-                                    bw[stage][p], bsc[stage][p]);
+                const int row = ti / B_TPR, c = k0 + (ti % B_TPR) * (8 * WPT);
+                load_p_guarded<WPT>(Pq + (e_tile >> 1), Ps + (e_tile >> 8), (uint32_t)(row * r + c), m0 + row < m ? r - c : 0,
+                                    bw[0][p], bsc[0][p]);
             }
+        }
+    };
+    auto shift_edge = [&](int stage) {   // kUnaligned, tiles at the edge: see edge_column
+        if constexpr (!DIRECT) {
+#pragma unroll
+            for (int p = 0; p < A_PER; ++p) av[stage][p] = shift_right_128(av[stage][p], a_shift[p]);
         }
     };
     auto sstore = [&](int stage) {
@@ -997,32 +1133,67 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     };
 
     // unrolled by NS (constant LDS stages), see the projection
+    if constexpr (DIRECT) {
 #pragma unroll
-    for (int u = 0; u < NS - 1; ++u) gload(u, u);
-    sstore(0);
-    if constexpr (DIRECT) wait_loads<0>();   // all of them: their order is not fixed here
-    lds_barrier();
-    for (int kt = 0; kt < KT; kt += NS) {
+        for (int u = 0; u < NS - 1; ++u) gload(u, u);
+        sstore(0);
+        wait_loads<0>();   // all of them: their order is not fixed here
+        lds_barrier();
+        for (int kt = 0; kt < KT; kt += NS) {
 #pragma unroll
-        for (int u = 0; u < NS; ++u) {
-            if constexpr (NS == 2) {
-                gload(kt + u + 1, u ^ 1);
-                if (u == 0 || kt + u < KT) mfma_step(u);
-                sstore(u ^ 1);
-            } else {
-                mfma_step(u);
-                gload(kt + u + NS - 1, (u + NS - 1) % NS);
-                sstore((u + 1) % NS);
-                __builtin_amdgcn_sched_group_barrier(0x100, BK / 16 * (2 * IB + JB), 0);
+            for (int u = 0; u < NS; ++u) {
+                if constexpr (NS == 2) {
+                    gload(kt + u + 1, u ^ 1);
+                    if (u == 0 || kt + u < KT) mfma_step(u);
+                    sstore(u ^ 1);
+                } else {
+                    mfma_step(u);
+                    gload(kt + u + NS - 1, (u + NS - 1) % NS);
+                    sstore((u + 1) % NS);
+                    __builtin_amdgcn_sched_group_barrier(0x100, BK / 16 * (2 * IB + JB), 0);
 #pragma unroll
-                for (int i = 0; i < BK / 16 * IB * JB; ++i) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
-                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                    for (int i = 0; i < BK / 16 * IB * JB; ++i) {
+                        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                        __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+                    }
+                }
+                landed();
+                lds_barrier();
+            }
+        }
+    } else {
+        static_assert(DIRECT || NS == 2, "two register sets");
+        auto pipeline = [&](auto at_edge) {
+            constexpr bool EDGE = decltype(at_edge)::value;
+            auto store = [&](int stage) {
+                if constexpr (EDGE) shift_edge(stage);
+                sstore(stage);
+            };
+            gload_unaligned(0, 0);
+            store(0);
+            lds_barrier();
+            for (int kt = 0; kt < KT_WHOLE; kt += 2) {
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    gload_unaligned(kt + u + 1, u ^ 1);
+                    mfma_step(u);
+                    store(u ^ 1);
+                    lds_barrier();
+                    if (u == 0 && kt + 1 >= KT_WHOLE) break;
                 }
             }
-            landed();
+        };
+        if (KT_WHOLE > 0) {
+            if (edge) pipeline(std::true_type());
+            else pipeline(std::false_type());
+        }
+        for (int kt = KT_WHOLE; kt < KT; ++kt) {
+            gload_checked(kt);
+            sstore(0);
+            lds_barrier();
+            mfma_step(0);
             lds_barrier();
         }
     }

@@ -72,15 +72,6 @@ struct LinBatch {
 // that are never stored); the same, but the chunk that straddles the end is the last whole one shifted; nothing.
 enum : int { kFetchAligned = 0, kFetchClamped = 1, kFetchShifted = 2, kFetchGuarded = 3 };
 
-// The 128 bits of v shifted right by `bits` < 128.
-__device__ __forceinline__ u32x4 shift_right_128(u32x4 v, int bits) {
-    const uint64_t lo = (uint64_t)v[1] << 32 | v[0], hi = (uint64_t)v[3] << 32 | v[2];
-    const int b = bits & 63;
-    const uint64_t h = hi >> b, l = (lo >> b) | ((hi << 1) << (63 - b));
-    const uint64_t rl = bits < 64 ? l : h, rh = bits < 64 ? h : 0;
-    return u32x4{(uint32_t)rl, (uint32_t)(rl >> 32), (uint32_t)rh, (uint32_t)(rh >> 32)};
-}
-
 // Staging of one operand tile: global -> registers (fetch) -> LDS (commit; INT8 is dequantized here).
 template <int LAYOUT, int XT, int BK, int NT = 256>
 struct LinStage {
@@ -113,19 +104,20 @@ struct LinStage {
             const int past = FETCH == kFetchShifted && !kFast ? min(max(x - (X - CH), 0), CH - 1) : 0;
             if constexpr (FETCH == kFetchClamped || FETCH == kFetchShifted) x = min(x, kFast ? X - 1 : X - CH);
             const KI k = k0 + (kFast ? tc : tr);
-            const int64_t row = kFast ? x : k, col = kFast ? k : x;
+            const auto row = kFast ? x : k;
+            const auto col = kFast ? k : x;
             int valid = CH;
             if constexpr (FETCH == kFetchGuarded) {
                 valid = kFast ? (x < X ? K - (int)k : 0) : ((int)k < K ? X - x : 0);
             }
-            const int64_t off = row * op.ld + col;
+            const int64_t off = (int64_t)row * op.ld + col;
             if constexpr (kInt8) {
                 const int8_t* src = static_cast<const int8_t*>(op.base) + off;
                 if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);
                 else v[q] = load16_i8_guarded(src, valid);
-                const int64_t block = (!kFast && FETCH == kFetchShifted ? xs : col) >> 8;
-                s[q] = valid > 0 ? op.scales[row * op.sgroups + block] : 0.f;
-                if constexpr (kZero) z[q] = valid > 0 ? op.zeros[row * op.sgroups + block] : 0.f;
+                const auto block = (!kFast && FETCH == kFetchShifted ? xs : col) >> 8;
+                s[q] = valid > 0 ? op.scales[(int64_t)row * op.sgroups + block] : 0.f;
+                if constexpr (kZero) z[q] = valid > 0 ? op.zeros[(int64_t)row * op.sgroups + block] : 0.f;
             } else {
                 const uint16_t* src = static_cast<const uint16_t*>(op.base) + off;
                 if constexpr (FETCH == kFetchAligned) v[q] = *reinterpret_cast<const u32x4*>(src);

@@ -96,3 +96,33 @@ def test_random_shapes_grouped_and_single(sweep):
             check(s, o, t, f"grouped, matrix {i} {shapes[i]}")
             o1 = o if i == 0 else Q.step(d["Wq"], d["Ws"], d["Gb"], d["Pq"], d["Ps"], w[0], w[1], t, HP, seed=seed, r=s.r)
             check(one, o1, t, f"single, matrix {i} {shapes[i]}")
+
+
+@pytest.mark.parametrize("m,n,r", [
+    (96, 129, 72), (97, 127, 64), (100, 261, 24), (64, 255, 8), (33, 134, 16), (130, 257, 72),   # around the column tiles
+    (31, 300, 16), (200, 5, 40), (64, 9, 64), (65, 12, 56),           # no whole K step, less than a chunk of columns, one chunk
+    (137, 264, 136), (208, 512, 200),                                 # aligned rows, r a multiple of 8 only: P's edge alone
+    (400, 21765, 136),                                                # 128-row tiles of both products
+    (130, 200, 64), (257, 1000, 96),                                  # aligned rows that share cache lines
+])
+def test_edges_of_unaligned_tiles(m, n, r):
+    t, seed = 3, 77
+    Wq, Ws = Q.quant_int8(I.weight_f32(m, n))
+    Pq, Ps = Q.quant_int4(I.projection_f32(m, r))
+    Gb = I.gradient_bf16(m, n, t)
+    rs = np.random.default_rng([m, n, r])
+    M = (rs.standard_normal((r, n)) * 5e-5).astype(np.float32)
+    V = ((rs.standard_normal((r, n)) * 5e-5) ** 2 + 1e-12).astype(np.float32)
+    o = Q.step(Wq, Ws, Gb, Pq, Ps, M, V, t, HP, seed=seed, r=r)
+
+    def state():
+        return qg.MatrixState(m, n, r, dev(Pq), dev(Ps), dev(Gb), dev(Wq), dev(Ws), dev(M), dev(V),
+                              torch.empty((r, n), dtype=torch.float32, device=DEV),
+                              torch.empty((r, n), dtype=torch.bfloat16, device=DEV))
+    s = state()
+    qg.step_many(qg.StepPlan([s]), qg.hparams(), seed, t)
+    qg.project(s.Pq, s.Ps, s.G, m, n, r, s.R)
+    check(s, o, t, "grouped")
+    s = state()
+    qg.step(s.Pq, s.Ps, s.G, s.Wq, s.Ws, s.M, s.V, s.R, s.N, m, n, r, qg.hparams(), seed, t)
+    check(s, o, t, "single")
