@@ -95,6 +95,38 @@ def test_orthonormalize_around_the_block_sizes(r):
     assert np.abs(got.T @ got - np.eye(r)).max() <= 1e-6
 
 
+@pytest.mark.parametrize("m,r", [(2048, 512), (1824, 544), (5952, 320)])
+@pytest.mark.parametrize("kind", ["random", "graded", "decaying", "spiky"])
+def test_orthonormalize_of_large_matrices(m, r, kind):
+    """Shapes whose products run on INT8 digits (m r^2 >= 2^29; 32 but not 64 or 128 dividing r): within fp32 rounding (2^-25 of
+    an element, 3e-8 relative) of the Gram-Schmidt factor in 64 bits, as the fp64 products of smaller ones."""
+    g = np.random.default_rng([m, r])
+    Y = g.standard_normal((m, r))
+    if kind == "graded":
+        Y *= np.logspace(3, -3, r)[None, :]
+    if kind == "decaying":
+        U, _ = np.linalg.qr(Y)
+        V, _ = np.linalg.qr(g.standard_normal((r, r)))
+        Y = (U * np.logspace(0, -6, r)[None, :]) @ V
+    if kind == "spiky":
+        Y[::97] *= 1000.0
+    Y = Y.astype(np.float32)
+    want = Q.orthonormalize(Y)
+    Qd, info = qg.orthonormalize(dev(Y))
+    got = host(Qd).astype(np.float64)
+    assert int(host(info)[0]) == 0
+    assert rel_fro(got, want) <= 6e-8
+    assert np.abs(got.T @ got - np.eye(r)).max() <= 1e-7
+
+
+def test_a_nan_column_of_a_large_matrix_is_reported():
+    Y = np.random.default_rng(1).standard_normal((2048, 512)).astype(np.float32)
+    Y[100, 300] = np.nan
+    Qd, info = qg.orthonormalize(dev(Y))
+    assert int(host(info)[0]) == 301
+    assert not np.isfinite(host(Qd)[:, 300]).any()
+
+
 @pytest.mark.parametrize("r,column", [(72, 20), (72, 70), (136, 0), (136, 79)])
 def test_orthonormalize_reports_a_column_with_a_nan(r, column):
     """The first pivot that is not a number is the column's own, whatever 16- or 64-wide block it lies in."""
