@@ -809,8 +809,8 @@ __global__ __launch_bounds__(256) void k_digits_x(const double* __restrict__ X, 
 // Product of two digit matrices, k fragments [kb0, kb1): a wave 32 x 64 results, a workgroup 64 x 128.  The fragments of a step
 // go straight into LDS, one wave-wide load each, NS steps in flight and two workgroups on a CU: read from memory by every wave
 // that needs them, with one wave per SIMD, the Gram matrices of sixteen 4096 x 1024 took 888 us, so 451 (fp64: 1760).  f(row,
-// column, value in units of both scales) for i < 32 xa, j < 32 xb.  KB: k fragments per x fragment; BP: planes of B, the fifth one a place
-// below the others; wave_kb1: where the wave's own columns end.
+// column, value in units of both scales) for i < 32 xa, j < 32 xb.  KB: k fragments per x fragment; BP: planes of B, the fifth
+// one a place below the others; wave_kb1: where the wave's own columns end.
 template <int BP, typename F>
 __device__ __forceinline__ void digit_product(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, int KB, int kb0,
                                               int kb1, int wave_kb1, int ti, int tj, int xa, int xb, uint8_t* smem, F f) {
@@ -904,8 +904,8 @@ __global__ __launch_bounds__(256, 2) void k_digit_gram(const uint8_t* __restrict
 
 // Q = Y X^T from the digits of Y (x = row) and of X 2^e.
 __global__ __launch_bounds__(256, 2) void k_digit_apply(const uint8_t* __restrict__ yp, int64_t yp_stride,
-                                                     const uint8_t* __restrict__ xp, const int32_t* __restrict__ rowexp, float* __restrict__ Q, int m, int r,
-                                                     BatchStride st) {
+                                                     const uint8_t* __restrict__ xp, const int32_t* __restrict__ rowexp,
+                                                     float* __restrict__ Q, int m, int r, BatchStride st) {
     yp += blockIdx.z * yp_stride;
     xp += blockIdx.z * (st.part * 8);
     rowexp += blockIdx.z * st.expo;
