@@ -38,7 +38,6 @@ constexpr int kKC = 16;               // K extent staged in LDS per barrier pair
                                       // per SIMD; 32 gave three workgroups and 9 % more time, 8 no further gain)
 constexpr int kPitchKF = kKC + 1;     // LDS pitch of a [64][k] chunk (k fastest): odd, so that the 16 rows a fragment
                                       // read touches at one k fall on 16 different bank pairs (36 gave 4-way conflicts)
-constexpr int kPitchKS = kNB + 16;    // LDS pitch of a [k][64] chunk (k slowest)
 
 // ROWS x COLS block at (row0, col0) of a row-major matrix (fp32 or fp64) -> registers -> LDS doubles.  Elements
 // outside [0, rows) x [0, cols) read as zero.  col0 and cols are even, so an element pair never straddles the edge.
@@ -120,7 +119,7 @@ __device__ __forceinline__ void for_each_acc(const f64x4 (&acc)[W][W], int lane,
 // out matrices of a round share the stride Y/Q (both are m x r fp32 arrays of the same batch layout).
 struct BatchStride {
     int64_t Y, Q, S, X, D, part, shift;
-    int64_t expo;     // exponents of Y's columns and of X's rows (32-bit words)
+    int64_t expo;     // exponents of Y's columns, of X's and of T's rows (32-bit words)
     int64_t planes;   // digits of Y (bytes)
 };
 
@@ -658,10 +657,12 @@ __global__ __launch_bounds__(256) void k_apply(const float* __restrict__ Y, cons
 // the products of their digits, each summed over k in int32 without rounding (v_mfma_i32_32x32x32_i8, about fifty times the
 // rate of the fp64 instruction) and added up in fp64 by weight.  Of the 16 digit products the one of the two lowest digits is
 // left out (2^-54 of the largest).  What is rounded is Y, to 2^-31 of its column's largest magnitude: the first Gram matrix is
-// that of a matrix within 2^-31 of Y (its shift, 2^-46 of the trace, is 2^-23 of a singular value), and the second round works
-// on T rounded so, which is finer than fp32: T's digits come from the fp64 product, through what its fp32 lost.  (The first round's
-// Q = Y X^T stays in fp64: X is large there and its terms cancel.)  Q against 64 bits, relative: 2.54e-8 where fp64 with T in fp32
-// gave 2.69e-8 (random 4096 x 1024) to 3.5e-8 (cond 1e7), 2.9e-8 where it gave 2.3e-7 (cond 1e9).
+// that of a matrix within 2^-31 of Y (its shift, 2^-46 of the trace, is 2^-23 of a singular value).  The second round works on T
+// rounded to 2^-31 of its ROW's largest magnitude (in units of a column, rows far below the others would lose their digits, and
+// Q's rows are quantized each by itself), which is finer than fp32: T's digits come from the fp64 product, through what its
+// fp32 lost.  (The first round's Q = Y X^T stays in fp64: X is large there and its terms cancel.)  Q against 64 bits, relative: 2.54e-8 where fp64 with T in fp32
+// gave 2.69e-8 (random 4096 x 1024) to 3.7e-8 (cond 1e7), 6.3e-8 where it gave 4.4e-7 (cond 1e9); of the worst row 2.8e-8 and
+// 2.9e-8, also where every 97th row is 1e-10 of the others.
 //
 // A plane is stored in 1 KB fragments of 32 x indices by 32 k indices, as a wave's lanes hold an MFMA operand (lane l: x = l %
 // 32, k = 16 (l / 32) ..+15), the four planes of a fragment one after another: an operand is one contiguous 16-byte load per
@@ -700,55 +701,107 @@ __device__ __forceinline__ int exponent_above(uint32_t bits) {
     return bits >= 0x7F800000u ? kNotFinite : max((int)(bits >> 23), 1) - 126;
 }
 
-// Digits of Y (+ low, see k_apply), x = column, k = row (m and r multiples of 32).
-__global__ __launch_bounds__(256) void k_digits(const float* __restrict__ Y, const float* __restrict__ low,
-                                                const uint32_t* __restrict__ maxbits, uint8_t* __restrict__ planes, int m, int r,
-                                                BatchStride st) {
+// The digits of a 32 x 32 tile of integers, x = column, k = row (or x = row, k = column) into one fragment.
+template <bool XROW>
+__device__ __forceinline__ void store_digits(const int (&tile)[32][33], uint8_t* __restrict__ frag) {
+    const int plane = threadIdx.x >> 6, lane = threadIdx.x & 63, x = lane & 31, k = 16 * (lane >> 5);
+    uint32_t w[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+    for (int j = 0; j < 16; ++j) w[j >> 2] |= digit_of(XROW ? tile[x][k + j] : tile[k + j][x], plane) << (8 * (j & 3));
+    *reinterpret_cast<u32x4*>(frag + plane * 1024 + lane * 16) = u32x4{w[0], w[1], w[2], w[3]};
+}
+
+// Digits of Y, x = column, k = row (m and r multiples of 32).
+__global__ __launch_bounds__(256) void k_digits(const float* __restrict__ Y, const uint32_t* __restrict__ maxbits,
+                                                uint8_t* __restrict__ planes, int m, int r, BatchStride st) {
     Y += blockIdx.z * st.Y;
     maxbits += blockIdx.z * st.expo;
     planes += blockIdx.z * st.planes;
     __shared__ int tile[32][33];
     const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4, c0 = blockIdx.x * 32, i0 = blockIdx.y * 32;
-    const int64_t at = (int64_t)(i0 + row) * r + c0 + col;
-    const f32x4 y = *reinterpret_cast<const f32x4*>(Y + at);
-    f32x4 l = {0.f, 0.f, 0.f, 0.f};
-    if (low != nullptr) l = *reinterpret_cast<const f32x4*>(low + blockIdx.z * (st.part * 2) + at);
+    const f32x4 y = *reinterpret_cast<const f32x4*>(Y + (int64_t)(i0 + row) * r + c0 + col);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const int e = exponent_above(maxbits[c0 + col + j]);
-        tile[row][col + j] = e == kNotFinite ? 0 : (int)rint(ldexp((double)y[j] + (double)l[j], kDigitBits - e));
+        tile[row][col + j] = e == kNotFinite ? 0 : (int)rint(ldexp((double)y[j], kDigitBits - e));
     }
     __syncthreads();
-    const int plane = t >> 6, lane = t & 63;
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 16; ++j) w[j >> 2] |= digit_of(tile[16 * (lane >> 5) + j][lane & 31], plane) << (8 * (j & 3));
-    const int64_t frag = (int64_t)blockIdx.x * (m / 32) + blockIdx.y;
-    *reinterpret_cast<u32x4*>(planes + (frag * 4 + plane) * 1024 + lane * 16) = u32x4{w[0], w[1], w[2], w[3]};
+    store_digits<false>(tile, planes + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096);
 }
 
-// The same digits with x = row, k = column.
-__global__ __launch_bounds__(256) void k_digits_turn(const uint8_t* __restrict__ from, uint8_t* __restrict__ to, int m, int r,
-                                                     int64_t from_stride, int64_t to_stride) {
-    from += blockIdx.z * from_stride;
-    to += blockIdx.z * to_stride;
+// Exponents of the rows of T (its finite elements: what is not is told by the exponents of the columns).  A wave per row.
+__global__ __launch_bounds__(256) void k_t_exponents(const float* __restrict__ T, int32_t* __restrict__ texp, int m, int r,
+                                                     BatchStride st) {
+    T += blockIdx.z * st.Y;
+    texp += blockIdx.z * st.expo;
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= m) return;
+    uint32_t mx = 0;
+#pragma unroll 8
+    for (int c = lane; c < r; c += 64) {
+        const uint32_t b = __builtin_bit_cast(uint32_t, T[(int64_t)i * r + c]) & 0x7FFFFFFFu;
+        mx = b < 0x7F800000u ? max(mx, b) : mx;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+    if (lane == 0) texp[i] = exponent_above(mx);
+}
+
+// Digits of T + low (see k_apply), x = row, k = column, in units of the row.
+__global__ __launch_bounds__(256) void k_digits_t(const float* __restrict__ T, const float* __restrict__ low,
+                                                  const int32_t* __restrict__ texp, uint8_t* __restrict__ rows, int64_t rows_stride,
+                                                  int r, BatchStride st) {
+    T += blockIdx.z * st.Y;
+    low += blockIdx.z * (st.part * 2);
+    texp += blockIdx.z * st.expo;
+    rows += blockIdx.z * rows_stride;
+    __shared__ int tile[32][33];
+    const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4, c0 = blockIdx.x * 32, i0 = blockIdx.y * 32;
+    const int64_t at = (int64_t)(i0 + row) * r + c0 + col;
+    const f32x4 y = *reinterpret_cast<const f32x4*>(T + at), l = *reinterpret_cast<const f32x4*>(low + at);
+    const int e = texp[i0 + row];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const bool finite = (__builtin_bit_cast(uint32_t, y[j]) & 0x7FFFFFFFu) < 0x7F800000u;
+        tile[row][col + j] = finite ? (int)rint(ldexp((double)y[j] + (double)l[j], kDigitBits - e)) : 0;
+    }
+    __syncthreads();
+    store_digits<true>(tile, rows + ((int64_t)blockIdx.y * (r / 32) + blockIdx.x) * 4096);
+}
+
+// From these the digits with x = column, k = row, in units of the column.
+__global__ __launch_bounds__(256) void k_digits_turn(const uint8_t* __restrict__ rows, int64_t rows_stride,
+                                                     const int32_t* __restrict__ texp, const uint32_t* __restrict__ maxbits,
+                                                     uint8_t* __restrict__ planes, int m, int r, BatchStride st) {
+    rows += blockIdx.z * rows_stride;
+    texp += blockIdx.z * st.expo;
+    maxbits += blockIdx.z * st.expo;
+    planes += blockIdx.z * st.planes;
     __shared__ __attribute__((aligned(16))) uint8_t frag[4 * 1024];
-    const int t = threadIdx.x, plane = t >> 6, lane = t & 63;
+    __shared__ int tile[32][33];
+    const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4;
     reinterpret_cast<u32x4*>(frag)[t] =
-        reinterpret_cast<const u32x4*>(from + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096)[t];
+        reinterpret_cast<const u32x4*>(rows + ((int64_t)blockIdx.y * (r / 32) + blockIdx.x) * 4096)[t];
     __syncthreads();
-    const int i = lane & 31;   // row; its digits sit at byte i % 16 of lanes c + 32 (i / 16)
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
+    const int f = texp[blockIdx.y * 32 + row];
+    // four columns' digits are neighbours: byte c % 16 of lane row + 32 (c / 16)
+    uint32_t d[4];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int c = 16 * (lane >> 5) + j;
-        w[j >> 2] |= (uint32_t)frag[plane * 1024 + (c + 32 * (i >> 4)) * 16 + (i & 15)] << (8 * (j & 3));
+    for (int p = 0; p < 4; ++p)
+        d[p] = *reinterpret_cast<const uint32_t*>(frag + p * 1024 + (row + 32 * (col >> 4)) * 16 + (col & 15));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int e = exponent_above(maxbits[blockIdx.x * 32 + col + j]);
+        int v = 0;
+#pragma unroll
+        for (int p = 3; p >= 0; --p) v = v * 256 + (int)(int8_t)(d[p] >> (8 * j));
+        tile[row][col + j] = e == kNotFinite ? 0 : (int)rint(ldexp((double)v, f - e));
     }
-    *reinterpret_cast<u32x4*>(to + (((int64_t)blockIdx.y * (r / 32) + blockIdx.x) * 4 + plane) * 1024 + lane * 16) =
-        u32x4{w[0], w[1], w[2], w[3]};
+    __syncthreads();
+    store_digits<false>(tile, planes + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096);
 }
 
-// Row j of X 2^e (e: the exponents of Y's columns): rowexp[j] with |X_jk 2^e_k| <= 2^rowexp[j] for k <= j.  A wave per row.
+// Row j of X: rowexp[j] with |X_jk| <= 2^rowexp[j] for k <= j, or kNotFinite if it meets a column of T that is not.  A wave per row.
 __global__ __launch_bounds__(256) void k_row_exponents(const double* __restrict__ X, const uint32_t* __restrict__ maxbits,
                                                        int32_t* __restrict__ rowexp, int r, BatchStride st) {
     X += blockIdx.z * st.X;
@@ -758,7 +811,7 @@ __global__ __launch_bounds__(256) void k_row_exponents(const double* __restrict_
     if (j >= r) return;
     int e = -(1 << 19);
     for (int k = lane; k <= j; k += 64) {
-        const double x = scale_by(X[(int64_t)j * r + k], exponent_above(maxbits[k]));
+        const double x = scale_by(X[(int64_t)j * r + k], maxbits[k] >= 0x7F800000u ? kNotFinite : 0);
         const int hi = (int)(__builtin_bit_cast(uint64_t, x) >> 52) & 0x7FF;   // 0: zero (or below every number of interest)
         if (hi == 0x7FF) e = kNotFinite;
         else if (hi != 0) e = max(e, hi - 1022);
@@ -768,14 +821,12 @@ __global__ __launch_bounds__(256) void k_row_exponents(const double* __restrict_
     if (lane == 0) rowexp[j] = e;
 }
 
-// Digits of X 2^e, x = row, for the fragments in the diagonal blocks of X and left of them: a fifth one below the other four
+// Digits of X, x = row, for the fragments in the diagonal blocks of X and left of them: a fifth one below the other four
 // (plane 4), since a result adds up the roundings of a whole row of X.
-__global__ __launch_bounds__(256) void k_digits_x(const double* __restrict__ X, const uint32_t* __restrict__ maxbits,
-                                                  const int32_t* __restrict__ rowexp, uint8_t* __restrict__ planes, int r,
-                                                  BatchStride st) {
+__global__ __launch_bounds__(256) void k_digits_x(const double* __restrict__ X, const int32_t* __restrict__ rowexp,
+                                                  uint8_t* __restrict__ planes, int r, BatchStride st) {
     if ((int)blockIdx.x * 32 / kNB > (int)blockIdx.y * 32 / kNB) return;
     X += blockIdx.z * st.X;
-    maxbits += blockIdx.z * st.expo;
     rowexp += blockIdx.z * st.expo;
     planes += blockIdx.z * (st.part * 8);
     __shared__ int8_t last[32][33];
@@ -784,9 +835,8 @@ __global__ __launch_bounds__(256) void k_digits_x(const double* __restrict__ X, 
     const int f = rowexp[j0 + row];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        const int k = k0 + col + q, e = exponent_above(maxbits[k]);
-        const bool finite = f != kNotFinite && e != kNotFinite;
-        const int64_t v = finite ? (int64_t)rint(ldexp(X[(int64_t)(j0 + row) * r + k], e - f + kDigitBits + 8)) : 0;
+        const int64_t v =
+            f != kNotFinite ? (int64_t)rint(ldexp(X[(int64_t)(j0 + row) * r + k0 + col + q], kDigitBits + 8 - f)) : 0;
         const int lowest = (int)(int8_t)v;
         tile[row][col + q] = (int)((v - lowest) >> 8);
         last[row][col + q] = (int8_t)lowest;
@@ -902,21 +952,23 @@ __global__ __launch_bounds__(256, 2) void k_digit_gram(const uint8_t* __restrict
     });
 }
 
-// Q = Y X^T from the digits of Y (x = row) and of X 2^e.
-__global__ __launch_bounds__(256, 2) void k_digit_apply(const uint8_t* __restrict__ yp, int64_t yp_stride,
-                                                     const uint8_t* __restrict__ xp, const int32_t* __restrict__ rowexp,
-                                                     float* __restrict__ Q, int m, int r, BatchStride st) {
-    yp += blockIdx.z * yp_stride;
+// Q = T X^T from the digits of the rows of both.
+__global__ __launch_bounds__(256, 2) void k_digit_apply(const uint8_t* __restrict__ tp, int64_t tp_stride,
+                                                        const int32_t* __restrict__ texp, const uint8_t* __restrict__ xp,
+                                                        const int32_t* __restrict__ rowexp, float* __restrict__ Q, int m, int r,
+                                                        BatchStride st) {
+    tp += blockIdx.z * tp_stride;
+    texp += blockIdx.z * st.expo;
     xp += blockIdx.z * (st.part * 8);
     rowexp += blockIdx.z * st.expo;
     Q += blockIdx.z * st.Q;
     __shared__ __attribute__((aligned(16))) uint8_t smem[digit_smem(5)];
     // X is zero above its diagonal blocks: a wave's 64 columns end with one
     const int wj = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 1, block = (int)blockIdx.y * 2;
-    digit_product<5>(yp, xp, r / 32, 0, min(r, (block + 2) * kNB) / 32, min(r, (block + wj + 1) * kNB) / 32, blockIdx.x, blockIdx.y,
+    digit_product<5>(tp, xp, r / 32, 0, min(r, (block + 2) * kNB) / 32, min(r, (block + wj + 1) * kNB) / 32, blockIdx.x, blockIdx.y,
                      m / 32, r / 32, smem, [&](int i, int j, double x) {
         const int f = rowexp[j];
-        Q[(int64_t)i * r + j] = (float)scale_by(x, f == kNotFinite ? kNotFinite : f - 2 * kDigitBits);
+        Q[(int64_t)i * r + j] = (float)scale_by(x, f == kNotFinite ? kNotFinite : f + texp[i] - 2 * kDigitBits);
     });
 }
 
@@ -938,7 +990,7 @@ static int gram_slices(int64_t m, int64_t r, int* slice_rows) {
 
 // Whether a shape's products run on INT8 digits (a function of the shape only, as the number of slices).  us per refresh,
 // fp64 / digits: 768 x 256 309 / 334, four of 1024 x 256 356 / 373, sixteen 547 / 517, one 2048 x 512 634 / 627, sixteen 1935 /
-// 1650, one 4096 x 512 764 / 700, one 4096 x 1024 1647 / 1393, sixteen 10184 / 7461.
+// 1650, one 4096 x 512 764 / 700, one 4096 x 1024 1647 / 1393, sixteen 10184 / 7530.
 static bool digits(int64_t m, int64_t r) {
     int slice_rows;
     gram_slices(m, r, &slice_rows);
@@ -968,7 +1020,7 @@ static OrthLayout orth_layout(int64_t m, int64_t r, int64_t batch) {
     L.part = L.T + bT * batch;
     L.shift = L.part + bP * batch;
     L.expo = L.shift + 256 * (size_t)batch;      // one double per matrix, 256 bytes apart
-    const size_t bE = align256((size_t)r * 8);
+    const size_t bE = digits(m, r) ? align256((size_t)(2 * r + m) * 4) : 0;   // columns of Y, rows of X, rows of T
     L.total = L.expo + bE * batch;
     L.st = BatchStride{(int64_t)(bT / 4), (int64_t)(bT / 4), (int64_t)(bS / 8), (int64_t)(bS / 8), (int64_t)(bD / 8),
                        (int64_t)(bP / 8), 256 / 8, (int64_t)(bE / 4), 0};
@@ -1021,11 +1073,12 @@ static int launch_range(const uint16_t* G, const uint16_t* Z, float* Y, int64_t 
 
 // One round on `batch` matrices (matrix b at Y + b * sYin, result at Q + b * sQout): Q = Y L^-T with L the Cholesky
 // factor of Y^T Y.
-// planes: m * r * 4 bytes at a stride of plane_stride for the digits of Y, or null; last: the second round, whose product with X
-// is one of digits too (they then replace Y).
+// planes: m * r * 4 bytes at a stride of plane_stride for the digits of Y, or null: Q's own, which the digits leave before the
+// result is written.  rows: in the second round as much at a stride of L.st.Y floats for the digits of its rows, else null.
+// With rows, Y may be Q, since it is read before its planes are written.
 static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout, int64_t m, int64_t r, int batch,
                           int32_t* info, double flag_factor, char* ws, const OrthLayout& L, uint8_t* planes,
-                          int64_t plane_stride, bool last, hipStream_t stream) {
+                          int64_t plane_stride, uint8_t* rows, hipStream_t stream) {
     double* S = reinterpret_cast<double*>(ws + L.S);
     double* X = reinterpret_cast<double*>(ws + L.X);
     double* Dinv = reinterpret_cast<double*>(ws + L.Dinv);
@@ -1037,6 +1090,8 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     st.planes = plane_stride;
     uint32_t* maxbits = reinterpret_cast<uint32_t*>(ws + L.expo);
     int32_t* rowexp = reinterpret_cast<int32_t*>(maxbits) + r;
+    int32_t* texp = rowexp + r;
+    const int64_t rows_stride = L.st.Y * 4;
     const int nt = (int)((r + kNB - 1) / kNB);
     const int pairs = nt * (nt + 1) / 2;
     int slice_rows;
@@ -1044,8 +1099,7 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     const dim3 blk(256);
     const unsigned B = (unsigned)batch;
     // what T lost to fp32 lies where the Gram slices do: written after round one has added them, read before round two writes them
-    float* low_in = reinterpret_cast<float*>(part);
-    float* low = planes && !last ? low_in : nullptr;
+    float* low = planes && !rows ? reinterpret_cast<float*>(part) : nullptr;
     auto blocks = [](int64_t n, int size) { return (unsigned)((n + size - 1) / size); };
     const unsigned nt32 = blocks(r, 32);
     // 32 x 32 blocks while 64 x 64 ones are about a workgroup per CU or fewer (us per refresh, always 64 / this line / up to
@@ -1056,8 +1110,15 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
         const int chunks = (int)((m + 511) / 512);
         hipLaunchKernelGGL(k_set_i32, dim3(blocks(st.expo * batch, 256)), blk, 0, stream, rowexp - r, 0, (int)(st.expo * batch));
         hipLaunchKernelGGL(k_column_max, dim3(blocks(r, 64), chunks, B), blk, 0, stream, Y, maxbits, (int)m, (int)r, 512, st);
-        hipLaunchKernelGGL(k_digits, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, last ? low_in : nullptr,
-                           maxbits, planes, (int)m, (int)r, st);
+        if (rows) {
+            hipLaunchKernelGGL(k_t_exponents, dim3(blocks(m, 4), 1, B), blk, 0, stream, Y, texp, (int)m, (int)r, st);
+            hipLaunchKernelGGL(k_digits_t, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, reinterpret_cast<const float*>(part),
+                               texp, rows, rows_stride, (int)r, st);
+            hipLaunchKernelGGL(k_digits_turn, dim3(nt32, blocks(m, 32), B), blk, 0, stream, rows, rows_stride, texp, maxbits,
+                               planes, (int)m, (int)r, st);
+        } else {
+            hipLaunchKernelGGL(k_digits, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, maxbits, planes, (int)m, (int)r, st);
+        }
         int tiles = 0;
         for (int ti = 0; ti < nt; ++ti) tiles += ti / 2 + 1;
         hipLaunchKernelGGL(k_digit_gram, dim3(tiles, slices, B), blk, 0, stream, planes, maxbits, part, (int)m, (int)r,
@@ -1088,15 +1149,12 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     }
     for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
         if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(kStrips * ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
-    if (planes && last) {
-        uint8_t* turned = reinterpret_cast<uint8_t*>(const_cast<float*>(Y));   // T, which nothing reads any more
+    if (rows) {
         uint8_t* xp = reinterpret_cast<uint8_t*>(part);
-        hipLaunchKernelGGL(k_digits_turn, dim3(nt32, blocks(m, 32), B), blk, 0, stream, planes, turned, (int)m, (int)r,
-                           plane_stride, sYin * 4);
         hipLaunchKernelGGL(k_row_exponents, dim3(blocks(r, 4), 1, B), blk, 0, stream, X, maxbits, rowexp, (int)r, st);
-        hipLaunchKernelGGL(k_digits_x, dim3(nt32, nt32, B), blk, 0, stream, X, maxbits, rowexp, xp, (int)r, st);
-        hipLaunchKernelGGL(k_digit_apply, dim3(blocks(m, 64), blocks(r, 128), B), blk, 0, stream, turned, sYin * 4, xp, rowexp, Q,
-                           (int)m, (int)r, st);
+        hipLaunchKernelGGL(k_digits_x, dim3(nt32, nt32, B), blk, 0, stream, X, rowexp, xp, (int)r, st);
+        hipLaunchKernelGGL(k_digit_apply, dim3(blocks(m, 64), blocks(r, 128), B), blk, 0, stream, rows, rows_stride, texp, xp,
+                           rowexp, Q, (int)m, (int)r, st);
     } else if ((int64_t)blocks(m, kNB) * nt * batch < kFewBlocks)
         hipLaunchKernelGGL(k_apply<32>, dim3(blocks(m, 32), nt32, B), blk, 0, stream, Y, X, Q, low, (int)m, (int)r, st);
     else
@@ -1110,10 +1168,14 @@ static int launch_orth(const float* Y, int64_t sY, float* Q, int64_t sQ, int64_t
     float* T = reinterpret_cast<float*>(ws + L.T);
     if (reset_info)
         hipLaunchKernelGGL(k_set_i32, dim3((batch + 255) / 256), dim3(256), 0, stream, info, 0, batch);
-    // the digits of Y, then of T, fit where Q will be
-    uint8_t* planes = digits(m, r) ? reinterpret_cast<uint8_t*>(Q) : nullptr;
-    launch_cholqr(Y, sY, T, L.st.Y, m, r, batch, info, 0.0, ws, L, planes, sQ * 4, false, stream);
-    launch_cholqr(T, L.st.Y, Q, sQ, m, r, batch, info, 16.0, ws, L, planes, sQ * 4, true, stream);
+    if (digits(m, r)) {   // T and the digits of Y's and T's columns lie where Q will be, those of T's rows where T is otherwise
+        uint8_t* planes = reinterpret_cast<uint8_t*>(Q);
+        launch_cholqr(Y, sY, Q, sQ, m, r, batch, info, 0.0, ws, L, planes, sQ * 4, nullptr, stream);
+        launch_cholqr(Q, sQ, Q, sQ, m, r, batch, info, 16.0, ws, L, planes, sQ * 4, reinterpret_cast<uint8_t*>(T), stream);
+    } else {
+        launch_cholqr(Y, sY, T, L.st.Y, m, r, batch, info, 0.0, ws, L, nullptr, 0, nullptr, stream);
+        launch_cholqr(T, L.st.Y, Q, sQ, m, r, batch, info, 16.0, ws, L, nullptr, 0, nullptr, stream);
+    }
     return check_launch();
 }
 

@@ -119,6 +119,26 @@ def test_orthonormalize_of_large_matrices(m, r, kind):
     assert np.abs(got.T @ got - np.eye(r)).max() <= 1e-7
 
 
+@pytest.mark.parametrize("m,r", [(2048, 512), (1824, 544)])
+def test_small_rows_of_a_large_matrix_keep_their_digits(m, r):
+    """Rows of Q are quantized each by itself: a row 1e-8 or 1e-12 of the others is as exact in itself as any row, up to what the
+    Gram matrix adds.  Q = Y T^-1 for one T, so a row's relative error is the fp32 rounding (2^-24) and that of T^-1 (for these,
+    cond(Y) about 3, below 1e-7)."""
+    g = np.random.default_rng([m, r, 5])
+    Y = g.standard_normal((m, r))
+    small = np.arange(m) % 97 == 3
+    Y[small] *= np.where(np.arange(small.sum()) % 2 == 0, 1e-8, 1e-12)[:, None]
+    Y = Y.astype(np.float32)
+    want = Q.orthonormalize(Y)
+    got = host(qg.orthonormalize(dev(Y))[0]).astype(np.float64)
+    assert rel_fro(got, want) <= 6e-8
+    # the oracle's own rows are exact to 1e-16 of the largest only; those of Y T^-1 with its T are to 1e-16 of themselves
+    T = want.T @ Y.astype(np.float64)
+    rows = np.linalg.solve(T.T, Y[small].astype(np.float64).T).T
+    err = np.linalg.norm(got[small] - rows, axis=1) / np.linalg.norm(rows, axis=1)
+    assert err.max() <= 2e-7
+
+
 def test_a_nan_column_of_a_large_matrix_is_reported():
     Y = np.random.default_rng(1).standard_normal((2048, 512)).astype(np.float32)
     Y[100, 300] = np.nan
