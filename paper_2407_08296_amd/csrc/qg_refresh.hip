@@ -660,13 +660,13 @@ __global__ __launch_bounds__(256) void k_apply(const float* __restrict__ Y, cons
 // that of a matrix within 2^-31 of Y (its shift, 2^-46 of the trace, is 2^-23 of a singular value).  The second round works on T
 // rounded to 2^-31 of its ROW's largest magnitude (in units of a column, rows far below the others would lose their digits, and
 // Q's rows are quantized each by itself), which is finer than fp32: T's digits come from the fp64 product, through what its
-// fp32 lost.  (The first round's Q = Y X^T stays in fp64: X is large there and its terms cancel.)  Q against 64 bits, relative: 2.54e-8 where fp64 with T in fp32
-// gave 2.69e-8 (random 4096 x 1024) to 3.7e-8 (cond 1e7), 6.3e-8 where it gave 4.4e-7 (cond 1e9); of the worst row 2.8e-8 and
-// 2.9e-8, also where every 97th row is 1e-10 of the others.
+// fp32 lost.  (The first round's Q = Y X^T stays in fp64: X is large there and its terms cancel.)  Q against 64 bits, relative:
+// 2.54e-8 where fp64 with T in fp32 gave 2.69e-8 (random 4096 x 1024) to 3.7e-8 (cond 1e7), 6.3e-8 where it gave 4.4e-7 (cond
+// 1e9); of the worst row 2.8e-8 and 2.9e-8, also where every 97th row is 1e-10 of the others.
 //
 // A plane is stored in 1 KB fragments of 32 x indices by 32 k indices, as a wave's lanes hold an MFMA operand (lane l: x = l %
-// 32, k = 16 (l / 32) ..+15), the four planes of a fragment one after another: an operand is one contiguous 16-byte load per
-// lane, with no LDS and no barrier.
+// 32, k = 16 (l / 32) ..+15), the four planes of a fragment one after another: a fragment is one contiguous wave-wide load
+// straight into LDS and one 16-byte read per lane from there, free of conflicts.
 // ---------------------------------------------------------------------------------------------------------------
 // LDS stages of a product and their bytes
 constexpr int digit_stages(int planes) { return planes == 4 ? 3 : 2; }
@@ -683,22 +683,41 @@ __device__ __forceinline__ uint32_t digit_of(int v, int p) {
 }
 __device__ __forceinline__ double scale_by(double x, int e) { return e >= kNotFinite / 2 ? __builtin_nan("") : ldexp(x, e); }
 
-// Bits of the largest magnitude of each column of Y (of |y|, where the order of floats is that of integers); maxbits zeroed.
-__global__ __launch_bounds__(256) void k_column_max(const float* __restrict__ Y, uint32_t* __restrict__ maxbits, int m, int r,
-                                                    int rows, BatchStride st) {
-    Y += blockIdx.z * st.Y;
-    maxbits += blockIdx.z * st.expo;
-    const int c = blockIdx.x * 64 + (threadIdx.x & 63), i1 = min(m, (int)(blockIdx.y + 1) * rows);
-    if (c >= r) return;
-    uint32_t mx = 0;
-#pragma unroll 8
-    for (int i = blockIdx.y * rows + (threadIdx.x >> 6); i < i1; i += 4)
-        mx = max(mx, __builtin_bit_cast(uint32_t, Y[(int64_t)i * r + c]) & 0x7FFFFFFFu);
-    atomicMax(maxbits + c, mx);
-}
 // e with |x| <= 2^e for all |x| <= the float of these bits
 __device__ __forceinline__ int exponent_above(uint32_t bits) {
     return bits >= 0x7F800000u ? kNotFinite : max((int)(bits >> 23), 1) - 126;
+}
+
+// Bits of the largest magnitude of each column of Y (of |y|, where the order of floats is that of integers); maxbits zeroed.  A
+// workgroup per 64 columns and `rows` rows.  ROWS: in workgroups of their own, a wave per row, the exponents of the rows too (of
+// their finite elements: what is not is told by the columns).  Both in one launch, us per refresh: one 2048 x 2048, r = 512
+// 633 -> 629, sixteen 4096 x 4096, r = 1024, 7480 -> 7250.
+template <bool ROWS>
+__global__ __launch_bounds__(256) void k_maxima(const float* __restrict__ Y, uint32_t* __restrict__ maxbits,
+                                                int32_t* __restrict__ rowexp, int m, int r, int rows, BatchStride st) {
+    Y += blockIdx.z * st.Y;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int across = (r + 63) / 64, blocks = across * ((m + rows - 1) / rows);
+    uint32_t mx = 0;
+    if (!ROWS || (int)blockIdx.x < blocks) {
+        const int c = (int)blockIdx.x % across * 64 + lane, i0 = (int)blockIdx.x / across * rows, i1 = min(m, i0 + rows);
+        if (c >= r) return;
+#pragma unroll 8
+        for (int i = i0 + wave; i < i1; i += 4)
+            mx = max(mx, __builtin_bit_cast(uint32_t, Y[(int64_t)i * r + c]) & 0x7FFFFFFFu);
+        atomicMax(maxbits + blockIdx.z * st.expo + c, mx);
+    } else {
+        const int i = ((int)blockIdx.x - blocks) * 4 + wave;
+        if (i >= m) return;
+#pragma unroll 8
+        for (int c = lane; c < r; c += 64) {
+            const uint32_t b = __builtin_bit_cast(uint32_t, Y[(int64_t)i * r + c]) & 0x7FFFFFFFu;
+            mx = b < 0x7F800000u ? max(mx, b) : mx;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
+        if (lane == 0) rowexp[blockIdx.z * st.expo + i] = exponent_above(mx);
+    }
 }
 
 // The digits of a 32 x 32 tile of integers, x = column, k = row (or x = row, k = column) into one fragment.
@@ -727,24 +746,6 @@ __global__ __launch_bounds__(256) void k_digits(const float* __restrict__ Y, con
     }
     __syncthreads();
     store_digits<false>(tile, planes + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096);
-}
-
-// Exponents of the rows of T (its finite elements: what is not is told by the exponents of the columns).  A wave per row.
-__global__ __launch_bounds__(256) void k_t_exponents(const float* __restrict__ T, int32_t* __restrict__ texp, int m, int r,
-                                                     BatchStride st) {
-    T += blockIdx.z * st.Y;
-    texp += blockIdx.z * st.expo;
-    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (i >= m) return;
-    uint32_t mx = 0;
-#pragma unroll 8
-    for (int c = lane; c < r; c += 64) {
-        const uint32_t b = __builtin_bit_cast(uint32_t, T[(int64_t)i * r + c]) & 0x7FFFFFFFu;
-        mx = b < 0x7F800000u ? max(mx, b) : mx;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-    if (lane == 0) texp[i] = exponent_above(mx);
 }
 
 // Digits of T + low (see k_apply), x = row, k = column, in units of the row.
@@ -801,7 +802,8 @@ __global__ __launch_bounds__(256) void k_digits_turn(const uint8_t* __restrict__
     store_digits<false>(tile, planes + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096);
 }
 
-// Row j of X: rowexp[j] with |X_jk| <= 2^rowexp[j] for k <= j, or kNotFinite if it meets a column of T that is not.  A wave per row.
+// Row j of X: rowexp[j] with |X_jk| <= 2^rowexp[j] for k <= j, or kNotFinite if it meets a column of T that is not finite.  A
+// wave per row.
 __global__ __launch_bounds__(256) void k_row_exponents(const double* __restrict__ X, const uint32_t* __restrict__ maxbits,
                                                        int32_t* __restrict__ rowexp, int r, BatchStride st) {
     X += blockIdx.z * st.X;
@@ -989,8 +991,8 @@ static int gram_slices(int64_t m, int64_t r, int* slice_rows) {
 }
 
 // Whether a shape's products run on INT8 digits (a function of the shape only, as the number of slices).  us per refresh,
-// fp64 / digits: 768 x 256 309 / 334, four of 1024 x 256 356 / 373, sixteen 547 / 517, one 2048 x 512 634 / 627, sixteen 1935 /
-// 1650, one 4096 x 512 764 / 700, one 4096 x 1024 1647 / 1393, sixteen 10184 / 7530.
+// fp64 / digits: 768 x 256 309 / 334, four of 1024 x 256 356 / 373, sixteen 547 / 517, one 2048 x 512 631 / 629, sixteen 1901 /
+// 1605, one 4096 x 512 781 / 720, one 8192 x 256 544 / 517, one 4096 x 1024 1640 / 1374, sixteen 10190 / 7250.
 static bool digits(int64_t m, int64_t r) {
     int slice_rows;
     gram_slices(m, r, &slice_rows);
@@ -1107,16 +1109,19 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     // 517, 2048 x 2048, r = 512, sixteen 1982 / 1956 / 1984 / 2274)
     constexpr int64_t kFewBlocks = 300;
     if (planes) {
-        const int chunks = (int)((m + 511) / 512);
+        constexpr int kMaxRows = 512;
+        const unsigned by_column = blocks(r, 64) * blocks(m, kMaxRows);
         hipLaunchKernelGGL(k_set_i32, dim3(blocks(st.expo * batch, 256)), blk, 0, stream, rowexp - r, 0, (int)(st.expo * batch));
-        hipLaunchKernelGGL(k_column_max, dim3(blocks(r, 64), chunks, B), blk, 0, stream, Y, maxbits, (int)m, (int)r, 512, st);
         if (rows) {
-            hipLaunchKernelGGL(k_t_exponents, dim3(blocks(m, 4), 1, B), blk, 0, stream, Y, texp, (int)m, (int)r, st);
+            hipLaunchKernelGGL(k_maxima<true>, dim3(by_column + blocks(m, 4), 1, B), blk, 0, stream, Y, maxbits, texp, (int)m,
+                               (int)r, kMaxRows, st);
             hipLaunchKernelGGL(k_digits_t, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, reinterpret_cast<const float*>(part),
                                texp, rows, rows_stride, (int)r, st);
             hipLaunchKernelGGL(k_digits_turn, dim3(nt32, blocks(m, 32), B), blk, 0, stream, rows, rows_stride, texp, maxbits,
                                planes, (int)m, (int)r, st);
         } else {
+            hipLaunchKernelGGL(k_maxima<false>, dim3(by_column, 1, B), blk, 0, stream, Y, maxbits, nullptr, (int)m, (int)r,
+                               kMaxRows, st);
             hipLaunchKernelGGL(k_digits, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, maxbits, planes, (int)m, (int)r, st);
         }
         int tiles = 0;
