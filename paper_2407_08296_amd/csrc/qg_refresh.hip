@@ -1134,10 +1134,11 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     else
         hipLaunchKernelGGL(k_gram<kNB>, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
-    // One launch per block column while its workgroups, one on a CU, are few (ms per refresh, fused / separate: one 4096 x
-    // 4096, r = 1024, 2.36 / 3.16, 16 of them 10.9 / 11.2, 32 20.8 / 19.9, 128 80.0 / 72.6; r = 512: 32 matrices 3.62 / 3.76, 96
-    // 9.74 / 9.32; r = 256: 32 0.85 / 0.91, 84 1.81 / 1.79).  The arithmetic is the same, and with it every bit.
-    const bool fused = batch * nt <= 384;
+    // One launch per block column up to 1024 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.38 /
+    // 1.82, 32 of them 14.0 / 14.2, 48 21.2 / 21.7, 128 54.6 / 54.3; 2048 x 2048, r = 512: 32 2.75 / 2.89, 128 10.4 / 10.5; 1024 x
+    // 1024: r = 256, 256 matrices 5.06 / 5.07, r = 128, 512 of them 5.34 / 5.32).  The arithmetic is the same, and with it every
+    // bit.
+    const bool fused = batch * nt <= 1024;
     hipLaunchKernelGGL(k_chol_diag<true>, dim3(1, 1, B), blk, 0, stream, S, (int)r, 0, Dinv, X, info, shift, flag_factor, st);
     for (int kb = 0; kb + 1 < nt; ++kb) {
         const int below = nt - kb - 1, left = below * (below + 1) / 2;

@@ -314,9 +314,10 @@ def test_batched_refresh_across_launch_groups(count):
         assert float(host(cos)[i]) == float(host(one[2])[0])
 
 
-@pytest.mark.parametrize("m,n,r,count", [(256, 264, 200, 96), (256, 264, 200, 97), (160, 200, 136, 129), (72, 96, 64, 385)])
+@pytest.mark.parametrize("m,n,r,count", [(256, 264, 200, 96), (256, 264, 200, 97), (160, 200, 136, 129), (72, 96, 64, 385),
+                                           (256, 264, 200, 256), (256, 264, 200, 257), (72, 96, 64, 1025)])
 def test_large_batches_equal_the_single_matrix_calls(m, n, r, count):
-    """Up to 384 block rows of 64 in a batch (96 matrices of r = 200) a block column of the factorization is one launch,
+    """Up to 1024 block rows of 64 in a batch (256 matrices of r = 200) a block column of the factorization is one launch,
     beyond that its parts are launches of their own: bit for bit the single call's result either way."""
     ins = [start(m, n, r, seed=s) for s in range(3)]
     up = [(bits_t(Gb), dev(Pq), dev(Ps)) for Gb, Pq, Ps in ins]
