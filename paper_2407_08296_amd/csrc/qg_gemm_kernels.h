@@ -166,7 +166,7 @@ __device__ __forceinline__ u32x4 shift_right_128(u32x4 v, int bits) {
 // partial one after it, checked), and a tile at the edge of the columns loads the last whole chunk of a row and shifts it when
 // it is stored (EDGE).  Addresses are a scalar base and a 32-bit byte offset per chunk that is fixed for the whole loop (as
 // running 64-bit pointers they took the registers of four tiles in flight and spilled), which covers row pitches up to 2^24;
-// beyond it, and for less than a chunk of columns, every step is a checked one.
+// beyond it, and for less than a chunk of columns (of G, N, or of P), every step is a checked one.
 __device__ __forceinline__ bool pipelined(int n, int ld) { return n >= 8 && ld <= (1 << 24); }
 
 // Chunk of eight columns from col on: first column loaded, and the shift in bits; columns at or past n give anything, for
@@ -439,7 +439,7 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
         int c = r0 + (ti % A_TPR) * (8 * WPT);
         if constexpr (!DIRECT) {
             a_next[p] = c > r - 8 * WPT;
-            c = min(c, r - 8 * WPT);       // (tiles of two words per fetch are for r > 64)
+            c = min(c, r - 8 * WPT);       // (r < 8 * WPT: not used, every step is checked)
         }
         a_el[p] = (uint32_t)((ti / A_TPR) * r + c);
     }
@@ -456,7 +456,9 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
     // Tile kt: P codes and scales into register set `stage`; G straight into LDS stage `stage` (kExact, kMasked) or into
     // registers (kUnaligned, stored by sstore).  A tile past the end (kt >= KT) loads nothing: its resources are empty (or,
     // kUnaligned, the last tile again).
-    const int KT_WHOLE = pipelined(n, ld) ? m / BK : 0;   // kUnaligned: steps of the pipeline
+    // kUnaligned: steps of the pipeline (a matrix of fewer columns of P than a fetch has codes, in a grouped launch whose tiles
+    // suit a larger r, has none)
+    const int KT_WHOLE = pipelined(n, ld) && r >= 8 * WPT ? m / BK : 0;
     auto gload = [&](int kt, int stage) {
         const int i0 = kt * BK;
         const int64_t e0 = (int64_t)i0 * r;

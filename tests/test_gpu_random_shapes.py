@@ -126,3 +126,31 @@ def test_edges_of_unaligned_tiles(m, n, r):
     s = state()
     qg.step(s.Pq, s.Ps, s.G, s.Wq, s.Ws, s.M, s.V, s.R, s.N, m, n, r, qg.hparams(), seed, t)
     check(s, o, t, "single")
+
+
+def test_small_rank_in_a_plan_of_large_unaligned_ones():
+    """A class takes its projection tile from the largest r it holds: 128 rows of R, whose fetch of P is two words (16 codes),
+    also for the matrices of r = 8 in it, whose rows of P are one word."""
+    t, seed = 2, 5
+    shapes = [(72, 41003, 72), (100, 301, 8), (64, 640, 8), (40, 12, 8), (33, 5, 8), (96, 131, 24)]
+    assert sum(-(-r // 128) * -(-n // 128) for _, n, r in shapes) > 320 and max(r for *_, r in shapes) > 64   # that tile
+    rs = np.random.default_rng(8)
+    data, mats = [], []
+    for li, (m, n, r) in enumerate(shapes):
+        Wq, Ws = Q.quant_int8(I.weight_f32(m, n, 0, li, 0))
+        Pq, Ps = Q.quant_int4(I.projection_f32(m, r, 0, li, 0))
+        Gb = I.gradient_bf16(m, n, t, 0, li, 0)
+        M = (rs.standard_normal((r, n)) * 5e-5).astype(np.float32)
+        V = ((rs.standard_normal((r, n)) * 5e-5) ** 2 + 1e-12).astype(np.float32)
+        data.append((Wq, Ws, Gb, Pq, Ps, M, V))
+        mats.append(qg.MatrixState(m, n, r, dev(Pq), dev(Ps), dev(Gb), dev(Wq), dev(Ws), dev(M), dev(V),
+                                   torch.empty((r, n), dtype=torch.float32, device=DEV),
+                                   torch.empty((r, n), dtype=torch.bfloat16, device=DEV)))
+    plan = qg.StepPlan(mats)
+    qg.project_many(plan)
+    R = [host(s.R) for s in mats]
+    qg.step_many(plan, qg.hparams(), seed, t)
+    for i, (s, d) in enumerate(zip(mats, data)):
+        o = Q.step(*d, t, HP, seed=(seed + i * 0x9E3779B97F4A7C15) % 2 ** 64, r=s.r)
+        assert rel_fro(R[i], o["R"]) <= 2e-5, shapes[i]
+        check(s, o, t, f"matrix {i} {shapes[i]}")
