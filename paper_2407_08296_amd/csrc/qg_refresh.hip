@@ -4,7 +4,7 @@
 //     R = dequant(P)^T G  (the projection kernel of the optimizer step)      bf16 MFMA
 //     Z = bf16(R)
 //     Y = G Z^T           (m x r)                                            bf16 MFMA, fp32 accumulation (qg_tile_gemm.h)
-//     Q = Y T^-1          with Y = Q T, T upper triangular, diag(T) > 0      fp64 MFMA (Cholesky QR), INT8 MFMA (large ones)
+//     Q = Y T^-1          with Y = Q T, T upper triangular, diag(T) > 0      fp64 MFMA (Cholesky QR)
 //     P <- quant_int4(Q)  (Sec. 3.3)
 // followed by the cosine check of Sec. 3.2 between the old and the new P.
 //
@@ -17,8 +17,6 @@
 // the first round's pivots positive for cond(Y) well beyond 1e8 at no cost in the result.  A column that is
 // numerically dependent on its predecessors (a last-round pivot no larger than the shift) is reported through
 // `info`; every kernel runs to completion whatever the data.
-#include <algorithm>
-
 #include "qg_cossim.h"
 #include "qg_tile_gemm.h"
 
@@ -38,6 +36,7 @@ constexpr int kKC = 16;               // K extent staged in LDS per barrier pair
                                       // per SIMD; 32 gave three workgroups and 9 % more time, 8 no further gain)
 constexpr int kPitchKF = kKC + 1;     // LDS pitch of a [64][k] chunk (k fastest): odd, so that the 16 rows a fragment
                                       // read touches at one k fall on 16 different bank pairs (36 gave 4-way conflicts)
+constexpr int kPitchKS = kNB + 16;    // LDS pitch of a [k][64] chunk (k slowest)
 
 // ROWS x COLS block at (row0, col0) of a row-major matrix (fp32 or fp64) -> registers -> LDS doubles.  Elements
 // outside [0, rows) x [0, cols) read as zero.  col0 and cols are even, so an element pair never straddles the edge.
@@ -119,8 +118,6 @@ __device__ __forceinline__ void for_each_acc(const f64x4 (&acc)[W][W], int lane,
 // out matrices of a round share the stride Y/Q (both are m x r fp32 arrays of the same batch layout).
 struct BatchStride {
     int64_t Y, Q, S, X, D, part, shift;
-    int64_t expo;     // exponents of Y's columns, of X's and of T's rows (32-bit words)
-    int64_t planes;   // digits of Y (bytes)
 };
 
 // 1 / sqrt(d) for d > 0 to fp64 accuracy: the hardware estimate and two Newton steps (the correctly rounded sqrt
@@ -454,8 +451,7 @@ __global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ S, int r
 #pragma unroll
     for (int q = 0; q < kNB * kNB / 256; ++q) T[(4 * q + (threadIdx.x >> 6)) * kPitchD + (threadIdx.x & 63)] = v[q];
     __syncthreads();
-    chol_diag_block(T, D, r, FIRST ? 0 : kb, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma,
-                    flag_factor);
+    chol_diag_block(T, D, r, FIRST ? 0 : kb, Dinv + blockIdx.z * st.D, X + blockIdx.z * st.X, info + blockIdx.z, sigma, flag_factor);
 }
 
 __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int r, int kb, const double* __restrict__ Dinv,
@@ -610,12 +606,11 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Q = Y X^T (X lower triangular: column block jb needs the contraction index up to the end of that block only).  low: what the
-// rounding to fp32 takes off (nullable; matrix b's at b times the stride of the Gram slices).
+// Q = Y X^T (X lower triangular: column block jb needs the contraction index up to the end of that block only)
 // ---------------------------------------------------------------------------------------------------------------
 template <int TB>
 __global__ __launch_bounds__(256) void k_apply(const float* __restrict__ Y, const double* __restrict__ X,
-                                               float* __restrict__ Q, float* __restrict__ low, int m, int r, BatchStride st) {
+                                               float* __restrict__ Q, int m, int r, BatchStride st) {
     using F = F64Tile<TB>;
     Y += blockIdx.z * st.Y;
     X += blockIdx.z * st.X;
@@ -644,333 +639,7 @@ __global__ __launch_bounds__(256) void k_apply(const float* __restrict__ Y, cons
     }
     for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
         const int gi = a0 + row, gj = b0 + col;
-        if (gi < m && gj < r) {
-            Q[(int64_t)gi * r + gj] = (float)x;
-            if (low != nullptr) low[blockIdx.z * (st.part * 2) + (int64_t)gi * r + gj] = (float)(x - (double)(float)x);
-        }
-    });
-}
-
-// ---------------------------------------------------------------------------------------------------------------
-// The products of large matrices on the INT8 matrix cores, exactly: a column of Y is scaled by a power of two to 31-bit
-// integers, these are cut into four balanced base-256 digits (planes of INT8), and a product of two such numbers is the sum of
-// the products of their digits, each summed over k in int32 without rounding (v_mfma_i32_32x32x32_i8, about fifty times the
-// rate of the fp64 instruction) and added up in fp64 by weight.  Of the 16 digit products the one of the two lowest digits is
-// left out (2^-54 of the largest).  What is rounded is Y, to 2^-31 of its column's largest magnitude: the first Gram matrix is
-// that of a matrix within 2^-31 of Y (its shift, 2^-46 of the trace, is 2^-23 of a singular value).  The second round works on T
-// rounded to 2^-31 of its ROW's largest magnitude (in units of a column, rows far below the others would lose their digits, and
-// Q's rows are quantized each by itself), which is finer than fp32: T's digits come from the fp64 product, through what its
-// fp32 lost.  (The first round's Q = Y X^T stays in fp64: X is large there and its terms cancel.)  Q against 64 bits, relative:
-// 2.54e-8 where fp64 with T in fp32 gave 2.69e-8 (random 4096 x 1024) to 3.7e-8 (cond 1e7), 6.3e-8 where it gave 4.4e-7 (cond
-// 1e9); of the worst row 2.8e-8 and 2.9e-8, also where every 97th row is 1e-10 of the others.
-//
-// A plane is stored in 1 KB fragments of 32 x indices by 32 k indices, as a wave's lanes hold an MFMA operand (lane l: x = l %
-// 32, k = 16 (l / 32) ..+15), the four planes of a fragment one after another: a fragment is one contiguous wave-wide load
-// straight into LDS and one 16-byte read per lane from there, free of conflicts.
-// ---------------------------------------------------------------------------------------------------------------
-// LDS stages of a product and their bytes
-constexpr int digit_stages(int planes) { return planes == 4 ? 3 : 2; }
-constexpr int digit_smem(int planes) { return digit_stages(planes) * (8 + 4 * planes) * 1024; }
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-typedef __attribute__((ext_vector_type(16))) int i32x16;
-constexpr int kDigitBits = 30;        // |integer| <= 2^30
-constexpr int kNotFinite = 1 << 20;   // exponent of a column with an infinity or a NaN
-
-// Element of plane p of the integer v: with 128 added to each of the three lower digits they are plain bytes.
-__device__ __forceinline__ uint32_t digit_of(int v, int p) {
-    const uint32_t w = (uint32_t)v + 0x00808080u;
-    return ((w >> (8 * p)) & 0xFFu) ^ (p < 3 ? 0x80u : 0u);
-}
-__device__ __forceinline__ double scale_by(double x, int e) { return e >= kNotFinite / 2 ? __builtin_nan("") : ldexp(x, e); }
-
-// e with |x| <= 2^e for all |x| <= the float of these bits
-__device__ __forceinline__ int exponent_above(uint32_t bits) {
-    return bits >= 0x7F800000u ? kNotFinite : max((int)(bits >> 23), 1) - 126;
-}
-
-// Bits of the largest magnitude of each column of Y (of |y|, where the order of floats is that of integers); maxbits zeroed.  A
-// workgroup per 64 columns and `rows` rows.  ROWS: in workgroups of their own, a wave per row, the exponents of the rows too (of
-// their finite elements: what is not is told by the columns).  Both in one launch, us per refresh: one 2048 x 2048, r = 512
-// 633 -> 629, sixteen 4096 x 4096, r = 1024, 7480 -> 7250.
-template <bool ROWS>
-__global__ __launch_bounds__(256) void k_maxima(const float* __restrict__ Y, uint32_t* __restrict__ maxbits,
-                                                int32_t* __restrict__ rowexp, int m, int r, int rows, BatchStride st) {
-    Y += blockIdx.z * st.Y;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int across = (r + 63) / 64, blocks = across * ((m + rows - 1) / rows);
-    uint32_t mx = 0;
-    if (!ROWS || (int)blockIdx.x < blocks) {
-        const int c = (int)blockIdx.x % across * 64 + lane, i0 = (int)blockIdx.x / across * rows, i1 = min(m, i0 + rows);
-        if (c >= r) return;
-#pragma unroll 8
-        for (int i = i0 + wave; i < i1; i += 4)
-            mx = max(mx, __builtin_bit_cast(uint32_t, Y[(int64_t)i * r + c]) & 0x7FFFFFFFu);
-        atomicMax(maxbits + blockIdx.z * st.expo + c, mx);
-    } else {
-        const int i = ((int)blockIdx.x - blocks) * 4 + wave;
-        if (i >= m) return;
-#pragma unroll 8
-        for (int c = lane; c < r; c += 64) {
-            const uint32_t b = __builtin_bit_cast(uint32_t, Y[(int64_t)i * r + c]) & 0x7FFFFFFFu;
-            mx = b < 0x7F800000u ? max(mx, b) : mx;
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) mx = max(mx, (uint32_t)__shfl_xor((int)mx, off, 64));
-        if (lane == 0) rowexp[blockIdx.z * st.expo + i] = exponent_above(mx);
-    }
-}
-
-// The digits of a 32 x 32 tile of integers, x = column, k = row (or x = row, k = column) into one fragment.
-template <bool XROW>
-__device__ __forceinline__ void store_digits(const int (&tile)[32][33], uint8_t* __restrict__ frag) {
-    const int plane = threadIdx.x >> 6, lane = threadIdx.x & 63, x = lane & 31, k = 16 * (lane >> 5);
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 16; ++j) w[j >> 2] |= digit_of(XROW ? tile[x][k + j] : tile[k + j][x], plane) << (8 * (j & 3));
-    *reinterpret_cast<u32x4*>(frag + plane * 1024 + lane * 16) = u32x4{w[0], w[1], w[2], w[3]};
-}
-
-// Digits of Y, x = column, k = row (m and r multiples of 32).
-__global__ __launch_bounds__(256) void k_digits(const float* __restrict__ Y, const uint32_t* __restrict__ maxbits,
-                                                uint8_t* __restrict__ planes, int m, int r, BatchStride st) {
-    Y += blockIdx.z * st.Y;
-    maxbits += blockIdx.z * st.expo;
-    planes += blockIdx.z * st.planes;
-    __shared__ int tile[32][33];
-    const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4, c0 = blockIdx.x * 32, i0 = blockIdx.y * 32;
-    const f32x4 y = *reinterpret_cast<const f32x4*>(Y + (int64_t)(i0 + row) * r + c0 + col);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = exponent_above(maxbits[c0 + col + j]);
-        tile[row][col + j] = e == kNotFinite ? 0 : (int)rint(ldexp((double)y[j], kDigitBits - e));
-    }
-    __syncthreads();
-    store_digits<false>(tile, planes + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096);
-}
-
-// Digits of T + low (see k_apply), x = row, k = column, in units of the row.
-__global__ __launch_bounds__(256) void k_digits_t(const float* __restrict__ T, const float* __restrict__ low,
-                                                  const int32_t* __restrict__ texp, uint8_t* __restrict__ rows, int64_t rows_stride,
-                                                  int r, BatchStride st) {
-    T += blockIdx.z * st.Y;
-    low += blockIdx.z * (st.part * 2);
-    texp += blockIdx.z * st.expo;
-    rows += blockIdx.z * rows_stride;
-    __shared__ int tile[32][33];
-    const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4, c0 = blockIdx.x * 32, i0 = blockIdx.y * 32;
-    const int64_t at = (int64_t)(i0 + row) * r + c0 + col;
-    const f32x4 y = *reinterpret_cast<const f32x4*>(T + at), l = *reinterpret_cast<const f32x4*>(low + at);
-    const int e = texp[i0 + row];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool finite = (__builtin_bit_cast(uint32_t, y[j]) & 0x7FFFFFFFu) < 0x7F800000u;
-        tile[row][col + j] = finite ? (int)rint(ldexp((double)y[j] + (double)l[j], kDigitBits - e)) : 0;
-    }
-    __syncthreads();
-    store_digits<true>(tile, rows + ((int64_t)blockIdx.y * (r / 32) + blockIdx.x) * 4096);
-}
-
-// From these the digits with x = column, k = row, in units of the column.
-__global__ __launch_bounds__(256) void k_digits_turn(const uint8_t* __restrict__ rows, int64_t rows_stride,
-                                                     const int32_t* __restrict__ texp, const uint32_t* __restrict__ maxbits,
-                                                     uint8_t* __restrict__ planes, int m, int r, BatchStride st) {
-    rows += blockIdx.z * rows_stride;
-    texp += blockIdx.z * st.expo;
-    maxbits += blockIdx.z * st.expo;
-    planes += blockIdx.z * st.planes;
-    __shared__ __attribute__((aligned(16))) uint8_t frag[4 * 1024];
-    __shared__ int tile[32][33];
-    const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4;
-    reinterpret_cast<u32x4*>(frag)[t] =
-        reinterpret_cast<const u32x4*>(rows + ((int64_t)blockIdx.y * (r / 32) + blockIdx.x) * 4096)[t];
-    __syncthreads();
-    const int f = texp[blockIdx.y * 32 + row];
-    // four columns' digits are neighbours: byte c % 16 of lane row + 32 (c / 16)
-    uint32_t d[4];
-#pragma unroll
-    for (int p = 0; p < 4; ++p)
-        d[p] = *reinterpret_cast<const uint32_t*>(frag + p * 1024 + (row + 32 * (col >> 4)) * 16 + (col & 15));
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const int e = exponent_above(maxbits[blockIdx.x * 32 + col + j]);
-        int v = 0;
-#pragma unroll
-        for (int p = 3; p >= 0; --p) v = v * 256 + (int)(int8_t)(d[p] >> (8 * j));
-        tile[row][col + j] = e == kNotFinite ? 0 : (int)rint(ldexp((double)v, f - e));
-    }
-    __syncthreads();
-    store_digits<false>(tile, planes + ((int64_t)blockIdx.x * (m / 32) + blockIdx.y) * 4096);
-}
-
-// Row j of X: rowexp[j] with |X_jk| <= 2^rowexp[j] for k <= j, or kNotFinite if it meets a column of T that is not finite.  A
-// wave per row.
-__global__ __launch_bounds__(256) void k_row_exponents(const double* __restrict__ X, const uint32_t* __restrict__ maxbits,
-                                                       int32_t* __restrict__ rowexp, int r, BatchStride st) {
-    X += blockIdx.z * st.X;
-    maxbits += blockIdx.z * st.expo;
-    rowexp += blockIdx.z * st.expo;
-    const int j = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (j >= r) return;
-    int e = -(1 << 19);
-    for (int k = lane; k <= j; k += 64) {
-        const double x = scale_by(X[(int64_t)j * r + k], maxbits[k] >= 0x7F800000u ? kNotFinite : 0);
-        const int hi = (int)(__builtin_bit_cast(uint64_t, x) >> 52) & 0x7FF;   // 0: zero (or below every number of interest)
-        if (hi == 0x7FF) e = kNotFinite;
-        else if (hi != 0) e = max(e, hi - 1022);
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off, 64));
-    if (lane == 0) rowexp[j] = e;
-}
-
-// Digits of X, x = row, for the fragments in the diagonal blocks of X and left of them: a fifth one below the other four
-// (plane 4), since a result adds up the roundings of a whole row of X.
-__global__ __launch_bounds__(256) void k_digits_x(const double* __restrict__ X, const int32_t* __restrict__ rowexp,
-                                                  uint8_t* __restrict__ planes, int r, BatchStride st) {
-    if ((int)blockIdx.x * 32 / kNB > (int)blockIdx.y * 32 / kNB) return;
-    X += blockIdx.z * st.X;
-    rowexp += blockIdx.z * st.expo;
-    planes += blockIdx.z * (st.part * 8);
-    __shared__ int8_t last[32][33];
-    __shared__ int tile[32][33];
-    const int t = threadIdx.x, row = t >> 3, col = (t & 7) * 4, k0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
-    const int f = rowexp[j0 + row];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const int64_t v =
-            f != kNotFinite ? (int64_t)rint(ldexp(X[(int64_t)(j0 + row) * r + k0 + col + q], kDigitBits + 8 - f)) : 0;
-        const int lowest = (int)(int8_t)v;
-        tile[row][col + q] = (int)((v - lowest) >> 8);
-        last[row][col + q] = (int8_t)lowest;
-    }
-    __syncthreads();
-    const int plane = t >> 6, lane = t & 63, k = 16 * (lane >> 5);
-    const int64_t frag = (int64_t)blockIdx.y * (r / 32) + blockIdx.x;
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int j = 0; j < 16; ++j) w[j >> 2] |= digit_of(tile[lane & 31][k + j], plane) << (8 * (j & 3));
-    *reinterpret_cast<u32x4*>(planes + (frag * 5 + plane) * 1024 + lane * 16) = u32x4{w[0], w[1], w[2], w[3]};
-    if (plane == 0) {
-        uint32_t z[4] = {0u, 0u, 0u, 0u};
-#pragma unroll
-        for (int j = 0; j < 16; ++j) z[j >> 2] |= (uint32_t)(uint8_t)last[lane & 31][k + j] << (8 * (j & 3));
-        *reinterpret_cast<u32x4*>(planes + (frag * 5 + 4) * 1024 + lane * 16) = u32x4{z[0], z[1], z[2], z[3]};
-    }
-}
-
-// Product of two digit matrices, k fragments [kb0, kb1): a wave 32 x 64 results, a workgroup 64 x 128.  The fragments of a step
-// go straight into LDS, one wave-wide load each, NS steps in flight and two workgroups on a CU: read from memory by every wave
-// that needs them, with one wave per SIMD, the Gram matrices of sixteen 4096 x 1024 took 888 us, so 451 (fp64: 1760).  f(row,
-// column, value in units of both scales) for i < 32 xa, j < 32 xb.  KB: k fragments per x fragment; BP: planes of B, the fifth
-// one a place below the others; wave_kb1: where the wave's own columns end.
-template <int BP, typename F>
-__device__ __forceinline__ void digit_product(const uint8_t* __restrict__ A, const uint8_t* __restrict__ B, int KB, int kb0,
-                                              int kb1, int wave_kb1, int ti, int tj, int xa, int xb, uint8_t* smem, F f) {
-    constexpr int NS = digit_stages(BP), FRAGS = 8 + 4 * BP, PER = FRAGS / 4;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wi = wave >> 1, wj = wave & 1;
-    uint32_t at[PER];        // of this wave's fragments at k fragment 0, and what one more adds
-    bool in_a[PER];
-#pragma unroll
-    for (int p = 0; p < PER; ++p) {
-        const int g = wave * PER + p;
-        in_a[p] = g < 8;
-        at[p] = in_a[p] ? (uint32_t)min(2 * ti + g / 4, xa - 1) * (uint32_t)(KB * 4096) + g % 4 * 1024
-                        : (uint32_t)min(4 * tj + (g - 8) / BP, xb - 1) * (uint32_t)(KB * BP * 1024) + (g - 8) % BP * 1024;
-    }
-    const __amdgpu_buffer_rsrc_t ra = make_rsrc(A), rb = make_rsrc(B);
-    auto load = [&](int kb, int stage) {
-        const uint32_t k = (uint32_t)min(kb, kb1 - 1);   // (past the end: the last one again, never read)
-#pragma unroll
-        for (int p = 0; p < PER; ++p)
-            buffer_load_lds16(in_a[p] ? ra : rb, smem + (stage * FRAGS + wave * PER + p) * 1024, lane * 16,
-                              at[p] + k * (in_a[p] ? 4096u : BP * 1024u));
-    };
-    i32x16 acc[6][2];   // by the sum of the digits' places, less one
-#pragma unroll
-    for (int l = 0; l < 6; ++l)
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[l][n][v] = 0;
-    auto multiply = [&](int stage) {
-        const uint8_t* frags = smem + stage * FRAGS * 1024 + lane * 16;
-        i32x4 a[4];
-#pragma unroll
-        for (int p = 0; p < 4; ++p) a[p] = *reinterpret_cast<const i32x4*>(frags + (4 * wi + p) * 1024);
-#pragma unroll
-        for (int n = 0; n < 2; ++n)
-#pragma unroll
-            for (int q = 0; q < BP; ++q) {
-                const i32x4 b = *reinterpret_cast<const i32x4*>(frags + (8 + (2 * wj + n) * BP + q) * 1024);
-#pragma unroll
-                for (int p = 0; p < 4; ++p) {
-                    const int place = p + (q < 4 ? q : -1);
-                    if (place > 0)
-                        acc[place - 1][n] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[p], b, acc[place - 1][n], 0, 0, 0);
-                }
-            }
-    };
-#pragma unroll
-    for (int u = 0; u < NS - 1; ++u) load(kb0 + u, u);
-    int stage = 0;
-    for (int kb = kb0; kb < kb1; ++kb) {
-        wait_loads<(NS - 2) * PER>();
-        lds_barrier();
-        load(kb + NS - 1, stage == 0 ? NS - 1 : stage - 1);
-        if (kb < wave_kb1) multiply(stage);
-        stage = stage + 1 == NS ? 0 : stage + 1;
-    }
-    wait_loads<0>();
-    const int ia = 2 * ti + wi, jb = 4 * tj + 2 * wj;
-    if (ia >= xa) return;
-#pragma unroll
-    for (int n = 0; n < 2; ++n) {
-        if (jb + n >= xb) break;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            double x = 0.0;
-#pragma unroll
-            for (int l = 5; l >= 0; --l) x = fma(x, 256.0, (double)acc[l][n][v]);
-            f(ia * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3), (jb + n) * 32 + (lane & 31), 256.0 * x);
-        }
-    }
-}
-
-// Slice blockIdx.y of S = Y^T Y, lower triangle of 64 x 128 tiles and what they cover above it.
-__global__ __launch_bounds__(256, 2) void k_digit_gram(const uint8_t* __restrict__ planes, const uint32_t* __restrict__ maxbits,
-                                                    double* __restrict__ part, int m, int r, int slice_rows, BatchStride st) {
-    planes += blockIdx.z * st.planes;
-    maxbits += blockIdx.z * st.expo;
-    int ti = 0, first = 0;   // row tile ti has ti / 2 + 1 tiles
-    while ((int)blockIdx.x >= first + ti / 2 + 1) first += ti++ / 2 + 1;
-    const int tj = blockIdx.x - first, xf = r / 32;
-    double* S = part + blockIdx.z * st.part + (int64_t)blockIdx.y * r * r;
-    const int kb0 = blockIdx.y * (slice_rows / 32), kb1 = min(m, (int)(blockIdx.y + 1) * slice_rows) / 32;
-    __shared__ __attribute__((aligned(16))) uint8_t smem[digit_smem(4)];
-    digit_product<4>(planes, planes, m / 32, kb0, kb1, kb1, ti, tj, xf, xf, smem, [&](int i, int j, double x) {
-        const int ei = exponent_above(maxbits[i]), ej = exponent_above(maxbits[j]);
-        S[(int64_t)i * r + j] = scale_by(x, ei == kNotFinite || ej == kNotFinite ? kNotFinite : ei + ej - 2 * kDigitBits);
-    });
-}
-
-// Q = T X^T from the digits of the rows of both.
-__global__ __launch_bounds__(256, 2) void k_digit_apply(const uint8_t* __restrict__ tp, int64_t tp_stride,
-                                                        const int32_t* __restrict__ texp, const uint8_t* __restrict__ xp,
-                                                        const int32_t* __restrict__ rowexp, float* __restrict__ Q, int m, int r,
-                                                        BatchStride st) {
-    tp += blockIdx.z * tp_stride;
-    texp += blockIdx.z * st.expo;
-    xp += blockIdx.z * (st.part * 8);
-    rowexp += blockIdx.z * st.expo;
-    Q += blockIdx.z * st.Q;
-    __shared__ __attribute__((aligned(16))) uint8_t smem[digit_smem(5)];
-    // X is zero above its diagonal blocks: a wave's 64 columns end with one
-    const int wj = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) & 1, block = (int)blockIdx.y * 2;
-    digit_product<5>(tp, xp, r / 32, 0, min(r, (block + 2) * kNB) / 32, min(r, (block + wj + 1) * kNB) / 32, blockIdx.x, blockIdx.y,
-                     m / 32, r / 32, smem, [&](int i, int j, double x) {
-        const int f = rowexp[j];
-        Q[(int64_t)i * r + j] = (float)scale_by(x, f == kNotFinite ? kNotFinite : f + texp[i] - 2 * kDigitBits);
+        if (gi < m && gj < r) Q[(int64_t)gi * r + gj] = (float)x;
     });
 }
 
@@ -990,21 +659,10 @@ static int gram_slices(int64_t m, int64_t r, int* slice_rows) {
     return (int)((m + *slice_rows - 1) / *slice_rows);
 }
 
-// Whether a shape's products run on INT8 digits (a function of the shape only, as the number of slices).  us per refresh,
-// fp64 / digits: 768 x 256 309 / 334, four of 1024 x 256 356 / 373, sixteen 547 / 517, one 2048 x 512 631 / 629, sixteen 1901 /
-// 1605, one 4096 x 512 781 / 720, one 8192 x 256 544 / 517, one 4096 x 1024 1640 / 1374, sixteen 10190 / 7250.
-static bool digits(int64_t m, int64_t r) {
-    int slice_rows;
-    gram_slices(m, r, &slice_rows);
-    // (sums of four products of digits over 2^15 indices fit in 32 bits)
-    return m % 32 == 0 && r % 32 == 0 && slice_rows % 32 == 0 && slice_rows <= (1 << 14) && r <= (1 << 14) &&
-           m * r * r >= (int64_t(1) << 29);
-}
-
 // Workspace of the orthonormalisation of `batch` matrices of one shape: per matrix S and X (r x r fp64), the
-// inverted diagonal blocks, the result of the first round T (fp32 m x r) and the Gram slices (or, if more, what T lost to fp32).
+// inverted diagonal blocks, the result of the first round T (fp32 m x r) and the Gram slices.
 struct OrthLayout {
-    size_t S, X, Dinv, T, part, shift, expo, total;
+    size_t S, X, Dinv, T, part, shift, total;
     BatchStride st;   // element strides between consecutive matrices; st.Y = st.Q = stride of T
 };
 static OrthLayout orth_layout(int64_t m, int64_t r, int64_t batch) {
@@ -1012,8 +670,7 @@ static OrthLayout orth_layout(int64_t m, int64_t r, int64_t batch) {
     int slice_rows;
     const int slices = gram_slices(m, r, &slice_rows);
     const size_t bS = align256((size_t)r * r * 8), bD = align256((size_t)nt * kNB * kNB * 8),
-                 bT = align256((size_t)m * r * 4),
-                 bP = align256(std::max((size_t)slices * r * r * 8, digits(m, r) ? (size_t)m * r * 4 : 0));
+                 bT = align256((size_t)m * r * 4), bP = align256((size_t)slices * r * r * 8);
     OrthLayout L;
     L.S = 0;
     L.X = L.S + bS * batch;
@@ -1021,11 +678,9 @@ static OrthLayout orth_layout(int64_t m, int64_t r, int64_t batch) {
     L.T = L.Dinv + bD * batch;
     L.part = L.T + bT * batch;
     L.shift = L.part + bP * batch;
-    L.expo = L.shift + 256 * (size_t)batch;      // one double per matrix, 256 bytes apart
-    const size_t bE = digits(m, r) ? align256((size_t)(2 * r + m) * 4) : 0;   // columns of Y, rows of X, rows of T
-    L.total = L.expo + bE * batch;
+    L.total = L.shift + 256 * (size_t)batch;     // one double per matrix, 256 bytes apart
     L.st = BatchStride{(int64_t)(bT / 4), (int64_t)(bT / 4), (int64_t)(bS / 8), (int64_t)(bS / 8), (int64_t)(bD / 8),
-                       (int64_t)(bP / 8), 256 / 8, (int64_t)(bE / 4), 0};
+                       (int64_t)(bP / 8), 256 / 8};
     return L;
 }
 
@@ -1075,12 +730,8 @@ static int launch_range(const uint16_t* G, const uint16_t* Z, float* Y, int64_t 
 
 // One round on `batch` matrices (matrix b at Y + b * sYin, result at Q + b * sQout): Q = Y L^-T with L the Cholesky
 // factor of Y^T Y.
-// planes: m * r * 4 bytes at a stride of plane_stride for the digits of Y, or null: Q's own, which the digits leave before the
-// result is written.  rows: in the second round as much at a stride of L.st.Y floats for the digits of its rows, else null.
-// With rows, Y may be Q, since it is read before its planes are written.
 static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout, int64_t m, int64_t r, int batch,
-                          int32_t* info, double flag_factor, char* ws, const OrthLayout& L, uint8_t* planes,
-                          int64_t plane_stride, uint8_t* rows, hipStream_t stream) {
+                          int32_t* info, double flag_factor, char* ws, const OrthLayout& L, hipStream_t stream) {
     double* S = reinterpret_cast<double*>(ws + L.S);
     double* X = reinterpret_cast<double*>(ws + L.X);
     double* Dinv = reinterpret_cast<double*>(ws + L.Dinv);
@@ -1089,63 +740,35 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     BatchStride st = L.st;
     st.Y = sYin;
     st.Q = sQout;
-    st.planes = plane_stride;
-    uint32_t* maxbits = reinterpret_cast<uint32_t*>(ws + L.expo);
-    int32_t* rowexp = reinterpret_cast<int32_t*>(maxbits) + r;
-    int32_t* texp = rowexp + r;
-    const int64_t rows_stride = L.st.Y * 4;
     const int nt = (int)((r + kNB - 1) / kNB);
     const int pairs = nt * (nt + 1) / 2;
     int slice_rows;
     const int slices = gram_slices(m, r, &slice_rows);
     const dim3 blk(256);
     const unsigned B = (unsigned)batch;
-    // what T lost to fp32 lies where the Gram slices do: written after round one has added them, read before round two writes them
-    float* low = planes && !rows ? reinterpret_cast<float*>(part) : nullptr;
     auto blocks = [](int64_t n, int size) { return (unsigned)((n + size - 1) / size); };
     const unsigned nt32 = blocks(r, 32);
     // 32 x 32 blocks while 64 x 64 ones are about a workgroup per CU or fewer (us per refresh, always 64 / this line / up to
     // 1000 / 9000 workgroups: 2048 x 2048, r = 512 705 / 652 / 653 / 651, 3000 x 700, r = 128, eight of them 552 / 507 / 515 /
     // 517, 2048 x 2048, r = 512, sixteen 1982 / 1956 / 1984 / 2274)
     constexpr int64_t kFewBlocks = 300;
-    if (planes) {
-        constexpr int kMaxRows = 512;
-        const unsigned by_column = blocks(r, 64) * blocks(m, kMaxRows);
-        hipLaunchKernelGGL(k_set_i32, dim3(blocks(st.expo * batch, 256)), blk, 0, stream, rowexp - r, 0, (int)(st.expo * batch));
-        if (rows) {
-            hipLaunchKernelGGL(k_maxima<true>, dim3(by_column + blocks(m, 4), 1, B), blk, 0, stream, Y, maxbits, texp, (int)m,
-                               (int)r, kMaxRows, st);
-            hipLaunchKernelGGL(k_digits_t, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, reinterpret_cast<const float*>(part),
-                               texp, rows, rows_stride, (int)r, st);
-            hipLaunchKernelGGL(k_digits_turn, dim3(nt32, blocks(m, 32), B), blk, 0, stream, rows, rows_stride, texp, maxbits,
-                               planes, (int)m, (int)r, st);
-        } else {
-            hipLaunchKernelGGL(k_maxima<false>, dim3(by_column, 1, B), blk, 0, stream, Y, maxbits, nullptr, (int)m, (int)r,
-                               kMaxRows, st);
-            hipLaunchKernelGGL(k_digits, dim3(nt32, blocks(m, 32), B), blk, 0, stream, Y, maxbits, planes, (int)m, (int)r, st);
-        }
-        int tiles = 0;
-        for (int ti = 0; ti < nt; ++ti) tiles += ti / 2 + 1;
-        hipLaunchKernelGGL(k_digit_gram, dim3(tiles, slices, B), blk, 0, stream, planes, maxbits, part, (int)m, (int)r,
-                           slice_rows, st);
-    } else if ((int64_t)pairs * slices * batch < kFewBlocks)
-        hipLaunchKernelGGL(k_gram<32>, dim3(nt32 * (nt32 + 1) / 2, slices, B), blk, 0, stream, Y, part, (int)m, (int)r,
-                           slice_rows, st);
+    if ((int64_t)pairs * slices * batch < kFewBlocks)
+        hipLaunchKernelGGL(k_gram<32>, dim3(nt32 * (nt32 + 1) / 2, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     else
         hipLaunchKernelGGL(k_gram<kNB>, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
-    // One launch per block column up to 1024 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.38 /
-    // 1.82, 32 of them 14.0 / 14.2, 48 21.2 / 21.7, 128 54.6 / 54.3; 2048 x 2048, r = 512: 32 2.75 / 2.89, 128 10.4 / 10.5; 1024 x
-    // 1024: r = 256, 256 matrices 5.06 / 5.07, r = 128, 512 of them 5.34 / 5.32).  The arithmetic is the same, and with it every
-    // bit.
+    // One launch per block column up to 1024 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.64 /
+    // 2.09, 32 of them 19.6 / 20.0, 48 28.8 / 29.2, 64 38.1 / 38.3, 128 75.03 / 74.99; 2048 x 2048, r = 512: 32 3.45 / 3.59, 128
+    // 12.3 / 12.4; 1024 x 1024: r = 256, 256 matrices 5.07 / 5.09, r = 128, 512 of them 5.33 / 5.34).  The arithmetic is the
+    // same, and with it every bit.
     const bool fused = batch * nt <= 1024;
     hipLaunchKernelGGL(k_chol_diag<true>, dim3(1, 1, B), blk, 0, stream, S, (int)r, 0, Dinv, X, info, shift, flag_factor, st);
     for (int kb = 0; kb + 1 < nt; ++kb) {
         const int below = nt - kb - 1, left = below * (below + 1) / 2;
         hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
         if (fused) {
-            hipLaunchKernelGGL(k_chol_update<true>, dim3(left + kStrips * kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X,
-                               info, shift, flag_factor, st);
+            hipLaunchKernelGGL(k_chol_update<true>, dim3(left + kStrips * kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info,
+                               shift, flag_factor, st);
         } else {
             hipLaunchKernelGGL(k_chol_update<false>, dim3(left, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
                                flag_factor, st);
@@ -1155,16 +778,10 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     }
     for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
         if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(kStrips * ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
-    if (rows) {
-        uint8_t* xp = reinterpret_cast<uint8_t*>(part);
-        hipLaunchKernelGGL(k_row_exponents, dim3(blocks(r, 4), 1, B), blk, 0, stream, X, maxbits, rowexp, (int)r, st);
-        hipLaunchKernelGGL(k_digits_x, dim3(nt32, nt32, B), blk, 0, stream, X, rowexp, xp, (int)r, st);
-        hipLaunchKernelGGL(k_digit_apply, dim3(blocks(m, 64), blocks(r, 128), B), blk, 0, stream, rows, rows_stride, texp, xp,
-                           rowexp, Q, (int)m, (int)r, st);
-    } else if ((int64_t)blocks(m, kNB) * nt * batch < kFewBlocks)
-        hipLaunchKernelGGL(k_apply<32>, dim3(blocks(m, 32), nt32, B), blk, 0, stream, Y, X, Q, low, (int)m, (int)r, st);
+    if ((int64_t)blocks(m, kNB) * nt * batch < kFewBlocks)
+        hipLaunchKernelGGL(k_apply<32>, dim3(blocks(m, 32), nt32, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
     else
-        hipLaunchKernelGGL(k_apply<kNB>, dim3(blocks(m, kNB), nt, B), blk, 0, stream, Y, X, Q, low, (int)m, (int)r, st);
+        hipLaunchKernelGGL(k_apply<kNB>, dim3(blocks(m, kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
 }
 
 // Cholesky QR twice: Y -> T -> Q.  info: `batch` consecutive device ints.
@@ -1174,14 +791,8 @@ static int launch_orth(const float* Y, int64_t sY, float* Q, int64_t sQ, int64_t
     float* T = reinterpret_cast<float*>(ws + L.T);
     if (reset_info)
         hipLaunchKernelGGL(k_set_i32, dim3((batch + 255) / 256), dim3(256), 0, stream, info, 0, batch);
-    if (digits(m, r)) {   // T and the digits of Y's and T's columns lie where Q will be, those of T's rows where T is otherwise
-        uint8_t* planes = reinterpret_cast<uint8_t*>(Q);
-        launch_cholqr(Y, sY, Q, sQ, m, r, batch, info, 0.0, ws, L, planes, sQ * 4, nullptr, stream);
-        launch_cholqr(Q, sQ, Q, sQ, m, r, batch, info, 16.0, ws, L, planes, sQ * 4, reinterpret_cast<uint8_t*>(T), stream);
-    } else {
-        launch_cholqr(Y, sY, T, L.st.Y, m, r, batch, info, 0.0, ws, L, nullptr, 0, nullptr, stream);
-        launch_cholqr(T, L.st.Y, Q, sQ, m, r, batch, info, 16.0, ws, L, nullptr, 0, nullptr, stream);
-    }
+    launch_cholqr(Y, sY, T, L.st.Y, m, r, batch, info, 0.0, ws, L, stream);
+    launch_cholqr(T, L.st.Y, Q, sQ, m, r, batch, info, 16.0, ws, L, stream);
     return check_launch();
 }
 

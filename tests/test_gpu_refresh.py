@@ -96,20 +96,28 @@ def test_orthonormalize_around_the_block_sizes(r):
 
 
 @pytest.mark.parametrize("m,r", [(2048, 512), (1824, 544), (5952, 320)])
-@pytest.mark.parametrize("kind", ["random", "graded", "decaying", "spiky"])
+@pytest.mark.parametrize("kind", ["random", "graded", "decaying", "spiky", "spiky decaying", "outlier gradient"])
 def test_orthonormalize_of_large_matrices(m, r, kind):
-    """Shapes whose products run on INT8 digits (m r^2 >= 2^29; 32 but not 64 or 128 dividing r): within fp32 rounding (2^-25 of
-    an element, 3e-8 relative) of the Gram-Schmidt factor in 64 bits, as the fp64 products of smaller ones."""
+    """Shapes of several Gram slices and block columns (32 but not 64 or 128 dividing r): within fp32 rounding (2^-25 of an
+    element, 3e-8 relative) of the Gram-Schmidt factor in 64 bits.  The last two kinds set the largest magnitudes of their columns
+    by one row and have cond(Y) around 1e6 to 1e7: what a Gram matrix loses relative to those magnitudes shows in info."""
     g = np.random.default_rng([m, r])
     Y = g.standard_normal((m, r))
     if kind == "graded":
         Y *= np.logspace(3, -3, r)[None, :]
-    if kind == "decaying":
+    if kind.endswith("decaying"):
         U, _ = np.linalg.qr(Y)
         V, _ = np.linalg.qr(g.standard_normal((r, r)))
         Y = (U * np.logspace(0, -6, r)[None, :]) @ V
     if kind == "spiky":
         Y[::97] *= 1000.0
+    if kind == "spiky decaying":
+        Y[7] *= 1000.0
+    if kind == "outlier gradient":          # Y = G (P^T G)^T of a low-rank gradient with noise
+        G = g.standard_normal((m, 24)) @ g.standard_normal((24, 2 * r)) + 3.0 * g.standard_normal((m, 2 * r))
+        G[7] *= 1000.0
+        P, _ = np.linalg.qr(Y)
+        Y = G @ (P.T @ G).T
     Y = Y.astype(np.float32)
     want = Q.orthonormalize(Y)
     Qd, info = qg.orthonormalize(dev(Y))
@@ -137,6 +145,27 @@ def test_small_rows_of_a_large_matrix_keep_their_digits(m, r):
     rows = np.linalg.solve(T.T, Y[small].astype(np.float64).T).T
     err = np.linalg.norm(got[small] - rows, axis=1) / np.linalg.norm(rows, axis=1)
     assert err.max() <= 2e-7
+
+
+@pytest.mark.parametrize("s", [1e-2, 1e-5, 1e-7, 1e-9])
+def test_small_blocks_of_a_row_keep_their_digits(s):
+    """Q is quantized in blocks of 256 elements, which at r = 512 are half rows: a block s times the other half of its row is as
+    exact in itself.  Rounded to fp32 are T and Q, each by 2^-24 of an element at most, together 2^-23; the sums in 64 bits and
+    the reference add next to nothing: 2^-22.5."""
+    m, r = 2048, 512
+    Y = np.random.default_rng([m, r, 7]).standard_normal((m, r))
+    Y[:m // 2, :r // 2] *= s
+    Y[m // 2:, r // 2:] *= s
+    Y = Y.astype(np.float32)
+    want = Q.orthonormalize(Y)
+    T = np.triu(want.T @ Y.astype(np.float64))    # (what is below the diagonal, rounding, would mix columns: 1e-16 over s)
+    want = np.linalg.solve(T.T, Y.astype(np.float64).T).T                  # rows exact in themselves,
+    want = np.linalg.solve(np.linalg.cholesky(want.T @ want), want.T).T    # and, with T's errors taken out, their blocks
+    Qd, info = qg.orthonormalize(dev(Y))
+    assert int(host(info)[0]) == 0
+    got = host(Qd).astype(np.float64)
+    err = np.linalg.norm((got - want).reshape(-1, 256), axis=1) / np.linalg.norm(want.reshape(-1, 256), axis=1)
+    assert err.max() <= 2.0 ** -22.5
 
 
 def test_a_nan_column_of_a_large_matrix_is_reported():
