@@ -165,14 +165,21 @@ __device__ __forceinline__ u32x4 shift_right_128(u32x4 v, int bits) {
 // The unaligned kernels load without checks: the K steps that lie inside the matrices run in a pipeline of their own (the last,
 // partial one after it, checked), and a tile at the edge of the columns loads the last whole chunk of a row and shifts it when
 // it is stored (EDGE).  Addresses are a scalar base and a 32-bit byte offset per chunk that is fixed for the whole loop (as
-// running 64-bit pointers they took the registers of four tiles in flight and spilled), which covers row pitches up to 2^24;
-// beyond it, and for less than a chunk of columns (of G, N, or of P), every step is a checked one.
-__device__ __forceinline__ bool pipelined(int n, int ld) { return n >= 8 && ld <= (1 << 24); }
+// running 64-bit pointers they took the registers of four tiles in flight and spilled).  Beyond row pitches of 2^24, where a
+// matrix has eight steps at most and memory sets the time, every step is a checked one (projection with Adam / back-projection,
+// ms: 120 x 33554437, r = 8, checked 2.9 / 4.8, in a pipeline with offsets up to 2^26 3.1 / 4.9; 60 x 67108860 4.0 / 9.2 and 4.5 /
+// 9.3; with every access checked in two or four stages 3.3 / 5.4 and 5.0 / 10.5).
+
+// Rows of an array of n columns whose chunks (see edge_column) lie inside it: all of them, or, with less than a chunk of columns,
+// those whose chunk ends in a later row (4096 x 5, r = 256, us: every step checked 174 / 28, so 58 / 17).
+__device__ __forceinline__ int chunk_rows(int rows, int n, int ld) { return n >= 8 ? rows : rows - (8 - n + ld - 1) / ld; }
+// Steps of the pipeline, of `rows` rows (see above).
+__device__ __forceinline__ int whole_steps(int rows, int bk, int ld) { return ld <= (1 << 24) ? rows / bk : 0; }
 
 // Chunk of eight columns from col on: first column loaded, and the shift in bits; columns at or past n give anything, for
-// results that are never stored.  n >= 8.
+// results that are never stored.
 __device__ __forceinline__ int edge_column(int col, int n, int& shift) {
-    const int c = min(col, n - 8);
+    const int c = min(col, max(n - 8, 0));
     shift = 16 * min(col - c, 7);
     return c;
 }
@@ -438,8 +445,9 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
         const int ti = t + p * NT;
         int c = r0 + (ti % A_TPR) * (8 * WPT);
         if constexpr (!DIRECT) {
-            a_next[p] = c > r - 8 * WPT;
-            c = min(c, r - 8 * WPT);       // (r < 8 * WPT: not used, every step is checked)
+            const int last = max(r - 8 * WPT, 0);
+            a_next[p] = c > last;
+            c = min(c, last);
         }
         a_el[p] = (uint32_t)((ti / A_TPR) * r + c);
     }
@@ -449,16 +457,16 @@ __device__ __forceinline__ void project_tile(const uint8_t* __restrict__ Pq, con
             b_off[p] = BD::lane_src_bytes(lane, ld, p);
         } else {
             const int ci = t + p * NT;
-            b_off[p] = 2u * element_offset(ci / BD::CPR, ld, edge_column(n0 + (ci % BD::CPR) * 8, max(n, 8), b_shift[p]));
+            b_off[p] = 2u * element_offset(ci / BD::CPR, ld, edge_column(n0 + (ci % BD::CPR) * 8, n, b_shift[p]));
         }
     }
 
     // Tile kt: P codes and scales into register set `stage`; G straight into LDS stage `stage` (kExact, kMasked) or into
     // registers (kUnaligned, stored by sstore).  A tile past the end (kt >= KT) loads nothing: its resources are empty (or,
     // kUnaligned, the last tile again).
-    // kUnaligned: steps of the pipeline (a matrix of fewer columns of P than a fetch has codes, in a grouped launch whose tiles
-    // suit a larger r, has none)
-    const int KT_WHOLE = pipelined(n, ld) && r >= 8 * WPT ? m / BK : 0;
+    // kUnaligned: steps of the pipeline.  (r < 8 * WPT, in a grouped launch whose tiles suit a larger r: the second word of a
+    // fetch is the next row's, for rows of R that are never stored.)
+    const int KT_WHOLE = whole_steps(min(chunk_rows(m, n, ld), r < 8 * WPT ? m - 1 : m), BK, ld);
     auto gload = [&](int kt, int stage) {
         const int i0 = kt * BK;
         const int64_t e0 = (int64_t)i0 * r;
@@ -989,14 +997,14 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                                            // the tile's rows (kUnaligned: rows past the last one are the last one again)
     int a_shift[DIRECT ? 1 : A_PER];       // kUnaligned, at the edge: see edge_column
     const bool edge = !DIRECT && n0 + BNn > n;
-    const int KT_WHOLE = pipelined(n, ld) ? r / BK : 0;   // kUnaligned: steps of the pipeline, as in the projection
+    const int KT_WHOLE = whole_steps(chunk_rows(r, n, ld), BK, ld);   // kUnaligned: steps of the pipeline, as in the projection
 #pragma unroll
     for (int p = 0; p < A_OFFS; ++p) {
         if constexpr (DIRECT) {
             a_off[p] = AD::lane_src_bytes(lane, ld, p);
         } else {
             const int ci = t + p * NT;
-            a_off[p] = 2u * element_offset(ci / AD::CPR, ld, edge_column(n0 + (ci % AD::CPR) * 8, max(n, 8), a_shift[p]));
+            a_off[p] = 2u * element_offset(ci / AD::CPR, ld, edge_column(n0 + (ci % AD::CPR) * 8, n, a_shift[p]));
         }
     }
 #pragma unroll

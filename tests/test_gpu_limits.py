@@ -126,10 +126,12 @@ def check_wide_step(m, n, r):
         assert np.allclose(host(Ws[:, g:g + 1].contiguous()), o["Ws"], rtol=1e-5, atol=0), g
 
 
-@pytest.mark.parametrize("m,n,r", [(8, 153391691, 8), (8, 300000001, 8), (16, 143200001, 16), (8, 536870911, 8)])
+@pytest.mark.parametrize("m,n,r", [(8, 153391691, 8), (8, 300000001, 8), (16, 143200001, 16), (8, 536870911, 8),
+                                   (70, 16777221, 40), (70, 16777211, 40)])
 def test_rows_far_apart(m, n, r):
     """Rows so long that the byte offset between the first and the last row of an epilogue run of M, V, R (4 * 7 * n >=
-    2^32), or of a tile of G or N (2 * 15 * n >= 2^32), no longer fits 32 bits; the last case is the widest matrix of all."""
+    2^32), or of a tile of G or N (2 * 15 * n >= 2^32), no longer fits 32 bits; the fourth case is the widest matrix of all.
+    The last two: whole K steps on both sides of 2^24, up to which they run unchecked."""
     check_wide_step(m, n, r)
 
 

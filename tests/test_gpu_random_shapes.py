@@ -104,6 +104,7 @@ def test_random_shapes_grouped_and_single(sweep):
     (137, 264, 136), (208, 512, 200),                                 # aligned rows, r a multiple of 8 only: P's edge alone
     (400, 21765, 136),                                                # 128-row tiles of both products
     (130, 200, 64), (257, 1000, 96),                                  # aligned rows that share cache lines
+    (321, 1, 8), (97, 7, 64), (64, 3, 16), (130, 2, 72), (96, 4, 96), (71, 6, 40),   # chunks that end in a later row
 ])
 def test_edges_of_unaligned_tiles(m, n, r):
     t, seed = 3, 77
