@@ -538,12 +538,80 @@ __device__ __forceinline__ void trinv_strip(const double* __restrict__ S, double
     }
 }
 
+// The whole block by one workgroup, a quarter of the staging per MFMA, for launches that fill the chip (see launch_trinv_row).  The order
+// of every sum is the strips': per 64 deep, even and odd quadruples of the contraction index apart.
+// At: kNB * kPitchKF, Bt: kNB * kPitchT doubles of LDS.
+constexpr int kPitchT = kNB + 2;      // LDS pitch of a 64 x 64 intermediate
+
+__device__ __forceinline__ void trinv_block(const double* __restrict__ S, double* __restrict__ X,
+                                            const double* __restrict__ Dinv, int r, int ib, int kb, double* At, double* Bt) {
+    constexpr int PITCH = F64Tile<kNB>::PITCH_KS;
+    static_assert(kNB * kPitchT >= kKC * PITCH, "the intermediate reuses the X chunk's buffer");
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
+    f64x4 sum[2][2], acc[2][2][2];
+    zero_acc(sum);
+    zero_acc(acc[0]);
+    zero_acc(acc[1]);
+    auto product = [&](const double* B, int pitch) {
+#pragma unroll
+        for (int k0 = 0; k0 < kKC; k0 += 4)
+            mma_chunk<4>(At + k0, kPitchKF, 1, B + k0 * pitch, 1, pitch, acc[(k0 / 4) & 1], lane, wi, wj);
+    };
+    BlockStage<kNB, kKC, kPitchKF, double> sa;
+    BlockStage<kKC, kNB, PITCH, double> sb;
+    const double* D = Dinv + (int64_t)ib * kNB * kNB;
+    const int k_end = ib * kNB;
+    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
+    sb.fetch(X, r, kb * kNB, kb * kNB, r, r);
+    for (int kc = kb * kNB; kc < k_end; kc += kKC) {
+        sa.commit(At);
+        sb.commit(Bt);
+        __syncthreads();
+        if (kc + kKC < k_end) {
+            sa.fetch(S, r, ib * kNB, kc + kKC, r, r);
+            sb.fetch(X, r, kc + kKC, kb * kNB, r, r);
+        } else {
+            sa.fetch(D, kNB, 0, 0, kNB, kNB);     // first chunk of the second product
+        }
+        product(Bt, PITCH);
+        if ((kc + kKC) % kNB == 0) {
+#pragma unroll
+            for (int a = 0; a < 2; ++a)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) sum[a][b] += acc[0][a][b] + acc[1][a][b];
+            zero_acc(acc[0]);
+            zero_acc(acc[1]);
+        }
+        __syncthreads();
+    }
+    double* Tm = Bt;
+    for_each_acc(sum, lane, wi, wj, [&](int row, int col, double x) { Tm[row * kPitchT + col] = x; });
+    for (int kc = 0; kc < kNB; kc += kKC) {
+        sa.commit(At);
+        __syncthreads();       // also publishes Tm on the first pass
+        if (kc + kKC < kNB) sa.fetch(D, kNB, 0, kc + kKC, kNB, kNB);
+        product(Tm + kc * kPitchT, kPitchT);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) sum[a][b] = acc[0][a][b] + acc[1][a][b];
+    for_each_acc(sum, lane, wi, wj, [&](int row, int col, double x) {
+        const int gi = ib * kNB + row, gj = kb * kNB + col;
+        if (gi < r && gj < r) X[(int64_t)gi * r + gj] = -x;
+    });
+}
+
+template <bool BLOCKS>
 __global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S, double* __restrict__ X,
                                                    const double* __restrict__ Dinv, int r, int ib, BatchStride st) {
-    __shared__ double At[kNB * kPitchD];
-    __shared__ double Bt[kNB * kPitchX];
-    trinv_strip(S + blockIdx.z * st.S, X + blockIdx.z * st.X, Dinv + blockIdx.z * st.D, r, ib, blockIdx.x / kStrips,
-                blockIdx.x % kStrips, At, Bt);
+    __shared__ double buf[BLOCKS ? kNB * (kPitchKF + kPitchT) : kNB * (kPitchD + kPitchX)];
+    S += blockIdx.z * st.S;
+    X += blockIdx.z * st.X;
+    Dinv += blockIdx.z * st.D;
+    if constexpr (BLOCKS) trinv_block(S, X, Dinv, r, ib, blockIdx.x, buf, buf + kNB * kPitchKF);
+    else trinv_strip(S, X, Dinv, r, ib, blockIdx.x / kStrips, blockIdx.x % kStrips, buf, buf + kNB * kPitchD);
 }
 
 // Workgroups 0 .. pairs-1: the trailing blocks of step kb.  FUSED: block (kb+1, kb+1) goes on to be factored, and workgroups
@@ -757,11 +825,19 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     else
         hipLaunchKernelGGL(k_gram<kNB>, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
-    // One launch per block column up to 1024 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.64 /
-    // 2.09, 32 of them 19.6 / 20.0, 48 28.8 / 29.2, 64 38.1 / 38.3, 128 75.03 / 74.99; 2048 x 2048, r = 512: 32 3.45 / 3.59, 128
-    // 12.3 / 12.4; 1024 x 1024: r = 256, 256 matrices 5.07 / 5.09, r = 128, 512 of them 5.33 / 5.34).  The arithmetic is the
-    // same, and with it every bit.
-    const bool fused = batch * nt <= 1024;
+    // One launch per block column up to 640 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.64 /
+    // 2.67, 32 of them 19.4 / 19.6, 48 28.6 / 28.4, 64 37.8 / 37.1, 128 75.0 / 72.4; 2048 x 2048, r = 512: 32 3.33 / 3.50, 128
+    // 12.1 / 12.0; 1024 x 1024, r = 256, 256 matrices 5.05 / 4.98).  The arithmetic is the same, and with it every bit.
+    const bool fused = batch * nt <= 640;
+    // Strips while whole blocks are fewer than the CUs or so (us, 16 matrices, 192 blocks strips 41 / blocks 48, 240 63 / 60; 40
+    // matrices: 120 13 / 16, 200 24.0 / 23.9, 400 77 / 56, 600 138 / 100; 128 matrices: 128 9 / 11, 256 23 / 15, 1920 388 / 238)
+    constexpr int kBlocksFrom = 200;
+    auto launch_trinv_row = [&](int ib) {
+        if ((int64_t)ib * batch >= kBlocksFrom)
+            hipLaunchKernelGGL(k_trinv_row<true>, dim3(ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
+        else
+            hipLaunchKernelGGL(k_trinv_row<false>, dim3(kStrips * ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
+    };
     hipLaunchKernelGGL(k_chol_diag<true>, dim3(1, 1, B), blk, 0, stream, S, (int)r, 0, Dinv, X, info, shift, flag_factor, st);
     for (int kb = 0; kb + 1 < nt; ++kb) {
         const int below = nt - kb - 1, left = below * (below + 1) / 2;
@@ -777,7 +853,7 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
         }
     }
     for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
-        if (ib > 0) hipLaunchKernelGGL(k_trinv_row, dim3(kStrips * ib, 1, B), blk, 0, stream, S, X, Dinv, (int)r, ib, st);
+        if (ib > 0) launch_trinv_row(ib);
     if ((int64_t)blocks(m, kNB) * nt * batch < kFewBlocks)
         hipLaunchKernelGGL(k_apply<32>, dim3(blocks(m, 32), nt32, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
     else
