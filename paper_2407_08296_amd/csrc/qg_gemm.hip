@@ -52,8 +52,10 @@ static auto with_mode(int mode, F f) {
 // 448 102 / 92: they cross between 384 and 448.  128 x 128 / 128 x 256, at the number of the latter: r = 256: 512 90 / 96,
 // 1024 175 / 188, 1536 278 / 280; r = 512: 768 170 / 172, 1152 261 / 264, 1536 348 / 338; r = 1024: 768 269 / 250, 896
 // 307 / 317, 1024 367 / 356, 1536 541 / 502.  Unaligned rows are staged through registers, which leaves the 128 x 256 instance two
-// workgroups per CU: 1.09 ms with 128 x 128 against 1.29 for the 1B model's 24 odd matrices.  A matrix of 64 rows of R or
-// fewer would leave half of every 128-row tile empty (64 x 100000, r = 64: 26 us; 128 x 128 34, 128 x 256 30).
+// workgroups per CU (us, 128 x 128 / 128 x 256: 24 of 2048 x 5461, r = 512, 655 / 715, eight of 4096 x 11007, r = 1024, 1262 /
+// 1310, 48 of 1024 x 1021, r = 256, 102 / 102); 64 x 128 / 128 x 128: 1024 x 1021, r = 256: T = 256 29 / 38, 384 34 / 40, 512 41 /
+// 42, 768 55 / 50; 2048 x 5461, r = 512: 344 70 / 72, 516 108 / 93, so their line could lie between 400 and 500.  A matrix of
+// 64 rows of R or fewer would leave half of every 128-row tile empty (64 x 100000, r = 64: 26 us; 128 x 128 34, 128 x 256 30).
 template <typename F>
 static auto with_proj(int cfg, F f) {
     if (cfg == kProj64) return f(ProjCfg<64, 128, 32, 2, 2, 4, 2, 2, 2>());
@@ -78,13 +80,14 @@ static int proj_config_of(int64_t n, int64_t ld, int64_t r, int64_t count) {
 // a half; below that 64 rows with four tiles in flight (us, 64 / 128 rows, at the number of the latter: 1024 x 1024, r = 256:
 // 128 9.1 / 13.4, 256 13.1 / 14.5, 320 18.9 / 19.8, 384 19.3 / 20.1, 448 22.1 / 20.5; 2048 x 2048, r = 512: 128 11.8 / 17.6,
 // 256 16.9 / 18.8, 384 25.1 / 25.7, 512 30.6 / 26.5; the weight tile shares the staging LDS, the VALU-heavy update epilogue of
-// one workgroup overlaps the main loops of the others).  Unaligned rows: as long as the 64-row tiles make about one round
-// of two workgroups per CU (1024 x 1021, r = 256: 256 38 / 46, 288 54 / 59; 20000 x 300, r = 64, 314: 48 / 40; 2048 x 5461,
-// r = 512, 352: 77 / 72).
+// one workgroup overlaps the main loops of the others).  Unaligned rows: up to 300, where the loops with checks on
+// every chunk crossed.  The present ones cross later, about where 64-row tiles make one round of three workgroups per CU (1024 x
+// 1021, r = 256: 256 22 / 31, 288 29 / 43, 384 29 / 41, 448 37 / 44; 20000 x 300, r = 64, 314: 25 / 37; 2048 x 5461, r = 512, 352:
+// 35 / 42; 2560 x 5461, 440: 47 / 42; 4096 x 4093, r = 1024, 512: 81 / 69).
 template <typename F>
 static auto with_bp(int cfg, F f) {
     if (cfg == kBp64) return f(BpCfg<64, 32, 2, 2, 4, 2, 2, 2>());
-    return f(BpCfg<kManyBpBM, 32, 2, 2, 2, 3, 3, 2>());   // the checked variant needs more registers
+    return f(BpCfg<kManyBpBM, 32, 2, 2, 2, 3, 3, 2>());   // unaligned operands pass through registers
 }
 int bp_config(int mode, int64_t tiles128) { return tiles128 < (mode == kUnaligned ? 300 : 384) ? kBp64 : kBp128; }
 int64_t bp_tiles_m(int cfg, int64_t m) { return with_bp(cfg, [&](auto c) { return (m + c.BM - 1) / c.BM; }); }
@@ -96,7 +99,6 @@ static auto with_adam_mode(int mode, bool lines, F f) {
     return with_mode(mode, f);
 }
 constexpr int wg_index(int mode) { return mode == kMaskedShared ? kMasked : mode; }
-
 
 // Tiles in flight: two in the unaligned kernels.  Their operands pass through registers, and those of four tiles spilled (with
 // the checks that kept the compiler from it, and from one K step to the next a load at a time at the edge, 2048 x 5461, r =
@@ -137,12 +139,15 @@ int launch_project_adam_many(const PlanHeader* plan_host, const PlanHeader* plan
         const int cnt = class_count(plan_host, cls), first = class_first(plan_host, cls);
         const uint32_t tiles = plan_host->proj_tiles[cls];
         if (cnt == 0 || tiles == 0) continue;
+        // (one matrix that shares lines decides for its class; us, 24 of 2048 x 5472, r = 512, one of them with n = 5464: 494 / 499,
+        // two 516 / 513, three 537 / 528, all 795 / 561)
         bool lines = true;
         for (int i = first; i < first + cnt; ++i) lines = lines && whole_lines(plan_matrices(plan_host)[i].ld);
         const int e = with_proj((int)plan_host->proj_cfg[cls], [&](auto c) {
             using C = decltype(c);
             return with_adam_mode(cls, lines, [&](auto mode) {
-                // (unaligned 128 x 128 tiles: four workgroups per CU, 24 of 2048 x 5461, r = 512, 713 -> 688 us)
+                // (unaligned 128 x 128 tiles: four workgroups per CU; us, three / four: 24 of 2048 x 5461, r = 512, 695 /
+                // 655, twelve 362 / 363, six of 4096 x 11007, r = 1024, 1000 / 958, 96 of 1024 x 1021, r = 256, 211 / 215)
                 constexpr int WG = mode() == kUnaligned && C::BM == 128 && C::BN == 128 ? 4 : C::kWg[wg_index(mode())];
                 hipLaunchKernelGGL((k_project_adam_many<C::BM, C::BN, C::BK, C::WGM, C::WGN, stages(mode(), C::NS), mode(), WG>),
                                    dim3(grid8(tiles)), dim3(C::NT), 0, stream, plan_dev, first, cnt, tiles, write_R, coef);

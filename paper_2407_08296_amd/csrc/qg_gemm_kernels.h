@@ -993,7 +993,7 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
     // tile's first code, m0*r, starts a block of 256 (m0 is a multiple of 64, r of 8); the K offset k0 does not,
     // so the index of a code's block scale takes one add and two shifts per step.
     constexpr int A_OFFS = DIRECT ? AD::VARIANTS : A_PER;
-    uint32_t a_off[A_OFFS], b_el[B_PER];   // N: byte or element offset, as G's in the projection; P: element offset inside
+    uint32_t a_off[A_OFFS], b_el[B_PER];   // N: byte offset, as G's in the projection; P: element offset inside
                                            // the tile's rows (kUnaligned: rows past the last one are the last one again)
     int a_shift[DIRECT ? 1 : A_PER];       // kUnaligned, at the edge: see edge_column
     const bool edge = !DIRECT && n0 + BNn > n;

@@ -538,8 +538,8 @@ __device__ __forceinline__ void trinv_strip(const double* __restrict__ S, double
     }
 }
 
-// The whole block by one workgroup, a quarter of the staging per MFMA, for launches that fill the chip (see launch_trinv_row).  The order
-// of every sum is the strips': per 64 deep, even and odd quadruples of the contraction index apart.
+// The whole block by one workgroup, a quarter of the staging per MFMA, for launches that fill the chip (see kBlocksFrom).  The
+// order of every sum is the strips': per 64 deep, even and odd quadruples of the contraction index apart.
 // At: kNB * kPitchKF, Bt: kNB * kPitchT doubles of LDS.
 constexpr int kPitchT = kNB + 2;      // LDS pitch of a 64 x 64 intermediate
 

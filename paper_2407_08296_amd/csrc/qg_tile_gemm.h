@@ -4,8 +4,9 @@
 // The contraction index of an operand is either its fast (contiguous) index - the operand is then staged as an
 // [x][k] tile and read with 16-byte LDS reads - or its slow index - staged as a [k][x] tile and read with the
 // transposing LDS reads of the optimizer step's kernels.  Rows may start at any element offset (n = 5461 in the
-// LLaMA-1B shapes): chunks are fetched with under-aligned wide loads, element by element only where a chunk
-// straddles the edge of the matrix.
+// LLaMA-1B shapes): chunks are fetched with under-aligned wide loads; past the edge of a matrix the last row or chunk is
+// fetched again, or the last whole chunk is shifted, and element by element goes only what straddles the end of the
+// contraction, or an operand of less than a chunk.
 #pragma once
 #include "qg_common.h"
 #include "qg_gemm_kernels.h"
@@ -813,25 +814,26 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    forward 2.24 -> 1.87, grad_input 1.82 -> 1.66 (256 x 256 x 32 with eight waves: 1.72; 256 x 128 x 64: forward
 //    unchanged at 2.24).  Two register sets where all tiles are whole (grad_input, 4096 tokens, 4096 -> 4096: 134 against
 //    137 with one; 8192 tokens 253 / 260); with ragged edges only where the last round of tiles leaves most CUs idle and the
-//    columns are whole (forward, 3000 tokens, 4096 -> 11008, 516 tiles: 334 / 371, but 5000 tokens, 2048 -> 5461, 440 tiles:
-//    161 / 158; 3000 tokens, 2048 -> 5461, 264 tiles with ragged columns: 160 / 145).
+//    columns are whole (forward, 3000 tokens, 4096 -> 11008, 516 tiles: 333 / 377).  That line is from edges with checks on every
+//    chunk; with clamped ones two sets are ahead elsewhere too (5000 tokens, 2048 -> 5461, 440 tiles: 122 / 135; 3000 tokens,
+//    2048 -> 5461, 264 tiles: 115 / 130; grad_input, 3000 tokens, 5461 columns: 134 / 138).
 //  * otherwise four waves: 128 x 128 x 64 when an operand is INT8 or both have k fast, with one register set where the
 //    tiles make one round of two workgroups per CU (256 < T <= 512) and two sets below and above: forward, 2048 tokens,
 //    2048 -> 2048 (T = 256) 26.7 with two against 31.3, 4096 tokens, 2048 -> 1280 (320) 40.0 / 36.0, 512 tokens, 4096 ->
 //    11008 (344) 75 / 67, 6000 tokens, 2048 -> 1920 (705) 74 / 77, 1024 tokens, 4096 -> 11008 (688) 124 / 135.  An INT8 B
-//    with k slow: two sets up to T = 256 only where rows and columns are whole (grad_input, 1024 tokens, 4096 -> 4096 45 /
-//    58, but 1000 tokens 80 / 77 and 4100 tokens, 768 -> 768 25.4 / 23.4), and beyond T = 512 128 x 128 x 32 with four
-//    workgroups per CU (4096 tokens, 2048 -> 2048 (512): 64-deep 42, 32-deep 44.5; 4100 tokens (528) 90 / 74; 3000 tokens,
-//    4096 -> 4096 (768) 179 / 150).
+//    with k slow: two sets up to T = 256 only where rows and columns are whole (grad_input, 1024 tokens, 4096 -> 4096 46 /
+//    57; ragged, with clamped edges, 1000 tokens 50 / 59 and 4100 tokens, 768 -> 768 13.3 / 14.4, but 1000 tokens, 5461 columns 54 /
+//    48), and beyond T = 512 128 x 128 x 32 with four workgroups per CU (4096 tokens, 2048 -> 2048 (512): 64-deep 42.5, 32-deep
+//    44; 4100 tokens (528) 62 / 55; 3000 tokens, 4096 -> 4096 (768) 132 / 125).
 //    grad_W: 128 x 256 x 32 when that fills the chip twice, 128 x 128 x 32 below, with two register sets up to T = 256
-//    (1000 tokens, 2048 x 2048: 16.0 against 19.7) and where everything is whole (2048 tokens, 3072 x 2048, T = 384: 37.1 /
-//    38.7; ragged, 2000 tokens, 3000 x 3000, T = 576: 91 / 85).
+//    (1000 tokens, 2048 x 2048: 17.1 against 18.1, 2000 x 2000 17.1 / 20.7) and where everything is whole (2048 tokens, 3072 x
+//    2048, T = 384: 37.1 / 38.7; ragged, 2000 tokens, 3000 x 3000, T = 576: 55.3 / 54.7, 3001 x 2048, T = 384: 100 / 69).
 //  * 64 x 64 x 64, four waves of one 32 x 32 block each, where 128 x 128 tiles would leave CUs idle: a K step of a lone
 //    workgroup is a serial chain (fragments, MFMAs, commit, barrier), 1.2 us for 128 x 128 x 64 before the commit and the
-//    fetches went between the MFMAs.  64 / 128: forward, 256 tokens, 768 -> 2048 (T = 32) 13.6 / 16.6, 256 x 4096 -> 11008
-//    (172) 46.5 / 46.3, 2048 tokens, 2048 -> 1664 (208) 30.9 / 25.4, but ragged, 3000 tokens, 2048 -> 1280 (240) 38.5 / 48.4
-//    and 300 tokens, 4096 -> 11008 (258) 70 / 103; grad_input, 1000 x 2048 -> 2048 (128) 29 / 41, 256 x 4096 -> 11008 (172)
-//    53 / 43; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 1024 tokens, 1536 x 2048 (192) 15.7 / 15.9, 1664 x 2048 (208)
+//    fetches went between the MFMAs.  64 / 128: forward, 1000 tokens, 768 -> 2048 (T = 128) 9.7 / 12.8, 256 x 4096 -> 11008
+//    (172) 47 / 48, 2048 tokens, 2048 -> 1664 (208) 31 / 27, ragged, 3000 tokens, 2048 -> 1280 (240) 33 / 29, but 1000 tokens,
+//    1024 -> 2736 (176) 14.5 / 15.9 and 300 tokens, 4096 -> 11008 (258) 60 / 64; grad_input, 1000 x 2048 -> 2048 (128) 20 / 31,
+//    256 x 4096 -> 11008 (172) 53 / 43; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 1024 tokens, 1536 x 2048 (192) 15.7 / 15.9, 1664 x 2048 (208)
 //    20.8 / 15.9.
 // ldc: row pitch of C in elements (0: N).
 template <int AL, int BL, typename OUT>
