@@ -171,7 +171,7 @@ __device__ __forceinline__ u32x4 shift_right_128(u32x4 v, int bits) {
 // 9.3; with every access checked in two or four stages 3.3 / 5.4 and 5.0 / 10.5).
 
 // Rows of an array of n columns whose chunks (see edge_column) lie inside it: all of them, or, with less than a chunk of columns,
-// those whose chunk ends in a later row (4096 x 5, r = 256, us: every step checked 174 / 28, so 58 / 17).
+// those whose chunk ends in a later row (projection with Adam of 4096 x 5, r = 256: every step checked 174 us, so 58).
 __device__ __forceinline__ int chunk_rows(int rows, int n, int ld) { return n >= 8 ? rows : rows - (8 - n + ld - 1) / ld; }
 // Steps of the pipeline, of `rows` rows (see above).
 __device__ __forceinline__ int whole_steps(int rows, int bk, int ld) { return ld <= (1 << 24) ? rows / bk : 0; }
@@ -997,7 +997,9 @@ __device__ __forceinline__ void backproject_tile(const uint8_t* __restrict__ Pq,
                                            // the tile's rows (kUnaligned: rows past the last one are the last one again)
     int a_shift[DIRECT ? 1 : A_PER];       // kUnaligned, at the edge: see edge_column
     const bool edge = !DIRECT && n0 + BNn > n;
-    const int KT_WHOLE = whole_steps(chunk_rows(r, n, ld), BK, ld);   // kUnaligned: steps of the pipeline, as in the projection
+    // kUnaligned: steps of the pipeline, as in the projection, but for less than a chunk of columns checked ones (chunk_rows here
+    // takes eight registers; 24 of 2048 x 5461, r = 512, 641 -> 644 us)
+    const int KT_WHOLE = n >= 8 ? whole_steps(r, BK, ld) : 0;
 #pragma unroll
     for (int p = 0; p < A_OFFS; ++p) {
         if constexpr (DIRECT) {
