@@ -31,12 +31,9 @@ typedef double f64x4 __attribute__((ext_vector_type(4)));
 typedef double f64x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kNB = 64;               // block size of the fp64 kernels: one workgroup (4 waves) per 64 x 64 block
-constexpr int kKC = 16;               // K extent staged in LDS per barrier pair: 20 KB of LDS per workgroup, so that six
-                                      // or more are resident per CU (the fp64 matrix pipe sustains more with more waves
-                                      // per SIMD; 32 gave three workgroups and 9 % more time, 8 no further gain)
+constexpr int kKC = 16;               // K extent staged in LDS per barrier pair: 20 KB of LDS per workgroup
 constexpr int kPitchKF = kKC + 1;     // LDS pitch of a [64][k] chunk (k fastest): odd, so that the 16 rows a fragment
                                       // read touches at one k fall on 16 different bank pairs (36 gave 4-way conflicts)
-constexpr int kPitchKS = kNB + 16;    // LDS pitch of a [k][64] chunk (k slowest)
 
 // ROWS x COLS block at (row0, col0) of a row-major matrix (fp32 or fp64) -> registers -> LDS doubles.  Elements
 // outside [0, rows) x [0, cols) read as zero.  col0 and cols are even, so an element pair never straddles the edge.
@@ -44,33 +41,38 @@ template <int ROWS, int COLS, int PITCH, typename T>
 struct BlockStage {
     static constexpr int PER = ROWS * COLS / 2 / 256;
     static_assert(ROWS * COLS % 512 == 0, "256 threads, two elements each");
-    double v[PER][2];
+    T v[PER][2];   // (as fetched: converted when written to LDS, so that nothing waits for the load before)
     __device__ __forceinline__ void fetch(const T* __restrict__ src, int64_t ld, int row0, int col0, int rows, int cols) {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int idx = threadIdx.x + 256 * q;
             const int gr = row0 + idx / (COLS / 2), gc = col0 + (idx % (COLS / 2)) * 2;
-            v[q][0] = v[q][1] = 0.0;
+            v[q][0] = v[q][1] = T(0);
             if (gr < rows && gc < cols) {
                 typedef T pair_t __attribute__((ext_vector_type(2)));
                 const pair_t p = *reinterpret_cast<const pair_t*>(src + (int64_t)gr * ld + gc);
-                v[q][0] = (double)p[0];
-                v[q][1] = (double)p[1];
+                v[q][0] = p[0];
+                v[q][1] = p[1];
             }
         }
     }
-    __device__ __forceinline__ void commit(double* dst) const {
+    // place(row): the row of dst that row `row` of the block goes to
+    template <typename Place>
+    __device__ __forceinline__ void commit(double* dst, Place place) const {
 #pragma unroll
         for (int q = 0; q < PER; ++q) {
             const int idx = threadIdx.x + 256 * q;
-            double* d = dst + (idx / (COLS / 2)) * PITCH + (idx % (COLS / 2)) * 2;
-            d[0] = v[q][0];
-            d[1] = v[q][1];
+            double* d = dst + place(idx / (COLS / 2)) * PITCH + (idx % (COLS / 2)) * 2;
+            d[0] = (double)v[q][0];
+            d[1] = (double)v[q][1];
         }
+    }
+    __device__ __forceinline__ void commit(double* dst) const {
+        commit(dst, [](int row) { return row; });
     }
 };
 
-// One K chunk (KC deep) of the workgroup's product on the fp64 matrix cores.  Wave (wi, wj) owns a quadrant of W x W blocks
+// One K chunk (KC deep) of a 64 x 64 product of the factorization, a chain of a few chunks each.  Wave (wi, wj) owns a quadrant of W x W blocks
 // of v_mfma_f64_16x16x4: lane l supplies A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16]; register v of the
 // result is element (i = 4 v + l / 16, j = l % 16).  Operand element (i, k) of A sits at At[i * a_pi + k * a_pk], element
 // (k, j) of B at Bt[j * b_pj + k * b_pk].
@@ -111,6 +113,70 @@ __device__ __forceinline__ void for_each_acc(const f64x4 (&acc)[W][W], int lane,
 #pragma unroll
             for (int v = 0; v < 4; ++v)
                 f((wi * W + a) * 16 + 4 * v + (lane >> 4), (wj * W + b) * 16 + (lane & 15), acc[a][b][v]);
+}
+
+// The same product on v_mfma_f64_4x4x4, four independent 4 x 4 x 4 products: lane l supplies A[i = l % 4][k = l / 16] and
+// B[k = l / 16][j = l % 4] of block l / 4 % 4 and gets D[i = l / 16][j = l % 4] of it.  Blocks 0, 1 and 2, 3 are given the same
+// four rows, 0, 2 and 1, 3 the same four columns: 8 x 8 results of two fragments, a quadrant of 16 W x 16 W from 2 W + 2 W.
+// On this chip it sustains 76 TFLOP/s on random operands, v_mfma_f64_16x16x4 36 to 50 (registers only, 8 waves per SIMD).
+struct Lane4 {
+    int a, b, i, j;   // row of A / column of B of the lane's fragment element, row / column of its result, in an 8 x 8 block
+    __device__ __forceinline__ explicit Lane4(int lane)
+        : a((lane >> 3 & 1) * 4 + (lane & 3)), b((lane >> 2 & 1) * 4 + (lane & 3)), i((lane >> 3 & 1) * 4 + (lane >> 4)), j(b) {}
+};
+
+// One K chunk, both operands [k][x]: a 16-byte read is two neighbouring x, so that fragment f of the 16 rows a pair of
+// fragments covers holds rows 2 l.a + f (columns 2 l.b + f).
+template <int KC, int PITCH, int W>
+__device__ __forceinline__ void mma4_kslow(const double* At, const double* Bt, double (&acc)[2 * W][2 * W], int lane, int wi, int wj) {
+    const Lane4 l(lane);
+    const double* ap = At + (lane >> 4) * PITCH + wi * 16 * W + 2 * l.a;
+    const double* bp = Bt + (lane >> 4) * PITCH + wj * 16 * W + 2 * l.b;
+#pragma unroll
+    for (int k0 = 0; k0 < KC; k0 += 4) {
+        f64x2 af[W], bf[W];
+#pragma unroll
+        for (int a = 0; a < W; ++a) af[a] = *reinterpret_cast<const f64x2*>(ap + k0 * PITCH + 16 * a);
+#pragma unroll
+        for (int b = 0; b < W; ++b) bf[b] = *reinterpret_cast<const f64x2*>(bp + k0 * PITCH + 16 * b);
+#pragma unroll
+        for (int a = 0; a < 2 * W; ++a)
+#pragma unroll
+            for (int b = 0; b < 2 * W; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(af[a / 2][a % 2], bf[b / 2][b % 2], acc[a][b], 0, 0, 0);
+    }
+}
+
+// Both operands [x][k]: a 16-byte read is two neighbouring k, of which an instruction takes four even or four odd ones.
+// Fragment f of A holds rows 8 f + l.a of the quadrant, fragment f of B the rows of Bt (columns of the result) 8 f + l.b.
+template <int KC, int PITCH, int W>
+__device__ __forceinline__ void mma4_kfast(const double* At, const double* Bt, double (&acc)[2 * W][2 * W], int lane, int wi, int wj) {
+    const Lane4 l(lane);
+    const double* ap = At + (wi * 16 * W + l.a) * PITCH + 2 * (lane >> 4);
+    const double* bp = Bt + (wj * 16 * W + l.b) * PITCH + 2 * (lane >> 4);
+#pragma unroll
+    for (int k0 = 0; k0 < KC; k0 += 8) {
+        f64x2 af[2 * W], bf[2 * W];
+#pragma unroll
+        for (int a = 0; a < 2 * W; ++a) af[a] = *reinterpret_cast<const f64x2*>(ap + 8 * a * PITCH + k0);
+#pragma unroll
+        for (int b = 0; b < 2 * W; ++b) bf[b] = *reinterpret_cast<const f64x2*>(bp + 8 * b * PITCH + k0);
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int a = 0; a < 2 * W; ++a)
+#pragma unroll
+                for (int b = 0; b < 2 * W; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_4x4x4f64(af[a][p], bf[b][p], acc[a][b], 0, 0, 0);
+    }
+}
+
+template <int W>
+__device__ __forceinline__ void zero_acc4(double (&acc)[W][W]) {
+#pragma unroll
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+        for (int b = 0; b < W; ++b) acc[a][b] = 0.0;
 }
 
 // A batch of matrices with the same m and r runs through the fp64 kernels in one launch each, matrix b =
@@ -189,51 +255,73 @@ __global__ void k_set_i32(int32_t* p, int32_t v, int count) {
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int kGramMaxSlices = 8;
 
-// The two products over m rows come with 64 x 64 blocks (TB) and 16-deep chunks for many workgroups, and with 32 x 32 blocks
-// and 64-deep chunks for few, where a workgroup's chain of chunks is what counts: a quarter of the MFMAs per chunk row, four
-// times the workgroups, a quarter of the barriers (768 x 256: k_gram 31 -> 15 us, k_apply 21 -> 9).  The order of every
-// sum is the same in both.
+// The two products over m rows come with 64 x 64 blocks (TB) and 16- or 32-deep chunks for many workgroups, and with 32 x 32
+// blocks and 64-deep chunks for few, where a workgroup's chain of chunks is what counts: a quarter of the MFMAs per chunk row,
+// four times the workgroups, a quarter of the barriers.  The order of every sum is the same in both.
+// Bound by the matrix pipe: sixteen 4096 x 4096, r = 1024 (73 GFLOP each launch) k_gram 1790 -> 1290 us (57 TFLOP/s), k_apply
+// 1520 -> 1340 (54), against 16 x 16 x 4 instructions, tiles dealt over the XCDs one by one and, in both, a wait for the next
+// chunk as soon as it was requested.  Measured beside it: k_gram with 32-deep chunks 1345, k_apply with 16-deep ones 1490; 128 x 128
+// blocks in two LDS stages 1450 and, spilling, 1850; a higher wave priority in mma() no change.
 template <int TB>
 struct F64Tile {
-    static constexpr int W = TB / 32, KC = TB == kNB ? kKC : 64;
-    static constexpr int PITCH_KF = KC + 1;                  // [x][k] chunk, k fastest
+    static constexpr int W = TB / 32;
+    static constexpr int KC_GRAM = TB == kNB ? kKC : 64, KC_APPLY = TB == kNB ? 32 : 64;
+    static constexpr int PITCH_KF = KC_APPLY + 2;            // [x][k] chunk, k fastest: 8 rows on 8 different groups of 4 banks
     static constexpr int PITCH_KS = TB + 16;                 // [k][x] chunk, k slowest
 };
 
-template <int TB>
-__global__ __launch_bounds__(256) void k_gram(const float* __restrict__ Y, double* __restrict__ part, int m, int r,
-                                              int slice_rows, BatchStride st) {
-    using F = F64Tile<TB>;
-    Y += blockIdx.z * st.Y;
-    part += blockIdx.z * st.part;
-    __shared__ double At[F::KC * F::PITCH_KS];
-    __shared__ double Bt[F::KC * F::PITCH_KS];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
-    int bi, bj;
-    lower_pair(blockIdx.x, bi, bj);
-    const bool diag = bi == bj;
-    const int k_begin = blockIdx.y * slice_rows, k_end = min(m, k_begin + slice_rows);
-    double* S = part + (int64_t)blockIdx.y * r * r;
-    BlockStage<F::KC, TB, F::PITCH_KS, float> sa, sb;
-    f64x4 acc[F::W][F::W];
-    zero_acc(acc);
-    sa.fetch(Y, r, k_begin, bi * TB, k_end, r);
-    if (!diag) sb.fetch(Y, r, k_begin, bj * TB, k_end, r);
-    for (int k0 = k_begin; k0 < k_end; k0 += F::KC) {
-        sa.commit(At);
-        if (!diag) sb.commit(Bt);
+// The chunks of a workgroup from k_begin on: fetch(k) brings the operands of one into registers, commit() writes them to LDS,
+// mma() multiplies.
+template <int KC, typename FETCH, typename COMMIT, typename MMA>
+__device__ __forceinline__ void f64_chunks(int k_begin, int k_end, FETCH fetch, COMMIT commit, MMA mma) {
+    fetch(k_begin);
+    for (int k = k_begin; k < k_end; k += KC) {
+        commit();
         __syncthreads();
-        if (k0 + F::KC < k_end) {
-            sa.fetch(Y, r, k0 + F::KC, bi * TB, k_end, r);
-            if (!diag) sb.fetch(Y, r, k0 + F::KC, bj * TB, k_end, r);
-        }
-        mma_chunk<F::KC>(At, 1, F::PITCH_KS, diag ? At : Bt, 1, F::PITCH_KS, acc, lane, wi, wj);
+        if (k + KC < k_end) fetch(k + KC);
+        mma();
         __syncthreads();
     }
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = bi * TB + row, gj = bj * TB + col;
-        if (gi < r && gj < r) S[(int64_t)gi * r + gj] = x;
-    });
+}
+
+template <int TB>
+__global__ __launch_bounds__(256, TB == kNB ? 6 : 1) void k_gram(const float* __restrict__ Y, double* __restrict__ part, int m, int r,
+                                              int slice_rows, uint32_t pairs, uint32_t slices, uint32_t tiles, BatchStride st) {
+    using F = F64Tile<TB>;
+    const uint32_t id = xcd_tile(blockIdx.x, gridDim.x);
+    if (id >= tiles) return;
+    const uint32_t slice = id / pairs % slices, z = id / pairs / slices;
+    Y += z * st.Y;
+    part += z * st.part;
+    __shared__ __attribute__((aligned(16))) double At[F::KC_GRAM * F::PITCH_KS];
+    __shared__ __attribute__((aligned(16))) double Bt[F::KC_GRAM * F::PITCH_KS];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
+    int bi, bj;
+    lower_pair(id % pairs, bi, bj);
+    const bool diag = bi == bj;
+    const int k_begin = slice * slice_rows, k_end = min(m, k_begin + slice_rows);
+    double* S = part + (int64_t)slice * r * r;
+    BlockStage<F::KC_GRAM, TB, F::PITCH_KS, float> sa, sb;
+    double acc[2 * F::W][2 * F::W];
+    zero_acc4(acc);
+    f64_chunks<F::KC_GRAM>(k_begin, k_end,
+        [&](int k) {
+            sa.fetch(Y, r, k, bi * TB, k_end, r);
+            if (!diag) sb.fetch(Y, r, k, bj * TB, k_end, r);
+        },
+        [&] {
+            sa.commit(At);
+            if (!diag) sb.commit(Bt);
+        },
+        [&] { mma4_kslow<F::KC_GRAM, F::PITCH_KS, F::W>(At, diag ? At : Bt, acc, lane, wi, wj); });
+    const Lane4 l(lane);
+#pragma unroll
+    for (int a = 0; a < 2 * F::W; ++a)
+#pragma unroll
+        for (int b = 0; b < F::W; ++b) {
+            const int gi = bi * TB + (wi * F::W + a / 2) * 16 + 2 * l.i + a % 2, gj = bj * TB + (wj * F::W + b) * 16 + 2 * l.j;
+            if (gi < r && gj < r) *reinterpret_cast<f64x2*>(S + (int64_t)gi * r + gj) = f64x2{acc[a][2 * b], acc[a][2 * b + 1]};
+        }
 }
 
 __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ part, double* __restrict__ S, int r,
@@ -676,39 +764,55 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
 // ---------------------------------------------------------------------------------------------------------------
 // Q = Y X^T (X lower triangular: column block jb needs the contraction index up to the end of that block only)
 // ---------------------------------------------------------------------------------------------------------------
+constexpr int kApplyStrip = 8;        // row tiles per strip of the tile numbering
+
 template <int TB>
 __global__ __launch_bounds__(256) void k_apply(const float* __restrict__ Y, const double* __restrict__ X,
-                                               float* __restrict__ Q, int m, int r, BatchStride st) {
+                                               float* __restrict__ Q, int m, int r, int tiles_m, int tiles_r, uint32_t tiles,
+                                               BatchStride st) {
     using F = F64Tile<TB>;
-    Y += blockIdx.z * st.Y;
-    X += blockIdx.z * st.X;
-    Q += blockIdx.z * st.Q;
-    __shared__ double At[TB * F::PITCH_KF];
-    __shared__ double Bt[TB * F::PITCH_KF];
+    const uint32_t id = xcd_tile(blockIdx.x, gridDim.x);
+    if (id >= tiles) return;
+    const uint32_t z = id / (uint32_t)(tiles_m * tiles_r);
+    const int tile = (int)(id % (uint32_t)(tiles_m * tiles_r));
+    Y += z * st.Y;
+    X += z * st.X;
+    Q += z * st.Q;
+    constexpr int NF = 2 * F::W;
+    __shared__ __attribute__((aligned(16))) double At[TB * F::PITCH_KF];
+    __shared__ __attribute__((aligned(16))) double Bt[TB * F::PITCH_KF];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
-    const int a0 = blockIdx.x * TB, b0 = blockIdx.y * TB;
+    // strips of eight row tiles, column tile by column tile, the longest contraction first
+    const int strip = tile / (kApplyStrip * tiles_r), in_strip = tile % (kApplyStrip * tiles_r);
+    const int strip_rows = min(kApplyStrip, tiles_m - strip * kApplyStrip);
+    const int a0 = (strip * kApplyStrip + in_strip % strip_rows) * TB, b0 = (tiles_r - 1 - in_strip / strip_rows) * TB;
     const int kend = min(r, (b0 / kNB + 1) * kNB);           // X is zero above its diagonal blocks
-    BlockStage<TB, F::KC, F::PITCH_KF, float> sa;
-    BlockStage<TB, F::KC, F::PITCH_KF, double> sb;
-    f64x4 acc[F::W][F::W];
-    zero_acc(acc);
-    sa.fetch(Y, r, a0, 0, m, r);
-    sb.fetch(X, r, b0, 0, r, r);
-    for (int kc = 0; kc < kend; kc += F::KC) {
-        sa.commit(At);
-        sb.commit(Bt);
-        __syncthreads();
-        if (kc + F::KC < kend) {
-            sa.fetch(Y, r, a0, kc + F::KC, m, r);
-            sb.fetch(X, r, b0, kc + F::KC, r, r);
-        }
-        mma_chunk<F::KC>(At, F::PITCH_KF, 1, Bt, F::PITCH_KF, 1, acc, lane, wi, wj);
-        __syncthreads();
+    BlockStage<TB, F::KC_APPLY, F::PITCH_KF, float> sa;
+    BlockStage<TB, F::KC_APPLY, F::PITCH_KF, double> sb;
+    double acc[NF][NF];
+    zero_acc4(acc);
+    // The 16 W columns of a quadrant are dealt out to its 2 W fragments, so that a lane ends up with 2 W neighbouring ones.
+    auto place = [](int c) { return c / (8 * NF) * (8 * NF) + c % NF * 8 + c % (8 * NF) / NF; };
+    f64_chunks<F::KC_APPLY>(0, kend,
+        [&](int k) {
+            sa.fetch(Y, r, a0, k, m, r);
+            sb.fetch(X, r, b0, k, r, r);
+        },
+        [&] {
+            sa.commit(At);
+            sb.commit(Bt, place);
+        },
+        [&] { mma4_kfast<F::KC_APPLY, F::PITCH_KF, F::W>(At, Bt, acc, lane, wi, wj); });
+    const Lane4 l(lane);
+    typedef float run_t __attribute__((ext_vector_type(NF)));
+#pragma unroll
+    for (int a = 0; a < NF; ++a) {
+        const int gi = a0 + (wi * NF + a) * 8 + l.i, gj = b0 + (wj * 8 + l.j) * NF;
+        run_t x;
+#pragma unroll
+        for (int b = 0; b < NF; ++b) x[b] = (float)acc[a][b];
+        if (gi < m && gj < r) *reinterpret_cast<run_t*>(Q + (int64_t)gi * r + gj) = x;
     }
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = a0 + row, gj = b0 + col;
-        if (gi < m && gj < r) Q[(int64_t)gi * r + gj] = (float)x;
-    });
 }
 
 static size_t align256(size_t b) { return (b + 255) & ~size_t(255); }
@@ -815,15 +919,21 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     const dim3 blk(256);
     const unsigned B = (unsigned)batch;
     auto blocks = [](int64_t n, int size) { return (unsigned)((n + size - 1) / size); };
-    const unsigned nt32 = blocks(r, 32);
+    auto gram = [&](auto kernel, int tb) {
+        const unsigned n = blocks(r, tb), np = n * (n + 1) / 2, tiles = np * slices * B;
+        hipLaunchKernelGGL(kernel, dim3((tiles + 7) / 8 * 8), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, np, (unsigned)slices, tiles, st);
+    };
+    auto apply = [&](auto kernel, int tb) {
+        const unsigned tm = blocks(m, tb), tr = blocks(r, tb), tiles = tm * tr * B;
+        hipLaunchKernelGGL(kernel, dim3((tiles + 7) / 8 * 8), blk, 0, stream, Y, X, Q, (int)m, (int)r, (int)tm, (int)tr, tiles, st);
+    };
     // 32 x 32 blocks while 64 x 64 ones are about a workgroup per CU or fewer (us per refresh, always 64 / this line / up to
-    // 1000 / 9000 workgroups: 2048 x 2048, r = 512 705 / 652 / 653 / 651, 3000 x 700, r = 128, eight of them 552 / 507 / 515 /
-    // 517, 2048 x 2048, r = 512, sixteen 1982 / 1956 / 1984 / 2274)
+    // 1000 / 9000 workgroups: 768 x 768, r = 256 318 / 284 / 285 / 284, 2048 x 2048, r = 512 626 / 595 / 597 / 596, four of them
+    // 802 / 803 / 803 / 820, sixteen 1724 / 1723 / 1723 / 1893, 3000 x 700, r = 128, eight of them 351 / 339 / 341 / 341)
     constexpr int64_t kFewBlocks = 300;
-    if ((int64_t)pairs * slices * batch < kFewBlocks)
-        hipLaunchKernelGGL(k_gram<32>, dim3(nt32 * (nt32 + 1) / 2, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
-    else
-        hipLaunchKernelGGL(k_gram<kNB>, dim3(pairs, slices, B), blk, 0, stream, Y, part, (int)m, (int)r, slice_rows, st);
+    const int64_t gram_blocks = (int64_t)pairs * slices * batch, apply_blocks = (int64_t)blocks(m, kNB) * nt * batch;
+    if (gram_blocks < kFewBlocks) gram(k_gram<32>, 32);
+    else gram(k_gram<kNB>, kNB);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
     // One launch per block column up to 640 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.64 /
     // 2.67, 32 of them 19.4 / 19.6, 48 28.6 / 28.4, 64 37.8 / 37.1, 128 75.0 / 72.4; 2048 x 2048, r = 512: 32 3.33 / 3.50, 128
@@ -854,10 +964,8 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     }
     for (int ib = fused ? nt - 1 : 1; ib < nt; ++ib)   // (none if nt is 1)
         if (ib > 0) launch_trinv_row(ib);
-    if ((int64_t)blocks(m, kNB) * nt * batch < kFewBlocks)
-        hipLaunchKernelGGL(k_apply<32>, dim3(blocks(m, 32), nt32, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
-    else
-        hipLaunchKernelGGL(k_apply<kNB>, dim3(blocks(m, kNB), nt, B), blk, 0, stream, Y, X, Q, (int)m, (int)r, st);
+    if (apply_blocks < kFewBlocks) apply(k_apply<32>, 32);
+    else apply(k_apply<kNB>, kNB);
 }
 
 // Cholesky QR twice: Y -> T -> Q.  info: `batch` consecutive device ints.
