@@ -74,22 +74,22 @@ struct LinBatch {
 enum : int { kFetchAligned = 0, kFetchClamped = 1, kFetchShifted = 2, kFetchGuarded = 3 };
 
 // Staging of one operand tile: global -> registers (fetch) -> LDS (commit; INT8 is dequantized here).
-template <int LAYOUT, int XT, int BK, int NT = 256>
+template <int LAYOUT, int XT, int BK, int NT = 256, int PADK = kPadK>
 struct LinStage {
     static constexpr bool kFast = LAYOUT == kBf16KFast || LAYOUT == kInt8KFast || LAYOUT == kInt8ZKFast;
     static constexpr bool kZero = LAYOUT == kInt8ZKFast || LAYOUT == kInt8ZKSlow;
     static constexpr bool kInt8 = LAYOUT == kInt8KFast || LAYOUT == kInt8KSlow || kZero;
     static constexpr int CH = kInt8 ? 16 : 8;                   // elements per 16-byte chunk (one block scale each)
     static constexpr int CPR = (kFast ? BK : XT) / CH;          // chunks per tile row
-    static constexpr int PITCH = kFast ? BK + kPadX : XT + kPadK;   // LDS pitch: [x][k] or [k][x]
+    static constexpr int PITCH = kFast ? BK + kPadX : XT + PADK;   // LDS pitch: [x][k] or [k][x]
     static constexpr int ELEMS = (kFast ? XT : BK) * PITCH;
     static constexpr int PER = XT * BK / CH / NT;               // chunks per thread (NT threads in the workgroup)
     static_assert(XT * BK % (CH * NT) == 0, "tile must divide evenly over the threads");
     u32x4 v[PER];
     float s[kInt8 ? PER : 1];
     float z[kZero ? PER : 1];
-    // NT = 64: every wave of the workgroup stages a tile of its own
-    __device__ static __forceinline__ int thread() { return NT == 64 ? threadIdx.x & 63 : threadIdx.x; }
+    // (a workgroup of more than NT threads: every NT of them stage tiles of their own)
+    __device__ static __forceinline__ int thread() { return threadIdx.x & (NT - 1); }
 
     // KI: int or int64_t.  Over a 64-bit k0 the compiler turns the addresses of a loop into running pointers; over a 32-bit
     // one it recomputes a 64-bit product per chunk and step (grad_W with 128 x 128 x 32 tiles, 2048 tokens, 2560 x 2048:
@@ -202,6 +202,9 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* 
 // each other.
 // WM: wave rows of the workgroup (2: 256 threads, several workgroups per CU; 4: 512 threads, one workgroup per CU - the
 // B tile, and with it the dequantization of an INT8 B operand, is then shared by twice as many MFMAs).
+// KG: groups of waves of the workgroup that take the steps in turn (group g the steps g, g + KG, ...), each with LDS stages of
+// its own; their sums are added in the order of the groups.  For a workgroup that has its CU to itself: the chain of steps is KG
+// times shorter, and a SIMD has a wave to issue while another waits.
 // EXACT: every tile lies inside the matrices, K is a whole number of steps, rows are 16-byte aligned.  Otherwise a workgroup
 // runs unchecked too, but for the last, partial step, with its x indices clamped to the operand's last row or chunk: the
 // checks cost a wave three branches per chunk, and the workgroups at the edge, which took them, were the last to end (1000
@@ -209,27 +212,31 @@ __device__ __forceinline__ void store_block(const f32x16& acc, float bj, float* 
 // an operand with k slow is not whole, the tile at its edge takes the last whole chunk and shifts it (1000 tokens, 2048 ->
 // 5461: grad_input 98.6 -> 50.9, grad_W 80.1 -> 48.1; with every element of that chunk checked and loaded alone, the few
 // workgroups of that edge took longer than all others together).  Checked are operands of less than a chunk.
-template <int AL, int BL, int MB, int TN, int BK, int WM>
+template <int AL, int BL, int MB, int TN, int BK, int WM, int KG = 1>
 struct TileGemm {
     static constexpr int TM = 32 * MB * WM, NT = 128 * WM;
-    using SA = LinStage<AL, TM, BK, NT>;
-    using SB = LinStage<BL, TN, BK, NT>;
+    static constexpr int PADK = KG > 1 ? 16 : kPadK;
+    using SA = LinStage<AL, TM, BK, NT, PADK>;
+    using SB = LinStage<BL, TN, BK, NT, PADK>;
     static constexpr int STAGING = 2 * (SA::ELEMS + SB::ELEMS), TRANSPOSE = 2 * WM * kTransposeFloats * 2;
     static constexpr int SMEM = STAGING > TRANSPOSE ? STAGING : TRANSPOSE;   // uint16 elements
 };
 
-template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM, bool DEEP>
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM, bool DEEP, int KG = 1>
 __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* __restrict__ bias,
                                           OUT* __restrict__ C, int64_t ldc, int M, int N, int K, int tiles_m, int tiles_n,
                                           uint32_t tile, uint16_t* smem) {
-    using T = TileGemm<AL, BL, MB, TN, BK, WM>;
+    using T = TileGemm<AL, BL, MB, TN, BK, WM, KG>;
     using SA = typename T::SA;
     using SB = typename T::SB;
     constexpr int TM = T::TM;
+    static_assert(KG == 1 || DEEP, "groups: two register sets");
+    const int group = KG == 1 ? 0 : __builtin_amdgcn_readfirstlane(threadIdx.x / T::NT);
+    smem += group * T::SMEM;
     auto At = [&](int stage) { return smem + stage * SA::ELEMS; };
     auto Bt = [&](int stage) { return smem + 2 * SA::ELEMS + stage * SB::ELEMS; };
     const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
+    const int wave = __builtin_amdgcn_readfirstlane((threadIdx.x & (T::NT - 1)) >> 6), wm = wave >> 1, wn = wave & 1;
     // Tiles are numbered in strips eight row tiles tall, column tile by column tile: the tiles in flight on an XCD share
     // eight A panels and a few B panels.
     const int strip = (int)(tile / (uint32_t)(kLinStrip * tiles_n)), in_strip = (int)(tile % (uint32_t)(kLinStrip * tiles_n));
@@ -292,23 +299,26 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
             }
             return;
         }
-        auto slab = [&](int kt) { return (KI)min(kt, KT - 1) * BK; };   // past the end: the last slab again, never consumed
+        // this group's i-th step; past the end: the last slab again, never consumed
+        auto slab = [&](int i) { return (KI)min(KG * i + group, KT - 1) * BK; };
+        const int n = (KT + KG - 1) / KG, all = KT % KG == 0 ? n : n - 1;   // steps of the longest group, of every group
         fetch(slab(0), 0);
         fetch(slab(1), DEEP);
         commit(0, 0);
         lds_barrier();
-        for (int kt = 0; kt + 1 < KT; kt += 2) {
+        int i = 0;
+        for (; i + 1 < all; i += 2) {
 #pragma unroll
             for (int u = 0; u < 2; ++u) {
-                // one scheduling region: fragment reads, the fetches of step kt + u + 2 and the commit of step kt + u + 1
+                // one scheduling region: fragment reads, the fetches of step i + u + 2 and the commit of step i + u + 1
                 // between the MFMAs
                 mfma_step(u);
-                fetch(slab(kt + u + 2), DEEP ? u : 0);
+                fetch(slab(i + u + 2), DEEP ? u : 0);
                 commit(DEEP ? u ^ 1 : 0, u ^ 1);
                 constexpr int READS = MB * (SA::kFast ? 1 : 2) + NB * (SB::kFast ? 1 : 2), MFMAS = MB * NB;
                 __builtin_amdgcn_sched_group_barrier(0x100, READS, 0);
 #pragma unroll
-                for (int i = 0; i < BK / 16 * MFMAS; ++i) {
+                for (int j = 0; j < BK / 16 * MFMAS; ++j) {
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     __builtin_amdgcn_sched_group_barrier(0x100, (READS + MFMAS - 1) / MFMAS, 0);
                     __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
@@ -318,8 +328,11 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
                 lds_barrier();
             }
         }
-        if (KT & 1) {
-            mfma_step(0);
+#pragma unroll
+        for (int u = 0; u < (KG == 1 ? 1 : 2); ++u) {   // at most one step is left, or two if only some groups have the last
+            if (i + u >= n) break;
+            if (KG == 1 || KG * (i + u) + group < KT) mfma_step(u);
+            if (KG > 1 && u == 0 && i + 1 < n) commit(1, 1);
             lds_barrier();
         }
     };
@@ -338,15 +351,39 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
                 else steps(std::integral_constant<int, kFetchShifted>(), whole);
             }
             if (whole * BK < K) {
-                sa[0].template fetch<kFetchGuarded>(A, i0, M, whole * BK, K);
-                sb[0].template fetch<kFetchGuarded>(B, j0, N, whole * BK, K);
-                sa[0].commit(At(0));
-                sb[0].commit(Bt(0));
+                const bool mine = KG == 1 || group == whole % KG;   // (wave-uniform)
+                if (mine) {
+                    sa[0].template fetch<kFetchGuarded>(A, i0, M, whole * BK, K);
+                    sb[0].template fetch<kFetchGuarded>(B, j0, N, whole * BK, K);
+                    sa[0].commit(At(0));
+                    sb[0].commit(Bt(0));
+                }
                 lds_barrier();
-                mfma_step(0);
+                if (mine) mfma_step(0);
                 lds_barrier();
             }
         }
+    }
+    if constexpr (KG > 1) {   // the groups' sums through LDS, group 0 adds them in order
+        static_assert(MB * NB * T::NT * 16 * 4 <= T::SMEM * 2, "they fit in a group's staging buffers");
+        const int t = threadIdx.x & (T::NT - 1);
+        if (group != 0) {
+#pragma unroll
+            for (int q = 0; q < MB * NB * 4; ++q) {
+                const f32x16& c = acc[q / 4 / NB][q / 4 % NB];
+                reinterpret_cast<f32x4*>(smem)[q * T::NT + t] = f32x4{c[q % 4 * 4], c[q % 4 * 4 + 1], c[q % 4 * 4 + 2], c[q % 4 * 4 + 3]};
+            }
+        }
+        __syncthreads();
+        if (group != 0) return;
+#pragma unroll
+        for (int g = 1; g < KG; ++g)
+#pragma unroll
+            for (int q = 0; q < MB * NB * 4; ++q) {
+                const f32x4 x = reinterpret_cast<const f32x4*>(smem + g * T::SMEM)[q * T::NT + t];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[q / 4 / NB][q / 4 % NB][q % 4 * 4 + e] += x[e];
+            }
     }
     float* tp = reinterpret_cast<float*>(smem) + wave * kTransposeFloats;
 #pragma unroll
@@ -360,18 +397,18 @@ __device__ __forceinline__ void tile_gemm(const LinOperand& A, const LinOperand&
         }
 }
 
-template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM, bool DEEP>
-__global__ __launch_bounds__(WM * 128, WM == 2 ? 2 : 1) void k_tile_gemm(LinOperand A, LinOperand B,
+template <int AL, int BL, bool EXACT, typename OUT, int MB, int TN, int BK, int WM, bool DEEP, int KG = 1>
+__global__ __launch_bounds__(WM * 128 * KG, KG > 1 ? (MB == 1 ? 4 : 2) : WM == 2 ? 2 : 1) void k_tile_gemm(LinOperand A, LinOperand B,
                                                       const uint16_t* __restrict__ bias,
                                                       OUT* __restrict__ C, int M, int N, int K, int tiles_m, int tiles_n,
                                                       LinBatch batch) {
-    __shared__ __attribute__((aligned(16))) uint16_t smem[TileGemm<AL, BL, MB, TN, BK, WM>::SMEM];
+    __shared__ __attribute__((aligned(16))) uint16_t smem[KG * TileGemm<AL, BL, MB, TN, BK, WM, KG>::SMEM];
     A.base = batch.a[blockIdx.y];
     B.base = static_cast<const char*>(B.base) + batch.strideB_bytes * blockIdx.y;
     // each XCD (own L2) takes a contiguous range of tiles
     const uint32_t tile = xcd_tile(blockIdx.x, gridDim.x);
     if (tile >= (uint32_t)(tiles_m * tiles_n)) return;
-    tile_gemm<AL, BL, EXACT, OUT, MB, TN, BK, WM, DEEP>(A, B, bias, C + batch.strideC * blockIdx.y, batch.ldc ? batch.ldc : N, M, N, K,
+    tile_gemm<AL, BL, EXACT, OUT, MB, TN, BK, WM, DEEP, KG>(A, B, bias, C + batch.strideC * blockIdx.y, batch.ldc ? batch.ldc : N, M, N, K,
                                                   tiles_m, tiles_n, tile, smem);
 }
 
@@ -749,7 +786,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_kfast_direct(LinOperand A, LinO
 }
 
 // DEEP_EXACT, DEEP_RAGGED: two register sets where every tile and step is whole, and where not.
-template <int AL, int BL, typename OUT, int MB, int TN, int BK, int WM, bool DEEP_EXACT, bool DEEP_RAGGED>
+template <int AL, int BL, typename OUT, int MB, int TN, int BK, int WM, bool DEEP_EXACT, bool DEEP_RAGGED, int KG = 1>
 static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M,
                                    int64_t N, int64_t K, hipStream_t st, const LinBatch* many, int count, int64_t ldc) {
     constexpr int TM = 32 * MB * WM;
@@ -767,10 +804,10 @@ static void launch_tile_gemm_shape(const LinOperand& A, const LinOperand& B, con
     // no checks at all when every tile and every step is whole and rows start 16-byte aligned
     const bool exact = M % TM == 0 && N % TN == 0 && K % BK == 0 && A.ld % 8 == 0 && B.ld % 16 == 0;
     if (exact)
-        hipLaunchKernelGGL((k_tile_gemm<AL, BL, true, OUT, MB, TN, BK, WM, DEEP_EXACT>), grid, dim3(128 * WM), 0, st, A, B, bias,
+        hipLaunchKernelGGL((k_tile_gemm<AL, BL, true, OUT, MB, TN, BK, WM, DEEP_EXACT, KG>), grid, dim3(128 * WM * KG), 0, st, A, B, bias,
                            C, (int)M, (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
     else
-        hipLaunchKernelGGL((k_tile_gemm<AL, BL, false, OUT, MB, TN, BK, WM, DEEP_RAGGED>), grid, dim3(128 * WM), 0, st, A, B, bias,
+        hipLaunchKernelGGL((k_tile_gemm<AL, BL, false, OUT, MB, TN, BK, WM, DEEP_RAGGED, KG>), grid, dim3(128 * WM * KG), 0, st, A, B, bias,
                            C, (int)M, (int)N, (int)K, (int)tiles_m, (int)tiles_n, batch);
 }
 
@@ -783,7 +820,8 @@ static bool lin_small(int64_t M, int64_t N, int count) {
 
 // Whether a product of the linear layer splits its contraction over the waves of a workgroup (T: its 32 x 32 tiles).  Against
 // the tiles of launch_tile_gemm, us, split / not: forward, 256 tokens, 768 -> 768 (T = 192) 4.0 / 6.6, 2048 -> 2048 (512) 9.2 /
-// 13.4, 1000 tokens, 2048 -> 768 (768) 11.3 / 13.3, 768 -> 768 6.4 / 6.9, but 1024 -> 1024 (1024) 9.0 / 8.2.  A weight with k
+// 13.4, 500 tokens, 1024 -> 1024 (512) 6.5 / 7.4, but 1000 tokens, 2048 ->
+// 768 (768) 13.0 / 11.8, 256 tokens, 1024 -> 2736 (688) 7.6 / 7.3.  A weight with k
 // slow (grad_input) needs twice the LDS per wave, and a chain that is long for the number of tiles: 256 tokens, 2048 -> 2048
 // (512) 11.7 / 13.9, 500 tokens, K = 3001, 1007 columns (512) 55 / 95, but with grad_W in the same launch 256 tokens, K = 768,
 // 2048 columns (512) 9.4 / 8.0, K = 1024, 2736 columns (688) 14.3 / 11.0.  grad_W: 512 x 512 (256), 1024 tokens 4.8 / 7.1, 4096
@@ -793,7 +831,7 @@ static bool lin_ksplit(int64_t M, int64_t N, int64_t K) {
     const int64_t T = ((M + 31) / 32) * ((N + 31) / 32);
     if (AL == kBf16KSlow && BL == kBf16KSlow) return T <= 320 && K >= 512;
     if (BL == kInt8KSlow || BL == kInt8ZKSlow) return T <= 512 && K >= 3 * T;
-    return T <= 768;
+    return T <= (K < 512 ? 768 : 512);
 }
 
 static LinProduct lin_product(const LinOperand& A, const LinOperand& B, uint16_t* C, int64_t M, int64_t N, int64_t K, int64_t ldc,
@@ -835,10 +873,18 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    1024 -> 2736 (176) 14.5 / 15.9 and 300 tokens, 4096 -> 11008 (258) 60 / 64; grad_input, 1000 x 2048 -> 2048 (128) 20 / 31,
 //    256 x 4096 -> 11008 (172) 53 / 43; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 1024 tokens, 1536 x 2048 (192) 15.7 / 15.9, 1664 x 2048 (208)
 //    20.8 / 15.9.
-// ldc: row pitch of C in elements (0: N).
+//  * two groups of waves (INT8 B, K >= 512) where these tiles would be at most a workgroup per CU, us, one group / two: 64 x 64,
+//    forward, 256 tokens, 4096 -> 4096 31.0 / 20.5, 500 tokens, 2048 -> 2048 13.6 / 11.2, 512 -> 2048 6.3 / 5.9 (256 -> 2048, 1000
+//    tokens, 6.0 / 6.5), 1024 -> 1024, 1000 tokens, 9.0 / 7.9, grad_input 256 x 11008 -> 4096 80 / 50; beyond 256 of these 128 x 64 up to
+//    as many, forward, 1000 tokens, 2048 -> 2048 21.7 / 18.9, 5461 -> 2048 62 / 57, grad_input 23.2 / 19.8 (two groups of
+//    64 x 64 tiles there 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2; rows that start unaligned, 900
+//    tokens, 1599 -> 1600, 20.9 / 23.5); 128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 /
+//    27.7, 256 tokens, 4096 -> 11008 43 / 38.  grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
+// ldc: row pitch of C in elements (0: N).  groups: whether two groups may be used.
 template <int AL, int BL, typename OUT>
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
-                            int64_t K, hipStream_t st, const LinBatch* many = nullptr, int count = 1, int64_t ldc = 0) {
+                            int64_t K, hipStream_t st, const LinBatch* many = nullptr, int count = 1, int64_t ldc = 0,
+                            bool groups = true) {
     if constexpr (AL == kBf16KFast && BL != kBf16KFast && BL != kBf16KSlow && std::is_same_v<OUT, uint16_t>) {
         if (many == nullptr && lin_ksplit<AL, BL>(M, N, K)) {
             const LinProduct p = lin_product(A, B, C, M, N, K, ldc ? ldc : N, 32);
@@ -854,6 +900,25 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
             if (lin_whole(p, 32)) eight ? launch(std::true_type(), Eight()) : launch(std::true_type(), Four());
             else eight ? launch(std::false_type(), Eight()) : launch(std::false_type(), Four());
             return check_launch();
+        }
+        // Two groups of waves per tile (see tile_gemm) while tiles are about a workgroup per CU or fewer
+        if (many == nullptr && groups && K >= 512) {
+            const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 63) / 64;
+            const bool wide = A.ld % 8 == 0 && (BL == kInt8KSlow || BL == kInt8ZKSlow || B.ld % 16 == 0);   // 16-byte aligned along k
+            auto launch = [&](auto mb, auto tn) {
+                launch_tile_gemm_shape<AL, BL, OUT, mb.value, tn.value, 64, 2, true, true, 2>(A, B, bias, C, M, N, K, st, nullptr, 1,
+                                                                                             ldc);
+                return check_launch();
+            };
+            using N64 = std::integral_constant<int, 64>;
+            using N128 = std::integral_constant<int, 128>;
+            if (!lin_small<AL, BL>(M, N, 1)) {
+                if (tiles_m * ((N + 127) / 128) <= 256) return launch(std::integral_constant<int, 2>(), N128());
+            } else if ((M + 63) / 64 * tiles_n <= 256) {
+                return launch(std::integral_constant<int, 1>(), N64());
+            } else if (tiles_m * tiles_n <= 256 && (wide || K >= 4096)) {
+                return launch(std::integral_constant<int, 2>(), N64());
+            }
         }
     }
     constexpr bool both_fast = (AL == kBf16KFast || AL == kInt8KFast || AL == kInt8ZKFast) &&
@@ -956,7 +1021,8 @@ static int launch_linear_backward(const LinOperand& A0, const LinOperand& B0, ui
     if (dx) {
         if (split0) {
             if (int e = launch_pair(true, false)) return e;
-        } else if (int e = launch_tile_gemm<kBf16KFast, BL, uint16_t>(A0, B0, nullptr, dx, M0, N0, K0, st, nullptr, 1, ldc0)) {
+        } else if (int e = launch_tile_gemm<kBf16KFast, BL, uint16_t>(A0, B0, nullptr, dx, M0, N0, K0, st, nullptr, 1, ldc0,
+                                                                                      !(pair0 && pair1))) {
             return e;
         }
     }

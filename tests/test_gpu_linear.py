@@ -117,6 +117,18 @@ def test_ragged_tiles_of_whole_chunks(tokens, m, n):
 
 
 @pytest.mark.parametrize("tokens,m,n", [
+    (512, 1152, 576), (500, 1100, 600), (500, 1101, 1025),   # 64 x 64 tiles, forward: 9 steps, whole and ragged, a partial one
+    (576, 640, 1664), (520, 700, 1500), (90, 515, 9000),     # ... grad_input
+    (1024, 1152, 576), (1000, 1100, 528), (1000, 576, 2048), (1000, 632, 1900),   # 128 x 64
+    (2048, 2048, 512), (2040, 2040, 600), (2048, 576, 1792), (1700, 605, 1601),   # 128 x 128
+])
+def test_two_groups_of_waves(tokens, m, n):
+    """The steps of the contraction dealt out to two groups: an odd number of them, a partial last one, edges of the tiles."""
+    test_forward(tokens, m, n)
+    test_backward(tokens, m, n)
+
+
+@pytest.mark.parametrize("tokens,m,n", [
     (512, 64, 64), (64, 512, 64), (32, 32, 32),      # whole 32 x 32 tiles, fewer steps than waves, one step
     (33, 31, 577), (100, 130, 1000),                 # ragged edges; 10 steps over 8 waves, the last one partial
     (544, 530, 70),                                  # four waves in the forward pass
