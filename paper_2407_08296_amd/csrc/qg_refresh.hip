@@ -171,6 +171,19 @@ __device__ __forceinline__ void mma4_kfast(const double* At, const double* Bt, d
     }
 }
 
+// f(row, col, value) for every result of the wave's quadrant, row and col inside the workgroup's block.
+template <bool KSLOW, int NF, typename F>
+__device__ __forceinline__ void for_each_acc4(const double (&acc)[NF][NF], int lane, int wi, int wj, F f) {
+    const Lane4 l(lane);
+#pragma unroll
+    for (int a = 0; a < NF; ++a)
+#pragma unroll
+        for (int b = 0; b < NF; ++b) {
+            if constexpr (KSLOW) f(wi * 8 * NF + a / 2 * 16 + 2 * l.i + a % 2, wj * 8 * NF + b / 2 * 16 + 2 * l.j + b % 2, acc[a][b]);
+            else f((wi * NF + a) * 8 + l.i, (wj * NF + b) * 8 + l.j, acc[a][b]);
+        }
+}
+
 template <int W>
 __device__ __forceinline__ void zero_acc4(double (&acc)[W][W]) {
 #pragma unroll
@@ -340,7 +353,8 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
 // ---------------------------------------------------------------------------------------------------------------
 // Blocked Cholesky S + sigma I = L L^T in place (lower triangle), right-looking, one block column per step kb:
 //   chol_diag_block: L_kk from the diagonal block, and X_kk = L_kk^-1 (to Dinv[kb] and to the diagonal block of X)
-//   k_chol_panel:    L_ik = S_ik X_kk^T for the blocks below
+//   k_chol_panel:    L_ik = S_ik X_kk^T for the blocks below, kept transposed as block (k, i) of S (whose upper triangle holds
+//                    nothing else), so that S_ik stays what it is for all that read it in the same launch
 //   k_chol_update:   S_ij -= L_ik L_jk^T for i >= j > kb, and in the same launch the next diagonal block (by the
 //                    workgroup that has just updated it) and block row kb of X = L^-1
 // Rows and columns at or past r (r not a multiple of 64) behave like an identity block.  A pivot that is not positive
@@ -544,32 +558,29 @@ __global__ __launch_bounds__(256) void k_chol_diag(double* __restrict__ S, int r
 
 __global__ __launch_bounds__(256) void k_chol_panel(double* __restrict__ S, int r, int kb, const double* __restrict__ Dinv,
                                                     BatchStride st) {
+    constexpr int P = kKC + 2;
     S += blockIdx.z * st.S;
     Dinv += blockIdx.z * st.D;
-    __shared__ double At[kNB * kPitchKF];
-    __shared__ double Bt[kNB * kPitchKF];
+    __shared__ __attribute__((aligned(16))) double At[kNB * P];
+    __shared__ __attribute__((aligned(16))) double Bt[kNB * P];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wi = wave >> 1, wj = wave & 1;
     const int ib = kb + 1 + blockIdx.x;
     const double* D = Dinv + (int64_t)kb * kNB * kNB;
-    BlockStage<kNB, kKC, kPitchKF, double> sa, sb;
-    f64x4 acc[2][2];
-    zero_acc(acc);
-    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
-    sb.fetch(D, kNB, 0, 0, kNB, kNB);
-    for (int kc = 0; kc < kNB; kc += kKC) {
-        sa.commit(At);
-        sb.commit(Bt);
-        __syncthreads();
-        if (kc + kKC < kNB) {
-            sa.fetch(S, r, ib * kNB, kb * kNB + kc + kKC, r, r);
-            sb.fetch(D, kNB, 0, kc + kKC, kNB, kNB);
-        }
-        mma_chunk(At, kPitchKF, 1, Bt, kPitchKF, 1, acc, lane, wi, wj);
-        __syncthreads();
-    }
-    for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
-        const int gi = ib * kNB + row, gj = kb * kNB + col;
-        if (gi < r && gj < r) S[(int64_t)gi * r + gj] = x;
+    BlockStage<kNB, kKC, P, double> sa, sb;
+    double acc[4][4];
+    zero_acc4(acc);
+    f64_chunks<kKC>(0, kNB,
+        [&](int k) {
+            sa.fetch(S, r, ib * kNB, kb * kNB + k, r, r);
+            sb.fetch(D, kNB, 0, k, kNB, kNB);
+        },
+        [&] {
+            sa.commit(At);
+            sb.commit(Bt);
+        },
+        [&] { mma4_kfast<kKC, P, 2>(At, Bt, acc, lane, wi, wj); });
+    for_each_acc4<false>(acc, lane, wi, wj, [&](int row, int col, double x) {
+        if (ib * kNB + row < r) S[(int64_t)(kb * kNB + col) * r + ib * kNB + row] = x;
     });
 }
 
@@ -590,35 +601,35 @@ __device__ __forceinline__ void trinv_strip(const double* __restrict__ S, double
     if (c0 >= r) return;
     BlockStage<kNB, kNB, kPitchD, double> sa;
     BlockStage<kNB, kSB, kPitchX, double> sb;
-    auto product = [&] {
+    auto product = [&](int a_pi, int a_pk) {   // element (i, k) of A at At[i * a_pi + k * a_pk]
         f64x4 acc[2] = {{0.0, 0.0, 0.0, 0.0}, {0.0, 0.0, 0.0, 0.0}};
-        const double *ap = At + (wave * kSB + l16) * kPitchD + l4, *bp = Bt + l4 * kPitchX + l16;
+        const double *ap = At + (wave * kSB + l16) * a_pi + l4 * a_pk, *bp = Bt + l4 * kPitchX + l16;
 #pragma unroll
         for (int k = 0; k < kNB; k += 4)
-            acc[(k / 4) & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[k], bp[k * kPitchX], acc[(k / 4) & 1], 0, 0, 0);
+            acc[(k / 4) & 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[k * a_pk], bp[k * kPitchX], acc[(k / 4) & 1], 0, 0, 0);
         return acc[0] + acc[1];
     };
     f64x4 sum{0.0, 0.0, 0.0, 0.0};
-    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
+    sa.fetch(S, r, kb * kNB, ib * kNB, r, r);
     sb.fetch(X, r, kb * kNB, c0, r, r);
     for (int j = kb; j < ib; ++j) {
         sa.commit(At);
         sb.commit(Bt);
         __syncthreads();
         if (j + 1 < ib) {
-            sa.fetch(S, r, ib * kNB, (j + 1) * kNB, r, r);
+            sa.fetch(S, r, (j + 1) * kNB, ib * kNB, r, r);
             sb.fetch(X, r, (j + 1) * kNB, c0, r, r);
         } else {
             sa.fetch(Dinv + (int64_t)ib * kNB * kNB, kNB, 0, 0, kNB, kNB);
         }
-        sum += product();
+        sum += product(1, kPitchD);
         __syncthreads();
     }
     sa.commit(At);
 #pragma unroll
     for (int v = 0; v < 4; ++v) Bt[(wave * kSB + 4 * v + l4) * kPitchX + l16] = sum[v];
     __syncthreads();
-    const f64x4 x = product();
+    const f64x4 x = product(kPitchD, 1);
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int i = ib * kNB + wave * kSB + 4 * v + l4, c = c0 + l16;
@@ -628,8 +639,10 @@ __device__ __forceinline__ void trinv_strip(const double* __restrict__ S, double
 
 // The whole block by one workgroup, a quarter of the staging per MFMA, for launches that fill the chip (see kBlocksFrom).  The
 // order of every sum is the strips': per 64 deep, even and odd quadruples of the contraction index apart.
-// At: kNB * kPitchKF, Bt: kNB * kPitchT doubles of LDS.
+// At: kTrinvA, Bt: kNB * kPitchT doubles of LDS.
 constexpr int kPitchT = kNB + 2;      // LDS pitch of a 64 x 64 intermediate
+constexpr int kTrinvA = kKC * F64Tile<kNB>::PITCH_KS;   // a chunk of L, then one of X_ii
+static_assert(kTrinvA >= kNB * kPitchKF, "either fits");
 
 __device__ __forceinline__ void trinv_block(const double* __restrict__ S, double* __restrict__ X,
                                             const double* __restrict__ Dinv, int r, int ib, int kb, double* At, double* Bt) {
@@ -640,28 +653,28 @@ __device__ __forceinline__ void trinv_block(const double* __restrict__ S, double
     zero_acc(sum);
     zero_acc(acc[0]);
     zero_acc(acc[1]);
-    auto product = [&](const double* B, int pitch) {
+    auto product = [&](int a_pi, int a_pk, const double* B, int pitch) {   // element (i, k) of A at At[i * a_pi + k * a_pk]
 #pragma unroll
         for (int k0 = 0; k0 < kKC; k0 += 4)
-            mma_chunk<4>(At + k0, kPitchKF, 1, B + k0 * pitch, 1, pitch, acc[(k0 / 4) & 1], lane, wi, wj);
+            mma_chunk<4>(At + k0 * a_pk, a_pi, a_pk, B + k0 * pitch, 1, pitch, acc[(k0 / 4) & 1], lane, wi, wj);
     };
-    BlockStage<kNB, kKC, kPitchKF, double> sa;
-    BlockStage<kKC, kNB, PITCH, double> sb;
+    BlockStage<kKC, kNB, PITCH, double> sa, sb;
+    BlockStage<kNB, kKC, kPitchKF, double> sd;
     const double* D = Dinv + (int64_t)ib * kNB * kNB;
     const int k_end = ib * kNB;
-    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
+    sa.fetch(S, r, kb * kNB, ib * kNB, r, r);
     sb.fetch(X, r, kb * kNB, kb * kNB, r, r);
     for (int kc = kb * kNB; kc < k_end; kc += kKC) {
         sa.commit(At);
         sb.commit(Bt);
         __syncthreads();
         if (kc + kKC < k_end) {
-            sa.fetch(S, r, ib * kNB, kc + kKC, r, r);
+            sa.fetch(S, r, kc + kKC, ib * kNB, r, r);
             sb.fetch(X, r, kc + kKC, kb * kNB, r, r);
         } else {
-            sa.fetch(D, kNB, 0, 0, kNB, kNB);     // first chunk of the second product
+            sd.fetch(D, kNB, 0, 0, kNB, kNB);     // first chunk of the second product
         }
-        product(Bt, PITCH);
+        product(1, PITCH, Bt, PITCH);
         if ((kc + kKC) % kNB == 0) {
 #pragma unroll
             for (int a = 0; a < 2; ++a)
@@ -675,10 +688,10 @@ __device__ __forceinline__ void trinv_block(const double* __restrict__ S, double
     double* Tm = Bt;
     for_each_acc(sum, lane, wi, wj, [&](int row, int col, double x) { Tm[row * kPitchT + col] = x; });
     for (int kc = 0; kc < kNB; kc += kKC) {
-        sa.commit(At);
+        sd.commit(At);
         __syncthreads();       // also publishes Tm on the first pass
-        if (kc + kKC < kNB) sa.fetch(D, kNB, 0, kc + kKC, kNB, kNB);
-        product(Tm + kc * kPitchT, kPitchT);
+        if (kc + kKC < kNB) sd.fetch(D, kNB, 0, kc + kKC, kNB, kNB);
+        product(kPitchKF, 1, Tm + kc * kPitchT, kPitchT);
         __syncthreads();
     }
 #pragma unroll
@@ -694,30 +707,36 @@ __device__ __forceinline__ void trinv_block(const double* __restrict__ S, double
 template <bool BLOCKS>
 __global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S, double* __restrict__ X,
                                                    const double* __restrict__ Dinv, int r, int ib, BatchStride st) {
-    __shared__ double buf[BLOCKS ? kNB * (kPitchKF + kPitchT) : kNB * (kPitchD + kPitchX)];
+    __shared__ double buf[BLOCKS ? kTrinvA + kNB * kPitchT : kNB * (kPitchD + kPitchX)];
     S += blockIdx.z * st.S;
     X += blockIdx.z * st.X;
     Dinv += blockIdx.z * st.D;
-    if constexpr (BLOCKS) trinv_block(S, X, Dinv, r, ib, blockIdx.x, buf, buf + kNB * kPitchKF);
+    if constexpr (BLOCKS) trinv_block(S, X, Dinv, r, ib, blockIdx.x, buf, buf + kTrinvA);
     else trinv_strip(S, X, Dinv, r, ib, blockIdx.x / kStrips, blockIdx.x % kStrips, buf, buf + kNB * kPitchD);
 }
 
-// Workgroups 0 .. pairs-1: the trailing blocks of step kb.  FUSED: block (kb+1, kb+1) goes on to be factored, and workgroups
-// the kStrips * kb after them take block row kb of X (L's row kb and X_kk are final, X's rows above too): in one launch the
-// three fill the chip together, and a block column costs two launches where it takes four.  But every workgroup then holds the
-// diagonal block's 156 registers and 42 KB of LDS, three on a CU; on its own the trailing update fits five.
-template <bool FUSED>
-__global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int r, int kb, int pairs,
+// Workgroups 0 .. pairs-1: the trailing blocks of step kb.  kUpdateFused: block (kb+1, kb+1) goes on to be factored, and
+// workgroups the kStrips * kb after them take block row kb of X (L's row kb and X_kk are final, X's rows above too): in one launch
+// the three fill the chip together, and a block column costs two launches where it takes four.  But every workgroup then holds
+// the diagonal block's registers and 42 KB of LDS, three on a CU; on its own the trailing update fits more.
+// kUpdatePanel: the panel too.  A workgroup forms the two blocks of L that it needs itself, 64 x 64 x 64 products of 1.7 us that
+// a launch of their own takes 5 us for; only where every workgroup has a CU, since there are three products instead of one.
+// (us per refresh, never / up to 128 / 256 / 512 workgroups: 768 x 768, r = 256 285 / 263 / 265 / 264, 2048 x 2048, r = 512 585 / 533 / 533 /
+// 533, sixteen of them 1676 / 1678 / 1675 / 1703, 4096 x 4096, r = 1024 1448 / 1334 / 1334 / 1336.)
+enum : int { kUpdateAlone = 0, kUpdateFused = 1, kUpdatePanel = 2 };
+
+template <int MODE>
+__global__ __launch_bounds__(256, MODE == kUpdateFused ? 3 : 1) void k_chol_update(double* __restrict__ S, int r, int kb, int pairs,
                                                      double* __restrict__ Dinv, double* __restrict__ X,
                                                      int32_t* __restrict__ info, const double* __restrict__ shift,
                                                      double flag_factor, BatchStride st) {
     S += blockIdx.z * st.S;
     X += blockIdx.z * st.X;
     Dinv += blockIdx.z * st.D;
-    constexpr int UPDATE = 2 * kNB * kPitchKF, BLOCK = kNB * (kPitchD + kPitchX);
-    __shared__ double buf[FUSED && BLOCK > UPDATE ? BLOCK : UPDATE];
-    double *At = buf, *Bt = buf + kNB * kPitchKF;
-    if constexpr (FUSED) {
+    constexpr int P = F64Tile<kNB>::PITCH_KS, PW = kNB + 2;   // pitch of a chunk of L, of a whole 64 x 64 block
+    constexpr int UPDATE = MODE == kUpdatePanel ? 3 * kNB * PW : 2 * kKC * P, BLOCK = kNB * (kPitchD + kPitchX);
+    __shared__ __attribute__((aligned(16))) double buf[MODE != kUpdateAlone && BLOCK > UPDATE ? BLOCK : UPDATE];
+    if constexpr (MODE != kUpdateAlone) {
         const int strip = (int)blockIdx.x - pairs;
         if (strip >= 0) {
             trinv_strip(S, X, Dinv, r, kb, strip / kStrips, strip % kStrips, buf, buf + kNB * kPitchD);
@@ -728,31 +747,58 @@ __global__ __launch_bounds__(256) void k_chol_update(double* __restrict__ S, int
     int pi, pj;
     lower_pair(blockIdx.x, pi, pj);
     const int ib = kb + 1 + pi, jb = kb + 1 + pj;
-    BlockStage<kNB, kKC, kPitchKF, double> sa, sb;
-    f64x4 acc[2][2];
-    zero_acc(acc);
-    sa.fetch(S, r, ib * kNB, kb * kNB, r, r);
-    sb.fetch(S, r, jb * kNB, kb * kNB, r, r);
-    for (int kc = 0; kc < kNB; kc += kKC) {
-        sa.commit(At);
-        sb.commit(Bt);
+    double acc[4][4];
+    zero_acc4(acc);
+    if constexpr (MODE == kUpdatePanel) {
+        BlockStage<kNB, kNB, PW, double> si, sj, sd;
+        double *Li = buf, *Lj = ib == jb ? Li : buf + kNB * PW, *D = buf + 2 * kNB * PW;
+        si.fetch(S, r, ib * kNB, kb * kNB, r, r);
+        sd.fetch(Dinv + (int64_t)kb * kNB * kNB, kNB, 0, 0, kNB, kNB);
+        if (ib != jb) sj.fetch(S, r, jb * kNB, kb * kNB, r, r);
+        si.commit(Li);
+        sd.commit(D);
+        if (ib != jb) sj.commit(Lj);
         __syncthreads();
-        if (kc + kKC < kNB) {
-            sa.fetch(S, r, ib * kNB, kb * kNB + kc + kKC, r, r);
-            sb.fetch(S, r, jb * kNB, kb * kNB + kc + kKC, r, r);
-        }
-        mma_chunk(At, kPitchKF, 1, Bt, kPitchKF, 1, acc, lane, wi, wj);
+        auto panel = [&](double* L) {   // L <- (L X_kk^T)^T
+            double x[4][4];
+            zero_acc4(x);
+            mma4_kfast<kNB, PW, 2>(L, D, x, lane, wi, wj);
+            __syncthreads();
+            for_each_acc4<false>(x, lane, wi, wj, [&](int row, int col, double v) { L[col * PW + row] = v; });
+        };
+        panel(Li);
+        if (ib != jb) panel(Lj);
         __syncthreads();
+        if (ib == jb)   // kept for X
+            for (int e = threadIdx.x; e < kNB * kNB; e += 256) {
+                const int k = e / kNB, row = e % kNB;
+                if (ib * kNB + row < r) S[(int64_t)(kb * kNB + k) * r + ib * kNB + row] = Li[k * PW + row];
+            }
+        mma4_kslow<kNB, PW, 2>(Li, Lj, acc, lane, wi, wj);
+        __syncthreads();
+    } else {
+        double *At = buf, *Bt = ib == jb ? At : buf + kKC * P;
+        BlockStage<kKC, kNB, P, double> sa, sb;
+        f64_chunks<kKC>(0, kNB,
+            [&](int k) {
+                sa.fetch(S, r, kb * kNB + k, ib * kNB, r, r);
+                if (ib != jb) sb.fetch(S, r, kb * kNB + k, jb * kNB, r, r);
+            },
+            [&] {
+                sa.commit(At);
+                if (ib != jb) sb.commit(Bt);
+            },
+            [&] { mma4_kslow<kKC, P, 2>(At, Bt, acc, lane, wi, wj); });
     }
-    if (!FUSED || blockIdx.x != 0) {
-        for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
+    if (MODE == kUpdateAlone || blockIdx.x != 0) {
+        for_each_acc4<true>(acc, lane, wi, wj, [&](int row, int col, double x) {
             const int gi = ib * kNB + row, gj = jb * kNB + col;
             if (gi < r && gj < r) S[(int64_t)gi * r + gj] -= x;
         });
         return;
     }
-    if constexpr (FUSED) {
-        for_each_acc(acc, lane, wi, wj, [&](int row, int col, double x) {
+    if constexpr (MODE != kUpdateAlone) {
+        for_each_acc4<true>(acc, lane, wi, wj, [&](int row, int col, double x) {
             const int gi = ib * kNB + row, gj = ib * kNB + col;
             buf[row * kPitchD + col] = (gi < r && gj < r) ? S[(int64_t)gi * r + gj] - x : (row == col ? 1.0 : 0.0);
         });
@@ -951,12 +997,13 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     hipLaunchKernelGGL(k_chol_diag<true>, dim3(1, 1, B), blk, 0, stream, S, (int)r, 0, Dinv, X, info, shift, flag_factor, st);
     for (int kb = 0; kb + 1 < nt; ++kb) {
         const int below = nt - kb - 1, left = below * (below + 1) / 2;
-        hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
+        const bool panel = fused && (int64_t)(left + kStrips * kb) * batch <= 256;
+        if (!panel) hipLaunchKernelGGL(k_chol_panel, dim3(below, 1, B), blk, 0, stream, S, (int)r, kb, Dinv, st);
         if (fused) {
-            hipLaunchKernelGGL(k_chol_update<true>, dim3(left + kStrips * kb, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info,
-                               shift, flag_factor, st);
+            hipLaunchKernelGGL(panel ? k_chol_update<kUpdatePanel> : k_chol_update<kUpdateFused>, dim3(left + kStrips * kb, 1, B), blk, 0,
+                               stream, S, (int)r, kb, left, Dinv, X, info, shift, flag_factor, st);
         } else {
-            hipLaunchKernelGGL(k_chol_update<false>, dim3(left, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
+            hipLaunchKernelGGL(k_chol_update<kUpdateAlone>, dim3(left, 1, B), blk, 0, stream, S, (int)r, kb, left, Dinv, X, info, shift,
                                flag_factor, st);
             hipLaunchKernelGGL(k_chol_diag<false>, dim3(1, 1, B), blk, 0, stream, S, (int)r, kb + 1, Dinv, X, info, shift,
                                flag_factor, st);
