@@ -172,6 +172,14 @@ def _stream() -> int:
 _BF16 = (torch.bfloat16, torch.int16, torch.uint16)
 
 
+def _bf16_rows(like: torch.Tensor, rows: int, cols: int) -> torch.Tensor:
+    """A new bf16 [rows][cols] where `like` is.  (us on a host where the call of a small layer takes 8: sizes as a tuple 3.9, as
+    arguments 2.0, new_empty 1.3, which gives a subclass's type for a subclass.)"""
+    if like.dtype is torch.bfloat16 and type(like) is torch.Tensor:
+        return like.new_empty(rows, cols)
+    return torch.empty(rows, cols, dtype=torch.bfloat16, device=like.device)
+
+
 def hparams(beta1=0.9, beta2=0.999, eps=1e-8, lr=1e-3, alpha=0.25) -> HParams:
     return HParams(beta1, beta2, eps, lr, alpha)
 
@@ -179,7 +187,7 @@ def hparams(beta1=0.9, beta2=0.999, eps=1e-8, lr=1e-3, alpha=0.25) -> HParams:
 # ---------------------------------------------------------------- quantizers
 def quant_int8(x: torch.Tensor):
     rows, cols = x.shape
-    q = torch.empty((rows, cols), dtype=torch.int8, device=x.device)
+    q = torch.empty(rows, cols, dtype=torch.int8, device=x.device)
     s = torch.empty((rows, (cols + GROUP - 1) // GROUP), dtype=torch.float32, device=x.device)
     _check(lib().qg_quant_int8(_ptr(x, (torch.float32,)), rows, cols, GROUP, _ptr(q), _ptr(s), _stream()))
     return q, s
@@ -196,14 +204,14 @@ def quant_int4(x: torch.Tensor):
 
 def dequant_int8(q: torch.Tensor, s: torch.Tensor) -> torch.Tensor:
     rows, cols = q.shape
-    x = torch.empty((rows, cols), dtype=torch.float32, device=q.device)
+    x = torch.empty(rows, cols, dtype=torch.float32, device=q.device)
     _check(lib().qg_dequant_int8(_ptr(q, (torch.int8,)), _ptr(s, (torch.float32,)), rows, cols, GROUP, _ptr(x),
                                  _stream()))
     return x
 
 
 def dequant_int4(q: torch.Tensor, s: torch.Tensor, rows: int, cols: int) -> torch.Tensor:
-    x = torch.empty((rows, cols), dtype=torch.float32, device=q.device)
+    x = torch.empty(rows, cols, dtype=torch.float32, device=q.device)
     _check(lib().qg_dequant_int4(_ptr(q, (torch.uint8,)), _ptr(s, (torch.float32,)), rows, cols, GROUP, _ptr(x),
                                  _stream()))
     return x
@@ -212,7 +220,7 @@ def dequant_int4(q: torch.Tensor, s: torch.Tensor, rows: int, cols: int) -> torc
 # ---------------------------------------------------------------- step pieces
 def project(Pq, Ps, G, m: int, n: int, r: int, R: torch.Tensor | None = None) -> torch.Tensor:
     if R is None:
-        R = torch.empty((r, n), dtype=torch.float32, device=G.device)
+        R = torch.empty(r, n, dtype=torch.float32, device=G.device)
     _check(lib().qg_project(_ptr(Pq, (torch.uint8,)), _ptr(Ps, (torch.float32,)), _ptr(G, _BF16), m, n, r, GROUP,
                             _ptr(R, (torch.float32,)), None, 0, _stream()))
     return R
@@ -240,7 +248,7 @@ def subspace_cossim(PqA, PsA, PqB, PsB, m: int, r: int, weights: torch.Tensor | 
     """qg_subspace_cossim, or qg_subspace_cossim_weighted when `weights` (fp32 [r]) is given."""
     nbytes = lib().qg_cossim_workspace_bytes(m, r)
     ws = torch.empty((max(nbytes, 16),), dtype=torch.uint8, device=PqA.device)
-    out = torch.empty((1,), dtype=torch.float32, device=PqA.device)
+    out = torch.empty(1, dtype=torch.float32, device=PqA.device)
     if weights is None:
         _check(lib().qg_subspace_cossim(_ptr(PqA, (torch.uint8,)), _ptr(PsA, (torch.float32,)), _ptr(PqB, (torch.uint8,)),
                                         _ptr(PsB, (torch.float32,)), m, r, GROUP, _ptr(out), _ptr(ws), nbytes, _stream()))
@@ -348,7 +356,7 @@ def backproject_update_sr_many(plan: StepPlan, hp: HParams, seed: int, step: int
 # ---------------------------------------------------------------- zero-point (asymmetric) INT8 weights
 def quant_int8_zp(x: torch.Tensor):
     rows, cols = x.shape
-    q = torch.empty((rows, cols), dtype=torch.int8, device=x.device)
+    q = torch.empty(rows, cols, dtype=torch.int8, device=x.device)
     s = torch.empty((rows, (cols + GROUP - 1) // GROUP), dtype=torch.float32, device=x.device)
     z = torch.empty_like(s)
     _check(lib().qg_quant_int8_zp(_ptr(x, (torch.float32,)), rows, cols, GROUP, _ptr(q), _ptr(s), _ptr(z), _stream()))
@@ -357,7 +365,7 @@ def quant_int8_zp(x: torch.Tensor):
 
 def dequant_int8_zp(q: torch.Tensor, s: torch.Tensor, z: torch.Tensor) -> torch.Tensor:
     rows, cols = q.shape
-    x = torch.empty((rows, cols), dtype=torch.float32, device=q.device)
+    x = torch.empty(rows, cols, dtype=torch.float32, device=q.device)
     _check(lib().qg_dequant_int8_zp(_ptr(q, (torch.int8,)), _ptr(s, (torch.float32,)), _ptr(z, (torch.float32,)), rows,
                                     cols, GROUP, _ptr(x), _stream()))
     return x
@@ -381,7 +389,7 @@ def int8_linear_zp_forward(x: torch.Tensor, Wq: torch.Tensor, Ws: torch.Tensor, 
                            bias: torch.Tensor | None = None):
     tokens, n = x.shape
     m = Wq.shape[0]
-    y = torch.empty((tokens, m), dtype=torch.bfloat16, device=x.device)
+    y = _bf16_rows(x, tokens, m)
     _check(lib().qg_int8_linear_zp_forward(_ptr(x, _BF16), _ptr(Wq, (torch.int8,)), _ptr(Ws, (torch.float32,)),
                                            _ptr(Wz, (torch.float32,)), _ptr(bias, _BF16), tokens, m, n, GROUP,
                                            _ptr(y), _stream()))
@@ -391,8 +399,8 @@ def int8_linear_zp_forward(x: torch.Tensor, Wq: torch.Tensor, Ws: torch.Tensor, 
 def int8_linear_zp_backward(dy: torch.Tensor, x: torch.Tensor | None, Wq, Ws, Wz, m: int, n: int,
                             want_dx: bool = True, want_G: bool = True):
     tokens = dy.shape[0]
-    dx = torch.empty((tokens, n), dtype=torch.bfloat16, device=dy.device) if want_dx else None
-    G = torch.empty((m, n), dtype=torch.bfloat16, device=dy.device) if want_G else None
+    dx = _bf16_rows(dy, tokens, n) if want_dx else None
+    G = _bf16_rows(dy, m, n) if want_G else None
     _check(lib().qg_int8_linear_zp_backward(_ptr(dy, _BF16), _ptr(x, _BF16), _ptr(Wq, (torch.int8,)),
                                             _ptr(Ws, (torch.float32,)), _ptr(Wz, (torch.float32,)), tokens, m, n, GROUP,
                                             _ptr(dx), _ptr(G), _stream()))
@@ -404,7 +412,7 @@ def int8_linear_t_zp_forward(x: torch.Tensor, Sq: torch.Tensor, Ss: torch.Tensor
     """Zero-point weight stored transposed (Sq: [n][m])."""
     tokens, n = x.shape
     m = Sq.shape[1]
-    y = torch.empty((tokens, m), dtype=torch.bfloat16, device=x.device)
+    y = _bf16_rows(x, tokens, m)
     _check(lib().qg_int8_linear_t_zp_forward(_ptr(x, _BF16), _ptr(Sq, (torch.int8,)), _ptr(Ss, (torch.float32,)),
                                              _ptr(Sz, (torch.float32,)), _ptr(bias, _BF16), tokens, m, n, GROUP,
                                              _ptr(y), _stream()))
@@ -414,8 +422,8 @@ def int8_linear_t_zp_forward(x: torch.Tensor, Sq: torch.Tensor, Ss: torch.Tensor
 def int8_linear_t_zp_backward(dy: torch.Tensor, x: torch.Tensor | None, Sq, Ss, Sz, m: int, n: int,
                               want_dx: bool = True, want_G: bool = True):
     tokens = dy.shape[0]
-    dx = torch.empty((tokens, n), dtype=torch.bfloat16, device=dy.device) if want_dx else None
-    G = torch.empty((n, m), dtype=torch.bfloat16, device=dy.device) if want_G else None
+    dx = _bf16_rows(dy, tokens, n) if want_dx else None
+    G = _bf16_rows(dy, n, m) if want_G else None
     _check(lib().qg_int8_linear_t_zp_backward(_ptr(dy, _BF16), _ptr(x, _BF16), _ptr(Sq, (torch.int8,)),
                                               _ptr(Ss, (torch.float32,)), _ptr(Sz, (torch.float32,)), tokens, m, n,
                                               GROUP, _ptr(dx), _ptr(G), _stream()))
@@ -425,7 +433,7 @@ def int8_linear_t_zp_backward(dy: torch.Tensor, x: torch.Tensor | None, Sq, Ss, 
 # ---------------------------------------------------------------- 8-bit Adam states
 def state8_quant(x: torch.Tensor, signed: bool):
     count = x.numel()
-    codes = torch.empty((count,), dtype=torch.uint8, device=x.device)
+    codes = torch.empty(count, dtype=torch.uint8, device=x.device)
     scales = torch.empty(((count + GROUP - 1) // GROUP,), dtype=torch.float32, device=x.device)
     _check(lib().qg_state8_quant(_ptr(x, (torch.float32,)), count, int(signed), _ptr(codes), _ptr(scales), _stream()))
     return codes, scales
@@ -455,7 +463,7 @@ def step8(Pq, Ps, G, Wq, Ws, Mq, Ms, Vq, Vs, R, N, m: int, n: int, r: int, hp: H
 def int8_linear_forward(x: torch.Tensor, Wq: torch.Tensor, Ws: torch.Tensor, bias: torch.Tensor | None = None):
     tokens, n = x.shape
     m = Wq.shape[0]
-    y = torch.empty((tokens, m), dtype=torch.bfloat16, device=x.device)
+    y = _bf16_rows(x, tokens, m)
     _check(lib().qg_int8_linear_forward(_ptr(x, _BF16), _ptr(Wq, (torch.int8,)), _ptr(Ws, (torch.float32,)),
                                         _ptr(bias, _BF16), tokens, m, n, GROUP, _ptr(y), _stream()))
     return y
@@ -464,8 +472,8 @@ def int8_linear_forward(x: torch.Tensor, Wq: torch.Tensor, Ws: torch.Tensor, bia
 def int8_linear_backward(dy: torch.Tensor, x: torch.Tensor | None, Wq: torch.Tensor | None, Ws: torch.Tensor | None,
                          m: int, n: int, want_dx: bool = True, want_G: bool = True):
     tokens = dy.shape[0]
-    dx = torch.empty((tokens, n), dtype=torch.bfloat16, device=dy.device) if want_dx else None
-    G = torch.empty((m, n), dtype=torch.bfloat16, device=dy.device) if want_G else None
+    dx = _bf16_rows(dy, tokens, n) if want_dx else None
+    G = _bf16_rows(dy, m, n) if want_G else None
     _check(lib().qg_int8_linear_backward(_ptr(dy, _BF16), _ptr(x, _BF16), _ptr(Wq, (torch.int8,)),
                                          _ptr(Ws, (torch.float32,)), tokens, m, n, GROUP, _ptr(dx), _ptr(G), _stream()))
     return dx, G
@@ -488,7 +496,7 @@ def int8_linear_t_forward(x: torch.Tensor, Sq: torch.Tensor, Ss: torch.Tensor, b
     """The layer on a weight stored transposed (Sq: [n][m])."""
     tokens, n = x.shape
     m = Sq.shape[1]
-    y = torch.empty((tokens, m), dtype=torch.bfloat16, device=x.device)
+    y = _bf16_rows(x, tokens, m)
     _check(lib().qg_int8_linear_t_forward(_ptr(x, _BF16), _ptr(Sq, (torch.int8,)), _ptr(Ss, (torch.float32,)),
                                           _ptr(bias, _BF16), tokens, m, n, GROUP, _ptr(y), _stream()))
     return y
@@ -498,8 +506,8 @@ def int8_linear_t_backward(dy: torch.Tensor, x: torch.Tensor | None, Sq: torch.T
                            m: int, n: int, want_dx: bool = True, want_G: bool = True):
     """Returns (dx [tokens][n], G_S [n][m]) for a weight stored transposed."""
     tokens = dy.shape[0]
-    dx = torch.empty((tokens, n), dtype=torch.bfloat16, device=dy.device) if want_dx else None
-    G = torch.empty((n, m), dtype=torch.bfloat16, device=dy.device) if want_G else None
+    dx = _bf16_rows(dy, tokens, n) if want_dx else None
+    G = _bf16_rows(dy, n, m) if want_G else None
     _check(lib().qg_int8_linear_t_backward(_ptr(dy, _BF16), _ptr(x, _BF16), _ptr(Sq, (torch.int8,)),
                                            _ptr(Ss, (torch.float32,)), tokens, m, n, GROUP, _ptr(dx), _ptr(G), _stream()))
     return dx, G
@@ -507,7 +515,7 @@ def int8_linear_t_backward(dy: torch.Tensor, x: torch.Tensor | None, Sq: torch.T
 
 # ---------------------------------------------------------------- subspace refresh
 def range_apply(G: torch.Tensor, Z: torch.Tensor, m: int, n: int, r: int) -> torch.Tensor:
-    Y = torch.empty((m, r), dtype=torch.float32, device=G.device)
+    Y = torch.empty(m, r, dtype=torch.float32, device=G.device)
     _check(lib().qg_range_apply(_ptr(G, _BF16), _ptr(Z, _BF16), m, n, r, _ptr(Y), _stream()))
     return Y
 
@@ -518,9 +526,9 @@ def orthonormalize(Y: torch.Tensor):
     nbytes = lib().qg_orthonormalize_workspace_bytes(m, r)
     if nbytes == 0:
         raise QGError("libqgalore: shape out of range")
-    ws = torch.empty((nbytes,), dtype=torch.uint8, device=Y.device)
+    ws = torch.empty(nbytes, dtype=torch.uint8, device=Y.device)
     Q = torch.empty_like(Y)
-    info = torch.empty((1,), dtype=torch.int32, device=Y.device)
+    info = torch.empty(1, dtype=torch.int32, device=Y.device)
     _check(lib().qg_orthonormalize(_ptr(Y, (torch.float32,)), m, r, _ptr(Q), _ptr(info), _ptr(ws), nbytes, _stream()))
     return Q, info
 
@@ -531,10 +539,10 @@ def subspace_refresh(Pq, Ps, G, m: int, n: int, r: int, passes: int = 1, workspa
     if nbytes == 0:
         raise QGError("libqgalore: shape out of range")
     if workspace is None:
-        workspace = torch.empty((nbytes,), dtype=torch.uint8, device=G.device)
+        workspace = torch.empty(nbytes, dtype=torch.uint8, device=G.device)
     Pq_new, Ps_new = torch.empty_like(Pq), torch.empty_like(Ps)
-    cos = torch.empty((1,), dtype=torch.float32, device=G.device)
-    info = torch.empty((1,), dtype=torch.int32, device=G.device)
+    cos = torch.empty(1, dtype=torch.float32, device=G.device)
+    info = torch.empty(1, dtype=torch.int32, device=G.device)
     _check(lib().qg_subspace_refresh(_ptr(Pq, (torch.uint8,)), _ptr(Ps, (torch.float32,)), _ptr(G, _BF16), m, n, r,
                                      GROUP, passes, _ptr(Pq_new), _ptr(Ps_new), _ptr(cos), _ptr(info),
                                      _ptr(workspace), workspace.numel(), _stream()))
@@ -553,15 +561,15 @@ def subspace_refresh_many(Pqs, Pss, Gs, m: int, n: int, r: int, passes: int = 1,
         nbytes = lib().qg_refresh_workspace_bytes(count, m, ld or n, r)
         if nbytes == 0:
             raise QGError("libqgalore: shape out of range")
-        workspace = torch.empty((nbytes,), dtype=torch.uint8, device=Gs[0].device)
+        workspace = torch.empty(nbytes, dtype=torch.uint8, device=Gs[0].device)
     if out is None:
         out = ([torch.empty_like(p) for p in Pqs], [torch.empty_like(p) for p in Pss])
     descs = (RefreshDesc * count)()
     for i in range(count):
         descs[i] = RefreshDesc(_ptr(Pqs[i], (torch.uint8,)), _ptr(Pss[i], (torch.float32,)), _ptr(Gs[i], _BF16),
                                _ptr(out[0][i], (torch.uint8,)), _ptr(out[1][i], (torch.float32,)))
-    cos = torch.empty((count,), dtype=torch.float32, device=Gs[0].device)
-    info = torch.empty((count,), dtype=torch.int32, device=Gs[0].device)
+    cos = torch.empty(count, dtype=torch.float32, device=Gs[0].device)
+    info = torch.empty(count, dtype=torch.int32, device=Gs[0].device)
     _check(lib().qg_subspace_refresh_many_ld(count, descs, m, n, ld, r, GROUP, passes, _ptr(cos), _ptr(info),
                                              _ptr(workspace), workspace.numel(), _stream()))
     return out[0], out[1], cos, info, workspace
@@ -590,6 +598,6 @@ def diag_mfma_f64_loop(iters: int, workgroups: int, sink: torch.Tensor) -> float
 
 
 def sr_uniform(seed: int, step: int, idx0: int, count: int, device="cuda") -> torch.Tensor:
-    out = torch.empty((count,), dtype=torch.float32, device=device)
+    out = torch.empty(count, dtype=torch.float32, device=device)
     _check(lib().qg_sr_uniform(seed, step, idx0, count, _ptr(out), _stream()))
     return out
