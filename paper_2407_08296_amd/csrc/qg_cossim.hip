@@ -13,52 +13,65 @@ constexpr int kCosRows = 64;  // rows per partial-sum chunk
 // Up to kCosBatchMax pairs of one shape per launch (gridDim.y of them), pointers by value (CosBatch); pair z uses the
 // workspace slice at z * ws_stride floats and writes cos_out[z].
 // partial[chunk][3][r]: dot, |a|^2, |b|^2 of each column over the chunk's rows.  A thread takes the two columns of one byte
-// over the rows of one chunk, kCosAhead rows of loads in flight, and workgroups are single waves.  What bounds a small call is
-// the length of a thread's chain over the 64 rows (768 x 256, us: eight columns of a word per thread 24, with kCosAhead rows in
-// flight 22, two columns 13; 16 pairs of 4096 x 1024: 50, 52 and 39).
-constexpr int kCosAhead = 16;
-static_assert(kCosRows % kCosAhead == 0, "whole groups of rows but for the last chunk");
+// over a quarter of the rows of one chunk, all of their loads in flight, and the four waves' sums are added in order.  What bounds
+// a small call is the length of a thread's chain (768 x 256, us: eight columns of a word per thread, 64 rows 24, two columns 13,
+// two columns, 16 rows 5; 16 pairs of 4096 x 1024: 50, 39, 37).
+constexpr int kCosWaves = 4, kCosAhead = kCosRows / kCosWaves;
 
-__global__ __launch_bounds__(64) void k_cossim_partial(CosBatch batch, int m, int r, int chunks, float* __restrict__ partial,
-                                                       int64_t ws_stride) {
+__global__ __launch_bounds__(64 * kCosWaves) void k_cossim_partial(CosBatch batch, int m, int r, int chunks,
+                                                                   float* __restrict__ partial, int64_t ws_stride) {
     const uint8_t* __restrict__ PqA = batch.PqA[blockIdx.y];
     const float* __restrict__ PsA = batch.PsA[blockIdx.y];
     const uint8_t* __restrict__ PqB = batch.PqB[blockIdx.y];
     const float* __restrict__ PsB = batch.PsB[blockIdx.y];
     partial += ws_stride * blockIdx.y;
-    const int half = r >> 1;
-    const int64_t item = (int64_t)blockIdx.x * 64 + threadIdx.x;
-    const int chunk = (int)(item / half), c = 2 * (int)(item % half);
-    if (chunk >= chunks) return;
-    const int i0 = chunk * kCosRows, i1 = min(m, i0 + kCosRows);
+    __shared__ float sums[kCosWaves - 1][6][64];
+    const int half = r >> 1, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int64_t item = (int64_t)blockIdx.x * 64 + lane;
+    const int chunk = min((int)(item / half), chunks - 1), c = 2 * (int)(item % half);   // (past the end: not stored)
+    const int i0 = chunk * kCosRows + wave * kCosAhead, i1 = min(m, i0 + kCosAhead);
     float dot[2] = {0.f, 0.f}, na[2] = {0.f, 0.f}, nb[2] = {0.f, 0.f};
-    for (int i = i0; i < i1; i += kCosAhead) {
-        uint32_t wa[kCosAhead], wb[kCosAhead];
-        float sa[kCosAhead], sb[kCosAhead];
+    uint32_t wa[kCosAhead], wb[kCosAhead];
+    float sa[kCosAhead], sb[kCosAhead];
 #pragma unroll
-        for (int q = 0; q < kCosAhead; ++q) {
-            const int64_t e = (int64_t)min(i + q, m - 1) * r + c;   // (past the end: the last row, not used)
-            wa[q] = PqA[e >> 1];
-            wb[q] = PqB[e >> 1];
-            sa[q] = PsA[e >> 8];
-            sb[q] = PsB[e >> 8];
-        }
+    for (int q = 0; q < kCosAhead; ++q) {
+        const int64_t e = (int64_t)min(i0 + q, m - 1) * r + c;   // (past the end: the last row, not used)
+        wa[q] = PqA[e >> 1];
+        wb[q] = PqB[e >> 1];
+        sa[q] = PsA[e >> 8];
+        sb[q] = PsB[e >> 8];
+    }
 #pragma unroll
-        for (int q = 0; q < kCosAhead; ++q) {
-            if (i + q >= i1) break;
+    for (int q = 0; q < kCosAhead; ++q) {
+        if (i0 + q >= i1) break;
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                const float a = (float)((int)((wa[q] >> (4 * j)) & 0xFu) - 8) * sa[q];
-                const float b = (float)((int)((wb[q] >> (4 * j)) & 0xFu) - 8) * sb[q];
-                dot[j] = __builtin_fmaf(a, b, dot[j]);
-                na[j] = __builtin_fmaf(a, a, na[j]);
-                nb[j] = __builtin_fmaf(b, b, nb[j]);
-            }
+        for (int j = 0; j < 2; ++j) {
+            const float a = (float)((int)((wa[q] >> (4 * j)) & 0xFu) - 8) * sa[q];
+            const float b = (float)((int)((wb[q] >> (4 * j)) & 0xFu) - 8) * sb[q];
+            dot[j] = __builtin_fmaf(a, b, dot[j]);
+            na[j] = __builtin_fmaf(a, a, na[j]);
+            nb[j] = __builtin_fmaf(b, b, nb[j]);
         }
     }
+    if (wave > 0) {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            sums[wave - 1][j][lane] = dot[j];
+            sums[wave - 1][2 + j][lane] = na[j];
+            sums[wave - 1][4 + j][lane] = nb[j];
+        }
+    }
+    __syncthreads();
+    if (wave > 0 || item / half >= chunks) return;
     float* out = partial + (int64_t)chunk * 3 * r + c;
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
+#pragma unroll
+        for (int w = 0; w < kCosWaves - 1; ++w) {
+            dot[j] += sums[w][j][lane];
+            na[j] += sums[w][2 + j][lane];
+            nb[j] += sums[w][4 + j][lane];
+        }
         out[j] = dot[j];
         out[r + j] = na[j];
         out[2 * r + j] = nb[j];
@@ -144,7 +157,7 @@ int launch_cossim_batch(const CosBatch& batch, int count, int64_t m, int64_t r, 
     const int chunks = (int)((m + kCosRows - 1) / kCosRows);
     const int64_t blocks = ((int64_t)chunks * (r >> 1) + 63) / 64;   // (m r < 2^32: fewer than 2^20)
     const int64_t stride = (int64_t)cossim_ws_floats(m, r);
-    hipLaunchKernelGGL(k_cossim_partial, dim3((unsigned)blocks, count), dim3(64), 0, stream, batch, (int)m, (int)r, chunks, ws,
+    hipLaunchKernelGGL(k_cossim_partial, dim3((unsigned)blocks, count), dim3(64 * kCosWaves), 0, stream, batch, (int)m, (int)r, chunks, ws,
                        stride);
     if (int e = check_launch()) return e;
     const int groups = (int)((r + kCosGroup - 1) / kCosGroup);
