@@ -981,10 +981,10 @@ static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout,
     if (gram_blocks < kFewBlocks) gram(k_gram<32>, 32);
     else gram(k_gram<kNB>, kNB);
     hipLaunchKernelGGL(k_gram_reduce, dim3((unsigned)((r * r + 255) / 256), 1, B), blk, 0, stream, part, S, (int)r, slices, st);
-    // One launch per block column up to 640 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.64 /
-    // 2.67, 32 of them 19.4 / 19.6, 48 28.6 / 28.4, 64 37.8 / 37.1, 128 75.0 / 72.4; 2048 x 2048, r = 512: 32 3.33 / 3.50, 128
-    // 12.1 / 12.0; 1024 x 1024, r = 256, 256 matrices 5.05 / 4.98).  The arithmetic is the same, and with it every bit.
-    const bool fused = batch * nt <= 640;
+    // One launch per block column up to 1024 block rows of 64 (ms per refresh, fused / separate: 4096 x 4096, r = 1024, one 1.33 /
+    // 1.90, 32 of them 16.6 / 17.2, 48 24.6 / 25.0, 64 32.2 / 32.7; 2048 x 2048, r = 512: 32 3.02 / 3.20, 128 11.01 / 11.04; 1024 x
+    // 1024, r = 256, 256 matrices 4.49 / 4.48).  The arithmetic is the same, and with it every bit.
+    const bool fused = batch * nt <= 1024;
     // Strips while whole blocks are fewer than the CUs or so (us, 16 matrices, 192 blocks strips 41 / blocks 48, 240 63 / 60; 40
     // matrices: 120 13 / 16, 200 24.0 / 23.9, 400 77 / 56, 600 138 / 100; 128 matrices: 128 9 / 11, 256 23 / 15, 1920 388 / 238)
     constexpr int kBlocksFrom = 200;
