@@ -411,9 +411,9 @@ def refresh_bench(args, shapes, mats):
                                                       workspace=ws, out=outs[(m, n, r)]), 1)
         per_shape[f"{m}x{n} r{r}"] = {"count": len(g), "single_call_ms": one, "batched_ms_per_matrix": many / len(g)}
     # what the fp64 matrix pipe sustains with nothing else to do: register-only loop, three 256-thread workgroups per
-    # CU (the residency of k_gram and k_apply) and eight (a full CU)
+    # CU and eight (a full CU); k_gram runs six, k_apply four
     sink = torch.empty((256 * 8 * 256,), dtype=torch.float32, device=dev)
-    ceilings = {"note": "register-only v_mfma_f64_16x16x4 loop, 8 independent accumulators per wave, TFLOP/s"}
+    ceilings = {"note": "register-only v_mfma_f64_4x4x4 loop, 32 independent accumulators per wave, TFLOP/s"}
     for per_cu in (3, 8):
         it = 2000
         fl = qg.diag_mfma_f64_loop(it, 256 * per_cu, sink)

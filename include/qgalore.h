@@ -416,7 +416,7 @@ int qg_backproject_update_sr_many(int count, const void* plan_host, const void* 
  * the data), 0 with constants.  sink: device, QG_DIAG_MFMA_WORKGROUPS * 512 floats (written so the loop is live).
  *
  * qg_diag_mfma_f64_loop: `workgroups` (1 .. 65536) workgroups of 256 threads; each wave issues iters rounds of 8
- * independent v_mfma_f64_16x16x4 on register operands: workgroups * 4 * iters * 8 * 2048 flop per launch, the
+ * times 4 independent v_mfma_f64_4x4x4 on register operands: workgroups * 4 * iters * 8 * 2048 flop per launch, the
  * ceiling of the fp64 matrix pipe for the kernels of the subspace refresh.  sink: workgroups * 256 floats. */
 #define QG_DIAG_MFMA_WORKGROUPS 512
 int qg_diag_clock_probe(int64_t ticks_100mhz, int64_t* out2, void* stream);

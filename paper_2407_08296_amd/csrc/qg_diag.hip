@@ -61,21 +61,34 @@ __global__ __launch_bounds__(512) void k_mfma_loop(long long iters, float* sink)
     sink[blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
-// The same for the fp64 matrix cores: rounds of 8 independent v_mfma_f64_16x16x4 on register operands, 256-thread
-// workgroups (the shape of the refresh's fp64 kernels; three of them per CU are resident there).
-typedef double diag_f64x4 __attribute__((ext_vector_type(4)));
+// The same for the fp64 matrix cores: rounds of 32 independent v_mfma_f64_4x4x4 on register operands that differ from
+// lane to lane, 256-thread workgroups (the shape of the refresh's two large fp64 products).
 __global__ __launch_bounds__(256) void k_mfma_f64_loop(long long iters, float* sink) {
-    diag_f64x4 acc[8];
+    double acc[4][8], a[4], b[8];
+    uint32_t h = mix32(threadIdx.x * 2654435761u + blockIdx.x);
+    auto operand = [&] {
+        h = mix32(h + 0x9E3779B9u);
+        return (double)(int32_t)h * 0x1p-31;
+    };
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = diag_f64x4{0.0, 0.0, 0.0, 0.0};
-    const double a = 1.0 + threadIdx.x * 0x1p-10, b = 2.0 - threadIdx.x * 0x1p-10;
+    for (int i = 0; i < 4; ++i) a[i] = operand();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = operand();
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[i][j] = 0.0;
     for (long long it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, acc[i], 0, 0, 0);
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[i], b[j], acc[i][j], 0, 0, 0);
     }
     double s = 0.0;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) s += (acc[i][0] + acc[i][1]) + (acc[i][2] + acc[i][3]);
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += acc[i][j];
     sink[blockIdx.x * blockDim.x + threadIdx.x] = (float)s;
 }
 
