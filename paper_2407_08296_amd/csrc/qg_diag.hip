@@ -68,7 +68,7 @@ __global__ __launch_bounds__(256) void k_mfma_f64_loop(long long iters, float* s
     uint32_t h = mix32(threadIdx.x * 2654435761u + blockIdx.x);
     auto operand = [&] {
         h = mix32(h + 0x9E3779B9u);
-        return (double)(int32_t)h * 0x1p-31;
+        return 0.5 + (double)h * 0x1p-32;   // in [0.5, 1.5)
     };
 #pragma unroll
     for (int i = 0; i < 4; ++i) a[i] = operand();
