@@ -946,6 +946,15 @@ static int launch_range(const uint16_t* G, const uint16_t* Z, float* Y, int64_t 
     return launch_tile_gemm<kBf16KFast, kBf16KFast, float>(A, B, nullptr, Y, m, r, n, st);
 }
 
+// k_gram and k_apply number the 64 x 64 tiles of a whole batch in one grid dimension, whose threads a launch counts in 32 bits.
+constexpr int64_t kMaxTiles = (int64_t(1) << 32) / 256 - 8;   // (a multiple of 8, as the grid is)
+static int64_t cholqr_tiles(int64_t m, int64_t r) {           // the larger of the two, per matrix
+    const int64_t nt = (r + kNB - 1) / kNB;
+    int slice_rows;
+    const int64_t gram = nt * (nt + 1) / 2 * gram_slices(m, r, &slice_rows), apply = (m + kNB - 1) / kNB * nt;
+    return gram > apply ? gram : apply;
+}
+
 // One round on `batch` matrices (matrix b at Y + b * sYin, result at Q + b * sQout): Q = Y L^-T with L the Cholesky
 // factor of Y^T Y.
 static void launch_cholqr(const float* Y, int64_t sYin, float* Q, int64_t sQout, int64_t m, int64_t r, int batch,
@@ -1093,7 +1102,8 @@ extern "C" int qg_subspace_refresh_many_ld(int count, const qg_refresh_desc* des
     if (!workspace) return QG_ERR_WORKSPACE;
     // as many matrices per batch as the workspace holds; R and Z are stored with the gradients' row pitch
     int batch = count < 32768 ? count : 32768;   // the batch index is a grid dimension
-    while (batch > 1 && refresh_layout(m, ld, r, batch).total > workspace_bytes) batch = (batch + 1) / 2;
+    while (batch > 1 && (refresh_layout(m, ld, r, batch).total > workspace_bytes || cholqr_tiles(m, r) * batch > kMaxTiles))
+        batch = (batch + 1) / 2;
     const RefreshLayout L = refresh_layout(m, ld, r, batch);
     if (L.total > workspace_bytes) return QG_ERR_WORKSPACE;
     char* ws = static_cast<char*>(workspace);

@@ -1,0 +1,33 @@
+"""The grids of the subspace refresh stay within what a launch can hold, for every batch that the entry point accepts: a host
+program (tests/launch_limits_driver.cpp) stands in for the runtime's launch call and looks at each one."""
+import os
+import subprocess
+
+import pytest
+
+from paper_2407_08296_amd import build as qg_build
+from paper_2407_08296_amd import qgalore as qg
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    qg.lib()
+    exe = str(tmp_path_factory.mktemp("launch") / "launch_limits_driver")
+    lib_dir = os.path.dirname(qg.LIB_PATH)
+    subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "c++", "-std=c++17", "-O1",
+                    "-I", os.path.join(qg_build.ROOT, "include"), os.path.join(HERE, "launch_limits_driver.cpp"), "-rdynamic",
+                    "-L", lib_dir, "-l:" + os.path.basename(qg.LIB_PATH), "-Wl,-rpath," + lib_dir, "-o", exe], check=True)
+    return exe
+
+
+@pytest.mark.parametrize("count,m,n,r", [
+    (1, 8, 8, 8), (3, 768, 768, 256), (16, 4096, 4096, 1024),
+    (32767, 32768, 8, 8), (32768, 32768, 8, 8),       # 512 row tiles of 64 per matrix: 2^24 tiles in all, and 512 fewer
+    (40000, 65536, 8, 8), (700, 1 << 21, 8, 8),       # more; fewer and longer matrices
+    (20000, 72, 72, 72), (1, 1 << 27, 8, 8),          # two block columns; the longest single matrix
+])
+def test_grids_of_a_refresh(driver, count, m, n, r):
+    p = subprocess.run([driver, str(count), str(m), str(n), str(r)], capture_output=True, text=True, timeout=300)
+    assert p.returncode == 0, p.stdout + p.stderr
