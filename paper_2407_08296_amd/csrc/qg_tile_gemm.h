@@ -904,7 +904,8 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
         // Two groups of waves per tile (see tile_gemm) while tiles are about a workgroup per CU or fewer
         if (many == nullptr && groups && K >= 512) {
             const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 63) / 64;
-            const bool wide = A.ld % 8 == 0 && (BL == kInt8KSlow || BL == kInt8ZKSlow || B.ld % 16 == 0);   // 16-byte aligned along k
+            // dense rows start 16-byte aligned along k (not the pitches: the order of the sums does not depend on them)
+            const bool wide = K % (BL == kInt8KSlow || BL == kInt8ZKSlow ? 8 : 16) == 0;
             auto launch = [&](auto mb, auto tn) {
                 launch_tile_gemm_shape<AL, BL, OUT, mb.value, tn.value, 64, 2, true, true, 2>(A, B, bias, C, M, N, K, st, nullptr, 1,
                                                                                              ldc);

@@ -202,7 +202,10 @@ def _pitched_bits(bits, rows, cols, ld, fill=0x7FC0):
     return dev(a.view(np.int16))
 
 
-@pytest.mark.parametrize("tokens,m,n", [(130, 333, 261), (77, 200, 521), (64, 519, 256), (96, 256, 1365)])
+@pytest.mark.parametrize("tokens,m,n", [
+    (130, 333, 261), (77, 200, 521), (64, 519, 256), (96, 256, 1365),
+    (1000, 2048, 2047), (1000, 2047, 2039),   # tiles chosen by the size of the contraction, whatever the pitch: forward, grad_input
+])
 def test_layer_with_row_pitches_equals_the_dense_layer(tokens, m, n):
     """qg_int8_linear_forward_ld / _backward_ld: activations, weight and gradients stored with rows a multiple of 16
     elements apart (NaN in the activations' padding, junk codes in the weight's).  The real columns get the oracle's
