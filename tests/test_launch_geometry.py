@@ -1,5 +1,5 @@
-"""The grids of the subspace refresh stay within what a launch can hold, for every batch that the entry point accepts: a host
-program (tests/launch_limits_driver.cpp) stands in for the runtime's launch call and looks at each one."""
+"""The launches of the library as the host decides on them: a host program (tests/launch_geometry_driver.cpp) stands in for
+the runtime's launch call and looks at each one."""
 import os
 import subprocess
 
@@ -14,12 +14,17 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 @pytest.fixture(scope="module")
 def driver(tmp_path_factory):
     qg.lib()
-    exe = str(tmp_path_factory.mktemp("launch") / "launch_limits_driver")
-    lib_dir = os.path.dirname(qg.LIB_PATH)
+    exe = str(tmp_path_factory.mktemp("launch") / "launch_geometry_driver")
+    lib_dir = os.path.dirname(os.path.abspath(qg.LIB_PATH))
     subprocess.run([os.environ.get("HIPCC", "/opt/rocm/bin/hipcc"), "-x", "c++", "-std=c++17", "-O1",
-                    "-I", os.path.join(qg_build.ROOT, "include"), os.path.join(HERE, "launch_limits_driver.cpp"), "-rdynamic",
+                    "-I", os.path.join(qg_build.ROOT, "include"), os.path.join(HERE, "launch_geometry_driver.cpp"), "-rdynamic",
                     "-L", lib_dir, "-l:" + os.path.basename(qg.LIB_PATH), "-Wl,-rpath," + lib_dir, "-o", exe], check=True)
-    return exe
+
+    def run(what, *sizes):
+        p = subprocess.run([exe, what, *map(str, sizes)], capture_output=True, text=True, timeout=300)
+        assert p.returncode == 0, p.stdout + p.stderr
+        return [tuple(int(v) for v in line.split()) for line in p.stdout.splitlines()[:-1]]   # (workgroups, threads)
+    return run
 
 
 @pytest.mark.parametrize("count,m,n,r", [
@@ -29,5 +34,5 @@ def driver(tmp_path_factory):
     (20000, 72, 72, 72), (1, 1 << 27, 8, 8),          # two block columns; the longest single matrix
 ])
 def test_grids_of_a_refresh(driver, count, m, n, r):
-    p = subprocess.run([driver, str(count), str(m), str(n), str(r)], capture_output=True, text=True, timeout=300)
-    assert p.returncode == 0, p.stdout + p.stderr
+    """They stay within what a launch can hold, for every batch that the entry point accepts."""
+    driver("refresh", count, m, n, r)
