@@ -878,7 +878,8 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    tokens, 6.0 / 6.5), 1024 -> 1024, 1000 tokens, 9.0 / 7.9, grad_input 256 x 11008 -> 4096 80 / 50; beyond 256 of these 128 x 64 up to
 //    as many, forward, 1000 tokens, 2048 -> 2048 21.7 / 18.9, 5461 -> 2048 62 / 57, grad_input 23.2 / 19.8 (two groups of
 //    64 x 64 tiles there 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2; rows that start unaligned, 900
-//    tokens, 1599 -> 1600, 20.9 / 23.5); 128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 /
+//    tokens, 1599 -> 1600, 20.9 / 23.5, and of a weight with k slow, transposed forward, 1000 tokens, 1024 -> 2047 13.2 / 14.6, 2048 -> 2047 23.3 / 24.4,
+//    5461 -> 2047 63.2 / 61.0); 128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 /
 //    27.7, 256 tokens, 4096 -> 11008 43 / 38.  grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
 // ldc: row pitch of C in elements (0: N).  groups: whether two groups may be used.
 template <int AL, int BL, typename OUT>
@@ -904,8 +905,8 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
         // Two groups of waves per tile (see tile_gemm) while tiles are about a workgroup per CU or fewer
         if (many == nullptr && groups && K >= 512) {
             const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 63) / 64;
-            // dense rows start 16-byte aligned along k (not the pitches: the order of the sums does not depend on them)
-            const bool wide = K % (BL == kInt8KSlow || BL == kInt8ZKSlow ? 8 : 16) == 0;
+            // dense rows start 16-byte aligned (not the pitches: the order of the sums does not depend on them)
+            const bool wide = BL == kInt8KSlow || BL == kInt8ZKSlow ? K % 8 == 0 && N % 16 == 0 : K % 16 == 0;
             auto launch = [&](auto mb, auto tn) {
                 launch_tile_gemm_shape<AL, BL, OUT, mb.value, tn.value, 64, 2, true, true, 2>(A, B, bias, C, M, N, K, st, nullptr, 1,
                                                                                              ldc);

@@ -36,3 +36,14 @@ def driver(tmp_path_factory):
 def test_grids_of_a_refresh(driver, count, m, n, r):
     """They stay within what a launch can hold, for every batch that the entry point accepts."""
     driver("refresh", count, m, n, r)
+
+
+@pytest.mark.parametrize("n,k,want", [
+    (2048, 2048, (256, 512)), (2047, 2048, (512, 256)), (2040, 1024, (512, 256)),   # whole rows of the weight, odd ones, rows of 8
+    (2047, 5461, (256, 512)),                                                        # a long contraction: two groups all the same
+])
+def test_two_groups_on_a_weight_with_k_slow(driver, n, k, want):
+    """1000 tokens.  128 x 64 tiles in two groups of waves (512 threads) where the weight's rows start 16-byte aligned, else
+    64 x 64 tiles (256 threads): grad_input of the layer k <- n, and the forward pass of the same weight stored transposed."""
+    assert driver("grad_input", 1000, k, n)[0] == want
+    assert driver("t_forward", 1000, n, k)[0] == want
