@@ -880,7 +880,9 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    64 x 64 tiles there 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2; rows that start unaligned, 900
 //    tokens, 1599 -> 1600, 20.9 / 23.5, and of a weight with k slow, transposed forward, 1000 tokens, 1024 -> 2047 13.2 / 14.6, 2048 -> 2047 23.3 / 24.4,
 //    5461 -> 2047 63.2 / 61.0); 128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 /
-//    27.7, 256 tokens, 4096 -> 11008 43 / 38.  grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
+//    27.7, 256 tokens, 4096 -> 11008 43 / 38, but not on a short contraction (2048 tokens, 2048 columns, forward, K = 512 10.7 / 11.0, 520
+//    14.3 / 15.1, 768 14.5 / 14.6, 1024 18.0 / 17.9; grad_input on whole tiles, 1024 tokens, 4096 columns, 512 10.4 / 11.0, 1024 17.3 / 17.7, 2048 29.6 /
+//    29.6; ragged, 1000 tokens, 3000 columns, 512 12.5 / 11.5, 513 16.0 / 16.4, 768 18.4 / 15.4).  grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
 // ldc: row pitch of C in elements (0: N).  groups: whether two groups may be used.
 template <int AL, int BL, typename OUT>
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
@@ -915,7 +917,9 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
             using N64 = std::integral_constant<int, 64>;
             using N128 = std::integral_constant<int, 128>;
             if (!lin_small<AL, BL>(M, N, 1)) {
-                if (tiles_m * ((N + 127) / 128) <= 256) return launch(std::integral_constant<int, 2>(), N128());
+                const bool slow = BL == kInt8KSlow || BL == kInt8ZKSlow, whole = M % 128 == 0 && N % 128 == 0;
+                const int64_t least = slow && whole ? 1536 : slow && K % 8 == 0 ? 512 : 768;
+                if (K >= least && tiles_m * ((N + 127) / 128) <= 256) return launch(std::integral_constant<int, 2>(), N128());
             } else if ((M + 63) / 64 * tiles_n <= 256) {
                 return launch(std::integral_constant<int, 1>(), N64());
             } else if (tiles_m * tiles_n <= 256 && (wide || K >= 4096)) {

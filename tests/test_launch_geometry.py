@@ -47,3 +47,15 @@ def test_two_groups_on_a_weight_with_k_slow(driver, n, k, want):
     64 x 64 tiles (256 threads): grad_input of the layer k <- n, and the forward pass of the same weight stored transposed."""
     assert driver("grad_input", 1000, k, n)[0] == want
     assert driver("t_forward", 1000, n, k)[0] == want
+
+
+@pytest.mark.parametrize("what,tokens,n,k,threads", [
+    ("forward", 2048, 2048, 520, 256), ("forward", 2000, 2000, 767, 256), ("forward", 2048, 2048, 768, 512),
+    ("grad_input", 1024, 4096, 512, 256), ("grad_input", 1024, 4096, 1535, 256), ("grad_input", 1024, 4096, 1536, 512),   # whole
+    ("grad_input", 1000, 3000, 512, 512), ("grad_input", 1000, 3000, 513, 256), ("grad_input", 1000, 3000, 769, 512),    # ragged
+])
+def test_shortest_contraction_of_two_groups_on_large_tiles(driver, what, tokens, n, k, threads):
+    """128 x 128 tiles, at most a workgroup per CU: n columns, contraction k."""
+    tiles = -(-tokens // 128) * -(-n // 128)
+    sizes = (tokens, n, k) if what == "forward" else (tokens, k, n)
+    assert driver(what, *sizes) == [(-(-tiles // 8) * 8, threads)]
