@@ -820,8 +820,11 @@ static bool lin_small(int64_t M, int64_t N, int count) {
 
 // Whether a product of the linear layer splits its contraction over the waves of a workgroup (T: its 32 x 32 tiles).  Against
 // the tiles of launch_tile_gemm, us, split / not: forward, 256 tokens, 768 -> 768 (T = 192) 4.0 / 6.6, 2048 -> 2048 (512) 9.2 /
-// 13.4, 500 tokens, 1024 -> 1024 (512) 6.5 / 7.4, but 1000 tokens, 2048 ->
-// 768 (768) 13.0 / 11.8, 256 tokens, 1024 -> 2736 (688) 7.6 / 7.3.  A weight with k
+// 13.4, 500 tokens, 1024 -> 1024 (512) 6.5 / 7.4.  From 513 to 768 of them two groups of waves (64 x 64 tiles, at most a workgroup per CU)
+// take 0.93 of the split's time on average over 22 shapes and ten lengths of the contraction from 512 to 11008: 0.78 to 0.91 where rows
+// start unaligned, 256 tokens, 2048 -> 3072 (768) 12.0 / 11.2, 4096 -> 3072 22.5 / 20.5, 2000 tokens, 11008 -> 384 (756) 62.7 / 52.4; they lose up
+// to 8 % at K = 2048 with some hundred ragged rows (500 tokens, 1280 columns (640) 11.3 / 12.2, 1000 tokens, 768 columns 11.7 / 12.2) and 2 to
+// 4 % on ragged tiles at K = 512.  Where they do not have a CU each, 32 tokens, 2048 -> 17408 (544) 12.9 / 19.9, 4096 -> 24576 (768) 24.7 / 37.0.  A weight with k
 // slow (grad_input) needs twice the LDS per wave, and a chain that is long for the number of tiles: 256 tokens, 2048 -> 2048
 // (512) 11.7 / 13.9, 500 tokens, K = 3001, 1007 columns (512) 55 / 95, but with grad_W in the same launch 256 tokens, K = 768,
 // 2048 columns (512) 9.4 / 8.0, K = 1024, 2736 columns (688) 14.3 / 11.0.  grad_W: 512 x 512 (256), 1024 tokens 4.8 / 7.1, 4096
@@ -831,7 +834,8 @@ static bool lin_ksplit(int64_t M, int64_t N, int64_t K) {
     const int64_t T = ((M + 31) / 32) * ((N + 31) / 32);
     if (AL == kBf16KSlow && BL == kBf16KSlow) return T <= 320 && K >= 512;
     if (BL == kInt8KSlow || BL == kInt8ZKSlow) return T <= 512 && K >= 3 * T;
-    return T <= (K < 512 ? 768 : 512);
+    if (T <= 512 || K < 512) return T <= 768;
+    return T <= 768 && ((M + 63) / 64) * ((N + 63) / 64) > 256;   // (else two groups of waves, see launch_tile_gemm)
 }
 
 static LinProduct lin_product(const LinOperand& A, const LinOperand& B, uint16_t* C, int64_t M, int64_t N, int64_t K, int64_t ldc,

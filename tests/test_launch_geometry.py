@@ -59,3 +59,12 @@ def test_shortest_contraction_of_two_groups_on_large_tiles(driver, what, tokens,
     tiles = -(-tokens // 128) * -(-n // 128)
     sizes = (tokens, n, k) if what == "forward" else (tokens, k, n)
     assert driver(what, *sizes) == [(-(-tiles // 8) * 8, threads)]
+
+
+@pytest.mark.parametrize("tokens,n,k,want", [
+    (32, 17408, 2048, (544, 256)), (20, 24576, 768, (768, 256)),       # 272 and 384 tiles of 64 x 64: contraction over four waves
+    (32, 16384, 2048, (512, 256)), (64, 12288, 2048, (192, 512)),      # up to 512 tiles of 32 x 32; 192 of 64 x 64, two groups
+    (32, 24576, 511, (768, 256)), (64, 12288, 511, (768, 256)),        # a short contraction
+])
+def test_few_rows_in_the_forward_pass(driver, tokens, n, k, want):
+    assert driver("forward", tokens, n, k) == [want]
