@@ -829,12 +829,18 @@ static bool lin_small(int64_t M, int64_t N, int count) {
 // (512) 11.7 / 13.9, 500 tokens, K = 3001, 1007 columns (512) 55 / 95, but with grad_W in the same launch 256 tokens, K = 768,
 // 2048 columns (512) 9.4 / 8.0, K = 1024, 2736 columns (688) 14.3 / 11.0.  grad_W: 512 x 512 (256), 1024 tokens 4.8 / 7.1, 4096
 // tokens 10.9 / 30, but 256 tokens with grad_input in the same launch 4.2 / 3.7, and 768 x 768 (576), 1024 tokens 9.5 / 7.4.
+// beside: the contraction of grad_W where a backward pass would run both products in one launch (whether it is asked for both or
+// not), 0 otherwise.  There are no two groups there, and 64 x 64 tiles, which are fewer, leave grad_W more of the chip.  From 513
+// to 768 tiles, a weight with k fast (stored transposed), both / grad_input alone, split and 64 x 64: 1000 tokens, K = 768, 768 columns (768)
+// 14.0 and 11.1 / 6.4 and 6.9, K = 2048 21.6 and 20.0 / 12.0 and 17.8, 500 tokens, K = 2048, 1280 columns (640) 17.9 and 19.4 / 11.3 and 17.8, 1000 tokens, K
+// = 4096, 640 columns 32.5 and 35.7 / 20.6 and 31.9, but 2000 tokens, K = 2048, 320 columns (630) 25.5 and 19.7 / 12.3 and 17.6.
 template <int AL, int BL>
-static bool lin_ksplit(int64_t M, int64_t N, int64_t K) {
+static bool lin_ksplit(int64_t M, int64_t N, int64_t K, int64_t beside) {
     const int64_t T = ((M + 31) / 32) * ((N + 31) / 32);
     if (AL == kBf16KSlow && BL == kBf16KSlow) return T <= 320 && K >= 512;
     if (BL == kInt8KSlow || BL == kInt8ZKSlow) return T <= 512 && K >= 3 * T;
     if (T <= 512 || K < 512) return T <= 768;
+    if (beside != 0) return T <= 768 && K >= 2048 && K >= 2 * beside;
     return T <= 768 && ((M + 63) / 64) * ((N + 63) / 64) > 256;   // (else two groups of waves, see launch_tile_gemm)
 }
 
@@ -887,13 +893,13 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    27.7, 256 tokens, 4096 -> 11008 43 / 38, but not on a short contraction (2048 tokens, 2048 columns, forward, K = 512 10.7 / 11.0, 520
 //    14.3 / 15.1, 768 14.5 / 14.6, 1024 18.0 / 17.9; grad_input on whole tiles, 1024 tokens, 4096 columns, 512 10.4 / 11.0, 1024 17.3 / 17.7, 2048 29.6 /
 //    29.6; ragged, 1000 tokens, 3000 columns, 512 12.5 / 11.5, 513 16.0 / 16.4, 768 18.4 / 15.4).  grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
-// ldc: row pitch of C in elements (0: N).  groups: whether two groups may be used.
+// ldc: row pitch of C in elements (0: N).  beside: see lin_ksplit; two groups only where it is 0.
 template <int AL, int BL, typename OUT>
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
                             int64_t K, hipStream_t st, const LinBatch* many = nullptr, int count = 1, int64_t ldc = 0,
-                            bool groups = true) {
+                            int64_t beside = 0) {
     if constexpr (AL == kBf16KFast && BL != kBf16KFast && BL != kBf16KSlow && std::is_same_v<OUT, uint16_t>) {
-        if (many == nullptr && lin_ksplit<AL, BL>(M, N, K)) {
+        if (many == nullptr && lin_ksplit<AL, BL>(M, N, K, beside)) {
             const LinProduct p = lin_product(A, B, C, M, N, K, ldc ? ldc : N, 32);
             auto launch = [&](auto exact, auto waves) {
                 hipLaunchKernelGGL((k_ksplit_gemm<BL, exact.value, waves.value>), dim3(lin_grid(p)), dim3(64 * waves.value), 0, st,
@@ -909,7 +915,7 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
             return check_launch();
         }
         // Two groups of waves per tile (see tile_gemm) while tiles are about a workgroup per CU or fewer
-        if (many == nullptr && groups && K >= 512) {
+        if (many == nullptr && beside == 0 && K >= 512) {
             const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 63) / 64;
             // dense rows start 16-byte aligned (not the pitches: the order of the sums does not depend on them)
             const bool wide = BL == kInt8KSlow || BL == kInt8ZKSlow ? K % 8 == 0 && N % 16 == 0 : K % 16 == 0;
@@ -1008,8 +1014,11 @@ template <int BL>
 static int launch_linear_backward(const LinOperand& A0, const LinOperand& B0, uint16_t* dx, int64_t M0, int64_t N0, int64_t K0,
                                   int64_t ldc0, const LinOperand& A1, const LinOperand& B1, uint16_t* G, int64_t M1, int64_t N1,
                                   int64_t K1, int64_t ldc1, hipStream_t st) {
-    const bool split0 = lin_ksplit<kBf16KFast, BL>(M0, N0, K0), split1 = lin_ksplit<kBf16KSlow, kBf16KSlow>(M1, N1, K1);
-    const bool pair0 = split0 || lin_small<kBf16KFast, BL>(M0, N0, 1), pair1 = split1 || ((M1 + 127) / 128) * ((N1 + 127) / 128) < 256;
+    const bool split1 = lin_ksplit<kBf16KSlow, kBf16KSlow>(M1, N1, K1, 0);
+    const bool pair1 = split1 || ((M1 + 127) / 128) * ((N1 + 127) / 128) < 256;
+    const int64_t fits = lin_small<kBf16KFast, BL>(M0, N0, 1) && pair1 ? K1 : 0;
+    const bool split0 = lin_ksplit<kBf16KFast, BL>(M0, N0, K0, fits);
+    const bool pair0 = split0 || lin_small<kBf16KFast, BL>(M0, N0, 1);
     const int tile0 = split0 ? 32 : 64, tile1 = split1 ? 32 : 64;
     const LinProduct p0 = lin_product(A0, B0, dx, M0, N0, K0, ldc0, tile0), p1 = lin_product(A1, B1, G, M1, N1, K1, ldc1, tile1);
     // `with0` of the first product's workgroups, `with1` of the second's
@@ -1032,7 +1041,7 @@ static int launch_linear_backward(const LinOperand& A0, const LinOperand& B0, ui
         if (split0) {
             if (int e = launch_pair(true, false)) return e;
         } else if (int e = launch_tile_gemm<kBf16KFast, BL, uint16_t>(A0, B0, nullptr, dx, M0, N0, K0, st, nullptr, 1, ldc0,
-                                                                                      !(pair0 && pair1))) {
+                                                                                      fits)) {
             return e;
         }
     }

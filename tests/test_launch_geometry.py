@@ -68,3 +68,22 @@ def test_shortest_contraction_of_two_groups_on_large_tiles(driver, what, tokens,
 ])
 def test_few_rows_in_the_forward_pass(driver, tokens, n, k, want):
     assert driver("forward", tokens, n, k) == [want]
+
+
+@pytest.mark.parametrize("tokens,m,n,split", [
+    (1000, 2048, 768, True), (500, 2048, 1280, True), (2000, 4096, 320, True),      # at least twice the tokens
+    (1000, 1999, 768, False), (2000, 2048, 320, False), (1000, 768, 768, False),    # less, or a short contraction
+    (500, 4096, 1280, False),                                                       # grad_W in a launch of its own: two groups
+    (1000, 2048, 512, True), (1000, 500, 768, True),                                # up to 512 tiles; up to a contraction of 511
+])
+def test_grad_input_of_a_transposed_weight(driver, tokens, m, n, split):
+    """513 to 768 tiles of 32 x 32: split over waves, or 64 x 64 tiles; alone and beside grad_W it is the same kernel."""
+    tiles32, tiles64 = -(-tokens // 32) * -(-n // 32), -(-tokens // 64) * -(-n // 64)
+    up8 = lambda v: -(-v // 8) * 8
+    assert driver("t_grad_input", tokens, m, n) == [(up8(tiles32 if split else tiles64), 512 if m == 4096 and not split else 256)]
+    both = driver("t_backward", tokens, m, n)
+    if len(both) == 2:
+        assert both[0] == driver("t_grad_input", tokens, m, n)[0]
+    else:
+        grad_w = [up8(-(-m // t) * -(-n // t)) for t in (32, 64)]
+        assert both[0][0] - up8(tiles32 if split else tiles64) in grad_w
