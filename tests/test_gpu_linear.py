@@ -116,14 +116,57 @@ def test_ragged_tiles_of_whole_chunks(tokens, m, n):
     test_backward(tokens, m, n)
 
 
+# Two groups of waves on a tile: (tile rows, tile columns, weight's layout along k, tokens, columns, contraction).  Whole tiles with an
+# odd and an even number of 64-deep steps; ragged ones whose partial last step falls to either group; rows that start unaligned.
+TWO_GROUPS = [
+    (64, 64, "fast", 512, 1152, 576), (64, 64, "fast", 512, 2048, 640), (64, 64, "fast", 500, 1100, 600), (64, 64, "fast", 500, 1101, 1025),
+    (64, 64, "slow", 512, 1152, 576), (64, 64, "slow", 512, 2048, 640), (64, 64, "slow", 500, 1100, 600), (64, 64, "slow", 500, 1101, 1025),
+    (128, 64, "fast", 1024, 1152, 576), (128, 64, "fast", 1024, 2048, 640), (128, 64, "fast", 1000, 1100, 592), (128, 64, "fast", 1000, 1100, 4101),
+    (128, 64, "fast", 1000, 1101, 4165),
+    (128, 64, "slow", 1024, 1152, 576), (128, 64, "slow", 1024, 2048, 640), (128, 64, "slow", 1000, 1104, 600), (128, 64, "slow", 1000, 1100, 4101),
+    (128, 64, "slow", 1000, 1101, 4165),
+    (128, 128, "fast", 2048, 2048, 832), (128, 128, "fast", 2048, 2048, 768), (128, 128, "fast", 2000, 2000, 840), (128, 128, "fast", 1999, 2001, 773),
+    (128, 128, "slow", 2048, 1280, 1600), (128, 128, "slow", 2048, 1280, 1536), (128, 128, "slow", 2000, 1270, 600), (128, 128, "slow", 1999, 1271, 773),
+]
+
+
+@pytest.mark.parametrize("zp", [False, True])
+@pytest.mark.parametrize("tm,tn,layout,tokens,cols,k", TWO_GROUPS)
+def test_two_groups_of_waves(tm, tn, layout, tokens, cols, k, zp):
+    """Every kernel of two groups: the forward pass of a weight as it is (k fast) and stored transposed (k slow), symmetric and
+    with zero points.  test_launch_geometry.py checks that these sizes take the tile named."""
+    g = np.random.default_rng([tokens, cols, k])
+    rows, row = (cols, k) if layout == "fast" else (k, cols)
+    W = (g.standard_normal((rows, row)) * 0.02 + (g.standard_normal((rows, 1)) * 0.02 if zp else 0)).astype(np.float32)
+    w = Q.quant_int8_zp(W) if zp else Q.quant_int8(W)
+    Wd = (Q.dequant_w_zp_bf16 if zp else Q.dequant_w_bf16)(*w)
+    xb = Q.f64_to_bf16_bits(g.standard_normal((tokens, k)))
+    bias = Q.f64_to_bf16_bits(g.standard_normal(cols))
+    forward = getattr(qg, "int8_linear" + ("_t" if layout == "slow" else "") + ("_zp" if zp else "") + "_forward")
+    y = forward(bits_t(xb, (tokens, k)), *(dev(a) for a in w), bits_t(bias, (cols,)))
+    want = Q.bf16_bits_to_f64(xb).reshape(tokens, k) @ (Wd.T if layout == "fast" else Wd) + Q.bf16_bits_to_f64(bias)[None, :]
+    check(host_f64(y), want, k, 0.04 if zp else 0.02)
+
+
+# grad_input in two groups (grad_W too large for one launch with it): (tile rows, tile columns, tokens, m, n), contraction m
+TWO_GROUPS_GRAD_INPUT = [
+    (64, 64, 256, 2112, 2112), (64, 64, 250, 2100, 2110),
+    (128, 64, 1024, 2112, 2048), (128, 64, 1000, 2048, 2048), (128, 64, 1000, 5461, 2048),
+    (128, 128, 2048, 2112, 2048), (128, 128, 2000, 2056, 2000),
+]
+
+
+@pytest.mark.parametrize("tm,tn,tokens,m,n", TWO_GROUPS_GRAD_INPUT)
+def test_two_groups_of_waves_in_grad_input(tm, tn, tokens, m, n):
+    test_backward(tokens, m, n)
+
+
 @pytest.mark.parametrize("tokens,m,n", [
-    (512, 1152, 576), (500, 1100, 600), (500, 1101, 1025),   # 64 x 64 tiles, forward: 9 steps, whole and ragged, a partial one
-    (576, 640, 1664), (520, 700, 1500), (90, 515, 9000),     # ... grad_input
-    (1024, 1152, 576), (1000, 1100, 528), (1000, 576, 2048), (1000, 632, 1900),   # 128 x 64
-    (2048, 2048, 512), (2040, 2040, 600), (2048, 576, 1792), (1700, 605, 1601),   # 128 x 128
+    (576, 640, 1664), (520, 700, 1500), (1000, 576, 2048),     # beside grad_W in one launch: one group
+    (90, 515, 9000), (1000, 632, 1900), (2048, 576, 1792), (1700, 605, 1601),   # rows or a contraction that two groups do not gain on
+    (512, 1152, 576), (1024, 1152, 576), (2048, 2048, 512), (2040, 2040, 600),
 ])
-def test_two_groups_of_waves(tokens, m, n):
-    """The steps of the contraction dealt out to two groups: an odd number of them, a partial last one, edges of the tiles."""
+def test_around_the_rules_of_two_groups(tokens, m, n):
     test_forward(tokens, m, n)
     test_backward(tokens, m, n)
 

@@ -7,6 +7,7 @@ import pytest
 
 from paper_2407_08296_amd import build as qg_build
 from paper_2407_08296_amd import qgalore as qg
+from test_gpu_linear import TWO_GROUPS, TWO_GROUPS_GRAD_INPUT
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 
@@ -87,3 +88,15 @@ def test_grad_input_of_a_transposed_weight(driver, tokens, m, n, split):
     else:
         grad_w = [up8(-(-m // t) * -(-n // t)) for t in (32, 64)]
         assert both[0][0] - up8(tiles32 if split else tiles64) in grad_w
+
+
+@pytest.mark.parametrize("tm,tn,layout,tokens,cols,k", TWO_GROUPS)
+def test_tiles_of_two_groups(driver, tm, tn, layout, tokens, cols, k):
+    tiles = -(-tokens // tm) * -(-cols // tn)
+    assert driver("forward" if layout == "fast" else "t_forward", tokens, cols, k) == [(-(-tiles // 8) * 8, 512)]
+
+
+@pytest.mark.parametrize("tm,tn,tokens,m,n", TWO_GROUPS_GRAD_INPUT)
+def test_tiles_of_two_groups_in_grad_input(driver, tm, tn, tokens, m, n):
+    tiles = -(-tokens // tm) * -(-n // tn)
+    assert driver("backward", tokens, m, n)[0] == driver("grad_input", tokens, m, n)[0] == (-(-tiles // 8) * 8, 512)
