@@ -192,9 +192,9 @@ __device__ __forceinline__ void zero_acc4(double (&acc)[W][W]) {
         for (int b = 0; b < W; ++b) acc[a][b] = 0.0;
 }
 
-// A batch of matrices with the same m and r runs through the fp64 kernels in one launch each, matrix b =
-// blockIdx.z; its pieces sit at these element strides from matrix 0's (all zero for a single matrix).  The in and
-// out matrices of a round share the stride Y/Q (both are m x r fp32 arrays of the same batch layout).
+// A batch of matrices with the same m and r runs through the fp64 kernels in one launch each (matrix b = blockIdx.z, or decoded
+// from the tile number in k_gram and k_apply); its pieces sit at these element strides from matrix 0's (all zero for a single
+// one).  The in and out matrices of a round share the stride Y/Q (both are m x r fp32 arrays of the same batch layout).
 struct BatchStride {
     int64_t Y, Q, S, X, D, part, shift;
 };
@@ -263,7 +263,7 @@ __global__ void k_set_i32(int32_t* p, int32_t v, int count) {
 
 // ---------------------------------------------------------------------------------------------------------------
 // S = Y^T Y in fp64, lower block triangle only (Y fp32 m x r; S r x r row-major).  The m rows are cut into
-// gridDim.y slices so that the launch fills the chip; slice s writes its partial sums to part + s * r * r and
+// slices so that the launch fills the chip; slice s writes its partial sums to part + s * r * r and
 // k_gram_reduce adds the slices in a fixed order (the result does not depend on scheduling).
 // ---------------------------------------------------------------------------------------------------------------
 constexpr int kGramMaxSlices = 8;
@@ -344,7 +344,7 @@ __global__ __launch_bounds__(256) void k_gram_reduce(const double* __restrict__ 
     const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= (int64_t)r * r) return;
     const int i = (int)(e / r), j = (int)(e % r);
-    if (j / kNB > i / kNB) return;                 // above the lower block triangle: never written, never read
+    if (j / kNB > i / kNB) return;                 // above the lower block triangle: no sums (the factor is kept there, see below)
     double sum = 0.0;
     for (int s = 0; s < slices; ++s) sum += part[(int64_t)s * r * r + e];
     S[e] = sum;
@@ -720,7 +720,8 @@ __global__ __launch_bounds__(256) void k_trinv_row(const double* __restrict__ S,
 // the three fill the chip together, and a block column costs two launches where it takes four.  But every workgroup then holds
 // the diagonal block's registers and 42 KB of LDS, three on a CU; on its own the trailing update fits more.
 // kUpdatePanel: the panel too.  A workgroup forms the two blocks of L that it needs itself, 64 x 64 x 64 products of 1.7 us that
-// a launch of their own takes 5 us for; only where every workgroup has a CU, since there are three products instead of one.
+// a launch of their own takes 5 us for; only where every workgroup has a CU, since there are three products instead of one and
+// 101 KB of LDS, one workgroup on a CU.
 // (us per refresh, never / up to 128 / 256 / 512 workgroups: 768 x 768, r = 256 285 / 263 / 265 / 264, 2048 x 2048, r = 512 585 / 533 / 533 /
 // 533, sixteen of them 1676 / 1678 / 1675 / 1703, 4096 x 4096, r = 1024 1448 / 1334 / 1334 / 1336.)
 enum : int { kUpdateAlone = 0, kUpdateFused = 1, kUpdatePanel = 2 };

@@ -345,11 +345,15 @@ def test_batched_refresh_across_launch_groups(count):
 
 @pytest.mark.parametrize("m,n,r,count", [(256, 264, 200, 96), (256, 264, 200, 97), (160, 200, 136, 129), (72, 96, 64, 385),
                                            (256, 264, 200, 256), (256, 264, 200, 257), (72, 96, 64, 1025),
-                                           (256, 264, 200, 66), (256, 264, 200, 160), (256, 264, 200, 161), (160, 168, 152, 100)])
+                                           (256, 264, 200, 66), (256, 264, 200, 160), (256, 264, 200, 161), (160, 168, 152, 100),
+                                           (256, 264, 200, 28), (256, 264, 200, 29), (256, 264, 200, 36), (256, 264, 200, 37),
+                                           (256, 264, 200, 42), (256, 264, 200, 43)])
 def test_large_batches_equal_the_single_matrix_calls(m, n, r, count):
-    """Up to 640 block rows of 64 in a batch (160 matrices of r = 200) a block column of the factorization is one launch,
-    beyond that its parts are launches of their own; the inverse's block rows come in strips for one matrix and whole from 200
-    blocks on: bit for bit the single call's result either way."""
+    """Up to 1024 block rows of 64 in a batch (256 matrices of r = 200) the update of a block column of the factorization, the next
+    diagonal block and a block row of the inverse are one launch, beyond that launches of their own; the panel is part of that launch
+    up to 256 workgroups (at r = 200 all three block columns up to 28 matrices, the first two up to 36, the first one up to 42); the
+    inverse's block rows come in strips for one matrix and whole from 200 blocks on: bit for bit the single call's result in
+    every case."""
     ins = [start(m, n, r, seed=s) for s in range(3)]
     up = [(bits_t(Gb), dev(Pq), dev(Ps)) for Gb, Pq, Ps in ins]
     single = [qg.subspace_refresh(Pq, Ps, G, m, n, r, 1) for G, Pq, Ps in up]
