@@ -820,20 +820,22 @@ static bool lin_small(int64_t M, int64_t N, int count) {
 
 // Whether a product of the linear layer splits its contraction over the waves of a workgroup (T: its 32 x 32 tiles).  Against
 // the tiles of launch_tile_gemm, us, split / not: forward, 256 tokens, 768 -> 768 (T = 192) 4.0 / 6.6, 2048 -> 2048 (512) 9.2 /
-// 13.4, 500 tokens, 1024 -> 1024 (512) 6.5 / 7.4.  From 513 to 768 of them two groups of waves (64 x 64 tiles, at most a workgroup per CU)
-// take 0.93 of the split's time on average over 22 shapes and ten lengths of the contraction from 512 to 11008: 0.78 to 0.91 where rows
-// start unaligned, 256 tokens, 2048 -> 3072 (768) 12.0 / 11.2, 4096 -> 3072 22.5 / 20.5, 2000 tokens, 11008 -> 384 (756) 62.7 / 52.4; they lose up
-// to 8 % at K = 2048 with some hundred ragged rows (500 tokens, 1280 columns (640) 11.3 / 12.2, 1000 tokens, 768 columns 11.7 / 12.2) and 2 to
-// 4 % on ragged tiles at K = 512.  Where they do not have a CU each, 32 tokens, 2048 -> 17408 (544) 12.9 / 19.9, 4096 -> 24576 (768) 24.7 / 37.0.  A weight with k
+// 13.4, 500 tokens, 1024 -> 1024 (512) 6.5 / 7.4.  From 513 to 768 of them two groups of waves (64 x 64 tiles, at most a workgroup
+// per CU) take 0.93 of the split's time on average over 22 shapes and ten lengths of the contraction from 512 to 11008: 0.78 to 0.91
+// where rows start unaligned, 256 tokens, 2048 -> 3072 (768) 12.0 / 11.2, 4096 -> 3072 22.5 / 20.5, 2000 tokens, 11008 -> 384 (756)
+// 62.7 / 52.4, 1000 tokens, 768 -> 768 the same; they lose up to 8 % at K = 2048 with some hundred ragged rows (500 tokens, 1280
+// columns (640) 11.3 / 12.2, 1000 tokens, 768 columns 11.7 / 12.2) and 2 to 4 % on ragged tiles at K = 512.  Where they do not have
+// a CU each, 32 tokens, 2048 -> 17408 (544) 12.9 / 19.9, 4096 -> 24576 (768) 24.7 / 37.0.  A weight with k
 // slow (grad_input) needs twice the LDS per wave, and a chain that is long for the number of tiles: 256 tokens, 2048 -> 2048
 // (512) 11.7 / 13.9, 500 tokens, K = 3001, 1007 columns (512) 55 / 95, but with grad_W in the same launch 256 tokens, K = 768,
 // 2048 columns (512) 9.4 / 8.0, K = 1024, 2736 columns (688) 14.3 / 11.0.  grad_W: 512 x 512 (256), 1024 tokens 4.8 / 7.1, 4096
 // tokens 10.9 / 30, but 256 tokens with grad_input in the same launch 4.2 / 3.7, and 768 x 768 (576), 1024 tokens 9.5 / 7.4.
 // beside: the contraction of grad_W where a backward pass would run both products in one launch (whether it is asked for both or
 // not), 0 otherwise.  There are no two groups there, and 64 x 64 tiles, which are fewer, leave grad_W more of the chip.  From 513
-// to 768 tiles, a weight with k fast (stored transposed), both / grad_input alone, split and 64 x 64: 1000 tokens, K = 768, 768 columns (768)
-// 14.0 and 11.1 / 6.4 and 6.9, K = 2048 21.6 and 20.0 / 12.0 and 17.8, 500 tokens, K = 2048, 1280 columns (640) 17.9 and 19.4 / 11.3 and 17.8, 1000 tokens, K
-// = 4096, 640 columns 32.5 and 35.7 / 20.6 and 31.9, but 2000 tokens, K = 2048, 320 columns (630) 25.5 and 19.7 / 12.3 and 17.6.
+// to 768 tiles, a weight with k fast (stored transposed), both products / grad_input alone, split and 64 x 64 tiles: 1000 tokens,
+// 768 columns (768), K = 768 14.0 and 11.1 / 6.4 and 6.9, K = 2048 21.6 and 20.0 / 12.0 and 17.8, 500 tokens, 1280 columns (640), K
+// = 2048 17.9 and 19.4 / 11.3 and 17.8, 1000 tokens, 640 columns, K = 4096 32.5 and 35.7 / 20.6 and 31.9, but 2000 tokens, 320 columns
+// (630), K = 2048 25.5 and 19.7 / 12.3 and 17.6.
 template <int AL, int BL>
 static bool lin_ksplit(int64_t M, int64_t N, int64_t K, int64_t beside) {
     const int64_t T = ((M + 31) / 32) * ((N + 31) / 32);
@@ -883,16 +885,21 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    1024 -> 2736 (176) 14.5 / 15.9 and 300 tokens, 4096 -> 11008 (258) 60 / 64; grad_input, 1000 x 2048 -> 2048 (128) 20 / 31,
 //    256 x 4096 -> 11008 (172) 53 / 43; grad_W, 2048 tokens, 1024 x 1024 (64) 13 / 29, 1024 tokens, 1536 x 2048 (192) 15.7 / 15.9, 1664 x 2048 (208)
 //    20.8 / 15.9.
-//  * two groups of waves (INT8 B, K >= 512) where these tiles would be at most a workgroup per CU, us, one group / two: 64 x 64,
-//    forward, 256 tokens, 4096 -> 4096 31.0 / 20.5, 500 tokens, 2048 -> 2048 13.6 / 11.2, 512 -> 2048 6.3 / 5.9 (256 -> 2048, 1000
-//    tokens, 6.0 / 6.5), 1024 -> 1024, 1000 tokens, 9.0 / 7.9, grad_input 256 x 11008 -> 4096 80 / 50; beyond 256 of these 128 x 64 up to
-//    as many, forward, 1000 tokens, 2048 -> 2048 21.7 / 18.9, 5461 -> 2048 62 / 57, grad_input 23.2 / 19.8 (two groups of
-//    64 x 64 tiles there 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2; rows that start unaligned, 900
-//    tokens, 1599 -> 1600, 20.9 / 23.5, and of a weight with k slow, transposed forward, 1000 tokens, 1024 -> 2047 13.2 / 14.6, 2048 -> 2047 23.3 / 24.4,
-//    5461 -> 2047 63.2 / 61.0); 128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 /
-//    27.7, 256 tokens, 4096 -> 11008 43 / 38, but not on a short contraction (2048 tokens, 2048 columns, forward, K = 512 10.7 / 11.0, 520
-//    14.3 / 15.1, 768 14.5 / 14.6, 1024 18.0 / 17.9; grad_input on whole tiles, 1024 tokens, 4096 columns, 512 10.4 / 11.0, 1024 17.3 / 17.7, 2048 29.6 /
-//    29.6; ragged, 1000 tokens, 3000 columns, 512 12.5 / 11.5, 513 16.0 / 16.4, 768 18.4 / 15.4).  grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
+//  * two groups of waves (INT8 B, K >= 512) where these tiles would be at most a workgroup per CU, us, one group / two:
+//    64 x 64, forward, 256 tokens, 4096 -> 4096 31.0 / 20.5, 500 tokens, 2048 -> 2048 13.6 / 11.2, 512 -> 2048 6.3 / 5.9, 1000 tokens,
+//    1024 -> 1024 9.0 / 7.9, grad_input 256 x 11008 -> 4096 80 / 50; shorter contractions go either way (500 tokens, 2048 columns, K =
+//    256 4.4 / 4.5, 320 4.6 / 4.8, 384 5.2 / 4.8, 448 5.3 / 5.3).
+//    128 x 64 where 64 x 64 ones are more than 256 and these are not: forward, 1000 tokens, 2048 -> 2048 21.7 / 18.9, grad_input 23.2 /
+//    19.8 (two groups of 64 x 64 tiles 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2).  Where rows
+//    start unaligned two groups lose on short contractions and gain on long ones; forward, 1000 tokens, 2048 columns, K = 2047 27.2 /
+//    30.0, 2501 31.4 / 31.2, 3001 36.3 / 34.3, 4001 47.4 / 43.6 and eleven other shapes alike (K = 2047 0.85 to 1.02 of two groups'
+//    time, 3001 0.96 to 1.10, 4101, 5000, 5461 and 7001 0.96 to 1.23, 1.08 on average), a weight with k slow and rows of 2047, transposed forward, 1000
+//    tokens, K = 1024 13.2 / 14.6, 2048 23.3 / 24.4, 5461 63.2 / 61.0: from 4096 on.
+//    128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 / 27.7, 256 tokens, 4096 -> 11008
+//    43 / 38, but not on a short contraction (2048 tokens, 2048 columns, forward, K = 512 10.7 / 11.0, 520 14.3 / 15.1, 768 14.5 / 14.6,
+//    1024 18.0 / 17.9; grad_input on whole tiles, 1024 tokens, 4096 columns, 512 10.4 / 11.0, 1024 17.3 / 17.7, 2048 29.6 / 29.6;
+//    ragged, 1000 tokens, 3000 columns, 512 12.5 / 11.5, 513 16.0 / 16.4, 768 18.4 / 15.4).
+//    grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
 // ldc: row pitch of C in elements (0: N).  beside: see lin_ksplit; two groups only where it is 0.
 template <int AL, int BL, typename OUT>
 static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint16_t* bias, OUT* C, int64_t M, int64_t N,
