@@ -40,8 +40,8 @@ def test_grids_of_a_refresh(driver, count, m, n, r):
 
 
 @pytest.mark.parametrize("n,k,want", [
-    (2048, 2048, (256, 512)), (2047, 2048, (512, 256)), (2040, 1024, (512, 256)),   # whole rows of the weight, odd ones, rows of 8
-    (2047, 5461, (256, 512)),                                                        # a long contraction: two groups all the same
+    (2048, 2000, (256, 512)), (2047, 2000, (512, 256)), (2040, 2040, (512, 256)),   # whole rows of the weight, odd ones, rows of 8
+    (2047, 2048, (256, 512)), (2048, 2049, (512, 256)), (2047, 5461, (256, 512)),    # a long contraction, but not of unaligned rows
 ])
 def test_two_groups_on_a_weight_with_k_slow(driver, n, k, want):
     """1000 tokens.  128 x 64 tiles in two groups of waves (512 threads) where the weight's rows start 16-byte aligned, else
