@@ -177,6 +177,7 @@ def test_around_the_rules_of_two_groups(tokens, m, n):
     (544, 530, 70),                                  # four waves in the forward pass
     (544, 200, 33), (600, 100, 130), (96, 300, 40),  # grad_input and grad_W split, only grad_W, only grad_input
     (200, 1500, 600), (64, 2048, 512),               # a long chain in grad_input
+    (20, 16500, 520),                                # few rows by many columns in the forward pass
 ])
 def test_contraction_split_over_waves(tokens, m, n):
     test_forward(tokens, m, n)

@@ -87,7 +87,8 @@ def check(got, want, k_terms, scale):
 
 
 @pytest.mark.parametrize("tokens,m,n", [(256, 512, 512), (130, 333, 264), (77, 521, 200), (1, 768, 256), (3, 5, 7),
-                                        (300, 2048, 768)])
+                                        (300, 2048, 768),
+                                        (1000, 2048, 768), (1000, 768, 768)])   # grad_input: 768 tiles, split and not
 def test_linear_on_transposed_storage(tokens, m, n):
     g = np.random.default_rng([tokens, m, n])
     Sq, Ss = Q.quant_int8(np.ascontiguousarray(I.weight_f32(m, n, 2).T))
