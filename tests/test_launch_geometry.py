@@ -40,12 +40,13 @@ def test_grids_of_a_refresh(driver, count, m, n, r):
 
 
 @pytest.mark.parametrize("n,k,want", [
-    (2048, 2000, (256, 512)), (2047, 2000, (512, 256)), (2040, 2040, (512, 256)),   # whole rows of the weight, odd ones, rows of 8
-    (2047, 2048, (256, 512)), (2048, 2049, (512, 256)), (2047, 5461, (256, 512)),    # a long contraction, but not of unaligned rows
+    (2048, 2000, (256, 512)), (2047, 2040, (512, 256)), (2047, 2048, (256, 512)),   # whole rows of the weight; odd ones
+    (2040, 1016, (512, 256)), (2040, 2040, (256, 512)),                             # rows of a multiple of 4
+    (2048, 2049, (512, 256)), (2047, 5461, (256, 512)),                             # a contraction of unaligned rows
 ])
 def test_two_groups_on_a_weight_with_k_slow(driver, n, k, want):
-    """1000 tokens.  128 x 64 tiles in two groups of waves (512 threads) where the weight's rows start 16-byte aligned, else
-    64 x 64 tiles (256 threads): grad_input of the layer k <- n, and the forward pass of the same weight stored transposed."""
+    """1000 tokens.  128 x 64 tiles in two groups of waves (512 threads) where the weight's rows start 16-byte aligned or the
+    contraction is long, else 64 x 64 tiles (256 threads): grad_input of the layer k <- n, and the forward pass of the same weight stored transposed."""
     assert driver("grad_input", 1000, k, n)[0] == want
     assert driver("t_forward", 1000, n, k)[0] == want
 
