@@ -890,13 +890,16 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    1024 -> 1024 9.0 / 7.9, grad_input 256 x 11008 -> 4096 80 / 50; shorter contractions go either way (500 tokens, 2048 columns, K =
 //    256 4.4 / 4.5, 320 4.6 / 4.8, 384 5.2 / 4.8, 448 5.3 / 5.3).
 //    128 x 64 where 64 x 64 ones are more than 256 and these are not: forward, 1000 tokens, 2048 -> 2048 21.7 / 18.9, grad_input 23.2 /
-//    19.8 (two groups of 64 x 64 tiles 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2).  Where rows
-//    start unaligned two groups lose on short contractions and gain on long ones; forward, 1000 tokens, 2048 columns, K = 2047 27.2 /
-//    30.0, 2501 31.4 / 31.2, 3001 36.3 / 34.3, 4001 47.4 / 43.6 and eleven other shapes alike (K = 2047 0.85 to 1.02 of two groups'
-//    time, 3001 0.96 to 1.10, 4101, 5000, 5461 and 7001 0.96 to 1.23, 1.08 on average), so from 4096 on.  A weight with k slow, 56 shapes of
-//    100 to 2000 tokens, one group's time over two groups': odd rows, K = 1024 0.95 on average, 2048 1.00, 3008 1.01 (transposed forward, 1000
-//    tokens, 2047 columns, K = 1024 13.2 / 14.6, 2048 23.3 / 24.4, 5461 63.2 / 61.0); rows of a multiple of 4, up to 1024 tokens, K = 768
-//    1.00, 1024 1.03, 2048 1.03, more tokens 0.93 and 0.97: from 2048 on, and from 1024 in the third case.
+//    19.8 (two groups of 64 x 64 tiles 20.1 and 22.4; 288 tiles of 128 x 64, 1500 tokens, 1536 -> 1536, 19.8 / 24.2).  Two groups' time
+//    over one's in 340 random products on aligned rows, forward and k slow alike: a whole number of steps, K = 512 to 576 1.02, 577 to 768 0.97,
+//    up to 1600 0.92, beyond 0.85; with a partial last step, which one group takes while the other waits, K = 512 to 640 1.09, 641 to 896
+//    1.03, 897 to 1024 0.99, up to 1600 0.96, beyond 0.88: from 640 and 960 on.  Where
+//    rows start unaligned two groups lose on short contractions and gain on long ones; forward, 1000 tokens, 2048 columns, K = 2047
+//    27.2 / 30.0, 2501 31.4 / 31.2, 3001 36.3 / 34.3, 4001 47.4 / 43.6 and eleven other shapes alike (K = 2047 0.85 to 1.02 of two
+//    groups' time, 3001 0.96 to 1.10, 4101, 5000, 5461 and 7001 0.96 to 1.23, 1.08 on average), so from 4096 on.  A weight with k slow,
+//    56 shapes of 100 to 2000 tokens, one group's time over two groups': odd rows, K = 1024 0.95 on average, 2048 1.00, 3008 1.01
+//    (transposed forward, 1000 tokens, 2047 columns, K = 1024 13.2 / 14.6, 2048 23.3 / 24.4, 5461 63.2 / 61.0); rows of a multiple of 4,
+//    up to 1024 tokens, K = 768 1.00, 1024 1.03, 2048 1.03, more tokens 0.93 and 0.97: from 2048 on, and from 1024 in the third case.
 //    128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 / 27.7, 256 tokens, 4096 -> 11008
 //    43 / 38, but not on a short contraction (2048 tokens, 2048 columns, forward, K = 512 10.7 / 11.0, 520 14.3 / 15.1, 768 14.5 / 14.6,
 //    1024 18.0 / 17.9; grad_input on whole tiles, 1024 tokens, 4096 columns, 512 10.4 / 11.0, 1024 17.3 / 17.7, 2048 29.6 / 29.6;
@@ -926,10 +929,7 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
         // Two groups of waves per tile (see tile_gemm) while tiles are about a workgroup per CU or fewer
         if (many == nullptr && beside == 0 && K >= 512) {
             const int64_t tiles_m = (M + 127) / 128, tiles_n = (N + 63) / 64;
-            // dense rows start 16-byte aligned; k slow: or those of A do and the contraction is long enough for the weight's (sizes,
-            // not the pitches: the order of the sums does not depend on them)
             constexpr bool slow = BL == kInt8KSlow || BL == kInt8ZKSlow;
-            const bool wide = slow ? K % 8 == 0 && (N % 16 == 0 || K >= (N % 4 == 0 && M <= 1024 ? 1024 : 2048)) : K % 16 == 0;
             auto launch = [&](auto mb, auto tn) {
                 launch_tile_gemm_shape<AL, BL, OUT, mb.value, tn.value, 64, 2, true, true, 2>(A, B, bias, C, M, N, K, st, nullptr, 1,
                                                                                              ldc);
@@ -943,8 +943,11 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
                 if (K >= least && tiles_m * ((N + 127) / 128) <= 256) return launch(std::integral_constant<int, 2>(), N128());
             } else if ((M + 63) / 64 * tiles_n <= 256) {
                 return launch(std::integral_constant<int, 1>(), N64());
-            } else if (tiles_m * tiles_n <= 256 && (wide || K >= 4096)) {
-                return launch(std::integral_constant<int, 2>(), N64());
+            } else if (tiles_m * tiles_n <= 256) {
+                // dense rows start 16-byte aligned; k slow: or those of A do and the contraction is long enough for the weight's
+                // (sizes, not the pitches: the order of the sums does not depend on them)
+                const bool wide = slow ? K % 8 == 0 && (N % 16 == 0 || K >= (N % 4 == 0 && M <= 1024 ? 1024 : 2048)) : K % 16 == 0;
+                if (wide ? K >= (K % 64 == 0 ? 640 : 960) : K >= 4096) return launch(std::integral_constant<int, 2>(), N64());
             }
         }
     }

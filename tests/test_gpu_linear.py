@@ -121,9 +121,9 @@ def test_ragged_tiles_of_whole_chunks(tokens, m, n):
 TWO_GROUPS = [
     (64, 64, "fast", 512, 1152, 576), (64, 64, "fast", 512, 2048, 640), (64, 64, "fast", 500, 1100, 600), (64, 64, "fast", 500, 1101, 1025),
     (64, 64, "slow", 512, 1152, 576), (64, 64, "slow", 512, 2048, 640), (64, 64, "slow", 500, 1100, 600), (64, 64, "slow", 500, 1101, 1025),
-    (128, 64, "fast", 1024, 1152, 576), (128, 64, "fast", 1024, 2048, 640), (128, 64, "fast", 1000, 1100, 592), (128, 64, "fast", 1000, 1100, 4101),
+    (128, 64, "fast", 1024, 1152, 704), (128, 64, "fast", 1024, 2048, 640), (128, 64, "fast", 1000, 1100, 976), (128, 64, "fast", 1000, 1100, 4101),
     (128, 64, "fast", 1000, 1101, 4165),
-    (128, 64, "slow", 1024, 1152, 576), (128, 64, "slow", 1024, 2048, 640), (128, 64, "slow", 1000, 1104, 600), (128, 64, "slow", 1000, 1100, 4101),
+    (128, 64, "slow", 1024, 1152, 704), (128, 64, "slow", 1024, 2048, 640), (128, 64, "slow", 1000, 1104, 1000), (128, 64, "slow", 1000, 1100, 4101),
     (128, 64, "slow", 1000, 1101, 4165),
     (128, 128, "fast", 2048, 2048, 832), (128, 128, "fast", 2048, 2048, 768), (128, 128, "fast", 2000, 2000, 840), (128, 128, "fast", 1999, 2001, 773),
     (128, 128, "slow", 2048, 1280, 1600), (128, 128, "slow", 2048, 1280, 1536), (128, 128, "slow", 2000, 1270, 600), (128, 128, "slow", 1999, 1271, 773),

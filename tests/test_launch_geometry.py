@@ -101,3 +101,10 @@ def test_tiles_of_two_groups(driver, tm, tn, layout, tokens, cols, k):
 def test_tiles_of_two_groups_in_grad_input(driver, tm, tn, tokens, m, n):
     tiles = -(-tokens // tm) * -(-n // tn)
     assert driver("backward", tokens, m, n)[0] == driver("grad_input", tokens, m, n)[0] == (-(-tiles // 8) * 8, 512)
+
+
+@pytest.mark.parametrize("what", ["forward", "t_forward"])
+@pytest.mark.parametrize("k,two", [(576, False), (608, False), (640, True), (656, False), (944, False), (960, True), (976, True)])
+def test_shortest_contraction_of_two_groups_on_128x64_tiles(driver, what, k, two):
+    """With a partial last step, which one group takes alone, longer than without."""
+    assert driver(what, 1800, 624, k) == [(152, 512) if two else (296, 256)]     # 15 x 10 and 29 x 10 tiles
