@@ -835,14 +835,15 @@ static bool lin_small(int64_t M, int64_t N, int count) {
 // to 768 tiles, a weight with k fast (stored transposed), both products / grad_input alone, split and 64 x 64 tiles: 1000 tokens,
 // 768 columns (768), K = 768 14.0 and 11.1 / 6.4 and 6.9, K = 2048 21.6 and 20.0 / 12.0 and 17.8, 500 tokens, 1280 columns (640), K
 // = 2048 17.9 and 19.4 / 11.3 and 17.8, 1000 tokens, 640 columns, K = 4096 32.5 and 35.7 / 20.6 and 31.9, but 2000 tokens, 320 columns
-// (630), K = 2048 25.5 and 19.7 / 12.3 and 17.6.
+// (630), K = 2048 25.5 and 19.7 / 12.3 and 17.6, and on unaligned rows 602 tokens, 1207 columns, K = 2416 30.0 and 26.0, 536 tokens, 1143 columns,
+// K = 3315 44.5 and 37.8.
 template <int AL, int BL>
 static bool lin_ksplit(int64_t M, int64_t N, int64_t K, int64_t beside) {
     const int64_t T = ((M + 31) / 32) * ((N + 31) / 32);
     if (AL == kBf16KSlow && BL == kBf16KSlow) return T <= 320 && K >= 512;
     if (BL == kInt8KSlow || BL == kInt8ZKSlow) return T <= 512 && K >= 3 * T;
     if (T <= 512 || K < 512) return T <= 768;
-    if (beside != 0) return T <= 768 && K >= 2048 && K >= 2 * beside;
+    if (beside != 0) return T <= 768 && K >= 2048 && K >= 2 * beside && K % 8 == 0 && N % 8 == 0;
     return T <= 768 && ((M + 63) / 64) * ((N + 63) / 64) > 256;   // (else two groups of waves, see launch_tile_gemm)
 }
 
@@ -899,11 +900,13 @@ static unsigned lin_grid(const LinProduct& p) { return (unsigned)((p.tiles_m * p
 //    groups' time, 3001 0.96 to 1.10, 4101, 5000, 5461 and 7001 0.96 to 1.23, 1.08 on average), so from 4096 on.  A weight with k slow,
 //    56 shapes of 100 to 2000 tokens, one group's time over two groups': odd rows, K = 1024 0.95 on average, 2048 1.00, 3008 1.01
 //    (transposed forward, 1000 tokens, 2047 columns, K = 1024 13.2 / 14.6, 2048 23.3 / 24.4, 5461 63.2 / 61.0); rows of a multiple of 4,
-//    up to 1024 tokens, K = 768 1.00, 1024 1.03, 2048 1.03, more tokens 0.93 and 0.97: from 2048 on, and from 1024 in the third case.
+//    up to 1024 tokens, K = 768 1.00, 1024 1.03, 2048 1.03, more tokens 0.93 and 0.97 (even ones are like these, 363 tokens, 4162
+//    columns, K = 1472 17.1 / 16.0): from 2048 on, and from 1024 on even rows up to 1024 tokens.
 //    128 x 128 x 64, forward, 1024 tokens, 4096 -> 4096 51 / 46, grad_input, 2000 tokens, 2000 -> 2000 37.5 / 27.7, 256 tokens, 4096 -> 11008
 //    43 / 38, but not on a short contraction (2048 tokens, 2048 columns, forward, K = 512 10.7 / 11.0, 520 14.3 / 15.1, 768 14.5 / 14.6,
 //    1024 18.0 / 17.9; grad_input on whole tiles, 1024 tokens, 4096 columns, 512 10.4 / 11.0, 1024 17.3 / 17.7, 2048 29.6 / 29.6;
-//    ragged, 1000 tokens, 3000 columns, 512 12.5 / 11.5, 513 16.0 / 16.4, 768 18.4 / 15.4).
+//    ragged, 1000 tokens, 3000 columns, 512 12.5 / 11.5, 513 16.0 / 16.4, 768 18.4 / 15.4,
+//    1733 tokens, 1456 columns, 595 17.4 / 16.2, 2165 tokens, 1296 columns, 571 16.9 / 15.8).
 //    grad_W gains nothing (1000 tokens, 2048 x 2048, 17.9 / 18.8).
 // ldc: row pitch of C in elements (0: N).  beside: see lin_ksplit; two groups only where it is 0.
 template <int AL, int BL, typename OUT>
@@ -939,14 +942,14 @@ static int launch_tile_gemm(const LinOperand& A, const LinOperand& B, const uint
             using N128 = std::integral_constant<int, 128>;
             if (!lin_small<AL, BL>(M, N, 1)) {
                 const bool whole = M % 128 == 0 && N % 128 == 0;
-                const int64_t least = slow && whole ? 1536 : slow && K % 8 == 0 ? 512 : 768;
+                const int64_t least = !slow ? 768 : whole ? 1536 : K % 8 == 0 ? 512 : 544;
                 if (K >= least && tiles_m * ((N + 127) / 128) <= 256) return launch(std::integral_constant<int, 2>(), N128());
             } else if ((M + 63) / 64 * tiles_n <= 256) {
                 return launch(std::integral_constant<int, 1>(), N64());
             } else if (tiles_m * tiles_n <= 256) {
                 // dense rows start 16-byte aligned; k slow: or those of A do and the contraction is long enough for the weight's
                 // (sizes, not the pitches: the order of the sums does not depend on them)
-                const bool wide = slow ? K % 8 == 0 && (N % 16 == 0 || K >= (N % 4 == 0 && M <= 1024 ? 1024 : 2048)) : K % 16 == 0;
+                const bool wide = slow ? K % 8 == 0 && (N % 16 == 0 || K >= (N % 2 == 0 && M <= 1024 ? 1024 : 2048)) : K % 16 == 0;
                 if (wide ? K >= (K % 64 == 0 ? 640 : 960) : K >= 4096) return launch(std::integral_constant<int, 2>(), N64());
             }
         }

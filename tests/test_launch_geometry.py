@@ -41,7 +41,7 @@ def test_grids_of_a_refresh(driver, count, m, n, r):
 
 @pytest.mark.parametrize("n,k,want", [
     (2048, 2000, (256, 512)), (2047, 2040, (512, 256)), (2047, 2048, (256, 512)),   # whole rows of the weight; odd ones
-    (2040, 1016, (512, 256)), (2040, 2040, (256, 512)),                             # rows of a multiple of 4
+    (2042, 1016, (512, 256)), (2042, 2040, (256, 512)),                             # even rows
     (2048, 2049, (512, 256)), (2047, 5461, (256, 512)),                             # a contraction of unaligned rows
 ])
 def test_two_groups_on_a_weight_with_k_slow(driver, n, k, want):
@@ -54,7 +54,7 @@ def test_two_groups_on_a_weight_with_k_slow(driver, n, k, want):
 @pytest.mark.parametrize("what,tokens,n,k,threads", [
     ("forward", 2048, 2048, 520, 256), ("forward", 2000, 2000, 767, 256), ("forward", 2048, 2048, 768, 512),
     ("grad_input", 1024, 4096, 512, 256), ("grad_input", 1024, 4096, 1535, 256), ("grad_input", 1024, 4096, 1536, 512),   # whole
-    ("grad_input", 1000, 3000, 512, 512), ("grad_input", 1000, 3000, 513, 256), ("grad_input", 1000, 3000, 769, 512),    # ragged
+    ("grad_input", 1000, 3000, 512, 512), ("grad_input", 1000, 3000, 543, 256), ("grad_input", 1000, 3000, 545, 512),    # ragged
 ])
 def test_shortest_contraction_of_two_groups_on_large_tiles(driver, what, tokens, n, k, threads):
     """128 x 128 tiles, at most a workgroup per CU: n columns, contraction k."""
@@ -76,6 +76,7 @@ def test_few_rows_in_the_forward_pass(driver, tokens, n, k, want):
     (1000, 2048, 768, True), (500, 2048, 1280, True), (2000, 4096, 320, True),      # at least twice the tokens
     (1000, 1999, 768, False), (2000, 2048, 320, False), (1000, 768, 768, False),    # less, or a short contraction
     (500, 4096, 1280, False),                                                       # grad_W in a launch of its own: two groups
+    (602, 2416, 1207, False), (536, 3315, 1144, False),                             # unaligned rows of x, of dy
     (1000, 2048, 512, True), (1000, 500, 768, True),                                # up to 512 tiles; up to a contraction of 511
 ])
 def test_grad_input_of_a_transposed_weight(driver, tokens, m, n, split):
